@@ -501,6 +501,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     g.Wt = Wq_packed;
     g.M = M;
     g.N = N;
+    g.K = K;
     g.Kpad = Kpad;
     g.r = ws.r;
     g.c = col_absmax;

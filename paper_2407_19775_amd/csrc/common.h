@@ -102,22 +102,29 @@ __device__ __forceinline__ void dma16(const void* src, uint32_t lds_addr) {
                : "memory");
 }
 
-// eight weight codes (bytes [8 t, 8 t + 8) of the lane's 16, already XORed with 0x80: u = q + 128)
-// -> the integers q as fp16.  The fp16 number 1024 + u has the bit pattern 0x6400 | u.
-__device__ inline v8h codes_to_half8(const v4u& wu, int t) {
+// The same from a wave-uniform address plus a byte offset per lane (no vector instruction to advance it).
+__device__ __forceinline__ void dma16_scalar_base(const void* base, uint32_t offset, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(offset), "s"(base), "s"(lds_addr)
+               : "memory");
+}
+
+// four weight codes, already XORed with 0x80 (u = q + 128) -> the integers q as fp16.  The fp16 number 1024 + u has
+// the bit pattern 0x6400 | u.
+__device__ __forceinline__ v2u codes_to_half4(uint32_t word) {
   typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-  v4u out;
-#pragma unroll
-  for (int d = 0; d < 2; ++d) {
-    const uint32_t word = wu[2 * t + d];
-    // bytes of {0x64646464 : word}: selectors 0-3 = word bytes, 4-7 = 0x64
-    const uint32_t lo = __builtin_amdgcn_perm(0x64646464u, word, 0x04010400u);   // [b0, 0x64, b1, 0x64] little end first
-    const uint32_t hi = __builtin_amdgcn_perm(0x64646464u, word, 0x04030402u);   // [b2, 0x64, b3, 0x64]
-    const h2 bias = {(_Float16)1152.0f, (_Float16)1152.0f};
-    out[2 * d] = __builtin_bit_cast(uint32_t, (h2)(__builtin_bit_cast(h2, lo) - bias));
-    out[2 * d + 1] = __builtin_bit_cast(uint32_t, (h2)(__builtin_bit_cast(h2, hi) - bias));
-  }
-  return __builtin_bit_cast(v8h, out);
+  // bytes of {0x64646464 : word}: selectors 0-3 = word bytes, 4-7 = 0x64
+  const uint32_t lo = __builtin_amdgcn_perm(0x64646464u, word, 0x04010400u);     // [b0, 0x64, b1, 0x64] little end first
+  const uint32_t hi = __builtin_amdgcn_perm(0x64646464u, word, 0x04030402u);     // [b2, 0x64, b3, 0x64]
+  const h2 bias = {(_Float16)1152.0f, (_Float16)1152.0f};
+  return v2u{__builtin_bit_cast(uint32_t, (h2)(__builtin_bit_cast(h2, lo) - bias)),
+             __builtin_bit_cast(uint32_t, (h2)(__builtin_bit_cast(h2, hi) - bias))};
+}
+// eight of them: words 2 t and 2 t + 1 of the lane's 16 bytes
+__device__ inline v8h codes_to_half8(const v4u& wu, int t) {
+  const v2u a = codes_to_half4(wu[2 * t]), b = codes_to_half4(wu[2 * t + 1]);
+  return __builtin_bit_cast(v8h, v4u{a[0], a[1], b[0], b[1]});
 }
 
 int device_cu_count();   // compute units of the current device (cached per device)

@@ -6,8 +6,7 @@ namespace mmd8 {
 
 // Critical columns handled on the fast path: they travel as extra 64-byte K-slabs of fp16 operands, 32 columns
 // each, prepared once per call by the pack kernels; they ride through the GEMM's slab ring behind the codes.
-// Columns beyond 32 kCriticalSlabs (inputs where a large share of the dimensions is critical) are multiplied 64
-// at a time after the ring has drained: fp16 activations straight from X, weight codes converted in registers.
+// Columns beyond 32 kCriticalSlabs (inputs where a large share of the dimensions is critical): see plan_critical_columns.
 constexpr int kOutlierSlab = 32;
 constexpr int kCriticalSlabs = 8;
 // Critical columns beyond those slabs.  Gathering them column by column in the GEMM's epilogue (gather_outlier_columns)
@@ -16,9 +15,10 @@ constexpr int kCriticalSlabs = 8;
 // gathers them once into further slabs of the same layout, Xg / Wg (g_slabs of them per panel, up to kGatherMax
 // columns, fewer where the weight side would exceed kGatherWeightBytesMax), and the GEMM takes those through its
 // ring behind the first crit_slabs: 1.5 us per slab of 32 columns on that call.  Only columns beyond both are
-// gathered in the epilogue, and from dense_from critical columns on the GEMM makes a second, fp16 pass over K
-// instead (dense_critical_columns in gemm_kernels.hip, 3.7 us per 64-column slab of K on that call): where that is
-// cheaper, the measured costs applied as ratios.
+// gathered in the epilogue, and from dense_from critical columns on the GEMM takes all of them along with the codes
+// instead (dense_tile in gemm_kernels.hip).  The line was drawn at 3.7 us per 64-column slab of K on that call, what a
+// second pass over K took; the single walk takes less, so calls above the line gained and those below it are
+// where they were.
 constexpr int kGatherMax = 2048;
 constexpr size_t kGatherWeightBytesMax = (size_t)96 << 20;
 struct CriticalPlan {
@@ -50,7 +50,7 @@ __host__ __device__ constexpr inline bool dense_critical_path(int n_out, int cri
 struct GemmArgs {
   const int8_t* Xq;      // activation codes, blocked layout (operand_layout.h), Mpad x Kpad
   const int8_t* Wt;      // weight codes, blocked layout, Npad x Kpad
-  int M, N, Kpad;
+  int M, N, K, Kpad;
   const float* r;        // [Mpad + 256]
   const float* c;        // [N]
   const uint16_t* bias;  // [N] or null

@@ -73,6 +73,14 @@ struct GemmCfg {
   static_assert((BM + BN) * 32 <= RING_BYTES, "epilogue staging must fit in the slab buffers");
 };
 
+// The tile configurations, by the number a caller can force one with (gemm.h):
+using Cfg0 = GemmCfg<128, 128, 2, 2, 3, 2>;
+using Cfg1 = GemmCfg<256, 128, 2, 2, 3, 2>;
+using Cfg2 = GemmCfg<128, 256, 2, 2, 3, 2>;
+using Cfg3 = GemmCfg<256, 256, 2, 4, 3, 2>;
+using Cfg4 = GemmCfg<256, 256, 2, 4, 4, 2>;   // the large tile: whole rounds of one tile per CU
+using Cfg5 = GemmCfg<128, 256, 2, 4, 4, 2>;   // remainders and less than one round of large tiles
+
 // own requests older than the newest kVm have landed, own LDS reads have returned; after the
 // barrier that holds for every wave of the workgroup
 template <int kVm>
@@ -253,149 +261,6 @@ __device__ __forceinline__ void gather_outlier_columns(const GemmArgs& a, const 
   }
 }
 
-// The 16-bit product over the critical feature dimensions ("Compression techniques", item 2) for an input where
-// hundreds or thousands of them are critical (dense_critical_path: none of them travelled as an fp16 slab then):
-// slab after slab of 64 columns.
-//   A side: the tile's rows of X itself (fp16, 128 contiguous bytes per row and slab), columns that are not
-//           critical set to zero, parked in LDS as rows of 144 bytes;
-//   B side: the slab of weight codes, fetched like in the main loop, the codes turned into fp16 integers in
-//           registers (codes_to_half8) as the decode kernels do.
-// The accumulators hold Y so far in fp32; sum_k X[m,k] q[n,k] lacks the column's step c[n] / 127, so they are
-// divided by it on entry and multiplied by it on exit (columns with c[n] = 0 have only zero codes: factor 1).
-// Against the slabs prepared by the pack kernel the weights are not rounded to fp16 after scaling: at most 2^-11
-// relative per term, as in the decode kernels.  Requests run several slabs ahead of the MFMAs (see kDepth).
-template <class Cfg>
-__device__ __forceinline__ void dense_critical_columns(const GemmArgs& a, const WavePos<Cfg>& p, v16i (&acc)[Cfg::TI][Cfg::TJ],
-                                                       int8_t* smem, const float (&cs)[Cfg::TJ]) {
-  constexpr int TI = Cfg::TI, TJ = Cfg::TJ;
-  constexpr int TPR = Cfg::kThreads / Cfg::BM;                      // threads per row of the activation tile
-  static_assert(Cfg::kThreads % Cfg::BM == 0 && TPR >= 1 && TPR <= 8, "whole threads per row");
-  constexpr int CPT = BK / TPR, NL = CPT / 8;                        // columns per thread, 16-byte loads per thread
-  constexpr int kRowBytes = 2 * BK + 16;                             // 144: rows 8 apart share banks, not rows next to each other
-  constexpr int A_LDS = (Cfg::BM * kRowBytes + 1023) / 1024 * 1024;
-  // Slabs in flight.  A slab's requests (this thread's pieces of the rows of X and the slab's mask byte into
-  // registers, the weight codes into an LDS buffer) go out kDepth slabs ahead: a slab's MFMAs take a quarter of the
-  // time its data takes to arrive.  One weight buffer more than that, so that a request never targets the buffer
-  // being read.  Every slab position issues the same kPerSlab requests in the same order (positions past the end
-  // ask for the last slab again), so the number still in flight behind a slab's weight codes is known; the loads
-  // into registers are the compiler's to wait for, and it counts only those, so its waits come out stricter than
-  // needed (about two slabs ahead instead of kDepth - 1), never looser.
-  constexpr int kBuffers = (Cfg::RING_BYTES - A_LDS) / Cfg::B_BYTES < 5 ? (Cfg::RING_BYTES - A_LDS) / Cfg::B_BYTES : 5;
-  constexpr int kDepth = kBuffers - 1;
-  constexpr int kPerSlab = NL + 1 + Cfg::B_DMA;                      // requests per slab and lane
-  static_assert(kDepth >= 1 && (kDepth - 1) * kPerSlab <= 63, "at least two weight buffers; the count fits the wait instruction");
-  int8_t* sA = smem;
-  int8_t* sB = smem + A_LDS;
-  const int lane = p.lane, wm = p.wm, wn = p.wn;
-  const int wave = wm * Cfg::WAVES_N + wn;
-  const int n_slabs = a.Kpad / BK;
-  const int row = threadIdx.x / TPR, part = threadIdx.x % TPR;
-  const uint16_t* xrow = a.X + (size_t)min(p.m0 + row, a.M - 1) * a.ldx + part * CPT;
-
-  float back[TJ];
-#pragma unroll
-  for (int j = 0; j < TJ; ++j) {
-    const float step = cs[j] * 127.0f;                               // c[n] / 127
-    back[j] = step != 0.0f ? step : 1.0f;
-    const float inv = step != 0.0f ? 1.0f / step : 1.0f;
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      v16f y = __builtin_bit_cast(v16f, acc[i][j]);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) y[e] *= inv;
-      acc[i][j] = __builtin_bit_cast(v16i, y);
-    }
-  }
-
-  v4u ra[kDepth][NL];
-  uint8_t fl[kDepth];
-  const uint32_t ldsB = (uint32_t)(uintptr_t)sB + wave * (kWave * 16);
-  // position `pos` of the sequence (slab pos, or the last slab again past the end) into register set u and weight
-  // buffer pos % kBuffers (a repeated request lands in a buffer that is not read any more)
-  auto request = [&](int pos, auto u_tag) __attribute__((always_inline)) {
-    constexpr int u = decltype(u_tag)::value;
-    const int s = min(pos, n_slabs - 1);
-#pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      // pieces beyond the row's end (the padding of K) re-read the row's first piece; none of their columns is critical
-      const int col = s * BK + part * CPT + 8 * q;
-      ra[u][q] = *reinterpret_cast<const v4u*>(xrow + (col < a.ldx ? col - part * CPT : -part * CPT));
-    }
-    fl[u] = a.mask[s * BK + lane];
-    const uint32_t dst = ldsB + (pos % kBuffers) * Cfg::B_BYTES;
-#pragma unroll
-    for (int j = 0; j < Cfg::B_DMA; ++j)
-      dma16(dma_source(a.Wt, p.n0, n_slabs, j, Cfg::kWaves, wave, lane) + (size_t)s * kBlockBytes,
-            dst + j * Cfg::kWaves * (kWave * 16));
-  };
-  auto iteration = [&](int s, auto u_tag) __attribute__((always_inline)) {
-    constexpr int u = decltype(u_tag)::value;                        // s % kDepth
-    // the weight codes of slab s have landed once only the requests of the kDepth - 1 positions after it are out
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"((kDepth - 1) * kPerSlab) : "memory");
-    // bit c: column 64 s + c is critical (positions past the end: nothing to multiply)
-    const uint64_t bits = s < n_slabs ? __builtin_amdgcn_ballot_w64(fl[u] != 0) : 0;
-    // park the rows of slab s, critical columns only
-#pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const uint32_t b8 = (uint32_t)(bits >> (part * CPT + 8 * q)) & 0xffu;
-      v4u v = ra[u][q];
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-        v[w] &= (((b8 >> (2 * w)) & 1u) ? 0x0000ffffu : 0u) | (((b8 >> (2 * w + 1)) & 1u) ? 0xffff0000u : 0u);
-      *reinterpret_cast<v4u*>(sA + row * kRowBytes + (part * CPT + 8 * q) * 2) = v;
-    }
-    wait_lds_and_sync();
-    // (past the end the last slab is asked for again: the count of requests in flight stays what the waits assume)
-    request(s + kDepth, u_tag);
-    if (bits != 0) {
-      const int8_t* fbase = sB + (s % kBuffers) * Cfg::B_BYTES + (wn * Cfg::WN / 32) * 2048 + lane * 16;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        v4u wu[TJ];
-#pragma unroll
-        for (int j = 0; j < TJ; ++j)
-          wu[j] = *reinterpret_cast<const v4u*>(fbase + j * 32 * BK + ks * 1024) ^ 0x80808080u;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          v8h xa[TI];
-#pragma unroll
-          for (int i = 0; i < TI; ++i)
-            xa[i] = *reinterpret_cast<const v8h*>(sA + (wm * Cfg::WM + i * 32 + (lane & 31)) * kRowBytes +
-                                                  (32 * ks + 16 * (lane >> 5) + 8 * t) * 2);
-#pragma unroll
-          for (int j = 0; j < TJ; ++j) {
-            const v8h wh = codes_to_half8(wu[j], t);
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-              acc[i][j] = __builtin_bit_cast(
-                  v16i, __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[i], wh, __builtin_bit_cast(v16f, acc[i][j]), 0, 0, 0));
-          }
-        }
-      }
-    }
-    wait_lds_and_sync();                                             // the parked rows and this weight buffer are read before they are written again
-  };
-
-  wait_lds_and_sync();                                               // every wave is done with the slab ring
-  [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
-    (request(U, std::integral_constant<int, U>{}), ...);
-    // whole groups of kDepth positions, one code path and no way out inside a group
-    for (int s = 0; s < n_slabs; s += kDepth) (iteration(s + U, std::integral_constant<int, U>{}), ...);
-  }(std::make_integer_sequence<int, kDepth>{});
-  // the requests repeated past the end are still on their way into registers and LDS
-  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-  wait_lds_and_sync();
-#pragma unroll
-  for (int j = 0; j < TJ; ++j)
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      v16f y = __builtin_bit_cast(v16f, acc[i][j]);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) y[e] *= back[j];
-      acc[i][j] = __builtin_bit_cast(v16i, y);
-    }
-}
-
 // bias, rounding to fp16, and stores, through LDS (the slab buffers are free by now).  Neighbouring lanes hold
 // neighbouring columns of the same rows; an even/odd lane pair swaps halves so that each lane has two adjacent
 // columns (4 bytes): the even lane of row e, the odd lane of row e + 1.  A wave parks 64 (or 32) rows of its
@@ -568,16 +433,13 @@ __device__ __forceinline__ void load_column_terms(const GemmArgs& a, const WaveP
 // kCoded: the output goes through an activation, takes a residual and / or leaves in blockwise-coded form
 // (store_tile_coded).
 // ------------------------------------------------------------------------------------------------
-// kDense: the critical columns are handled by dense_critical_columns after the loop instead of through fp16 slabs
-// and the gather (the kernel decides; the two cases are compiled apart, see k_gemm_mixed).
-template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kDense>
+template <class Cfg, bool kTap, bool kFull, bool kCoded>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
   constexpr int TI = Cfg::TI, TJ = Cfg::TJ, NKS = Cfg::NKS, STAGES = Cfg::kStages;
 
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  reset_column_flags(a.flag_reset, a.Kpad);
   int tm, tn;
   if (!tile_of_block(a, blockIdx.x, tm, tn)) return;
   const WavePos<Cfg> p(tm * Cfg::BM, tn * Cfg::BN, wave, lane);
@@ -587,7 +449,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   // columns each: at most crit_slabs of them in Xo / Wo, then at most g_slabs further ones in Xg / Wg; columns
   // beyond those are gathered after the loop) and those of a low-rank adapter (T on the activation side, B on the
   // weight side), which start at slab crit_slabs of Xo / Wo.
-  const int crit_all = kDense ? 0 : ceil_div(n_out, kOutlierSlab);
+  const int crit_all = ceil_div(n_out, kOutlierSlab);
   const int crit_used = min(a.crit_slabs, crit_all);
   const int more_used = a.Xg ? min(a.g_slabs, crit_all - crit_used) : 0;
   const int total_slabs = n_slabs + crit_used + more_used + (a.f_slabs - a.crit_slabs);
@@ -765,9 +627,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   if (s < total_slabs) iteration(s, none{}, no{}, yes{});
   // every wave passed the last barrier after its last LDS read of the ring: the slab buffers are
   // free for the gather staging, which starts with a barrier of its own before writing them
-  if constexpr (kDense)
-    dense_critical_columns<Cfg>(a, p, acc, smem, cs);
-  else if (n_out > kOutlierSlab * (crit_used + more_used))
+  if (n_out > kOutlierSlab * (crit_used + more_used))
     gather_outlier_columns<Cfg>(a, p, acc, smem, kOutlierSlab * (crit_used + more_used), n_out);
   if constexpr (kCoded)
     store_tile_coded<Cfg, kFull>(a, p, acc, bn, smem, wave);
@@ -775,30 +635,266 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
     store_tile<Cfg, kFull>(a, p, acc, bn, smem, wave);
 }
 
-// The tile routine for input with very many critical columns, as a function of its own: the kernels sit at the edge
-// of their register budget, and with this rarely taken path compiled into the same body every one of them spilled
-// registers (up to 320; the gather of single columns next to it ran twice as long).  Its only argument is the
-// address of the kernel's own arguments where the launch put them (a function does not receive that address by
-// itself, and arguments arrive in vector registers: made uniform again here, so that the arguments are read into
-// scalar registers as in the kernel).
-template <class Cfg, bool kTap, bool kFull, bool kCoded>
-__device__ __noinline__ void gemm_tile_dense(uint32_t args_lo, uint32_t args_hi) {
+// Input with very many critical columns (heavy-tailed activations: dense_critical_path; no fp16 slab was prepared
+// then).  Both products of the method in one walk over K, 64 columns (a slab) at a time:
+//   int8:   the codes of X (critical columns hold zeros) times the weight codes, exact, in accumulators of its own;
+//   16-bit: the rows of X itself times the same weight codes, those of columns that are not critical masked to zero (in
+//           such a column every entry is below the threshold, hence finite), turned into fp16 integers in registers
+//           (codes_to_half8) as the decode kernels do.  The column's step c[n] / 127
+//           is applied once to the fp32 sum (against the prepared slabs the weights are not rounded to fp16 after
+//           scaling: at most 2^-11 relative per term).
+// A tile is 128 rows high, a wave owns 64 x 64 of it (two sets of four 32 x 32 accumulators: 128 registers), and
+// everything of a slab comes through one ring of three LDS buffers by global_load_lds_dwordx4, two slabs ahead:
+// codes and weight codes as in the main loop, the rows of X 128 bytes per row, eight rows per instruction.  Row R
+// keeps its 16-byte piece q at place q ^ (R / 2 % 8), which the per-lane source address arranges, so that 16 lanes of a
+// fragment read (neighbouring rows, the same piece) meet every bank once.  The masks of 256 slabs at a time are expanded into LDS (a
+// byte per column).
+// What bounds it: the 24 MFMAs of a wave and slab need 1536 cycles per SIMD (0.64 us at 2.4 GHz).
+template <int kBN>
+struct DenseCfg {
+  using Tile = typename std::conditional<kBN == 256, Cfg5, Cfg0>::type;   // wave positions and the output stages
+  static_assert(Tile::BM == 128 && Tile::BN == kBN && Tile::WM == 64 && Tile::WN == 64, "128 rows, waves of 64 x 64");
+  static constexpr int kCodes = 128 * BK, kRows = 128 * BK * 2, kWeights = kBN * BK;
+  static constexpr int kStage = kCodes + kRows + kWeights, kStages = 3;
+  static constexpr int kMaskSlabs = 256;
+  static constexpr int LDS_BYTES = kStages * kStage + kMaskSlabs * BK;
+  static constexpr int X_DMA = 128 * BK * 2 / 1024 / Tile::kWaves;
+  static constexpr int kPerSlab = Tile::A_DMA + X_DMA + Tile::B_DMA;       // requests per wave and slab
+  static_assert(LDS_BYTES >= Tile::RING_BYTES && LDS_BYTES <= 160 * 1024, "LDS");
+};
+
+template <int kBN>
+__device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, int8_t* smem) {
+  using D = DenseCfg<kBN>;
+  using Cfg = typename D::Tile;
+  constexpr int TI = Cfg::TI, TJ = Cfg::TJ;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const WavePos<Cfg> p(m0, n0, wave, lane);
+  const int n_slabs = a.Kpad / BK, last = n_slabs - 1;
+  int8_t* s_mask = smem + D::kStages * D::kStage;
+
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem + wave * (kWave * 16);
+  // the codes: a scalar address per slab and a constant offset per lane and request (the loop's vector instructions
+  // are what it has to save); the rows of X: a pointer per request
+  const int8_t* baseA = dma_source(a.Xq, m0, n_slabs, 0, Cfg::kWaves, wave, 0);
+  const int8_t* baseB = dma_source(a.Wt, n0, n_slabs, 0, Cfg::kWaves, wave, 0);
+  const uint16_t* srcX[D::X_DMA];
+  const int piece = 8 * ((lane & 7) ^ (4 * (wave & 1) + (lane >> 4)));   // first column of this lane's piece of a row
+#pragma unroll
+  for (int j = 0; j < D::X_DMA; ++j)
+    srcX[j] = a.X + (size_t)min(m0 + 8 * (j * Cfg::kWaves + wave) + (lane >> 3), a.M - 1) * a.ldx + piece;
+  const int whole_slabs = a.K / BK;
+  // request d of slab s into buffer `stage`
+  auto request = [&](int s, int stage, int d) __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + stage * D::kStage;
+    if (d < Cfg::A_DMA) {
+      dma16_scalar_base(baseA + (size_t)s * kBlockBytes + d * Cfg::kWaves * 1024, lane * 16, dst + d * Cfg::kWaves * 1024);
+    } else if (d < Cfg::A_DMA + D::X_DMA) {
+      const int j = d - Cfg::A_DMA;
+      const uint16_t* src = srcX[j] + (size_t)s * BK;
+      // a piece beyond the end of the row (the padding of K; K is a multiple of 16) is filled with mask bytes: finite
+      // numbers, and its weights are masked to zero
+      if (s >= whole_slabs && s * BK + piece >= a.K) src = reinterpret_cast<const uint16_t*>(a.mask);
+      dma16(src, dst + D::kCodes + j * Cfg::kWaves * 1024);
+    } else {
+      const int j = d - Cfg::A_DMA - D::X_DMA;
+      dma16_scalar_base(baseB + (size_t)s * kBlockBytes + j * Cfg::kWaves * 1024, lane * 16,
+                        dst + D::kCodes + D::kRows + j * Cfg::kWaves * 1024);
+    }
+  };
+  auto fill_masks = [&](int s0) {
+    const int words = min(D::kMaskSlabs, n_slabs - s0) * (BK / 4);
+    for (int t = threadIdx.x; t < words; t += Cfg::kThreads)
+      reinterpret_cast<uint32_t*>(s_mask)[t] = reinterpret_cast<const uint32_t*>(a.mask + (size_t)s0 * BK)[t] * 0xffu;   // bytes of 0 or 1
+  };
+
+  struct Frags {
+    v4i x[TI], w[TJ];        // codes of both sides, one k-step
+    v4u xf[2][TI], mk;       // rows of X, the two halves of the k-step; 0xff per critical column
+  };
+  const int a_off = (p.wm * Cfg::WM / 32) * 2048 + lane * 16;
+  const int b_off = D::kCodes + D::kRows + (p.wn * Cfg::WN / 32) * 2048 + lane * 16;
+  int x_off[TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) x_off[i] = D::kCodes + (p.wm * Cfg::WM + i * 32 + p.lr) * (BK * 2);
+  // read n (0 .. kReads - 1) of the fragments of k-step ks of slab s, in the order in which they are needed
+  constexpr int kReads = TI + TJ + 1 + 2 * TI;
+  auto read_frag = [&](int s, int stage, int ks, Frags& f, int n) __attribute__((always_inline)) {
+    const int8_t* base = smem + stage * D::kStage;
+    if (n == 2) {
+      f.mk = *reinterpret_cast<const v4u*>(s_mask + (s % D::kMaskSlabs) * BK + (2 * ks + p.lg) * 16);
+    } else if (n < 5) {
+      const int e = n > 2;
+      if (n == 0 || n == 3)
+        f.x[e] = *reinterpret_cast<const v4i*>(base + a_off + e * 2048 + ks * 1024);
+      else
+        f.w[e] = *reinterpret_cast<const v4i*>(base + b_off + e * 2048 + ks * 1024);
+    } else {
+      const int t = (n - 5) / TI, i = (n - 5) % TI;
+      const int q = 4 * ks + 2 * p.lg + t;                             // columns 8 q .. 8 q + 8 of the slab
+      f.xf[t][i] = *reinterpret_cast<const v4u*>(base + x_off[i] + ((q ^ (p.lr >> 1 & 7)) * 16));
+    }
+  };
+  static_assert(TI == 2 && TJ == 2, "the orders of reads, conversions and MFMAs are written for 2 x 2 tiles");
+
+  v16i acc[TI][TJ];
+  v16f accf[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0, accf[i][j][e] = 0.0f;
+
+  Frags f[2];
+  // In iteration s slab s + 2 is requested into the buffer of slab s - 1, which every wave finished reading before the
+  // barrier of iteration s - 1; past the end the last slab is asked for again, so that the count in flight is fixed.
+  // One k-step: 12 MFMAs, and between any two of them one fragment read of the next k-step, the conversion of four
+  // weight codes (the first ones ahead of their MFMA by four) and at times a request, fenced so that they stay there: a
+  // wave issues in order, and a burst of reads that finds the LDS queue full holds up the MFMAs behind it (with the
+  // reads in one go a slab took 1.05 us).
+  auto multiply = [&](const Frags& g, auto&& between) __attribute__((always_inline)) {
+    v2u wh[2 * TJ][2];
+#pragma unroll
+    for (int n = 0; n < 12; ++n) {
+      if (n < 4) {
+        const int i = n & 1, j = n >> 1;
+        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(g.x[i], g.w[j], acc[i][j], 0, 0, 0);
+      } else {
+        const int c = (n - 4) >> 1, t = c >> 1, j = c & 1, i = n & 1;
+        const v4u h = v4u{wh[c][0][0], wh[c][0][1], wh[c][1][0], wh[c][1][1]};
+        accf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, g.xf[t][i]), __builtin_bit_cast(v8h, h), accf[i][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      between(n);
+      if (n < 8) {
+        const int c = n >> 1, t = c >> 1, j = c & 1, d = n & 1;
+        wh[c][d] = codes_to_half4(((uint32_t)g.w[j][2 * t + d] & g.mk[2 * t + d]) ^ 0x80808080u);   // other columns: zero
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  __syncthreads();                                                     // (a second tile of this workgroup: LDS is free)
+#pragma unroll
+  for (int d = 0; d < D::kPerSlab; ++d) request(0, 0, d);
+#pragma unroll
+  for (int d = 0; d < D::kPerSlab; ++d) request(min(1, last), 1, d);
+  fill_masks(0);
+  wait_slab_and_sync<D::kPerSlab>();
+#pragma unroll
+  for (int n = 0; n < kReads; ++n) read_frag(0, 0, 0, f[0], n);
+  int stage = 0, s = 0;
+  for (int s0 = D::kMaskSlabs;; s0 += D::kMaskSlabs) {
+    for (; s < min(s0, n_slabs); ++s) {
+      const int stage1 = stage == 2 ? 0 : stage + 1, stage2 = stage1 == 2 ? 0 : stage1 + 1;
+      multiply(f[0], [&](int n) __attribute__((always_inline)) {
+        if (n < kReads) read_frag(s, stage, 1, f[1], n);
+        // the requests of slab s + 2
+        const int d = n * D::kPerSlab / 12;
+        if (d < D::kPerSlab && (d * 12 + D::kPerSlab - 1) / D::kPerSlab == n) request(min(s + 2, last), stage2, d);
+      });
+      multiply(f[1], [&](int n) __attribute__((always_inline)) {
+        // slab s + 1 has landed for every wave
+        if (n == 0) wait_slab_and_sync<D::kPerSlab>();
+        if (n < kReads) read_frag(min(s + 1, last), stage1, 0, f[0], n);
+      });
+      stage = stage1;
+    }
+    if (s0 >= n_slabs) break;
+    // (a loop of its own: with the loads of the masks inside it the compiler waited for every request in flight at the
+    // end of each slab)
+    __syncthreads();                                                   // every wave has read the masks so far
+    fill_masks(s0);
+    __syncthreads();
+    read_frag(s0, stage, 0, f[0], 2);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");                   // the requests repeated past the end
+
+  float cs[TJ], bn[TJ];
+  load_column_terms<Cfg>(a, p, cs, bn);
+  if (a.tap_acc) tap_accumulators<Cfg>(a, p, acc);
+  float step[TJ];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) step[j] = a.c[min(p.nw + j * 32 + p.lr, a.N - 1)] / 127.0f;
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    float rm[16];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const v4f v = *reinterpret_cast<const v4f*>(a.r + p.mw + i * 32 + 8 * q + 4 * p.lg);
+      rm[4 * q] = v[0], rm[4 * q + 1] = v[1], rm[4 * q + 2] = v[2], rm[4 * q + 3] = v[3];
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      v16f y;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) y[e] = (float)acc[i][j][e] * (rm[e] * cs[j]) + accf[i][j][e] * step[j];
+      acc[i][j] = __builtin_bit_cast(v16i, y);
+    }
+  }
+  // an adapter's low-rank operands: at most two slabs, straight from where they were prepared
+  for (int fs = a.crit_slabs; fs < a.f_slabs; ++fs) {
+    const int8_t* xs = reinterpret_cast<const int8_t*>(a.Xo) + ((size_t)(p.mw >> 8) * a.f_slabs + fs) * kBlockBytes + (p.mw & 255) * BK + lane * 16;
+    const int8_t* ws = reinterpret_cast<const int8_t*>(a.Wo) + ((size_t)(p.nw >> 8) * a.f_slabs + fs) * kBlockBytes + (p.nw & 255) * BK + lane * 16;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      v8h xa[TI], wb[TJ];
+#pragma unroll
+      for (int i = 0; i < TI; ++i) xa[i] = *reinterpret_cast<const v8h*>(xs + i * 2048 + ks * 1024);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) wb[j] = *reinterpret_cast<const v8h*>(ws + j * 2048 + ks * 1024);
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          acc[i][j] = __builtin_bit_cast(v16i, __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[i], wb[j], __builtin_bit_cast(v16f, acc[i][j]), 0, 0, 0));
+    }
+  }
+  if (a.codes || a.residual || a.gelu)
+    store_tile_coded<Cfg, false>(a, p, acc, bn, smem, wave);
+  else
+    store_tile<Cfg, false>(a, p, acc, bn, smem, wave);
+}
+
+// ... as a function of its own: the kernels sit at the edge of their register budget, and with this rarely taken path
+// compiled into the same body every one of them spilled registers.  It walks the 128-row pieces of the kernel's
+// BM x BN tile.  Its address arguments are that of the kernel's own arguments where the launch put them (a function
+// does not receive that address by itself, and arguments arrive in vector registers: made uniform again here, so that
+// the arguments are read into scalar registers as in the kernel) and that of the LDS buffers (named in here, their
+// address would be read from memory again for every use).
+template <int kBN>
+__device__ __noinline__ void gemm_tile_dense(uint32_t args_lo, uint32_t args_hi, uint32_t lds, uint32_t bm, uint32_t bn) {
+  int8_t* smem = (int8_t*)(__attribute__((address_space(3))) int8_t*)(uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
   using constant_bytes = const __attribute__((address_space(4))) char*;
   const uint64_t address = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)args_lo) |
                            (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)args_hi) << 32;
   const GemmArgs a = *(const GemmArgs*)(constant_bytes)address;
-  gemm_tile<Cfg, kTap, kFull, kCoded, true>(a);
+  const int BM = __builtin_amdgcn_readfirstlane((int)bm), BN = __builtin_amdgcn_readfirstlane((int)bn);
+  int tm, tn;
+  if (!tile_of_block(a, blockIdx.x, tm, tn)) return;
+  for (int n0 = tn * BN; n0 < min((tn + 1) * BN, a.N); n0 += kBN)
+    for (int m0 = tm * BM; m0 < min((tm + 1) * BM, a.M); m0 += 128) dense_tile<kBN>(a, m0, n0, smem);
 }
+
+template <class Cfg>
+using DenseOf = DenseCfg<Cfg::kWaves == 8 ? 256 : 128>;
+template <class Cfg>
+constexpr int kLaunchLds = Cfg::LDS_BYTES > DenseOf<Cfg>::LDS_BYTES ? Cfg::LDS_BYTES : DenseOf<Cfg>::LDS_BYTES;
 
 template <class Cfg, bool kTap, bool kFull, bool kCoded>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixed(const GemmArgs a) {
   const int n_out = __builtin_amdgcn_readfirstlane(*a.n_out);
+  reset_column_flags(a.flag_reset, a.Kpad);
   if (dense_critical_path(n_out, a.crit_slabs, a.dense_from, a.W_master != nullptr)) {
     const uint64_t address = (uint64_t)(const char*)__builtin_amdgcn_kernarg_segment_ptr();   // `a` is the first argument
-    gemm_tile_dense<Cfg, kTap, kFull, kCoded>((uint32_t)address, (uint32_t)(address >> 32));
+    extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+    uint32_t lds = (uint32_t)(uintptr_t)smem;
+    asm volatile("" : "+s"(lds));                                      // (else the compiler names it in the function after all)
+    gemm_tile_dense<Cfg::kWaves == 8 ? 256 : 128>((uint32_t)address, (uint32_t)(address >> 32), lds, Cfg::BM, Cfg::BN);
     return;
   }
-  gemm_tile<Cfg, kTap, kFull, kCoded, false>(a);
+  gemm_tile<Cfg, kTap, kFull, kCoded>(a);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -813,7 +909,7 @@ static hipError_t ensure_lds_attribute() {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_set[dev]) return hipSuccess;
   const void* fn = reinterpret_cast<const void*>(&k_gemm_mixed<Cfg, kTap, kFull, kCoded>);
-  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLaunchLds<Cfg>);
   if (e == hipSuccess) attr_set[dev] = true;
   return e;
 }
@@ -822,7 +918,7 @@ template <class Cfg, bool kTap, bool kFull, bool kCoded>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t stream) {
   if (hipError_t e = ensure_lds_attribute<Cfg, kTap, kFull, kCoded>(); e != hipSuccess) return e;
   const int grid = ceil_div(a.tiles_m * a.tiles_n, 8) * 8;
-  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded>), dim3(grid), dim3(Cfg::kThreads), Cfg::LDS_BYTES, stream, a);
+  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded>), dim3(grid), dim3(Cfg::kThreads), kLaunchLds<Cfg>, stream, a);
   return hipGetLastError();
 }
 
@@ -843,13 +939,6 @@ static hipError_t launch_cfg(GemmArgs a, hipStream_t stream) {
 }
 
 // every instantiation launch_cfg can reach
-// The tile configurations, by the number a caller can force one with (gemm.h):
-using Cfg0 = GemmCfg<128, 128, 2, 2, 3, 3>;   // 49 KB of LDS: three workgroups per CU
-using Cfg1 = GemmCfg<256, 128, 2, 2, 3, 2>;
-using Cfg2 = GemmCfg<128, 256, 2, 2, 3, 2>;
-using Cfg3 = GemmCfg<256, 256, 2, 4, 3, 2>;
-using Cfg4 = GemmCfg<256, 256, 2, 4, 4, 2>;   // the large tile: whole rounds of one tile per CU
-using Cfg5 = GemmCfg<128, 256, 2, 4, 4, 2>;   // remainders and less than one round of large tiles
 template <class Cfg>
 static hipError_t prepare_cfg() {
   hipError_t e = ensure_lds_attribute<Cfg, true, false, false>();
@@ -871,8 +960,8 @@ hipError_t prepare_gemm_kernels() {
 }
 
 static hipError_t launch_variant(const GemmArgs& a, int variant, hipStream_t stream) {
-  // coded output with blocks wider than the 128-column tiles: the 256-column tile of the same height class
-  if (a.codes && a.code_log_block > 7 && (variant == 0 || variant == 1)) variant = 2;
+  // coded output with blocks wider than the 128-column tiles (the dense pass of four-wave kernels has such tiles too)
+  if (a.codes && a.code_log_block > 7 && variant < 3) variant = 5;
   switch (variant) {
     case 1: return launch_cfg<Cfg1>(a, stream);
     case 2: return launch_cfg<Cfg2>(a, stream);
