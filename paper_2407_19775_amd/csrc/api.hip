@@ -80,14 +80,17 @@ struct Workspace {
   float* lora_part;    // adapter only: partial sums of the down-projection when K is split between workgroups
   int8_t* xq;          // Mpad x Kpad codes, blocked layout
   uint16_t* xf;        // decode path only: [64][Kpad] fp16
-  float* partial;      // decode path only: split-K partial outputs
+  float* partial;      // split-K partial outputs, or null
+  int gemm_splits;     // ranges of K of the tiled GEMM, 1: not split
   uint16_t* h;         // coded output only, where the encoder runs as a kernel of its own: [M][N] fp16
   size_t bytes;
 };
 // r: rank of an adapter (0: none).  exit_block: block size of a coded output (0: plain output).
 static bool exit_fuses(int M, int K, int N, int block);
 // gathered_rows: room for further slabs of critical columns (not in the fixed-size static workspace)
-static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_block = 0, bool gathered_rows = true) {
+// split_k: room for the partial outputs of a tiled GEMM whose K is split
+static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_block = 0, bool gathered_rows = true,
+                       bool split_k = true) {
   const size_t Kpad = packed_k(K), Mpad = packed_n(M), Npad = packed_n(N);
   Workspace w;
   size_t off = 0;
@@ -128,6 +131,8 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
     if (pb == 0) pb = (size_t)Mc * N * sizeof(float);
     if (pb) w.partial = reinterpret_cast<float*>(take(pb));
   }
+  w.gemm_splits = split_k && M > kSkinnyChunkedMaxM ? plan_gemm_splits(M, K, N) : 1;
+  if (w.gemm_splits > 1) w.partial = reinterpret_cast<float*>(take((size_t)w.gemm_splits * M * N * sizeof(float)));
   w.lora_t = r > 0 ? reinterpret_cast<uint16_t*>(take((size_t)M * kLoraMaxRank * 2)) : nullptr;
   w.lora_part = nullptr;
   if (r > 0 && M > 0) {
@@ -317,7 +322,10 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   if (lora && (!lora->A || !lora->B || !aligned(lora->A, 16) || !aligned(lora->B, 16) ||
                (lora->T_out && !aligned(lora->T_out, 16))))
     return MMD8_E_ARG;
-  const Workspace ws = carve(workspace, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, gathered_rows);
+  Workspace ws = carve(workspace, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, gathered_rows);
+  // a workspace that was sized for more rows (where K is not split) still serves fewer: without the split
+  if (ws.gemm_splits > 1 && workspace_bytes < ws.bytes)
+    ws = carve(workspace, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, gathered_rows, false);
   if (workspace_bytes < ws.bytes) return MMD8_E_WORKSPACE;
   // a coded output is written by the layer's last kernel where that is possible, otherwise by the encoder after it
   const bool encodes = exit && exit->block > 0;
@@ -526,6 +534,8 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     g.Wg = ws.wg;
     g.g_slabs = ws.g_slabs;
     g.dense_from = ws.dense_from;
+    g.splits = ws.gemm_splits;
+    g.partial = ws.gemm_splits > 1 ? ws.partial : nullptr;
     if (readings) {
       g.W_master = readings->W_master;
       g.ldw_master = readings->ldw;

@@ -88,6 +88,10 @@ struct GemmArgs {
   const uint16_t* Wg;    // likewise for the weight side (both or neither)
   int g_slabs;
   int dense_from;        // critical columns from which the call takes the dense pass (plan_critical_columns)
+  // Split K (plan_gemm_splits): every tile is shared out between `splits` workgroups, slabs_per_split slabs of codes
+  // each, whose fp32 sums meet in partial [splits][M][N].
+  float* partial;        // null: no split
+  int splits, slabs_per_split;   // (slabs_per_split is filled by the launcher)
 };
 
 // Workgroup 0 of the kernel that ends a call puts the scan's column flags back to zero (the next
@@ -100,7 +104,11 @@ __device__ inline void reset_column_flags(uint8_t* flags, int Kpad) {
 }
 
 // variant selects a tile configuration, 0..5 (anything else: automatic); every variant computes the same result.
-hipError_t launch_gemm_mixed(const GemmArgs& a, int variant, hipStream_t stream);
+// With `partial` given and the choice automatic, K is split into a.splits ranges.
+hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream);
+// Ranges of K for a call of more than 128 rows whose 128 x 256 tiles leave half of the chip or more without a
+// workgroup; 1: no split.
+int plan_gemm_splits(int M, int K, int N);
 // sets the LDS attribute of every GEMM kernel on the current device (otherwise done by a kernel's first launch,
 // which must then not happen while a stream is being captured)
 hipError_t prepare_gemm_kernels();

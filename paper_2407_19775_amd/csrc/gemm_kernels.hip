@@ -23,7 +23,9 @@
 #include "codec_device.h"
 #include "common.h"
 #include "gemm.h"
+#include "launchers.h"
 #include "operand_layout.h"
+#include "skinny.h"
 
 namespace mmd8 {
 
@@ -96,12 +98,16 @@ __device__ inline void sync_only() { asm volatile("s_barrier" : : : "memory"); }
 // block rows fastest), so the 32 tiles an XCD works on at once share 8 activation panels and 4 weight panels:
 // 12 panel streams through its L2 instead of the 18 of a plain rows-fastest order with 16 tile rows (measured on
 // the 70B-shaped linears at 4096 tokens: 1.4-2.1 % faster; identical for up to 8 tile rows).
-__device__ inline bool tile_of_block(const GemmArgs& a, int bid, int& tm, int& tn) {
+// Split K: the ranges of K one after the other, each over all tiles, so that an XCD reads few ranges of both operands
+// and a weight byte mostly comes into one L2 only.
+__device__ inline bool tile_of_block(const GemmArgs& a, int bid, int& tm, int& tn, int& split) {
   constexpr int kBlockRows = 8, kBandCols = 4;
   const int n_tiles = a.tiles_m * a.tiles_n;
-  const int per_xcd = ceil_div(n_tiles, 8);
-  const int logical = (bid % 8) * per_xcd + bid / 8;
-  if (logical >= n_tiles) return false;
+  const int per_xcd = ceil_div(n_tiles * a.splits, 8);
+  int logical = (bid % 8) * per_xcd + bid / 8;
+  if (logical >= n_tiles * a.splits) return false;
+  split = logical / n_tiles;
+  logical -= split * n_tiles;
   const int band_tiles = a.tiles_m * kBandCols;                    // (every band but the last is full)
   const int band = logical / band_tiles;
   const int w = min(kBandCols, a.tiles_n - band * kBandCols);      // width of this band
@@ -133,7 +139,8 @@ struct WavePos {
         lg(lane_ >> 5), mw(m0_ + (wave / Cfg::WAVES_N) * Cfg::WM), nw(n0_ + (wave % Cfg::WAVES_N) * Cfg::WN) {}
 };
 
-template <class Cfg>
+// (split K: the ranges add up in a buffer that the launcher zeroed; integers, so in any order)
+template <class Cfg, bool kSplit>
 __device__ __forceinline__ void tap_accumulators(const GemmArgs& a, const WavePos<Cfg>& p, v16i (&acc)[Cfg::TI][Cfg::TJ]) {
 #pragma unroll
   for (int i = 0; i < Cfg::TI; ++i)
@@ -142,7 +149,12 @@ __device__ __forceinline__ void tap_accumulators(const GemmArgs& a, const WavePo
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int m = p.mw + i * 32 + 8 * (e / 4) + 4 * p.lg + (e % 4), n = p.nw + j * 32 + p.lr;
-        if (m < a.M && n < a.N) a.tap_acc[(size_t)m * a.tap_ld + n] = acc[i][j][e];
+        if (m < a.M && n < a.N) {
+          if constexpr (kSplit)
+            atomicAdd(a.tap_acc + (size_t)m * a.tap_ld + n, acc[i][j][e]);
+          else
+            a.tap_acc[(size_t)m * a.tap_ld + n] = acc[i][j][e];
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -415,6 +427,26 @@ __device__ __forceinline__ void store_tile_coded(const GemmArgs& a, const WavePo
   }
 }
 
+// Split K: the fp32 sums of this workgroup's range, [split][M][N]; the kernel that adds the ranges up
+// (launch_add_splits) does what the stores above do.  32 lanes write 128 contiguous bytes of a row.
+template <class Cfg>
+__device__ __forceinline__ void store_partial(const GemmArgs& a, const WavePos<Cfg>& p, v16i (&acc)[Cfg::TI][Cfg::TJ], int split) {
+#pragma unroll
+  for (int i = 0; i < Cfg::TI; ++i)
+#pragma unroll
+    for (int j = 0; j < Cfg::TJ; ++j) {
+      const v16f y = __builtin_bit_cast(v16f, acc[i][j]);
+      const int n = p.nw + j * 32 + p.lr;
+      float* dst = a.partial + ((size_t)split * a.M + p.mw + i * 32 + 4 * p.lg) * a.N + n;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int row = 8 * (e / 4) + (e % 4);
+        if (p.mw + i * 32 + 4 * p.lg + row < a.M && n < a.N) dst[(size_t)row * a.N] = y[e];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 template <class Cfg>
 __device__ __forceinline__ void load_column_terms(const GemmArgs& a, const WavePos<Cfg>& p, float (&cs)[Cfg::TJ],
                                          float (&bn)[Cfg::TJ]) {
@@ -433,17 +465,22 @@ __device__ __forceinline__ void load_column_terms(const GemmArgs& a, const WaveP
 // kCoded: the output goes through an activation, takes a residual and / or leaves in blockwise-coded form
 // (store_tile_coded).
 // ------------------------------------------------------------------------------------------------
-template <class Cfg, bool kTap, bool kFull, bool kCoded>
+// kSplit: the workgroup multiplies one of a.splits ranges of K (slabs of codes and of fp16 operands alike) and leaves
+// fp32 sums.
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
   constexpr int TI = Cfg::TI, TJ = Cfg::TJ, NKS = Cfg::NKS, STAGES = Cfg::kStages;
 
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  int tm, tn;
-  if (!tile_of_block(a, blockIdx.x, tm, tn)) return;
+  int tm, tn, split;
+  if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;
   const WavePos<Cfg> p(tm * Cfg::BM, tn * Cfg::BN, wave, lane);
-  const int n_slabs = a.Kpad / BK;
+  const int all_slabs = a.Kpad / BK;
+  // this workgroup's slabs of codes
+  const int first = kSplit ? split * a.slabs_per_split : 0;
+  const int n_slabs = kSplit ? min(a.slabs_per_split, all_slabs - first) : all_slabs;
   const int n_out = __builtin_amdgcn_readfirstlane(*a.n_out);
   // Behind the slabs of codes, through the same ring: the fp16 slabs of the critical columns that are in use (32
   // columns each: at most crit_slabs of them in Xo / Wo, then at most g_slabs further ones in Xg / Wg; columns
@@ -452,7 +489,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   const int crit_all = ceil_div(n_out, kOutlierSlab);
   const int crit_used = min(a.crit_slabs, crit_all);
   const int more_used = a.Xg ? min(a.g_slabs, crit_all - crit_used) : 0;
-  const int total_slabs = n_slabs + crit_used + more_used + (a.f_slabs - a.crit_slabs);
+  const int all_fp16 = crit_used + more_used + (a.f_slabs - a.crit_slabs);
+  const int first_fp16 = kSplit ? all_fp16 * split / a.splits : 0;     // ... and of fp16 operands
+  const int total_slabs = n_slabs + (kSplit ? all_fp16 * (split + 1) / a.splits - first_fp16 : all_fp16);
   // from this tile's slabs in Xo / Wo to its further slabs in Xg / Wg: the same place in a panel, other panel sizes
   // (two allocations: the distance as a difference of addresses, not of pointers)
   const ptrdiff_t to_more_x = (ptrdiff_t)(reinterpret_cast<uintptr_t>(a.Xg) - reinterpret_cast<uintptr_t>(a.Xo)) +
@@ -470,12 +509,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   const int8_t* srcWo[Cfg::B_DMA];
 #pragma unroll
   for (int j = 0; j < Cfg::A_DMA; ++j) {
-    srcA[j] = dma_source(a.Xq, p.m0, n_slabs, j, Cfg::kWaves, wave, lane);
+    srcA[j] = dma_source(a.Xq, p.m0, all_slabs, j, Cfg::kWaves, wave, lane) + (ptrdiff_t)first * kBlockBytes;
     srcXo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Xo), p.m0, a.f_slabs, j, Cfg::kWaves, wave, lane);
   }
 #pragma unroll
   for (int j = 0; j < Cfg::B_DMA; ++j) {
-    srcB[j] = dma_source(a.Wt, p.n0, n_slabs, j, Cfg::kWaves, wave, lane);
+    srcB[j] = dma_source(a.Wt, p.n0, all_slabs, j, Cfg::kWaves, wave, lane) + (ptrdiff_t)first * kBlockBytes;
     srcWo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Wo), p.n0, a.f_slabs, j, Cfg::kWaves, wave, lane);
   }
   // request d (0 .. DMA_PER_SLAB-1) of the slab at position `pos` of the ring's sequence: the A rows first, then the
@@ -484,7 +523,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   auto issue_dma = [&](int pos, int stage, int d, auto fp16_tag) {
     constexpr bool kF = decltype(fp16_tag)::value;
     const uint32_t base = lds0 + stage * Cfg::STAGE_BYTES + wave * (kWave * 16);
-    const int f = pos - n_slabs;                                    // among the fp16 slabs in use
+    const int f = pos - n_slabs + first_fp16;                       // among the fp16 slabs in use
     // its place: slab f of Xo / Wo, slab f - crit_used of Xg / Wg, or an adapter's slab behind the crit_slabs of Xo / Wo
     ptrdiff_t off = (ptrdiff_t)(!kF ? pos : f < crit_used ? f : f - crit_used - more_used + a.crit_slabs) * kBlockBytes;
     if (kF && f >= crit_used && f < crit_used + more_used)
@@ -620,16 +659,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   for (; s < n_slabs && s + AHEAD < total_slabs; ++s) iteration(s, halves{}, yes{}, no{});  // the first fp16 slabs requested
   for (; s < n_slabs && s + 1 < total_slabs; ++s) iteration(s, none{}, yes{}, no{});
   if (s < n_slabs) iteration(s++, none{}, no{}, no{});              // the last slab when nothing follows it
-  if constexpr (kTap) tap_accumulators<Cfg>(a, p, acc);
+  if constexpr (kTap) tap_accumulators<Cfg, kSplit>(a, p, acc);
   dequantize_in_place<Cfg>(p, acc, a.r + p.m0, cs);
   for (; s + AHEAD < total_slabs; ++s) iteration(s, halves{}, yes{}, yes{});
   for (; s + 1 < total_slabs; ++s) iteration(s, none{}, yes{}, yes{});
   if (s < total_slabs) iteration(s, none{}, no{}, yes{});
   // every wave passed the last barrier after its last LDS read of the ring: the slab buffers are
   // free for the gather staging, which starts with a barrier of its own before writing them
-  if (n_out > kOutlierSlab * (crit_used + more_used))
+  if (n_out > kOutlierSlab * (crit_used + more_used) && (!kSplit || split == a.splits - 1))
     gather_outlier_columns<Cfg>(a, p, acc, smem, kOutlierSlab * (crit_used + more_used), n_out);
-  if constexpr (kCoded)
+  if constexpr (kSplit)
+    store_partial<Cfg>(a, p, acc, split);
+  else if constexpr (kCoded)
     store_tile_coded<Cfg, kFull>(a, p, acc, bn, smem, wave);
   else
     store_tile<Cfg, kFull>(a, p, acc, bn, smem, wave);
@@ -664,14 +705,15 @@ struct DenseCfg {
 };
 
 template <int kBN>
-__device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, int8_t* smem) {
+__device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, int split, int8_t* smem) {
   using D = DenseCfg<kBN>;
   using Cfg = typename D::Tile;
   constexpr int TI = Cfg::TI, TJ = Cfg::TJ;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const WavePos<Cfg> p(m0, n0, wave, lane);
-  const int n_slabs = a.Kpad / BK, last = n_slabs - 1;
+  const int n_slabs = a.Kpad / BK;
+  const int first = split * a.slabs_per_split, end = min(first + a.slabs_per_split, n_slabs), last = end - 1;
   int8_t* s_mask = smem + D::kStages * D::kStage;
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem + wave * (kWave * 16);
@@ -704,7 +746,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
     }
   };
   auto fill_masks = [&](int s0) {
-    const int words = min(D::kMaskSlabs, n_slabs - s0) * (BK / 4);
+    const int words = min(D::kMaskSlabs, end - s0) * (BK / 4);
     for (int t = threadIdx.x; t < words; t += Cfg::kThreads)
       reinterpret_cast<uint32_t*>(s_mask)[t] = reinterpret_cast<const uint32_t*>(a.mask + (size_t)s0 * BK)[t] * 0xffu;   // bytes of 0 or 1
   };
@@ -723,7 +765,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
   auto read_frag = [&](int s, int stage, int ks, Frags& f, int n) __attribute__((always_inline)) {
     const int8_t* base = smem + stage * D::kStage;
     if (n == 2) {
-      f.mk = *reinterpret_cast<const v4u*>(s_mask + (s % D::kMaskSlabs) * BK + (2 * ks + p.lg) * 16);
+      f.mk = *reinterpret_cast<const v4u*>(s_mask + ((s - first) % D::kMaskSlabs) * BK + (2 * ks + p.lg) * 16);
     } else if (n < 5) {
       const int e = n > 2;
       if (n == 0 || n == 3)
@@ -777,16 +819,16 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
   };
   __syncthreads();                                                     // (a second tile of this workgroup: LDS is free)
 #pragma unroll
-  for (int d = 0; d < D::kPerSlab; ++d) request(0, 0, d);
+  for (int d = 0; d < D::kPerSlab; ++d) request(first, 0, d);
 #pragma unroll
-  for (int d = 0; d < D::kPerSlab; ++d) request(min(1, last), 1, d);
-  fill_masks(0);
+  for (int d = 0; d < D::kPerSlab; ++d) request(min(first + 1, last), 1, d);
+  fill_masks(first);
   wait_slab_and_sync<D::kPerSlab>();
 #pragma unroll
-  for (int n = 0; n < kReads; ++n) read_frag(0, 0, 0, f[0], n);
-  int stage = 0, s = 0;
-  for (int s0 = D::kMaskSlabs;; s0 += D::kMaskSlabs) {
-    for (; s < min(s0, n_slabs); ++s) {
+  for (int n = 0; n < kReads; ++n) read_frag(first, 0, 0, f[0], n);
+  int stage = 0, s = first;
+  for (int s0 = first + D::kMaskSlabs;; s0 += D::kMaskSlabs) {
+    for (; s < min(s0, end); ++s) {
       const int stage1 = stage == 2 ? 0 : stage + 1, stage2 = stage1 == 2 ? 0 : stage1 + 1;
       multiply(f[0], [&](int n) __attribute__((always_inline)) {
         if (n < kReads) read_frag(s, stage, 1, f[1], n);
@@ -801,7 +843,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
       });
       stage = stage1;
     }
-    if (s0 >= n_slabs) break;
+    if (s0 >= end) break;
     // (a loop of its own: with the loads of the masks inside it the compiler waited for every request in flight at the
     // end of each slab)
     __syncthreads();                                                   // every wave has read the masks so far
@@ -813,7 +855,12 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
 
   float cs[TJ], bn[TJ];
   load_column_terms<Cfg>(a, p, cs, bn);
-  if (a.tap_acc) tap_accumulators<Cfg>(a, p, acc);
+  if (a.tap_acc) {
+    if (a.splits > 1)
+      tap_accumulators<Cfg, true>(a, p, acc);
+    else
+      tap_accumulators<Cfg, false>(a, p, acc);
+  }
   float step[TJ];
 #pragma unroll
   for (int j = 0; j < TJ; ++j) step[j] = a.c[min(p.nw + j * 32 + p.lr, a.N - 1)] / 127.0f;
@@ -834,7 +881,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
     }
   }
   // an adapter's low-rank operands: at most two slabs, straight from where they were prepared
-  for (int fs = a.crit_slabs; fs < a.f_slabs; ++fs) {
+  for (int fs = a.crit_slabs; fs < (split == a.splits - 1 ? a.f_slabs : 0); ++fs) {
     const int8_t* xs = reinterpret_cast<const int8_t*>(a.Xo) + ((size_t)(p.mw >> 8) * a.f_slabs + fs) * kBlockBytes + (p.mw & 255) * BK + lane * 16;
     const int8_t* ws = reinterpret_cast<const int8_t*>(a.Wo) + ((size_t)(p.nw >> 8) * a.f_slabs + fs) * kBlockBytes + (p.nw & 255) * BK + lane * 16;
 #pragma unroll
@@ -851,7 +898,9 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
           acc[i][j] = __builtin_bit_cast(v16i, __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[i], wb[j], __builtin_bit_cast(v16f, acc[i][j]), 0, 0, 0));
     }
   }
-  if (a.codes || a.residual || a.gelu)
+  if (a.splits > 1)
+    store_partial<Cfg>(a, p, acc, split);
+  else if (a.codes || a.residual || a.gelu)
     store_tile_coded<Cfg, false>(a, p, acc, bn, smem, wave);
   else
     store_tile<Cfg, false>(a, p, acc, bn, smem, wave);
@@ -871,10 +920,10 @@ __device__ __noinline__ void gemm_tile_dense(uint32_t args_lo, uint32_t args_hi,
                            (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)args_hi) << 32;
   const GemmArgs a = *(const GemmArgs*)(constant_bytes)address;
   const int BM = __builtin_amdgcn_readfirstlane((int)bm), BN = __builtin_amdgcn_readfirstlane((int)bn);
-  int tm, tn;
-  if (!tile_of_block(a, blockIdx.x, tm, tn)) return;
+  int tm, tn, split;
+  if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;
   for (int n0 = tn * BN; n0 < min((tn + 1) * BN, a.N); n0 += kBN)
-    for (int m0 = tm * BM; m0 < min((tm + 1) * BM, a.M); m0 += 128) dense_tile<kBN>(a, m0, n0, smem);
+    for (int m0 = tm * BM; m0 < min((tm + 1) * BM, a.M); m0 += 128) dense_tile<kBN>(a, m0, n0, split, smem);
 }
 
 template <class Cfg>
@@ -882,7 +931,7 @@ using DenseOf = DenseCfg<Cfg::kWaves == 8 ? 256 : 128>;
 template <class Cfg>
 constexpr int kLaunchLds = Cfg::LDS_BYTES > DenseOf<Cfg>::LDS_BYTES ? Cfg::LDS_BYTES : DenseOf<Cfg>::LDS_BYTES;
 
-template <class Cfg, bool kTap, bool kFull, bool kCoded>
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixed(const GemmArgs a) {
   const int n_out = __builtin_amdgcn_readfirstlane(*a.n_out);
   reset_column_flags(a.flag_reset, a.Kpad);
@@ -894,13 +943,13 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixe
     gemm_tile_dense<Cfg::kWaves == 8 ? 256 : 128>((uint32_t)address, (uint32_t)(address >> 32), lds, Cfg::BM, Cfg::BN);
     return;
   }
-  gemm_tile<Cfg, kTap, kFull, kCoded>(a);
+  gemm_tile<Cfg, kTap, kFull, kCoded, kSplit>(a);
 }
 
 // ------------------------------------------------------------------------------------------------
 // The kernels need more LDS than a kernel gets by default; the attribute is set once per instantiation and device,
 // by prepare_gemm_kernels() (called when a workspace is set up) or else by the first launch.
-template <class Cfg, bool kTap, bool kFull, bool kCoded>
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
 static hipError_t ensure_lds_attribute() {
   // per device: the attribute belongs to the device's code object.  Two threads may both find it unset and set
   // it twice, which is harmless.
@@ -908,17 +957,17 @@ static hipError_t ensure_lds_attribute() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_set[dev]) return hipSuccess;
-  const void* fn = reinterpret_cast<const void*>(&k_gemm_mixed<Cfg, kTap, kFull, kCoded>);
+  const void* fn = reinterpret_cast<const void*>(&k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit>);
   const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLaunchLds<Cfg>);
   if (e == hipSuccess) attr_set[dev] = true;
   return e;
 }
 
-template <class Cfg, bool kTap, bool kFull, bool kCoded>
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t stream) {
-  if (hipError_t e = ensure_lds_attribute<Cfg, kTap, kFull, kCoded>(); e != hipSuccess) return e;
-  const int grid = ceil_div(a.tiles_m * a.tiles_n, 8) * 8;
-  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded>), dim3(grid), dim3(Cfg::kThreads), kLaunchLds<Cfg>, stream, a);
+  if (hipError_t e = ensure_lds_attribute<Cfg, kTap, kFull, kCoded, kSplit>(); e != hipSuccess) return e;
+  const int grid = ceil_div(a.tiles_m * a.tiles_n * a.splits, 8) * 8;
+  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit>), dim3(grid), dim3(Cfg::kThreads), kLaunchLds<Cfg>, stream, a);
   return hipGetLastError();
 }
 
@@ -926,6 +975,8 @@ template <class Cfg>
 static hipError_t launch_cfg(GemmArgs a, hipStream_t stream) {
   a.tiles_m = ceil_div(a.M, Cfg::BM);
   a.tiles_n = ceil_div(a.N, Cfg::BN);
+  a.splits = 1;
+  a.slabs_per_split = a.Kpad / BK;
   const bool full = (a.M % Cfg::BM == 0) && (a.N % Cfg::BN == 0);
   if (a.codes || a.residual || a.gelu) {
     if (a.codes && Cfg::BN % (1 << a.code_log_block) != 0) return hipErrorInvalidValue;   // a block would leave the tile
@@ -956,6 +1007,8 @@ hipError_t prepare_gemm_kernels() {
   if (e == hipSuccess) e = prepare_cfg<Cfg3>();
   if (e == hipSuccess) e = prepare_cfg<Cfg4>();
   if (e == hipSuccess) e = prepare_cfg<Cfg5>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, true, false, false, true>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, false, false, false, true>();
   return e;
 }
 
@@ -991,8 +1044,42 @@ static GemmArgs column_range(const GemmArgs& a, int n0, int n) {
   return b;
 }
 
-hipError_t launch_gemm_mixed(const GemmArgs& a, int variant, hipStream_t stream) {
+int plan_gemm_splits(int M, int K, int N) {
+  const int n_slabs = packed_k(K) / BK, cus = device_cu_count();
+  const long tiles = (long)ceil_div(M, Cfg5::BM) * ceil_div(N, Cfg5::BN);
+  if (M <= 128 || 2 * tiles > cus) return 1;
+  // us of a call with s ranges: the slabs of a workgroup (0.45 each), its start and end, and with more than one range
+  // the kernel that adds them up and the 8 bytes per output and range that the sums cost.  Measured (whole calls, without /
+  // with the split): 256 x 11008 x 4096 86 / 44 us (8 ranges), 256 x 4096 x 4096 38.6 / 31.0, 400 x 8192 x 2048 57.7 / 35.4,
+  // 256 x 4096 x 12288 43.8 / 41.2 (2 ranges; with most columns critical 114 / 80); no gain, and none taken by this
+  // rule: 1000 x 4096 x 4096 40.2 / 41.6, 512 x 2048 x 2048 25.9 / 29.2, 200 x 1024 x 1024 19.2 / 21.0.
+  auto cost = [&](int s) {
+    const double one = 0.45 * ceil_div(n_slabs, s) + 5.0;
+    return s == 1 ? one : one + 7.0 + (double)s * M * N * 8.0 / 8.0e6;
+  };
+  int best = 1;
+  for (int s = 2; s * tiles <= cus && n_slabs / s >= 4; ++s)
+    if (cost(s) < cost(best)) best = s;
+  return ceil_div(n_slabs, ceil_div(n_slabs, best));
+}
+
+hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
   if (variant >= 0 && variant <= 5) return launch_variant(a, variant, stream);
+  if (a.partial && a.splits > 1) {
+    const int n_slabs = a.Kpad / BK;
+    a.slabs_per_split = ceil_div(n_slabs, a.splits);
+    if (ceil_div(n_slabs, a.slabs_per_split) != a.splits) return hipErrorInvalidValue;   // every range has a slab
+    a.tiles_m = ceil_div(a.M, Cfg5::BM);
+    a.tiles_n = ceil_div(a.N, Cfg5::BN);
+    hipError_t e = hipSuccess;
+    if (a.tap_acc) e = launch_fill_u32(reinterpret_cast<uint32_t*>(a.tap_acc), 0u, (size_t)a.M * a.tap_ld, stream);
+    if (e == hipSuccess)
+      e = a.tap_acc ? launch_one<Cfg5, true, false, false, true>(a, stream) : launch_one<Cfg5, false, false, false, true>(a, stream);
+    if (e != hipSuccess) return e;
+    const SplitSum sum = {a.partial, a.splits, a.M, a.N, a.bias, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
+                          a.codes, a.code_absmax, a.codes ? 1 << a.code_log_block : 0};
+    return launch_add_splits(sum, stream);
+  }
   // Automatic.  The 256 x 256 tile with the four-slab ring is the most efficient per CU, but it runs
   // in rounds of one tile per CU.  Whole rounds go to it; a remainder that would leave a good part of
   // the chip idle is launched separately with 128 x 256 tiles (same ring depth, twice as many

@@ -70,6 +70,23 @@ inline bool panel_prep_fits(int M, const SkinnyPlan& plan) {
 
 hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t stream);
 
+// Y = f16(sum of the ranges of K, in order, + bias), then GELU, then the residual; with codes, the result (also stored
+// in Y, contiguous, where given) leaves blockwise-coded.
+struct SplitSum {
+  const float* partial;       // [splits][M][N]
+  int splits, M, N;           // N a multiple of 8
+  const uint16_t* bias;
+  const uint16_t* residual;   // [M][ldr] or null
+  int ldr;
+  int gelu;
+  uint16_t* Y;
+  int ldy;
+  uint8_t* codes;             // or null
+  float* code_absmax;
+  int code_block;
+};
+hipError_t launch_add_splits(const SplitSum& s, hipStream_t stream);
+
 // One or two rows, whole layer in one kernel (k_gemm_rows): a workgroup owns 32 output columns and its eight
 // waves share out the K range, so nothing is split between workgroups and no second kernel adds partial
 // outputs.  The rows' codes and fp16 critical columns for the whole of K live in LDS (3 bytes per element).

@@ -433,6 +433,45 @@ __global__ __launch_bounds__(kCodecThreads) void k_skinny_finalize_coded(const F
   encode_spans(src, src.MN, block, codes, absmax, blocks_per_span, n_spans, kExitCode);
 }
 
+// The ranges of K of a tiled GEMM added up: four neighbouring columns of a row per thread (16-byte loads, four ranges
+// in flight at a time), a row per blockIdx.y.  Bound by the bytes of the partial sums, which the GEMM has just
+// written: most are still in the last-level cache.
+__global__ __launch_bounds__(256) void k_add_splits(const SplitSum a) {
+  const int n = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4, m = blockIdx.y;
+  if (n >= a.N) return;
+  const size_t MN = (size_t)a.M * a.N;
+  const float* p = a.partial + (size_t)m * a.N + n;
+  v4f y = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  int s = 0;
+  for (; s + 4 <= a.splits; s += 4, p += 4 * MN) {
+    v4f q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const v4f*>(p + u * MN);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[i] += q[u][i];
+  }
+  for (; s < a.splits; ++s, p += MN) {
+    const v4f q = *reinterpret_cast<const v4f*>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] += q[i];
+  }
+  uint32_t h[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    h[i] = float_to_half_bits(a.bias ? y[i] + half_lo_to_float(a.bias[n + i]) : y[i]);
+    if (a.gelu) h[i] = gelu_to_half_bits(half_lo_to_float(h[i]));
+  }
+  if (a.residual) {
+    const v2u res = *reinterpret_cast<const v2u*>(a.residual + (size_t)m * a.ldr + n);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      h[i] = float_to_half_bits(half_lo_to_float(h[i]) + ((i & 1) ? half_hi_to_float(res[i >> 1]) : half_lo_to_float(res[i >> 1])));
+  }
+  *reinterpret_cast<v2u*>(a.Y + (size_t)m * a.ldy + n) = v2u{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+}
+
 __global__ void k_fill_i32(int32_t* __restrict__ p, size_t n) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = 0;
@@ -489,6 +528,26 @@ static hipError_t launch_panel(const SkinnyArgs& a, const SkinnyPlan& plan, hipS
              : launch_panel_cfg<PanelCfg<1, 4>, false>(a, plan.splits, stream);
 }
 
+static hipError_t launch_finalize_coded(const FinalizedHalves& src, int block, uint8_t* codes, float* absmax,
+                                        uint8_t* flag_reset, int Kpad, hipStream_t stream) {
+  // spans of about 2048 elements (every thread of the workgroup has a chunk), whole blocks each
+  const int blocks_per_span = block >= 2048 ? 1 : 2048 / block;
+  const size_t span = (size_t)blocks_per_span * block, n_spans = (src.MN + span - 1) / span;
+  hipLaunchKernelGGL(k_skinny_finalize_coded, dim3((unsigned)n_spans), dim3(kCodecThreads), 0, stream, src, block, codes, absmax,
+                     blocks_per_span, n_spans, flag_reset, Kpad);
+  return hipGetLastError();
+}
+
+hipError_t launch_add_splits(const SplitSum& a, hipStream_t stream) {
+  if (a.codes) {
+    const FinalizedHalves src = {a.partial, a.splits, a.N, (size_t)a.M * a.N, a.bias, a.residual, a.ldr, a.Y};
+    return launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, nullptr, 0, stream);
+  }
+  if (a.M > 65535) return hipErrorInvalidValue;                    // (a grid dimension; splits are for a few thousand rows at most)
+  hipLaunchKernelGGL(k_add_splits, dim3(ceil_div(a.N, 1024), a.M), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t stream) {
   a.n_slabs = plan.n_slabs;
   a.tiles_n = plan.tiles_n;
@@ -502,13 +561,8 @@ hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t 
   hipError_t e = launch_panel(a, plan, stream);
   if (e != hipSuccess) return e;
   if (split && a.codes) {
-    // spans of about 2048 elements (every thread of the workgroup has a chunk), whole blocks each
-    const int blocks_per_span = a.code_block >= 2048 ? 1 : 2048 / a.code_block;
-    const size_t span = (size_t)blocks_per_span * a.code_block, n_spans = (n + span - 1) / span;
     const FinalizedHalves src = {a.partial, plan.splits, a.N, n, a.bias, a.residual, a.ldr, a.Y};
-    hipLaunchKernelGGL(k_skinny_finalize_coded, dim3((unsigned)n_spans), dim3(kCodecThreads), 0, stream, src, a.code_block,
-                       a.codes, a.code_absmax, blocks_per_span, n_spans, a.flag_reset_late, a.Kpad);
-    e = hipGetLastError();
+    e = launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, a.flag_reset_late, a.Kpad, stream);
   } else if (split) {
     hipLaunchKernelGGL(k_skinny_finalize, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a.partial, plan.splits,
                        a.M, a.N, a.bias, a.lora_T, a.lora_ldt, a.lora_B, a.lora_r, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
