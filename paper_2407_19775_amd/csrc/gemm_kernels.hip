@@ -19,6 +19,7 @@
 // large problems, smaller tiles for small ones); fragments are double-buffered in registers.
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "codec_device.h"
 #include "common.h"
@@ -64,11 +65,14 @@ struct GemmCfg {
   static constexpr int A_DMA = BM / ROWS_PER_DMA / kWaves;         // DMA instructions per wave per slab
   static constexpr int B_DMA = BN / ROWS_PER_DMA / kWaves;
   static constexpr int DMA_PER_SLAB = A_DMA + B_DMA;
-  static constexpr int kAhead = kStages - 1;                       // slabs requested ahead of the MFMAs
+  // Small wave tiles have registers left for the fragments of a whole slab next to those being multiplied: a slab is
+  // read from LDS while the one before it is multiplied, and its buffer is free one iteration earlier.
+  static constexpr bool kSlabAhead = TI * TJ <= 4;
+  static constexpr int kAhead = kSlabAhead ? kStages : kStages - 1;  // slabs requested ahead of the MFMAs
   static_assert(BM % (ROWS_PER_DMA * kWaves) == 0 && BN % (ROWS_PER_DMA * kWaves) == 0, "tile/wave mismatch");
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole MFMA tiles");
   static_assert(NKS == 2, "fragment buffering below is written for two k-steps per slab");
-  static_assert(kStages >= 3 && kStages <= 4, "ring of three or four slabs");
+  static_assert(kStages >= 3 && (kStages - 1) * DMA_PER_SLAB <= 63, "the requests in flight fit the wait instruction's count");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
   static_assert(BM <= 256, "row scales are staged with one 1 KB request");
   // gather staging of critical columns beyond the slab: [rows][16 k] fp16 for both operands
@@ -552,13 +556,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
     a_off[ks] = (p.wm * Cfg::WM / 32) * 2048 + ks * 1024 + p.lane * 16;
     b_off[ks] = Cfg::A_BYTES + (p.wn * Cfg::WN / 32) * 2048 + ks * 1024 + p.lane * 16;
   }
-  v4i fa[2][TI], fb[2][TJ];
-  auto read_frags = [&](int stage, int ks, int buf) {
+  v4i fa[2 * NKS][TI], fb[2 * NKS][TJ];                            // (kSlabAhead: two slabs; else two k-steps)
+  // fragment q of a k-step, in the order in which the MFMAs need them: the first row's, the columns', the other rows'
+  auto read_frag = [&](int stage, int ks, int buf, int q) __attribute__((always_inline)) {
     const int8_t* base = smem + stage * Cfg::STAGE_BYTES;
-#pragma unroll
-    for (int i = 0; i < TI; ++i) fa[buf][i] = *reinterpret_cast<const v4i*>(base + a_off[ks] + i * 32 * BK);
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) fb[buf][j] = *reinterpret_cast<const v4i*>(base + b_off[ks] + j * 32 * BK);
+    if (q == 0 || q > TJ) {
+      const int i = q == 0 ? 0 : q - TJ;
+      fa[buf][i] = *reinterpret_cast<const v4i*>(base + a_off[ks] + i * 32 * BK);
+    } else {
+      fb[buf][q - 1] = *reinterpret_cast<const v4i*>(base + b_off[ks] + (q - 1) * 32 * BK);
+    }
   };
 
   v16i acc[TI][TJ];
@@ -608,21 +615,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
                                                            __builtin_bit_cast(v16f, acc[i][j]), 0, 0, 0));
         else
           acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
-        if (t == 0) {
-          // the first MFMA of the k-step goes out before any new LDS read, so the wait for its
-          // fragments (read during the previous k-step) is already satisfied
-          __builtin_amdgcn_sched_barrier(0);
-          if (ks + 1 < NKS) {
-            read_frags(stage, ks + 1, nxt);
-          } else {
-            // last k-step of the slab: make slab s+1 visible, then prefetch its first fragments.
-            // Still allowed in flight: slabs s+2 .. s+kAhead-1 in full and the part of slab
-            // s+kAhead requested during the earlier k-steps of this iteration
-            wait_slab_and_sync<kIssue ? (AHEAD - 2) * Cfg::DMA_PER_SLAB + kBeforeWait : 0>();
-            if (kNext) read_frags(stage1, 0, nxt);
-          }
-          __builtin_amdgcn_sched_barrier(0);
+        // the first MFMA of the k-step goes out before any new LDS read, so the wait for its
+        // fragments (read during the previous k-step) is already satisfied
+        __builtin_amdgcn_sched_barrier(0);
+        // last k-step of the slab: make slab s+1 visible, then prefetch its first fragments.
+        // Still allowed in flight: slabs s+2 .. s+kAhead-1 in full and the part of slab
+        // s+kAhead requested during the earlier k-steps of this iteration
+        if (t == 0 && ks + 1 == NKS) wait_slab_and_sync<kIssue ? (AHEAD - 2) * Cfg::DMA_PER_SLAB + kBeforeWait : 0>();
+        if (ks + 1 < NKS || kNext) {
+#pragma unroll
+          for (int q = t * (TI + TJ) / MFMAS; q < (t + 1) * (TI + TJ) / MFMAS; ++q)
+            read_frag(ks + 1 < NKS ? stage : stage1, ks + 1 < NKS ? ks + 1 : 0, nxt, q);
         }
+        __builtin_amdgcn_sched_barrier(0);
         // request d with ceil(d SLOTS / DPS) == slot, if there is one (at most one: DPS <= SLOTS)
         {
           const int slot = ks * MFMAS + t;
@@ -639,32 +644,101 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
     }
     stage = stage1;
   };
+  // kSlabAhead: slab s has its fragments in set `par`; those of slab s + 1 are read into the other set, one read
+  // between any two MFMAs.  With one k-step of four MFMAs between a read and its use, as the large tile has it with
+  // eight, every k-step took the LDS latency: 4096 -> 22016 at 512 rows on 128 x 128 tiles 130 us, now 90.
+  auto slab_step = [&](int s, auto par_tag, auto issue_tag, auto next_tag, auto fp16_tag) __attribute__((always_inline)) {
+    constexpr int par = decltype(par_tag)::value, kIssueKind = decltype(issue_tag)::value;
+    constexpr bool kIssue = kIssueKind != 0, kNext = decltype(next_tag)::value, kFp16 = decltype(fp16_tag)::value;
+    const int stage1 = (stage + 1 == STAGES) ? 0 : stage + 1;
+    // slab s + 1 has landed, and every wave has read slab s, whose buffer the requests of slab s + kAhead go to.  In
+    // flight behind it: kAhead - 2 slabs, fewer once nothing is requested any more
+    if constexpr (kIssue) {
+      wait_slab_and_sync<(AHEAD - 2) * Cfg::DMA_PER_SLAB>();
+    } else if constexpr (kNext) {
+      const int behind = total_slabs - 2 - s;
+      if (AHEAD > 3 && behind >= 2)
+        wait_slab_and_sync<2 * Cfg::DMA_PER_SLAB>();
+      else if (behind == 1)
+        wait_slab_and_sync<Cfg::DMA_PER_SLAB>();
+      else
+        wait_slab_and_sync<0>();
+    }
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int t = 0; t < MFMAS; ++t) {
+        const int i = t / TJ, j = t % TJ, cur = par * NKS + ks;
+        if constexpr (kFp16)
+          acc[i][j] = __builtin_bit_cast(
+              v16i, __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, fa[cur][i]), __builtin_bit_cast(v8h, fb[cur][j]),
+                                                           __builtin_bit_cast(v16f, acc[i][j]), 0, 0, 0));
+        else
+          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        const int slot = ks * MFMAS + t;
+        if (kNext) {
+          constexpr int kReads = NKS * (TI + TJ);
+#pragma unroll
+          for (int q = slot * kReads / SLOTS; q < (slot + 1) * kReads / SLOTS; ++q)
+            read_frag(stage1, q / (TI + TJ), (par ^ 1) * NKS + q / (TI + TJ), q % (TI + TJ));
+        }
+        const int d = slot * DPS_ / SLOTS;
+        if (kIssue && d < DPS_ && (d * SLOTS + DPS_ - 1) / DPS_ == slot)
+          issue_dma(s + AHEAD, stage, d, std::bool_constant<kIssueKind == 2>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    stage = stage1;
+  };
+  auto step = [&](int s, auto issue_tag, auto next_tag, auto fp16_tag) __attribute__((always_inline)) {
+    if constexpr (!Cfg::kSlabAhead) {
+      iteration(s, issue_tag, next_tag, fp16_tag);
+    } else {
+      // (one set after the other by copying: a choice between the two sets at run time costs 170 spilled registers)
+      slab_step(s, std::integral_constant<int, 0>{}, issue_tag, next_tag, fp16_tag);
+      if constexpr (decltype(next_tag)::value) {
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+#pragma unroll
+          for (int i = 0; i < TI; ++i) fa[ks][i] = fa[NKS + ks][i];
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) fb[ks][j] = fb[NKS + ks][j];
+        }
+      }
+    }
+  };
   using yes = std::true_type;
   using no = std::false_type;
 
   int issued = 0;
   for (; issued < AHEAD && issued < total_slabs; ++issued) issue_slab(issued, issued);
-  if (issued == 1)
-    wait_slab_and_sync<0>();
-  else if (issued == 2)
-    wait_slab_and_sync<Cfg::DMA_PER_SLAB>();
-  else
-    wait_slab_and_sync<2 * Cfg::DMA_PER_SLAB>();
-  read_frags(0, 0, 0);
+  // slab 0 has landed once only the requests of the others are out
+  [&]<int... kLater>(std::integer_sequence<int, kLater...>) __attribute__((always_inline)) {
+    ((issued == kLater + 1 ? wait_slab_and_sync<kLater * Cfg::DMA_PER_SLAB>() : void()), ...);
+  }(std::make_integer_sequence<int, AHEAD>{});
+#pragma unroll
+  for (int q = 0; q < (Cfg::kSlabAhead ? NKS : 1) * (TI + TJ); ++q) read_frag(0, q / (TI + TJ), q / (TI + TJ), q % (TI + TJ));
   int s = 0;
   using none = std::integral_constant<int, 0>;
   using codes = std::integral_constant<int, 1>;
   using halves = std::integral_constant<int, 2>;
-  for (; s + AHEAD < n_slabs; ++s) iteration(s, codes{}, yes{}, no{});                      // nearly all of the time
-  for (; s < n_slabs && s + AHEAD < total_slabs; ++s) iteration(s, halves{}, yes{}, no{});  // the first fp16 slabs requested
-  for (; s < n_slabs && s + 1 < total_slabs; ++s) iteration(s, none{}, yes{}, no{});
-  if (s < n_slabs) iteration(s++, none{}, no{}, no{});              // the last slab when nothing follows it
+  // nearly all of the time
+  if constexpr (Cfg::kSlabAhead) {
+    for (; s + AHEAD + 1 < n_slabs; s += 2) {
+      slab_step(s, std::integral_constant<int, 0>{}, codes{}, yes{}, no{});
+      slab_step(s + 1, std::integral_constant<int, 1>{}, codes{}, yes{}, no{});
+    }
+  }
+  for (; s + AHEAD < n_slabs; ++s) step(s, codes{}, yes{}, no{});
+  for (; s < n_slabs && s + AHEAD < total_slabs; ++s) step(s, halves{}, yes{}, no{});  // the first fp16 slabs requested
+  for (; s < n_slabs && s + 1 < total_slabs; ++s) step(s, none{}, yes{}, no{});
+  if (s < n_slabs) step(s++, none{}, no{}, no{});              // the last slab when nothing follows it
   if constexpr (kTap) tap_accumulators<Cfg, kSplit>(a, p, acc);
   dequantize_in_place<Cfg>(p, acc, a.r + p.m0, cs);
-  for (; s + AHEAD < total_slabs; ++s) iteration(s, halves{}, yes{}, yes{});
-  for (; s + 1 < total_slabs; ++s) iteration(s, none{}, yes{}, yes{});
-  if (s < total_slabs) iteration(s, none{}, no{}, yes{});
-  // every wave passed the last barrier after its last LDS read of the ring: the slab buffers are
+  for (; s + AHEAD < total_slabs; ++s) step(s, halves{}, yes{}, yes{});
+  for (; s + 1 < total_slabs; ++s) step(s, none{}, yes{}, yes{});
+  if (s < total_slabs) step(s, none{}, no{}, yes{});
+  // every wave passes a barrier after its last LDS read of the ring (the stores below begin with one): the slab buffers are
   // free for the gather staging, which starts with a barrier of its own before writing them
   if (n_out > kOutlierSlab * (crit_used + more_used) && (!kSplit || split == a.splits - 1))
     gather_outlier_columns<Cfg>(a, p, acc, smem, kOutlierSlab * (crit_used + more_used), n_out);
@@ -701,7 +775,8 @@ struct DenseCfg {
   static constexpr int LDS_BYTES = kStages * kStage + kMaskSlabs * BK;
   static constexpr int X_DMA = 128 * BK * 2 / 1024 / Tile::kWaves;
   static constexpr int kPerSlab = Tile::A_DMA + X_DMA + Tile::B_DMA;       // requests per wave and slab
-  static_assert(LDS_BYTES >= Tile::RING_BYTES && LDS_BYTES <= 160 * 1024, "LDS");
+  static_assert(LDS_BYTES >= Tile::kWaves * 64 * (Tile::WN * 2 + 16) + DynamicCode::kCells * 8 && LDS_BYTES <= 160 * 1024,
+                "LDS (the output stages need that much of it at most)");
 };
 
 template <int kBN>
@@ -1044,6 +1119,8 @@ static GemmArgs column_range(const GemmArgs& a, int n0, int n) {
   return b;
 }
 
+// 128 x 128 tiles that fit in one round
+static bool one_round_of_small_tiles(int M, int N) { return (long)ceil_div(M, 128) * ceil_div(N, 128) <= device_cu_count(); }
 int plan_gemm_splits(int M, int K, int N) {
   const int n_slabs = packed_k(K) / BK, cus = device_cu_count();
   const long tiles = (long)ceil_div(M, Cfg5::BM) * ceil_div(N, Cfg5::BN);
@@ -1054,8 +1131,8 @@ int plan_gemm_splits(int M, int K, int N) {
   // 256 x 4096 x 12288 43.8 / 41.2 (2 ranges; with most columns critical 114 / 80); no gain, and none taken by this
   // rule: 1000 x 4096 x 4096 40.2 / 41.6, 512 x 2048 x 2048 25.9 / 29.2, 200 x 1024 x 1024 19.2 / 21.0.
   auto cost = [&](int s) {
-    const double one = 0.45 * ceil_div(n_slabs, s) + 5.0;
-    return s == 1 ? one : one + 7.0 + (double)s * M * N * 8.0 / 8.0e6;
+    if (s == 1) return (one_round_of_small_tiles(M, N) ? 0.37 : 0.45) * n_slabs + 5.0;
+    return 0.45 * ceil_div(n_slabs, s) + 5.0 + 10.0 + (double)s * M * N * 8.0 / 8.0e6;
   };
   int best = 1;
   for (int s = 2; s * tiles <= cus && n_slabs / s >= 4; ++s)
@@ -1108,7 +1185,7 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
   // (where the 128 x 256 tiles would need a second round and the 256 x 256 ones fit in one, the large tiles win:
   // 4096 -> 12288 at 768 rows 61 against 71 us, 4096 -> 22016 at 512 rows 61 against 70)
   if (a.M > 128 && tiles_128x256 > cus) return launch_variant(a, 4, stream);
-  if (a.M > 64 && (tiles_128x256 >= 64 || a.Kpad / BK >= 128)) return launch_variant(a, 5, stream);
+  if (a.M > 64 && !one_round_of_small_tiles(a.M, a.N)) return launch_variant(a, 5, stream);
   return launch_variant(a, 0, stream);
 }
 

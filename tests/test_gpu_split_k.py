@@ -53,7 +53,7 @@ def test_ways_out(tau):
 
 def test_workspace_of_an_unsplit_call_still_serves():
     """A workspace that was sized for more rows than the split is for: the call goes through without the split."""
-    M, K, N = 129, 2048, 1024
+    M, K, N = 129, 8192, 1024
     rng = np.random.default_rng(3)
     X, W = wl.to_fp16(rng.standard_normal((M, K)).astype(np.float32)), wl.gaussian_weight(K, N, 0.02, rng)
     pw, Xg = binding.prequantize_weight(to_gpu(W)), to_gpu(X)
