@@ -113,7 +113,7 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   w.wo = reinterpret_cast<uint16_t*>(take(Npad * kOutlierSlab * 2 * w.f_slabs));
   // (the same count decides for the dense pass with and without the further slabs, so that a call gives the same
   // bits whichever workspace it runs in; a workspace without them gathers tile by tile up to that count)
-  const CriticalPlan cp = plan_critical_columns((int)(Kpad / kSlabBytes), Npad, w.crit_slabs == kCriticalSlabs);
+  const CriticalPlan cp = plan_critical_columns(M, (int)(Kpad / kSlabBytes), Npad, w.crit_slabs == kCriticalSlabs);
   w.g_slabs = gathered_rows ? cp.g_slabs : 0;
   w.dense_from = cp.dense_from;
   w.xg = w.g_slabs > 0 ? reinterpret_cast<uint16_t*>(take(Mpad * kOutlierSlab * 2 * w.g_slabs)) : nullptr;

@@ -14,9 +14,9 @@ from test_gpu_linear import check_linear, exactly_n_critical
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K,N,n_crit", [(129, 8208, 264, 5), (130, 11008, 1000, 0), (333, 8192, 520, 300), (257, 4112, 72, 2900)])
+@pytest.mark.parametrize("M,K,N,n_crit", [(129, 8208, 264, 5), (130, 11008, 1000, 0), (333, 8192, 520, 300), (129, 32768, 72, 2400)])
 def test_ranges_of_k(M, K, N, n_crit):
-    """2900 of 4112 columns: more than the fp16 slabs hold, fewer than the walk over all of K takes: gathered by the
+    """2400 of 32768 columns: more than the fp16 slabs hold, fewer than the walk over all of K takes: gathered by the
     last range."""
     rng = np.random.default_rng([M, K, N])
     X, _ = exactly_n_critical(rng, M, K, n_crit)
