@@ -337,21 +337,54 @@ __global__ __launch_bounds__(Cfg::kThreads, 2) void k_gemm_panel(const SkinnyArg
     }
 }
 
+// kCols neighbouring sums of `splits` ranges, added in index order, eight loads in flight at a time.  (Added one load
+// after the other, sixteen ranges cost the kernel sixteen memory latencies.)
+template <int kCols>
+__device__ __forceinline__ void add_ranges(const float* __restrict__ p, int splits, size_t MN, float (&y)[kCols]) {
+  static_assert(kCols == 1 || kCols == 4, "a dword or four");
+  typedef typename std::conditional<kCols == 1, float, v4f>::type Piece;
+  auto add = [&](const Piece& q) {
+    if constexpr (kCols == 1) {
+      y[0] += q;
+    } else {
+#pragma unroll
+      for (int i = 0; i < kCols; ++i) y[i] += q[i];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < kCols; ++i) y[i] = 0.0f;
+  int s = 0;
+  auto batch = [&](auto n_tag) {
+    constexpr int kN = decltype(n_tag)::value;
+    Piece q[kN];
+#pragma unroll
+    for (int u = 0; u < kN; ++u) q[u] = *reinterpret_cast<const Piece*>(p + u * MN);
+#pragma unroll
+    for (int u = 0; u < kN; ++u) add(q[u]);
+    s += kN;
+    p += kN * MN;
+  };
+  while (s + 8 <= splits) batch(std::integral_constant<int, 8>{});
+  if (s + 4 <= splits) batch(std::integral_constant<int, 4>{});
+  if (s + 2 <= splits) batch(std::integral_constant<int, 2>{});
+  if (s < splits) batch(std::integral_constant<int, 1>{});
+}
+
 // Y[m,n] = f16( sum_s partial[s][m][n] + bias[n] + sum_j T[m][j] B[n][j] ), splits added in index
 // order, then the bias, then the low-rank term (T: [M][ldt] fp16, B: [N][r] fp16, r a multiple of 8;
-// r == 0: no such term).
+// r == 0: no such term).  A row per blockIdx.y.
 __global__ __launch_bounds__(256) void k_skinny_finalize(const float* __restrict__ partial, int splits, int M, int N,
                                                          const uint16_t* __restrict__ bias,
                                                          const uint16_t* __restrict__ T, int ldt,
                                                          const uint16_t* __restrict__ B, int r,
                                                          const uint16_t* residual /* may alias Y */, int ldr, int gelu,
                                                          uint16_t* Y, int ldy, uint8_t* flag_reset, int Kpad) {
-  reset_column_flags(flag_reset, Kpad);
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)M * N) return;
-  const int m = (int)(i / N), n = (int)(i % N);
-  float y = 0.0f;
-  for (int s = 0; s < splits; ++s) y += partial[(size_t)s * M * N + i];
+  if (blockIdx.y == 0) reset_column_flags(flag_reset, Kpad);
+  const int m = blockIdx.y, n = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (n >= N) return;
+  float sum[1];
+  add_ranges<1>(partial + (size_t)m * N + n, splits, (size_t)M * N, sum);
+  float y = sum[0];
   if (bias) y += half_lo_to_float(bias[n]);
   if (r > 0) {
     float low = 0.0f;
@@ -433,30 +466,14 @@ __global__ __launch_bounds__(kCodecThreads) void k_skinny_finalize_coded(const F
   encode_spans(src, src.MN, block, codes, absmax, blocks_per_span, n_spans, kExitCode);
 }
 
-// The ranges of K of a tiled GEMM added up: four neighbouring columns of a row per thread (16-byte loads, four ranges
-// in flight at a time), a row per blockIdx.y.  Bound by the bytes of the partial sums, which the GEMM has just
+// The ranges of K of a tiled GEMM added up: four neighbouring columns of a row per thread (16-byte loads), a row
+// per blockIdx.y.  Bound by the bytes of the partial sums, which the GEMM has just
 // written: most are still in the last-level cache.
 __global__ __launch_bounds__(256) void k_add_splits(const SplitSum a) {
   const int n = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4, m = blockIdx.y;
   if (n >= a.N) return;
-  const size_t MN = (size_t)a.M * a.N;
-  const float* p = a.partial + (size_t)m * a.N + n;
-  v4f y = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-  int s = 0;
-  for (; s + 4 <= a.splits; s += 4, p += 4 * MN) {
-    v4f q[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const v4f*>(p + u * MN);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) y[i] += q[u][i];
-  }
-  for (; s < a.splits; ++s, p += MN) {
-    const v4f q = *reinterpret_cast<const v4f*>(p);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] += q[i];
-  }
+  float y[4];
+  add_ranges<4>(a.partial + (size_t)m * a.N + n, a.splits, (size_t)a.M * a.N, y);
   uint32_t h[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -564,7 +581,7 @@ hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t 
     const FinalizedHalves src = {a.partial, plan.splits, a.N, n, a.bias, a.residual, a.ldr, a.Y};
     e = launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, a.flag_reset_late, a.Kpad, stream);
   } else if (split) {
-    hipLaunchKernelGGL(k_skinny_finalize, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a.partial, plan.splits,
+    hipLaunchKernelGGL(k_skinny_finalize, dim3(ceil_div(a.N, 256), a.M), dim3(256), 0, stream, a.partial, plan.splits,
                        a.M, a.N, a.bias, a.lora_T, a.lora_ldt, a.lora_B, a.lora_r, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
                        a.flag_reset_late, a.Kpad);
     e = hipGetLastError();
