@@ -50,10 +50,12 @@ __device__ inline v4u flags16(const uint8_t* __restrict__ flag, int k0) {
   return *reinterpret_cast<const v4u*>(flag + k0) & 0x01010101u;
 }
 
-template <int kScanRows>
-__global__ __launch_bounds__(kThreads) void k_scan(const uint16_t* __restrict__ X, int M, int K, int ldx,
+// kT threads per workgroup: with few rows and more than 4096 columns 1024, so that a row is one pass of two loads per
+// thread (11008 columns were three passes of 256 threads, each a memory latency).
+template <int kScanRows, int kT = kThreads>
+__global__ __launch_bounds__(kT) void k_scan(const uint16_t* __restrict__ X, int M, int K, int ldx,
                                                    uint32_t th, int Kpad, uint8_t* __restrict__ flag, float* __restrict__ r_out) {
-  __shared__ uint32_t s_part[kScanRows][kThreads / kWave];
+  __shared__ uint32_t s_part[kScanRows][kT / kWave];
   const int m0 = blockIdx.x * kScanRows;
   const us2 th2 = as_us2(th | (th << 16));
   us2 rowt[kScanRows];
@@ -61,7 +63,7 @@ __global__ __launch_bounds__(kThreads) void k_scan(const uint16_t* __restrict__ 
   for (int i = 0; i < kScanRows; ++i) rowt[i] = as_us2(0u);
 
   // two column groups per pass: eight 16-byte loads in flight per thread
-  for (int kk = threadIdx.x * 8; kk < K; kk += 2 * kThreads * 8) {
+  for (int kk = threadIdx.x * 8; kk < K; kk += 2 * kT * 8) {
     v4u raw2[2][kScanRows];
 #pragma unroll
     for (int g = 0; g < 2; ++g)
@@ -70,12 +72,12 @@ __global__ __launch_bounds__(kThreads) void k_scan(const uint16_t* __restrict__ 
         // rows past M (and a missing second group) read as zeros: sub-threshold for tau > 0, and
         // for tau <= 0 every column is flagged by the real rows anyway
         raw2[g][i] = v4u{0, 0, 0, 0};
-        const int kc = kk + g * kThreads * 8;
+        const int kc = kk + g * kT * 8;
         if (m0 + i < M && kc < K) raw2[g][i] = *reinterpret_cast<const v4u*>(X + (size_t)(m0 + i) * ldx + kc);
       }
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-    const int k0 = kk + g * kThreads * 8;
+    const int k0 = kk + g * kT * 8;
     if (k0 >= K) break;
     const v4u (&raw)[kScanRows] = raw2[g];
     uint32_t col_and[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
@@ -109,7 +111,7 @@ __global__ __launch_bounds__(kThreads) void k_scan(const uint16_t* __restrict__ 
   if (threadIdx.x < kScanRows && m0 + threadIdx.x < M) {
     uint32_t m = 0;
 #pragma unroll
-    for (int w = 0; w < kThreads / kWave; ++w) m = max(m, s_part[threadIdx.x][w]);
+    for (int w = 0; w < kT / kWave; ++w) m = max(m, s_part[threadIdx.x][w]);
     // top bit set: a sub-threshold entry exists and its pattern is m + th (mod 2^16)
     r_out[m0 + threadIdx.x] = (m & 0x8000u) ? half_lo_to_float((m + th) & 0xffffu) : 0.0f;
   }
@@ -314,6 +316,10 @@ __device__ inline void gather_outlier_slab_one(const uint16_t* __restrict__ X, i
   }
 }
 
+// kFine (the decode kernels' operands, at most 64 rows): a wave takes one k-step of a slab and 32 rows, a quarter of
+// what it takes otherwise: the whole tensor is a few hundred KB and the kernel a chain of latencies, so what counts
+// is how little each wave has to do (64 x 4096: 5.4 us with the whole slab and 64 rows, 3.5 now).
+template <bool kFine>
 __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ X, int M, int K, int ldx,
                                                    const uint8_t* __restrict__ flag,
                                                    const float* __restrict__ r, int8_t* __restrict__ Xq,
@@ -334,11 +340,13 @@ __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ 
     return;
   }
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int slab = blockIdx.x * kPackSlabs + wave;
+  const int slab = kFine ? blockIdx.x * (kPackSlabs / 2) + (wave >> 1) : blockIdx.x * kPackSlabs + wave;
   if (slab >= n_slabs) return;
   const int rl = lane & 31, g = lane >> 5;
+  constexpr int kRowSteps = kFine ? 1 : kPackRowSteps;
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
+  for (int step = 0; step < (kFine ? 1 : 2); ++step) {
+    const int ks = kFine ? (wave & 1) : step;
     const int ch = 2 * ks + g;
     const int k0 = slab * kSlabBytes + ch * 16;
     const bool in_k = k0 < K;                         // K % 16 == 0: a piece is all inside or all padding
@@ -348,11 +356,11 @@ __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ 
 #pragma unroll
       for (int w = 0; w < 4; ++w) keep[w] = (0x01010101u - f[w]) * 0xffu;   // bytes are 0 or 1: no carries
     }
-    const int m0 = blockIdx.y * kPackRows + rl;
-    v4u a[kPackRowSteps], b[kPackRowSteps];
-    float rm[kPackRowSteps];
+    const int m0 = blockIdx.y * 32 * kRowSteps + rl;
+    v4u a[kRowSteps], b[kRowSteps];
+    float rm[kRowSteps];
 #pragma unroll
-    for (int i = 0; i < kPackRowSteps; ++i) {
+    for (int i = 0; i < kRowSteps; ++i) {
       const int m = m0 + i * 32;
       a[i] = b[i] = v4u{0, 0, 0, 0};
       rm[i] = 0.0f;
@@ -363,7 +371,7 @@ __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ 
       }
     }
 #pragma unroll
-    for (int i = 0; i < kPackRowSteps; ++i) {
+    for (int i = 0; i < kRowSteps; ++i) {
       const int m = m0 + i * 32;
       if (m >= M) break;
       const float scale = (rm[i] == 0.0f) ? 0.0f : 127.0f / rm[i];   // IEEE division
@@ -658,6 +666,8 @@ hipError_t launch_scan(const uint16_t* X, int M, int K, int ldx, uint32_t th, in
     hipLaunchKernelGGL(k_scan<4>, dim3(ceil_div(M, 4)), dim3(kThreads), 0, stream, X, M, K, ldx, th, Kpad, flag, r);
   else if (M >= 2 * want)
     hipLaunchKernelGGL(k_scan<2>, dim3(ceil_div(M, 2)), dim3(kThreads), 0, stream, X, M, K, ldx, th, Kpad, flag, r);
+  else if (K > 2 * kThreads * 8)
+    hipLaunchKernelGGL((k_scan<1, 1024>), dim3(M), dim3(1024), 0, stream, X, M, K, ldx, th, Kpad, flag, r);
   else
     hipLaunchKernelGGL(k_scan<1>, dim3(M), dim3(kThreads), 0, stream, X, M, K, ldx, th, Kpad, flag, r);
   return hipGetLastError();
@@ -672,7 +682,8 @@ hipError_t launch_row_absmax_noncritical(const uint16_t* X, int M, int K, int ld
 hipError_t launch_pack(const uint16_t* X, int M, int K, int ldx, const uint8_t* flag, const float* r, int8_t* Xq,
                        int Kpad, int8_t* tap_xq, uint16_t* Xf, const PackOutliers& o, hipStream_t stream, bool list_columns) {
   const int n_slabs = Kpad / kSlabBytes;
-  const int gx = ceil_div(n_slabs, kPackSlabs), pack_y = ceil_div(M, kPackRows);
+  const bool fine = Xf != nullptr;
+  const int gx = ceil_div(n_slabs, fine ? kPackSlabs / 2 : kPackSlabs), pack_y = ceil_div(M, fine ? 32 : kPackRows);
   // the slabs of critical columns are for the tiled GEMM kernels; the decode kernel reads Xf instead
   // (one extra block still lists the critical columns)
   const int slab_items = Xf ? 0 : (M + o.N) * (kOutlierSlab / 8);
@@ -681,7 +692,10 @@ hipError_t launch_pack(const uint16_t* X, int M, int K, int ldx, const uint8_t* 
   if (!list_columns && !Xf) return hipErrorInvalidValue;
   const int slab_y = list_columns ? max(1, ceil_div(ceil_div(slab_items, kThreads), gx)) : 0;
   const dim3 grid(gx, pack_y + slab_y);
-  hipLaunchKernelGGL(k_pack, grid, dim3(kThreads), 0, stream, X, M, K, ldx, flag, r, Xq, n_slabs, tap_xq, pack_y, Xf, o);
+  if (fine)
+    hipLaunchKernelGGL(k_pack<true>, grid, dim3(kThreads), 0, stream, X, M, K, ldx, flag, r, Xq, n_slabs, tap_xq, pack_y, Xf, o);
+  else
+    hipLaunchKernelGGL(k_pack<false>, grid, dim3(kThreads), 0, stream, X, M, K, ldx, flag, r, Xq, n_slabs, tap_xq, pack_y, Xf, o);
   return hipGetLastError();
 }
 
