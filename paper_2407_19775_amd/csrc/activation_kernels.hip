@@ -587,7 +587,7 @@ __global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ 
 
 // After k_prep: the first `slab_blocks` workgroups list the critical columns (the first one
 // publishes the list, the count and the byte mask) and build the fp16 slab of the first
-// kOutlierSlab of them; each of the remaining workgroups owns 64 rows (lane = row) and 4096 columns or a multiple
+// kOutlierSlab of them; each of the remaining workgroups owns 64 rows (lane = row) and a share of the columns
 // and clears the codes of the critical columns in those rows with byte stores of zero.  Driven by the
 // flags themselves, so any number of critical columns is handled the same way.
 __global__ __launch_bounds__(kThreads) void k_outlier_columns(const uint16_t* __restrict__ X, int M, int K, int ldx,
@@ -604,7 +604,7 @@ __global__ __launch_bounds__(kThreads) void k_outlier_columns(const uint16_t* __
     gather_further_slabs(X, M, ldx, n_slabs, o, blockIdx.x * kThreads + threadIdx.x, slab_blocks * kThreads, s_idx, s_n_out);
     return;
   }
-  // A clearing workgroup owns 64 rows (lane = row) and clear_units units of 16 columns (a multiple of 64), a quarter
+  // A clearing workgroup owns 64 rows (lane = row) and clear_units units of 16 columns (a multiple of 4), a quarter
   // of them per wave, taken 64 at a time: lane l of a wave looks at unit u0 + l.  (With input whose columns are
   // nearly all critical the clearing is the longest part of the preparation unless many waves share a row.)
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -737,9 +737,10 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
   const int row_groups = ceil_div(M, kWave), units = n_slabs * (kSlabBytes / 16);
   const int groups_256 = row_groups * ceil_div(units, kThreads);
   const int merge = max(1, ceil_div(groups_256, max(1, device_cu_count() / 4)));
-  // (a few hundred rows: a quarter of that per workgroup, 16 units per wave, so that heavy-tailed input, where every
-  // unit has columns to clear, does not leave the clearing to four workgroups)
-  const int clear_units = groups_256 <= 16 ? kThreads / 4 : kThreads * merge;
+  // (a few hundred rows: as many units per wave as a workgroup for every fourth CU leaves, four at least: heavy-tailed
+  // input, where every unit has columns to clear, takes a memory latency per unit of a wave)
+  const int few = max(16, round_up(ceil_div(row_groups * units, max(1, device_cu_count() / 4)), 4));
+  const int clear_units = groups_256 <= 16 ? few : kThreads * merge;
   const int clear_blocks = row_groups * ceil_div(units, clear_units);
   hipLaunchKernelGGL(k_outlier_columns, dim3(slab_blocks + clear_blocks), dim3(kThreads), 0, stream, X, M, K, ldx, flag, Xq,
                      n_slabs, tap_xq, slab_blocks, clear_units, o);
