@@ -164,17 +164,19 @@ int mmd8_mixed_int8_linear(const mmd8_half* X /*DEVICE*/, int M, int K, int ldx,
                            const mmd8_debug_taps* taps /*HOST struct or NULL*/, void* stream);
 
 /* mmd8_mixed_int8_linear for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments, results (bit for bit) and errors, without the
- * workspace: the library's own device array of MMD8_STATIC_WORKSPACE_BYTES serves as one (every GPU the library
- * runs on holds it until the process ends; that is enough for up to 64 rows of every Llama-7B- and
- * 70B-shaped linear).  The array takes the layout of a workspace of mmd8_linear_workspace_bytes(M, K, N) bytes,
- * or, where that does not fit, the same less the slabs in which calls of more than 128 rows gather the critical
- * columns beyond the first 256 (those are then gathered tile by tile, and an output may differ from the other
- * entry point's in its last bit for inputs that have so many); a problem that does not fit either way returns
- * MMD8_E_WORKSPACE and launches nothing.  The call allocates and frees nothing and synchronises nothing; the
- * first call on a device looks up the array's address and sets kernel attributes (make it before a capture
- * starts).  All calls on one GPU share the one array: calls that overlap in time (two streams, two threads)
- * race; order them. */
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments, results (bit for bit, but for the cases below)
+ * and errors, without the workspace: the library's own device array of MMD8_STATIC_WORKSPACE_BYTES serves as one
+ * (every GPU the library runs on holds it until the process ends; that is enough for up to 64 rows of every
+ * Llama-7B- and 70B-shaped linear).  The array takes the layout of a workspace of
+ * mmd8_linear_workspace_bytes(M, K, N) bytes or, where that does not fit, the first of these that does: the same
+ * without the sums of a split K (more than 128 rows, few tiles); without the slabs in which calls of more than 128
+ * rows gather the critical columns beyond the first 256 (those are then gathered tile by tile); without both.
+ * Without the sums of a split, or without the slabs for an input that has so many critical columns, an output may
+ * differ from the other entry point's in its last bit; all integers are the same.  A problem that does not fit in
+ * any of these ways returns MMD8_E_WORKSPACE and launches nothing.  The call allocates and frees nothing and
+ * synchronises nothing; the first call on a device looks up the array's address and sets kernel attributes (make
+ * it before a capture starts).  All calls on one GPU share the one array: calls that overlap in time (two streams,
+ * two threads) race; order them. */
 #define MMD8_STATIC_WORKSPACE_BYTES (32u << 20)
 int mmd8_mixed_int8_linear_static(const mmd8_half* X /*DEVICE*/, int M, int K, int ldx,
                                   const int8_t* Wq_packed /*DEVICE*/, uint32_t Wq_layout, const float* col_absmax /*DEVICE [N]*/, int N,

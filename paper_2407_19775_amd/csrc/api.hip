@@ -144,6 +144,18 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   w.bytes = off;
   return w;
 }
+// The layout of a call in a workspace of `have` bytes: with room for the sums of a split K where that fits, else
+// without (what a workspace held before K was ever split still serves); may_drop_slabs (the fixed-size array): then
+// likewise without the further slabs.  The slabs go last: 200 x 4096 x 4096 in 32 MiB, which hold one of the two, takes
+// 58 us with them and 100 with the split when 15 % of the columns are critical; 30.5 and 30.0 us when few are.
+// bytes > have: it fits in none of these ways.
+static Workspace fit(void* base, size_t have, int M, int K, int N, int r, int exit_block, bool may_drop_slabs) {
+  Workspace w = carve(base, M, K, N, r, exit_block);
+  if (w.bytes > have) w = carve(base, M, K, N, r, exit_block, true, false);
+  if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, true);
+  if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, false);
+  return w;
+}
 // A coded output is produced by the kernel that ends the layer when no block of it is shared between
 // workgroups: the tiled GEMM needs blocks inside its 256-column tiles; the decode path encodes where it sums
 // its partial outputs, any block size, as long as its second pass of 64 rows starts on a block boundary.  The
@@ -301,7 +313,7 @@ struct Adapter {   // low-rank factors of W' = W + B A
 static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_packed, uint32_t Wq_layout, const float* col_absmax, int N,
                       const mmd8_half* bias, float tau, mmd8_half* Y, int ldy, void* workspace, size_t workspace_bytes,
                       const mmd8_debug_taps* taps, const CodedInput* coded, const Adapter* lora, const CodedExit* exit,
-                      void* stream, bool gelu = false, const Readings* readings = nullptr, bool gathered_rows = true) {
+                      void* stream, bool gelu = false, const Readings* readings = nullptr, bool may_drop_slabs = false) {
   if (M < 0) return MMD8_E_ARG;
   if (int s = check_linear_shape(K, N)) return s;
   if (isnan(tau)) return MMD8_E_ARG;
@@ -322,10 +334,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   if (lora && (!lora->A || !lora->B || !aligned(lora->A, 16) || !aligned(lora->B, 16) ||
                (lora->T_out && !aligned(lora->T_out, 16))))
     return MMD8_E_ARG;
-  Workspace ws = carve(workspace, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, gathered_rows);
-  // a workspace that was sized for more rows (where K is not split) still serves fewer: without the split
-  if (ws.gemm_splits > 1 && workspace_bytes < ws.bytes)
-    ws = carve(workspace, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, gathered_rows, false);
+  const Workspace ws = fit(workspace, workspace_bytes, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, may_drop_slabs);
   if (workspace_bytes < ws.bytes) return MMD8_E_WORKSPACE;
   // a coded output is written by the layer's last kernel where that is possible, otherwise by the encoder after it
   const bool encodes = exit && exit->block > 0;
@@ -585,10 +594,7 @@ int mmd8_mixed_int8_linear_static(const mmd8_half* X, int M, int K, int ldx, con
                                   const mmd8_debug_taps* taps, void* stream) {
   if (M < 0) return MMD8_E_ARG;
   if (int s = check_linear_shape(K, N)) return s;
-  // (the array is small: the further slabs of critical columns only where they fit, else the GEMM gathers those
-  // columns tile by tile)
-  const bool further_slabs = carve(nullptr, M, K, N, 0, 0, true).bytes <= (size_t)MMD8_STATIC_WORKSPACE_BYTES;
-  if (!further_slabs && carve(nullptr, M, K, N, 0, 0, false).bytes > (size_t)MMD8_STATIC_WORKSPACE_BYTES)
+  if (fit(nullptr, MMD8_STATIC_WORKSPACE_BYTES, M, K, N, 0, 0, true).bytes > (size_t)MMD8_STATIC_WORKSPACE_BYTES)
     return MMD8_E_WORKSPACE;   // too large for the array
   if (Wq_layout != kPackedLayoutTag) return MMD8_E_VERSION;
   if (M == 0) return isnan(tau) ? MMD8_E_ARG : MMD8_OK;
@@ -614,7 +620,7 @@ int mmd8_mixed_int8_linear_static(const mmd8_half* X, int M, int K, int ldx, con
     ws = w.ptr;
   }
   const int s = run_linear(const_cast<mmd8_half*>(X), M, K, ldx, Wq_packed, Wq_layout, col_absmax, N, bias, tau, Y, ldy, ws,
-                           MMD8_STATIC_WORKSPACE_BYTES, taps, nullptr, nullptr, nullptr, stream, false, nullptr, further_slabs);
+                           MMD8_STATIC_WORKSPACE_BYTES, taps, nullptr, nullptr, nullptr, stream, false, nullptr, true);
   if (s == MMD8_E_HIP) {   // some kernels of the call may have run: the head is cleared again before the next call
     std::lock_guard<std::mutex> lock(g_static_mu);
     g_static_ws[dev].head_zero = false;

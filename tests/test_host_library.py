@@ -270,6 +270,19 @@ def test_the_entry_point_without_a_workspace_refuses_sizes_beyond_its_array():
     assert call(0, 128, 64) == 0 and call(0, 128, 64, tau=float("nan")) == -1
 
 
+@pytest.mark.parametrize("M,K,N", [(256, 11008, 4096), (333, 11008, 4096), (512, 11008, 4096), (768, 11008, 4096), (1024, 11008, 4096),
+                                   (256, 8192, 8192), (512, 8192, 8192), (192, 28672, 8192), (512, 28672, 8192), (256, 13824, 5120),
+                                   (768, 13824, 5120), (512, 8192, 2048), (1536, 8192, 2048)])
+def test_the_entry_point_without_a_workspace_serves_what_fits_without_the_sums_of_a_split(M, K, N):
+    """Too large for the array with the sums of a split K, not without them.  The size check comes before that of the
+    layout tag, which ends the call here: no pointer is used."""
+    L = binding.lib()
+    fake, y = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x40000000)
+    assert L.mmd8_linear_workspace_bytes(M, K, N) > binding.STATIC_WORKSPACE_BYTES
+    assert L.mmd8_mixed_int8_linear_static(fake, M, K, K, fake, L.mmd8_packed_weight_layout() + 1, fake, N, None, 6.0, y, N,
+                                           None, None) == -5
+
+
 def test_variant_entry_points_check_their_arguments():
     L = binding.lib()
     fake, y = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x40000000)

@@ -10,6 +10,7 @@ import torch
 from oracle import mixed_linear as ml
 from paper_2407_19775_amd import binding, workloads as wl
 from gpu_util import assert_y_close, to_gpu, to_np
+from test_gpu_linear import exactly_n_critical
 
 pytestmark = pytest.mark.gpu
 
@@ -70,6 +71,23 @@ def test_interleaved_with_calls_that_bring_their_own_workspace_and_thresholds():
         binding.mixed_int8_linear_static(Xg[:3], pw, tau, Y2, bias=bg)
         torch.cuda.synchronize()
         assert torch.equal(Y, ref) and torch.equal(Y2, ref2), tau
+
+
+@pytest.mark.parametrize("M,K,N,n_crit", [(200, 4096, 4096, 600), (256, 11008, 4096, 5)])
+def test_sizes_that_fit_without_the_sums_of_a_split(M, K, N, n_crit):
+    """Rows for which K is split, in an array without room for the sums: the call goes through unsplit, with the further
+    slabs where there are any to fill, and gives the bits of a call that brings its own workspace and is not split."""
+    assert binding.lib().mmd8_linear_workspace_bytes(M, K, N) > binding.STATIC_WORKSPACE_BYTES
+    rng = np.random.default_rng([M, K, n_crit])
+    X, _ = exactly_n_critical(rng, M, K, n_crit)
+    pw = binding.prequantize_weight(to_gpu(wl.gaussian_weight(K, N, 0.02, rng)))
+    Xg = to_gpu(X)
+    ref, t = binding.mixed_int8_linear(Xg, pw, wl.TAU, taps=True, tuning=binding.tune_gemm_tiles(0))
+    assert int(t["n_outliers"].item()) == n_crit
+    Y = torch.empty_like(ref)
+    binding.mixed_int8_linear_static(Xg, pw, wl.TAU, Y)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, ref)
 
 
 def test_sizes_beyond_the_array_are_refused_and_nothing_is_written():
