@@ -149,7 +149,10 @@ typedef struct {
  * Workspace protocol: a workspace is set up once with mmd8_linear_workspace_init (it zeroes a
  * small head of counters and column flags; everything else may hold anything).  Every call
  * leaves the head zeroed again, so the same workspace serves any number of calls of any shape
- * that fits, one after the other on one stream.  Two calls must not use one workspace at the
+ * that fits, one after the other on one stream.  A size given for M rows does not fall with M from 129 rows on, and
+ * a workspace of that size serves calls of 129 to M rows with the results, bit for bit, of one sized for them.  (A
+ * smaller workspace that has no room for the sums of a split K, and is not too small otherwise, serves as well: K is
+ * then not split, and an output may differ in its last bit.)  Two calls must not use one workspace at the
  * same time.  After a call that returned MMD8_E_HIP, set the workspace up again.
  * mmd8_linear_workspace_init also sets the kernels' attributes on the current device; the calls of the layer made
  * after it allocate nothing, synchronise nothing and change no device state, so they can be captured in a HIP

@@ -111,8 +111,8 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   w.f_slabs = w.crit_slabs + lora_slabs(r);
   w.xo = reinterpret_cast<uint16_t*>(take(Mpad * kOutlierSlab * 2 * w.f_slabs));
   w.wo = reinterpret_cast<uint16_t*>(take(Npad * kOutlierSlab * 2 * w.f_slabs));
-  // (the same count decides for the dense pass with and without the further slabs, so that a call gives the same
-  // bits whichever workspace it runs in; a workspace without them gathers tile by tile up to that count)
+  // (the same count decides for the dense pass with and without the further slabs: a workspace without them gathers
+  // tile by tile up to that count)
   const CriticalPlan cp = plan_critical_columns(M, (int)(Kpad / kSlabBytes), Npad, w.crit_slabs == kCriticalSlabs);
   w.g_slabs = gathered_rows ? cp.g_slabs : 0;
   w.dense_from = cp.dense_from;
@@ -155,6 +155,19 @@ static Workspace fit(void* base, size_t have, int M, int K, int N, int r, int ex
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, true);
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, false);
   return w;
+}
+// What a caller is told to bring for up to M rows.  A call of fewer rows has fewer codes and slabs, but it may be one
+// whose K is split where that of M rows is not: room for the sums of any of them (at most 32 MB on 256 compute units),
+// so that what a call does, and the last bit of its output, does not depend on how many rows its workspace was sized
+// for.  Within a row of tiles the plan splits the fewest rows into the most ranges.
+static size_t workspace_bytes_for(int M, int K, int N, int r = 0, int exit_block = 0) {
+  size_t sums = 0;
+  const int last = device_cu_count() / 2 / (packed_n(N) / 256) * 128;   // (tiles on more than half of the compute units: no split)
+  for (int m = kSkinnyChunkedMaxM + 1; m <= M && m <= last; m += 128) {
+    const size_t splits = plan_gemm_splits(m, K, N), rows = m + 127 < M ? m + 127 : M;
+    if (splits > 1) sums = sums > splits * rows * N ? sums : splits * rows * N;
+  }
+  return carve(nullptr, M, K, N, r, exit_block, true, false).bytes + round_up_sz(sums * sizeof(float), 256);
 }
 // A coded output is produced by the kernel that ends the layer when no block of it is shared between
 // workgroups: the tiled GEMM needs blocks inside its 256-column tiles; the decode path encodes where it sums
@@ -266,11 +279,11 @@ int mmd8_unpack_weight(const int8_t* Wq_packed, uint32_t Wq_layout, int K, int N
 
 size_t mmd8_linear_workspace_bytes(int M, int K, int N) {
   if (M < 0 || check_linear_shape(K, N) != MMD8_OK) return 0;
-  return carve(nullptr, M, K, N).bytes;
+  return workspace_bytes_for(M, K, N);
 }
 size_t mmd8_linear_lora_workspace_bytes(int M, int K, int N, int r) {
   if (M < 0 || check_linear_shape(K, N) != MMD8_OK || check_lora_rank(r) != MMD8_OK) return 0;
-  return carve(nullptr, M, K, N, r).bytes;
+  return workspace_bytes_for(M, K, N, r);
 }
 
 int mmd8_linear_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {
@@ -660,7 +673,7 @@ int mmd8_mixed_int8_linear_residual(const mmd8_half* X, int M, int K, int ldx, c
 
 size_t mmd8_linear_to_codes_workspace_bytes(int M, int K, int N, int block) {
   if (M < 0 || check_linear_shape(K, N) != MMD8_OK || check_block(block) != MMD8_OK) return 0;
-  return carve(nullptr, M, K, N, 0, block).bytes;
+  return workspace_bytes_for(M, K, N, 0, block);
 }
 
 int mmd8_mixed_int8_linear_to_codes(const mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_packed,

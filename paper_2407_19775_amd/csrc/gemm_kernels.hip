@@ -1130,13 +1130,12 @@ int plan_gemm_splits(int M, int K, int N) {
   // with the split): 256 x 11008 x 4096 86 / 44 us (8 ranges), 256 x 4096 x 4096 38.6 / 31.0, 400 x 8192 x 2048 57.7 / 35.4,
   // 256 x 4096 x 12288 43.8 / 41.2 (2 ranges; with most columns critical 114 / 80); no gain, and none taken by this
   // rule: 1000 x 4096 x 4096 40.2 / 41.6, 512 x 2048 x 2048 25.9 / 29.2, 200 x 1024 x 1024 19.2 / 21.0.
-  auto cost = [&](int s) {
-    if (s == 1) return (one_round_of_small_tiles(M, N) ? 0.37 : 0.45) * n_slabs + 5.0;
-    return 0.45 * ceil_div(n_slabs, s) + 5.0 + 10.0 + (double)s * M * N * 8.0 / 8.0e6;
-  };
   int best = 1;
-  for (int s = 2; s * tiles <= cus && n_slabs / s >= 4; ++s)
-    if (cost(s) < cost(best)) best = s;
+  double least = (one_round_of_small_tiles(M, N) ? 0.37 : 0.45) * n_slabs + 5.0;
+  for (int s = 2; s * tiles <= cus && n_slabs / s >= 4; ++s) {
+    const double cost = 0.45 * ceil_div(n_slabs, s) + 5.0 + 10.0 + (double)s * M * N * 8.0 / 8.0e6;
+    if (cost < least) best = s, least = cost;
+  }
   return ceil_div(n_slabs, ceil_div(n_slabs, best));
 }
 

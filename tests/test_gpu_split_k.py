@@ -64,3 +64,14 @@ def test_workspace_of_an_unsplit_call_still_serves():
     ref = ml.mixed_int8_linear(X, Wq, c, wl.TAU, None)["Y"]
     assert_y_close(to_np(Y), ref)
     assert_y_close(to_np(out), ref)
+
+
+def test_workspace_of_more_rows_gives_the_same_bits():
+    """1025 rows are not split and need less for themselves than 129 to 256 rows with the sums of their ranges."""
+    K, N = 11008, 4096
+    rng = np.random.default_rng(4)
+    X, _ = exactly_n_critical(rng, 256, K, 40)
+    pw, Xg = binding.prequantize_weight(to_gpu(wl.gaussian_weight(K, N, 0.02, rng))), to_gpu(X)
+    ws = binding.linear_workspace(1025, K, N, Xg.device)
+    for M in (129, 200, 256):
+        assert torch.equal(binding.mixed_int8_linear(Xg[:M], pw, wl.TAU, workspace=ws), binding.mixed_int8_linear(Xg[:M], pw, wl.TAU))

@@ -109,6 +109,16 @@ def test_sizes_and_layout_tag():
     assert L.mmd8_linear_workspace_bytes(-1, 4096, 4096) == 0
 
 
+@pytest.mark.parametrize("K,N", [(11008, 4096), (4096, 4096), (8192, 2048), (4096, 1024), (28672, 8192), (2048, 264)])
+def test_a_workspace_for_more_rows_serves_fewer(K, N):
+    """K is split for some row counts and not for larger ones: the size asked for must not fall in between."""
+    L = binding.lib()
+    rows = [129] + list(range(130, 3000, 37)) + list(range(256, 3000, 128)) + list(range(257, 3000, 128))
+    for size in (lambda m: L.mmd8_linear_workspace_bytes(m, K, N), lambda m: L.mmd8_linear_to_codes_workspace_bytes(m, K, N, 64)):
+        sizes = [size(m) for m in sorted(rows)]
+        assert sizes == sorted(sizes)
+
+
 def test_bad_arguments_are_rejected_before_any_launch():
     L = binding.lib()
     fake = ctypes.c_void_p(0x1000)         # aligned, never dereferenced: every call below must fail first
