@@ -113,7 +113,8 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   w.wo = reinterpret_cast<uint16_t*>(take(Npad * kOutlierSlab * 2 * w.f_slabs));
   // (the same count decides for the dense pass with and without the further slabs: a workspace without them gathers
   // tile by tile up to that count)
-  const CriticalPlan cp = plan_critical_columns(M, (int)(Kpad / kSlabBytes), Npad, w.crit_slabs == kCriticalSlabs);
+  w.gemm_splits = split_k && M > kSkinnyChunkedMaxM ? plan_gemm_splits(M, K, N) : 1;
+  const CriticalPlan cp = plan_critical_columns(M, (int)(Kpad / kSlabBytes), Npad, w.crit_slabs == kCriticalSlabs, w.gemm_splits);
   w.g_slabs = gathered_rows ? cp.g_slabs : 0;
   w.dense_from = cp.dense_from;
   w.xg = w.g_slabs > 0 ? reinterpret_cast<uint16_t*>(take(Mpad * kOutlierSlab * 2 * w.g_slabs)) : nullptr;
@@ -131,7 +132,6 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
     if (pb == 0) pb = (size_t)Mc * N * sizeof(float);
     if (pb) w.partial = reinterpret_cast<float*>(take(pb));
   }
-  w.gemm_splits = split_k && M > kSkinnyChunkedMaxM ? plan_gemm_splits(M, K, N) : 1;
   if (w.gemm_splits > 1) w.partial = reinterpret_cast<float*>(take((size_t)w.gemm_splits * M * N * sizeof(float)));
   w.lora_t = r > 0 ? reinterpret_cast<uint16_t*>(take((size_t)M * kLoraMaxRank * 2)) : nullptr;
   w.lora_part = nullptr;

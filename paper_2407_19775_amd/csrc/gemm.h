@@ -17,35 +17,14 @@ constexpr int kCriticalSlabs = 8;
 // ring behind the first crit_slabs: 1.5 us per slab of 32 columns on that call.  Only columns beyond both are
 // gathered in the epilogue, and from dense_from critical columns on the GEMM takes all of them along with the codes
 // instead (dense_tile in gemm_kernels.hip), where that is cheaper.
-// Where the line lies: the walk with both products costs the same whatever their number, a slab of columns costs its
-// preparation and, per round of 128 x 256 tiles, its place in the ring.  Both ways measured at 8 to 90 % critical columns
-// (us, walk / slabs): 150 x 4096 x 4096 52 / 51 at 15 %, 55 / 93 at 50 %; 256 x 4096 x 12288 70 / 65 at 15 %, 71 / 83 at
-// 25 %, 73 / 211 at 70 %; 1024 x 4096 x 12288 171 / 150 at 35 %, 171 / 186 at 50 %; 2048 x 4096 x 12288 333 / 285 at 50 %,
-// 336 / 493 at 70 %; 2048 x 1024 x 4096 84 / 69 at 70 %, 84 / 90 at 90 %; 4096 x 8192 x 10240 909 / 552 at 25 %, 937 / 1561
-// at 50 %.  The formula is a fit to where those cross.
 constexpr int kGatherMax = 2048;
 constexpr size_t kGatherWeightBytesMax = (size_t)96 << 20;
 struct CriticalPlan {
   int g_slabs;      // further slabs of 32 critical columns in Xg / Wg, 0: none
   int dense_from;   // critical columns from which a call takes the dense pass
 };
-inline CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further_slabs) {
-  CriticalPlan p = {0, 0};
-  if (further_slabs) {
-    size_t cols = (size_t)n_slabs * 32;                              // half of the columns at most
-    if (cols > (size_t)kGatherMax) cols = kGatherMax;
-    const size_t fit = kGatherWeightBytesMax / (Npad * 2);
-    if (cols > fit) cols = fit;
-    p.g_slabs = (int)(cols / kOutlierSlab);
-  }
-  const int in_slabs = kOutlierSlab * (kCriticalSlabs + p.g_slabs);
-  const double rounds = (double)ceil_div(M, 128) * ((double)Npad / 256) / 256;   // of 128 x 256 tiles on 256 compute units
-  double from = 200 + 0.2 * M + (0.09 + 0.17 * rounds) * 64 * n_slabs;
-  // (columns beyond the slabs cost more each: 0.147 us per round against 0.022 + 0.02 per round)
-  if (from > in_slabs) from = in_slabs + (from - in_slabs) * (0.022 + 0.02 * rounds) / (rounds > 1 ? 0.147 * rounds : 0.147);
-  p.dense_from = from < 1e9 ? (int)from : 1000000000;
-  return p;
-}
+// splits: ranges into which the tiled GEMM's K is split (plan_gemm_splits; 1: not split)
+CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further_slabs, int splits);
 // Whether a call takes the dense pass for its critical columns.  Then no fp16 slab is prepared or read at all.  The
 // same decision in the kernel that prepares the slabs and in the GEMM, from the count that both read; never with
 // original 16-bit weight rows (the dense pass multiplies the weight codes).

@@ -1139,6 +1139,34 @@ int plan_gemm_splits(int M, int K, int N) {
   return ceil_div(n_slabs, ceil_div(n_slabs, best));
 }
 
+// Where the line between slabs and dense_tile lies.  The walk with both products costs the same whatever their number:
+// more than the walk over the codes by an amount that grows with the slabs of a range, with the rounds of tiles and, where
+// the ranges leave fp32 sums, with those.  A column in a slab costs its preparation and, per round, its place in the ring,
+// 0.028 + 0.014 us per round; a column beyond the slabs 0.14 us per round.  The formula is a fit to 75 calls of 130 to
+// 4096 rows, K of 512 to 32768, split and not, each measured both ways with 2 to 100 % of the columns critical and
+// weights that come from memory: the way taken is 0.3 % slower than the better one on average, 6 % at worst where it is the
+// walk (333 x 4096 x 22016 at 30 %) and 31 % where it is the slabs (1024 x 1024 x 1024 at 45 %).  Whole calls, us, walk /
+// slabs: 256 x 4096 x 4096 48 / 49 at 10 %, 48 / 74 at 25 %; 256 x 11008 x 4096 78 / 93 at 10 %, not split 137 / 148 at
+// 16 %; 1024 x 4096 x 12288 167 / 164 at 40 %, 169 / 186 at 50 %; 2048 x 4096 x 12288 326 / 280 at 50 %, 329 / 488 at 70 %;
+// 2048 x 1024 x 4096 84 / 69 at 70 %, 85 / 90 at 90 %; 4096 x 8192 x 10240 896 / 661 at 30 %, 907 / 1108 at 40 %.
+CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further_slabs, int splits) {
+  CriticalPlan p = {0, 0};
+  if (further_slabs) {
+    size_t cols = (size_t)n_slabs * 32;                              // half of the columns at most
+    if (cols > (size_t)kGatherMax) cols = kGatherMax;
+    const size_t fit = kGatherWeightBytesMax / (Npad * 2);
+    if (cols > fit) cols = fit;
+    p.g_slabs = (int)(cols / kOutlierSlab);
+  }
+  const int in_slabs = kOutlierSlab * (kCriticalSlabs + p.g_slabs);
+  const double rounds = (double)ceil_div(M, 128) * ((double)Npad / 256) / device_cu_count();   // of 128 x 256 tiles
+  double from = 0.35 * M + 64.0 * n_slabs / splits * (0.13 + 0.12 * rounds);
+  if (splits > 1) from += 75e-6 * splits * M * (double)Npad;
+  if (from > in_slabs) from = in_slabs + (from - in_slabs) * (0.028 + 0.014 * rounds) / (0.14 * (rounds > 1 ? rounds : 1));
+  p.dense_from = from < 1e9 ? (int)from : 1000000000;
+  return p;
+}
+
 hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
   if (variant >= 0 && variant <= 5) return launch_variant(a, variant, stream);
   if (a.partial && a.splits > 1) {

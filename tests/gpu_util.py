@@ -1,6 +1,10 @@
-"""Helpers shared by the GPU parity tests."""
+"""Helpers shared by the GPU parity tests and those of the host-side plans."""
+import ctypes
+
 import numpy as np
 import torch
+
+from paper_2407_19775_amd import binding
 
 
 def to_gpu(a: np.ndarray) -> torch.Tensor:
@@ -29,12 +33,21 @@ def assert_y_close(y_gpu: np.ndarray, y_ref: np.ndarray, rel: float = 1e-2):
     return fro, worst
 
 
-def critical_column_plan(K: int, N: int):
+def gemm_splits(M: int, K: int, N: int) -> int:
+    """Ranges into which the tiled GEMM splits K, as the library plans it (a C++ function of it, outside its C ABI)."""
+    f = binding.lib()._ZN4mmd816plan_gemm_splitsEiii
+    f.argtypes, f.restype = [ctypes.c_int] * 3, ctypes.c_int
+    return f(M, K, N)
+
+
+class CriticalPlan(ctypes.Structure):
+    _fields_ = [("g_slabs", ctypes.c_int), ("dense_from", ctypes.c_int)]
+
+
+def critical_column_plan(M: int, K: int, N: int, splits: int = None):
     """How many critical columns the tiled GEMM takes as fp16 slabs through its ring, and from how many on it makes
-    its dense pass instead (the host-side plan of csrc/gemm.h, restated for the tests that aim at either side)."""
-    n_slabs = (K + 127) // 128 * 2
-    npad = (N + 255) // 256 * 256
-    cols = min(n_slabs * 32, 2048, (96 << 20) // (npad * 2))
-    in_slabs = 32 * (8 + cols // 32)
-    left = 3.7 * n_slabs - in_slabs * (1.5 / 32)
-    return in_slabs, in_slabs + (int(left / 0.44) if left > 0 else 0)
+    its dense pass instead, by the library's own plan (a C++ function of it, outside its C ABI)."""
+    f = binding.lib()._ZN4mmd821plan_critical_columnsEiimbi
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_bool, ctypes.c_int], CriticalPlan
+    p = f(M, (K + 127) // 128 * 2, (N + 255) // 256 * 256, True, splits or gemm_splits(M, K, N))
+    return 32 * (8 + p.g_slabs), max(257, p.dense_from)          # (never for what the first eight slabs hold)

@@ -21,7 +21,7 @@ def test_ragged_ends(M, K, N, variant):
     x[5, 3] = np.float16(65504.0)
     tau = 0.75
     flag = ml.outlier_mask(x, tau)
-    assert critical_column_plan(K, N)[1] <= int(flag.sum())
+    assert critical_column_plan(M, K, N)[1] <= int(flag.sum())
     padded = torch.full((M, K + 24), float("nan"), dtype=torch.float16, device="cuda")
     X = padded[:, :K]
     X.copy_(torch.from_numpy(x))

@@ -9,7 +9,7 @@ import torch
 
 from oracle import mixed_linear as ml
 from paper_2407_19775_amd import binding, workloads as wl
-from gpu_util import critical_column_plan, assert_y_close, to_gpu, to_np
+from gpu_util import critical_column_plan, gemm_splits, assert_y_close, to_gpu, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -249,26 +249,42 @@ def exactly_n_critical(rng, M, K, n_crit):
 @pytest.mark.parametrize("variant", [4, 0, 2])
 @pytest.mark.parametrize("n_crit", [0, 1, 31, 32, 33, 64, 65, 100, 255, 256, 257, 300])
 def test_counts_of_critical_columns_around_the_slab_limits(n_crit, variant):
-    """The tiled GEMM takes critical columns 32 at a time as fp16 slabs, up to 256 of them, and adds the rest from
-    rows the preparation gathered: counts on both sides of every border between those paths, over several row
+    """The tiled GEMM takes critical columns 32 at a time as fp16 slabs, up to 256 of them, and the rest as further
+    slabs that the preparation gathered (all of them below the count from which it walks K with both products): counts on both sides of every border between those paths, over several row
     panels and a ragged tail."""
     M, K, N = 600, 1040, 520
     rng = np.random.default_rng([n_crit, variant])
     X, cols = exactly_n_critical(rng, M, K, n_crit)
     flag = ml.outlier_mask(X, 6.0)
-    assert np.array_equal(np.flatnonzero(flag), cols)
+    assert np.array_equal(np.flatnonzero(flag), cols) and n_crit < critical_column_plan(M, K, N)[1]
     bias = wl.gaussian_bias(N, 0.1, rng) if n_crit % 2 else None
     check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=bias, tuning=binding.tune_gemm_tiles(variant))
 
 
-@pytest.mark.parametrize("variant", [4, 5, 0])
-@pytest.mark.parametrize("n_crit", [257, 300, 1312, 1344, 1345, 1485, 1486, 1550])
+@pytest.mark.parametrize("variant", [None, 4, 5, 0])
+@pytest.mark.parametrize("n_crit", [257, 300, 800, 832, 833, "last in the epilogue", "first of the dense pass", 1000])
 def test_counts_of_critical_columns_around_the_change_to_the_dense_pass(n_crit, variant):
-    """34 slabs of K: up to 1344 critical columns travel as fp16 slabs (8, then up to 34 further ones), up to 1485
-    the ones beyond are gathered in the GEMM's epilogue, from 1486 on all of them go through the second, fp16 pass
-    over K."""
+    """18 slabs of K: up to 832 critical columns travel as fp16 slabs (8, then up to 18 further ones), a few more are
+    gathered in the GEMM's epilogue, and from the planned count on all of them go with the codes in one walk over K."""
+    M, K, N = 2600, 1040, 264
+    in_slabs, dense_from = critical_column_plan(M, K, N)
+    assert gemm_splits(M, K, N) == 1 and in_slabs == 832 and in_slabs + 1 < dense_from - 1 and dense_from < 1000
+    n_crit = {"last in the epilogue": dense_from - 1, "first of the dense pass": dense_from}.get(n_crit, n_crit)
+    rng = np.random.default_rng([n_crit, 0 if variant is None else variant, 7])
+    X, cols = exactly_n_critical(rng, M, K, n_crit)
+    assert np.array_equal(np.flatnonzero(ml.outlier_mask(X, 6.0)), cols)
+    check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=wl.gaussian_bias(N, 0.1, rng),
+                 tuning=0 if variant is None else binding.tune_gemm_tiles(variant))
+
+
+@pytest.mark.parametrize("variant", [4, 5, 0])
+@pytest.mark.parametrize("n_crit", [257, 300, "last in slabs", "first of the dense pass", 1344, 1345, 1486, 1550])
+def test_counts_of_critical_columns_around_the_change_to_the_dense_pass_with_few_rows(n_crit, variant):
+    """With 300 rows the walk over K takes over long before the slabs are full (1344 columns)."""
     M, K, N = 300, 2096, 264
-    assert critical_column_plan(K, N) == (1344, 1486)
+    in_slabs, dense_from = critical_column_plan(M, K, N)
+    assert in_slabs == 1344 and 300 < dense_from - 1 and dense_from < 1344
+    n_crit = {"last in slabs": dense_from - 1, "first of the dense pass": dense_from}.get(n_crit, n_crit)
     rng = np.random.default_rng([n_crit, variant, 7])
     X, cols = exactly_n_critical(rng, M, K, n_crit)
     assert np.array_equal(np.flatnonzero(ml.outlier_mask(X, 6.0)), cols)
@@ -298,7 +314,7 @@ def test_most_columns_critical_over_many_rows(M, K, N, variant):
     rng = np.random.default_rng([M, K, variant])
     X = wl.to_fp16(rng.standard_t(3.0, size=(M, K)).astype(np.float32))
     n = int(ml.outlier_mask(X, wl.TAU).sum())
-    assert n >= critical_column_plan(K, N)[1], n               # the dense pass
+    assert n >= critical_column_plan(M, K, N)[1], n               # the dense pass
     W = wl.gaussian_weight(K, N, 0.05, rng)
     check_linear(X, W, wl.TAU, bias=wl.gaussian_bias(N, 0.1, rng), tuning=binding.tune_gemm_tiles(variant))
 

@@ -8,7 +8,7 @@ from oracle import blockwise_codec as bc
 from oracle import boundary_exit as be
 from oracle import mixed_linear as ml
 from paper_2407_19775_amd import binding, workloads as wl
-from gpu_util import assert_y_close, to_gpu, to_np
+from gpu_util import assert_y_close, critical_column_plan, gemm_splits, to_gpu, to_np
 from test_gpu_linear import check_linear, exactly_n_critical
 
 pytestmark = pytest.mark.gpu
@@ -16,11 +16,23 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,K,N,n_crit", [(129, 8208, 264, 5), (130, 11008, 1000, 0), (333, 8192, 520, 300), (129, 32768, 72, 2400)])
 def test_ranges_of_k(M, K, N, n_crit):
-    """2400 of 32768 columns: more than the fp16 slabs hold, fewer than the walk over all of K takes: gathered by the
-    last range."""
+    """300 of 8192 columns: further slabs, shared out between the ranges; 2400 of 32768: the walk over K, in ranges."""
     rng = np.random.default_rng([M, K, N])
     X, _ = exactly_n_critical(rng, M, K, n_crit)
+    assert gemm_splits(M, K, N) > 1 and (n_crit >= critical_column_plan(M, K, N)[1]) == (n_crit == 2400)
     check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=wl.gaussian_bias(N, 0.1, rng))
+
+
+def test_columns_beyond_the_slabs_in_a_split_call():
+    """2400 of 8192 columns: more than the fp16 slabs hold, fewer than the walk over all of K takes: gathered by the
+    last range."""
+    M, K, N = 6000, 8192, 264
+    in_slabs, dense_from = critical_column_plan(M, K, N)
+    assert gemm_splits(M, K, N) > 1 and in_slabs == 2304 and 2400 < dense_from
+    rng = np.random.default_rng([M, K, N])
+    X, _ = exactly_n_critical(rng, M, K, 2400)
+    rows = np.concatenate([np.arange(0, 260), np.arange(M - 200, M)])
+    check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=wl.gaussian_bias(N, 0.1, rng), rows=rows)
 
 
 @pytest.mark.parametrize("tau", [6.0, 0.75])

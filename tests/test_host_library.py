@@ -9,6 +9,7 @@ import pytest
 
 from oracle import dynamic_code as dc
 from paper_2407_19775_amd import binding
+from gpu_util import critical_column_plan
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -117,6 +118,17 @@ def test_a_workspace_for_more_rows_serves_fewer(K, N):
     for size in (lambda m: L.mmd8_linear_workspace_bytes(m, K, N), lambda m: L.mmd8_linear_to_codes_workspace_bytes(m, K, N, 64)):
         sizes = [size(m) for m in sorted(rows)]
         assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("M,K,N,at,walk", [(1576, 1024, 3072, 717, False), (1576, 1024, 3072, 922, True), (2048, 1024, 4096, 819, False),
+                                           (2048, 1024, 4096, 922, True), (256, 4096, 12288, 410, False), (256, 4096, 12288, 819, True),
+                                           (256, 11008, 4096, 440, False), (256, 11008, 4096, 1101, True), (140, 32768, 1024, 655, True),
+                                           (2048, 4096, 12288, 2048, False), (2048, 4096, 12288, 2867, True),
+                                           (4096, 8192, 10240, 2458, False), (4096, 8192, 10240, 3277, True),
+                                           (1024, 4096, 12288, 1434, False), (1024, 4096, 12288, 2048, True)])
+def test_dense_pass_from_where_it_is_the_faster_way(M, K, N, at, walk):
+    """Counts of critical columns at which one way measured 10 % or more faster than the other (256 compute units)."""
+    assert (at >= critical_column_plan(M, K, N)[1]) == walk
 
 
 def test_bad_arguments_are_rejected_before_any_launch():

@@ -73,7 +73,7 @@ def test_interleaved_with_calls_that_bring_their_own_workspace_and_thresholds():
         assert torch.equal(Y, ref) and torch.equal(Y2, ref2), tau
 
 
-@pytest.mark.parametrize("M,K,N,n_crit", [(200, 4096, 4096, 600), (256, 11008, 4096, 5)])
+@pytest.mark.parametrize("M,K,N,n_crit", [(200, 4096, 4096, 500), (256, 11008, 4096, 5)])
 def test_sizes_that_fit_without_the_sums_of_a_split(M, K, N, n_crit):
     """Rows for which K is split, in an array without room for the sums: the call goes through unsplit, with the further
     slabs where there are any to fill, and gives the bits of a call that brings its own workspace and is not split."""
