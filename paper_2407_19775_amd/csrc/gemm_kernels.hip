@@ -1003,8 +1003,15 @@ __device__ __noinline__ void gemm_tile_dense(uint32_t args_lo, uint32_t args_hi,
 
 template <class Cfg>
 using DenseOf = DenseCfg<Cfg::kWaves == 8 ? 256 : 128>;
+// LDS of a launch: the walk's only where a call can come to it (never with original weight rows, nor where its line lies
+// beyond K), so that two workgroups of 128 x 128 tiles fit a compute unit otherwise: 64 x 8192 x 57344 with original rows,
+// two rounds of such tiles, 118 us; 129 with room for the walk, 126 with the three workgroups of fewer registers before.
 template <class Cfg>
-constexpr int kLaunchLds = Cfg::LDS_BYTES > DenseOf<Cfg>::LDS_BYTES ? Cfg::LDS_BYTES : DenseOf<Cfg>::LDS_BYTES;
+constexpr int kMostLds = Cfg::LDS_BYTES > DenseOf<Cfg>::LDS_BYTES ? Cfg::LDS_BYTES : DenseOf<Cfg>::LDS_BYTES;
+template <class Cfg>
+static int launch_lds(const GemmArgs& a) {
+  return dense_critical_path(a.K, a.crit_slabs, a.dense_from, a.W_master != nullptr) ? kMostLds<Cfg> : Cfg::LDS_BYTES;
+}
 
 template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixed(const GemmArgs a) {
@@ -1033,7 +1040,7 @@ static hipError_t ensure_lds_attribute() {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_set[dev]) return hipSuccess;
   const void* fn = reinterpret_cast<const void*>(&k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit>);
-  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLaunchLds<Cfg>);
+  const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMostLds<Cfg>);
   if (e == hipSuccess) attr_set[dev] = true;
   return e;
 }
@@ -1042,7 +1049,7 @@ template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t stream) {
   if (hipError_t e = ensure_lds_attribute<Cfg, kTap, kFull, kCoded, kSplit>(); e != hipSuccess) return e;
   const int grid = ceil_div(a.tiles_m * a.tiles_n * a.splits, 8) * 8;
-  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit>), dim3(grid), dim3(Cfg::kThreads), kLaunchLds<Cfg>, stream, a);
+  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit>), dim3(grid), dim3(Cfg::kThreads), launch_lds<Cfg>(a), stream, a);
   return hipGetLastError();
 }
 

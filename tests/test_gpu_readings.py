@@ -99,6 +99,14 @@ def test_many_critical_columns_and_thresholds():
     assert int(ml.outlier_mask(X, 2.5).sum()) > 64
 
 
+@pytest.mark.parametrize("tau", [wl.TAU, 0.0])
+def test_more_small_tiles_than_compute_units(tau):
+    """Up to 64 rows with original weight rows: 128 x 128 tiles for any width, here two on some compute units, in the LDS
+    that such a tile needs without the walk that these calls never take (tau = 0: all 272 columns critical)."""
+    X, W, b = problem(40, 272, 34000, 6, heavy=True)
+    check(X, W, b, tau, "sub_threshold", True)
+
+
 def test_llama7b_linear_at_full_size():
     shape = wl.LLAMA_7B_LINEARS[1]
     X, _ = wl.prefill_activation(2, 11, 2048, shape.K)
