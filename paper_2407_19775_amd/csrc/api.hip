@@ -366,9 +366,12 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   const PackOutliers po = {ws.idx, ws.n_out, ws.mask, t.outlier_mask, t.outlier_idx, t.n_outliers,
                            Wq_packed, col_absmax, N, ws.xo, ws.wo, ws.f_slabs, ws.crit_slabs,
                            readings ? readings->W_master : nullptr, readings ? readings->ldw : 0, ws.xg, ws.wg, ws.g_slabs, ws.dense_from};
-  // Up to 128 rows go through the decode kernels, 64 rows at a time (the weights are streamed twice for more
-  // than 64): for activations with few critical columns that costs what the tiled GEMM costs at this size, and
-  // with heavy-tailed activations (hundreds of critical columns) it is ten times faster.
+  // Up to 128 rows go through the decode kernels, 64 rows at a time (the weights are streamed twice for more than 64).
+  // The tiled GEMM takes over at 129.  The two routes at the border, us per call at 128 / 129 rows, weights from memory:
+  // 4096 -> 12288 59 / 41 with few critical columns, 64 / 69 with 90 % of them critical; 4096 -> 22016 88 / 49 and 92 / 91;
+  // 11008 -> 4096 61 / 44 and 66 / 74; 8192 -> 57344 205 / 139 and 248 / 355; 28672 -> 8192 146 / 108 and 150 / 227.  So the
+  // two passes lose on the usual input and win on the heavy-tailed input that decoding meets, and which of them a call
+  // brings is known only on the device.
   // (the decode kernels multiply the critical columns with the weight codes themselves: original 16-bit rows go
   // through the tiled GEMM whatever the number of rows)
   const bool skinny = M <= kSkinnyChunkedMaxM && !(readings && readings->W_master);

@@ -9,14 +9,15 @@
 // whole tiles, so the main loop has no bounds checks.  A workgroup owns one BM x BN tile of Y.
 // K is walked in slabs of 64 bytes.  A slab of both operands goes from global memory straight
 // into LDS (global_load_lds_dwordx4: no register staging, every wave instruction copies 1 KB that
-// is contiguous in HBM) through a ring of LDS buffers, two or three slabs ahead of the MFMAs.  The
+// is contiguous in HBM) through a ring of LDS buffers, two to four slabs ahead of the MFMAs.  The
 // blocks are fragment-major already in HBM: the 64 lanes of an MFMA operand read 64 consecutive
 // 16-byte pieces.  A lane's 16 bytes feed one operand row of the 32x32x32 MFMA; the k order
 // inside the instruction is irrelevant as long as both operands use the same piece for the same
 // lane group, which they do.
 //
 // One kernel, k_gemm_mixed, instantiated for several tile configurations (256 x 256 with eight waves for
-// large problems, smaller tiles for small ones); fragments are double-buffered in registers.
+// large problems, smaller tiles for small ones); fragments are double-buffered in registers, by k-steps or, where the
+// wave tile is small enough, by whole slabs.
 #include <atomic>
 #include <type_traits>
 #include <utility>
@@ -93,8 +94,6 @@ template <int kVm>
 __device__ inline void wait_slab_and_sync() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kVm) : "memory");
 }
-__device__ inline void wait_lds_and_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
-__device__ inline void sync_only() { asm volatile("s_barrier" : : : "memory"); }
 
 // Tile assignment.  Consecutive workgroup ids land on different XCDs (8 of them, each with its own L2), so XCD x
 // gets the ids x, x + 8, ...: a contiguous run of the tile order below, 32 tiles (one per CU) at a time.  The order
@@ -463,14 +462,14 @@ __device__ __forceinline__ void load_column_terms(const GemmArgs& a, const WaveP
 }
 
 // ------------------------------------------------------------------------------------------------
-// Generic kernel: 4 waves, one wave per SIMD or two workgroups per CU, small tiles.
+// One tile: the slabs of codes, then those of fp16 operands, then the epilogue.
 // kFull: M and N are multiples of the tile, so no output store needs a bounds check.
 // kTap: also write the raw int32 accumulators (parity checks).
 // kCoded: the output goes through an activation, takes a residual and / or leaves in blockwise-coded form
 // (store_tile_coded).
-// ------------------------------------------------------------------------------------------------
 // kSplit: the workgroup multiplies one of a.splits ranges of K (slabs of codes and of fp16 operands alike) and leaves
 // fp32 sums.
+// ------------------------------------------------------------------------------------------------
 template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
@@ -738,8 +737,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   for (; s + AHEAD < total_slabs; ++s) step(s, halves{}, yes{}, yes{});
   for (; s + 1 < total_slabs; ++s) step(s, none{}, yes{}, yes{});
   if (s < total_slabs) step(s, none{}, no{}, yes{});
-  // every wave passes a barrier after its last LDS read of the ring (the stores below begin with one): the slab buffers are
-  // free for the gather staging, which starts with a barrier of its own before writing them
+  // What follows writes the slab buffers, and begins with a barrier: every wave has then read its last fragments.  (The
+  // sums of a range go straight from registers.)  With K split the last range gathers the columns beyond the slabs.
   if (n_out > kOutlierSlab * (crit_used + more_used) && (!kSplit || split == a.splits - 1))
     gather_outlier_columns<Cfg>(a, p, acc, smem, kOutlierSlab * (crit_used + more_used), n_out);
   if constexpr (kSplit)
@@ -1132,11 +1131,15 @@ int plan_gemm_splits(int M, int K, int N) {
   const int n_slabs = packed_k(K) / BK, cus = device_cu_count();
   const long tiles = (long)ceil_div(M, Cfg5::BM) * ceil_div(N, Cfg5::BN);
   if (M <= 128 || 2 * tiles > cus) return 1;
-  // us of a call with s ranges: the slabs of a workgroup (0.45 each), its start and end, and with more than one range
-  // the kernel that adds them up and the 8 bytes per output and range that the sums cost.  Measured (whole calls, without /
-  // with the split): 256 x 11008 x 4096 86 / 44 us (8 ranges), 256 x 4096 x 4096 38.6 / 31.0, 400 x 8192 x 2048 57.7 / 35.4,
-  // 256 x 4096 x 12288 43.8 / 41.2 (2 ranges; with most columns critical 114 / 80); no gain, and none taken by this
-  // rule: 1000 x 4096 x 4096 40.2 / 41.6, 512 x 2048 x 2048 25.9 / 29.2, 200 x 1024 x 1024 19.2 / 21.0.
+  // us of a call with s ranges: the slabs of a workgroup (0.45 each, 0.37 in one round of small tiles), its start and end,
+  // and with more than one range the kernel that adds them up and the 8 bytes per output and range that the sums cost.
+  // Measured (whole calls, few critical columns, weights that come from memory, without / with the split this rule takes):
+  // 256 x 11008 x 4096 79 / 50 us (8 ranges), 256 x 4096 x 4096 39.7 / 31.5 (5), 1024 x 8192 x 2048 66 / 49 (4), 1576 x
+  // 4096 x 1024 43.8 / 39.8 (4), 1024 x 11008 x 4096 84 / 72 (2), 200 x 2816 x 2048 31.9 / 29.6 (9).  No gain, and none
+  // taken: 512 x 2048 x 2048 26.3 / 29.1 (2), 256 x 4096 x 12288 41.4 / 42.2 (2).  The rule takes more ranges than would be
+  // best here and there (256 x 11008 x 4096 44.6 with 5, 200 x 2816 x 2048 25.8 with 4) and leaves out some that pay (2048 x
+  // 4096 x 1024 44.0 / 38.5 with 3): 5 % off the best count on average over 38 shapes, never slower than no split.  With
+  // weights that are still in the last-level cache the split gains less (200 x 2816 x 2048 24.5 / 27.1).
   int best = 1;
   double least = (one_round_of_small_tiles(M, N) ? 0.37 : 0.45) * n_slabs + 5.0;
   for (int s = 2; s * tiles <= cus && n_slabs / s >= 4; ++s) {
@@ -1211,13 +1214,11 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
     }
     return launch_variant(a, 4, stream);
   }
-  // Less than one round of large tiles: 128 x 256 with eight waves and the four-slab ring, unless that leaves most
-  // of the chip without a workgroup and K is short, where 128 x 128 tiles (up to three per CU) do better.  Measured
-  // on the 7B linears at 160-1024 rows: 4096 -> 12288 at 256 rows 39 us against 47 with the four-wave 128 x 256
-  // tile chosen before, 11008 -> 4096 (32 workgroups, 172 slabs) 73 against 79 with 128 x 128; 4096 -> 4096 stays
-  // with 128 x 128 (33 against 35).
-  // (where the 128 x 256 tiles would need a second round and the 256 x 256 ones fit in one, the large tiles win:
-  // 4096 -> 12288 at 768 rows 61 against 71 us, 4096 -> 22016 at 512 rows 61 against 70)
+  // Less than one round of large tiles: 128 x 128 tiles where they fit one round, else 128 x 256 with eight waves and the
+  // four-slab ring.  (Measured, 128 x 128 / 128 x 256: 256 x 4096 x 12288 32 / 36 us, 1000 x 4096 x 4096 37 / 42, 1024 x
+  // 2048 x 1024 24 / 27; 300 x 4096 x 12288, where the small tiles are a round and a bit, 52 / 39.)  Where the 128 x 256
+  // tiles would need a second round and the 256 x 256 ones fit in one, the large tiles win: 4096 -> 12288 at 768 rows 61
+  // against 71 us, 4096 -> 22016 at 512 rows 61 against 70.
   if (a.M > 128 && tiles_128x256 > cus) return launch_variant(a, 4, stream);
   if (a.M > 64 && !one_round_of_small_tiles(a.M, a.N)) return launch_variant(a, 5, stream);
   return launch_variant(a, 0, stream);

@@ -11,7 +11,7 @@ import torch
 
 from oracle import lora, mixed_linear as ml
 from paper_2407_19775_amd import binding, workloads as wl
-from gpu_util import assert_y_close, to_gpu, to_np
+from gpu_util import assert_y_close, critical_column_plan, to_gpu, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -77,8 +77,10 @@ def test_no_critical_column_and_many(tau, M):
 @pytest.mark.parametrize("n_crit,r", [(1, 64), (33, 16), (70, 40), (200, 8), (256, 64), (257, 24), (700, 16), (830, 40)])
 def test_critical_column_slabs_next_to_the_adapter(n_crit, r, variant):
     """1 to 8 fp16 slabs of critical columns in use (the unused ones are skipped), then the adapter's one or two
-    slabs behind them in the same ring; 257: one more column, in a ninth slab from the further ones."""
+    slabs behind them in the same ring; 257: one more column, in a ninth slab from the further ones; 700 and 830: the walk
+    over K."""
     M, K, N = 300, 1040, 520
+    assert (n_crit >= critical_column_plan(M, K, N)[1]) == (n_crit >= 700)
     rng = np.random.default_rng([n_crit, r, variant])
     x = np.clip(rng.standard_normal((M, K)), -5.0, 5.0).astype(np.float32)
     cols = np.sort(rng.choice(K, n_crit, replace=False))
@@ -91,11 +93,30 @@ def test_critical_column_slabs_next_to_the_adapter(n_crit, r, variant):
     check_lora(X, wl.gaussian_weight(K, N, 0.02, rng), A, B, 6.0, tuning=binding.tune_gemm_tiles(variant))
 
 
+@pytest.mark.parametrize("variant", [None, 0])
+@pytest.mark.parametrize("n_crit,r", [(700, 16), (830, 40), (850, 64)])
+def test_further_slabs_and_the_epilogue_gather_next_to_the_adapter(n_crit, r, variant):
+    """Many rows: 700 and 830 columns in the first and the further slabs, 850 a few more than those hold (832)."""
+    M, K, N = 2600, 1040, 520
+    in_slabs, dense_from = critical_column_plan(M, K, N)
+    assert in_slabs == 832 and 850 < dense_from
+    rng = np.random.default_rng([n_crit, r])
+    x = np.clip(rng.standard_normal((M, K)), -5.0, 5.0).astype(np.float32)
+    cols = np.sort(rng.choice(K, n_crit, replace=False))
+    for j, k in enumerate(cols):
+        x[(11 * j) % M, k] = (-1.0) ** j * (7.0 + j % 40)
+    A = wl.to_fp16(rng.standard_normal((r, K)).astype(np.float32) * 0.05)
+    B = wl.to_fp16(rng.standard_normal((N, r)).astype(np.float32) * 0.05)
+    check_lora(wl.to_fp16(x), wl.gaussian_weight(K, N, 0.02, rng), A, B, 6.0,
+               tuning=0 if variant is None else binding.tune_gemm_tiles(variant))
+
+
 @pytest.mark.parametrize("variant", [4, 2])
 def test_dense_pass_next_to_the_adapter(variant):
-    """1600 of 2096 columns critical: no slab of critical columns, the adapter's slab, then the second, fp16 pass
-    over K."""
+    """1600 of 2096 columns critical: no slab of critical columns, the walk over K with both products, then the adapter's
+    slab."""
     M, K, N, n_crit, r = 300, 2096, 264, 1600, 16
+    assert n_crit >= critical_column_plan(M, K, N)[1]
     rng = np.random.default_rng([n_crit, r, variant, 3])
     x = np.clip(rng.standard_normal((M, K)), -5.0, 5.0).astype(np.float32)
     cols = np.sort(rng.choice(K, n_crit, replace=False))
