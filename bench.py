@@ -33,8 +33,8 @@ INT8_POWER_LIMITED_TOPS = 3468.0
 # (70B-shaped layer, 4096 tokens) and the 7B-shaped step.  Valid for the GEMM source they were measured on:
 # reported as null once that file has changed.
 GEMM_TRAFFIC_BYTES_PER_LAUNCH = 1185.3e6
-GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 182.6e6
-GEMM_TRAFFIC_SOURCE_SHA256 = "d31feb445e95096b1c0fff96f120c4d970f74e19a65f82518998941645101b22"
+GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 182.8e6
+GEMM_TRAFFIC_SOURCE_SHA256 = "2e7e74ac7976a1b60842d4b51b17c4176509de018f1bbdb1187d20cbc5e20b33"
 
 
 def parse():
