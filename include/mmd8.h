@@ -130,8 +130,8 @@ typedef struct {
   uint32_t tuning;
 } mmd8_debug_taps;
 #define MMD8_TUNE_GEMM_TILES(v)    ((uint32_t)((v) + 1) & 0xfu) /* tiled GEMM (more than 128 rows): tile configuration v = 0..5 */
-#define MMD8_TUNE_SEPARATE_PREP    0x10u  /* up to 8 rows: run the scan and pack kernels instead of letting the multiplying kernel prepare its own operands */
-#define MMD8_TUNE_NO_ROWS_KERNEL   0x20u  /* one or two rows: use the split-K kernels instead of the single-kernel form */
+#define MMD8_TUNE_SEPARATE_PREP    0x10u  /* up to 8 rows in the split-K kernels: run the scan and pack kernels instead of letting the multiplying kernel prepare its own operands */
+#define MMD8_TUNE_NO_ROWS_KERNEL   0x20u  /* up to 8 rows: use the split-K kernels where the layer would be a single kernel */
 
 /* The layer, per call (tau: threshold; X read as X[m*ldx + k]; Y written as Y[m*ldy + n]):
  *     flag[k]  = any_m |X[m,k]| >= tau

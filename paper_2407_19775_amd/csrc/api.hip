@@ -172,9 +172,9 @@ static size_t workspace_bytes_for(int M, int K, int N, int r = 0, int exit_block
 // A coded output is produced by the kernel that ends the layer when no block of it is shared between
 // workgroups: the tiled GEMM needs blocks inside its 256-column tiles; the decode path encodes where it sums
 // its partial outputs, any block size, as long as its second pass of 64 rows starts on a block boundary.  The
-// first few rows are a single kernel with 32 columns per workgroup and nothing to sum afterwards: the encoder follows it.
+// first few rows are a single kernel with nothing to sum afterwards: the encoder follows it.
 static bool exit_fuses(int M, int K, int N, int block) {
-  if (rows_kernel_fits(M, packed_k(K))) return false;
+  if (rows_kernel_fits(M, packed_k(K), N)) return false;
   if (M <= kSkinnyChunkedMaxM) return M <= kSkinnyMaxM || ((size_t)kSkinnyMaxM * N) % block == 0;
   return (block == 64 || block == 128 || block == 256) && N % block == 0;
 }
@@ -378,11 +378,11 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   // A few rows (at most kPanelPrepMaxM): the decode GEMM kernel prepares its own operands (scales, codes, critical
   // columns) from X, and the scan and pack kernels are left out.  Not when their outputs are asked for through the taps.
   const bool wants_prep_taps = t.outlier_mask || t.row_absmax || t.xq || t.n_outliers || t.outlier_idx;
-  // One or two rows (while their operands fit in LDS): the whole layer is one kernel (k_gemm_rows).  When the taps of the
+  // A few rows (while their operands fit in LDS): the whole layer is one kernel (k_gemm_rows).  When the taps of the
   // preparation are asked for, the scan and pack kernels run ahead of it for their sake only.
   // (alternative readings: always the separate scan and pack kernels, which is where they differ)
   const bool may_own_prep = !(t.tuning & MMD8_TUNE_SEPARATE_PREP) && !readings;
-  const bool rows_path = may_own_prep && !(t.tuning & MMD8_TUNE_NO_ROWS_KERNEL) && rows_kernel_fits(M, Kpad);
+  const bool rows_path = !readings && !(t.tuning & MMD8_TUNE_NO_ROWS_KERNEL) && rows_kernel_fits(M, Kpad, N);
   const bool own_prep = skinny && !rows_path && !wants_prep_taps && may_own_prep && panel_prep_fits(M, plan_skinny(M, K, N));
   // coded activations are decoded by the one-pass preparation kernel itself where that kernel runs
   // (element offsets are held in 32 bits there); otherwise by the decoder, ahead of the usual kernels

@@ -590,109 +590,137 @@ hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t 
 }
 
 // ------------------------------------------------------------------------------------------------
-// One or two rows: the whole layer in one kernel.  A workgroup owns 32 output columns (one 32-row group of
-// Wt); wave w of its eight takes slabs w, w + 8, ... of the K range, straight from HBM into registers four
-// slabs ahead, with no barrier in the loop: the activation side is read-only by then.  It is made once per
-// workgroup, for the whole of K, as in the kPrep panel kernel (row scales from a pass over the rows, then
-// codes with the critical columns zero and an fp16 copy that keeps only them), stored as plain rows in LDS;
-// a lane builds its MFMA fragment from the row it stands for and lanes beyond M feed zeros.  The eight partial
-// results meet in LDS: the int32 sums are exact, the fp32 sums of the 16-bit part are added in wave order, so
-// the output does not depend on timing.  No split between workgroups, hence no partial outputs in HBM and no
-// second kernel.
+// A few rows: the whole layer in one kernel.  A workgroup of sixteen waves has a compute unit to itself.  It prepares
+// the activation side once, for the whole of K, as plain rows in LDS (row scales from a pass over the rows, codes with
+// the critical columns zero, an fp16 copy that keeps only those), then walks its share of the 16-column tiles of the
+// output (half a 32-row group of Wt each): wave w multiplies slabs w, w + 16, ... of every tile, weights straight from
+// memory into registers eight slabs ahead, on from one tile to the next, with no barrier: the operands are read-only by
+// then.  A lane builds its MFMA fragment from the row it stands for, lanes beyond the rows feed zeros.  The sixteen
+// partial results of a tile are left in LDS and added at the end: the int32 sums are exact, the fp32 sums of the 16-bit
+// part are added in wave order, so the output does not depend on timing.  No split of K between workgroups, hence no
+// partial outputs in memory and no second kernel.
+//
+// What bounds it: the weights' bytes, and the microseconds before the first and after the last of them.  A kernel that does
+// nothing but read them takes 9.1 us for 4096 x 12288 (4.0 us for 4096 x 4096, 14.6 for 4096 x 22016, 8.2 for 11008 x 4096),
+// weights from memory, launch included; this one 11.9, 6.5, 18.6 and 11 at one row.
+// Order of the requests: a compute unit's loads come back in the order in which they were made, so the rows of X and the
+// terms of the output columns are asked for before any weight; the other way round the preparation cannot begin before
+// the first weights have come from memory.  For the same reason few weights are requested ahead (48 KB per compute unit):
+// with 128 KB the rows, and whatever else a wave asks for, queue behind them, and a 7B layer takes 48.5 us at one row
+// instead of 45.9.  And a compute unit prepares once: with two or three workgroups on it (32 columns each) the rows of
+// the second queued behind the weights of the first.  A layer of one / two / four rows took 53 / 63 / 68 us when the weights
+// were requested first, in workgroups of 32 columns (four rows: with K split between workgroups); 45.9 / 52.9 / 60.9 now.
+// kM: rows, at most (1, 2, 4, 8).  kChunks: 8-column chunks of the rows per thread (a number the compiler knows, so that
+// they are loaded all together: a load under a condition is waited for before the next one is issued).
 // ------------------------------------------------------------------------------------------------
-// kCols: output columns per workgroup.  32 (one group of Wt, v_mfma_i32_32x32x32_i8) by default; 16 (half a group,
-// v_mfma_i32_16x16x64_i8 / v_mfma_f32_16x16x32_f16, whose lanes take the same 16-byte pieces of the blocked layout in
-// another order) when 32 would leave compute units without a workgroup (N up to 8192 on 256 of them).  (Two groups
-// per workgroup, for shapes with more groups than the chip holds workgroups at once, was slower: the registers then
-// allow a prefetch of only two slabs, and the 4096 -> 22016 linear took 29.9 us instead of 21.6.)
-constexpr int kRowsAhead = 4;   // weight slabs a wave has requested ahead of the one it multiplies (2 KB each); 8: slower (registers: 4 instead of 7 waves per SIMD; a 7B layer at one token 64 us instead of 56)
-template <bool kTap, int kCols>
-__global__ __launch_bounds__(512, 4) void k_gemm_rows(const SkinnyArgs a) {
-  static_assert(kCols == 32 || kCols == 16, "one group of 32 weight rows, or half of one");
-  constexpr int WAVES = 8, kThreads = WAVES * kWave, kAhead = kRowsAhead;
-  constexpr int kPieces = kCols == 32 ? 2 : 1;                       // 16-byte weight pieces per lane and slab
-  extern __shared__ __attribute__((aligned(16))) int8_t s_ops[];     // [M][Kpad] codes, then [M][Kpad] fp16
+template <int kM, int kChunks>
+__global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyArgs a) {
+  constexpr int WAVES = kRowsWaves, kThreads = WAVES * kWave, kAhead = 3;
+  extern __shared__ __attribute__((aligned(16))) int8_t s_ops[];     // rows_lds_bytes: operands, chunk flags, sums
   __shared__ uint8_t s_any[MMD8_MAX_K / kSlabBytes];
-  __shared__ uint32_t s_part[kRowsMaxM][WAVES];
-  __shared__ float s_r[kRowsMaxM], s_scale[kRowsMaxM];
-  __shared__ uint8_t s_over[kRowsMaxOperandBytes / 3 / 8];   // per 8-column chunk, rows one after the other: bits "at or above the threshold"
-  __shared__ int32_t s_acc[WAVES][kRowsMaxM][kCols];
-  __shared__ float s_accf[WAVES][kRowsMaxM][kCols];
+  __shared__ uint32_t s_part[kM][WAVES];
+  __shared__ float s_r[kM], s_scale[kM];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  // the operand row / output column a lane stands for, and which 16-byte piece of the k range it holds
-  const int lr = lane & (kCols - 1), lg = lane / kCols;
+  // the operand row / output column a lane stands for, and which 16-byte piece of the slab it holds
+  const int lr = lane & 15, lg = lane >> 4;
   const int n_slabs = a.n_slabs, Kpad = n_slabs * kSlabBytes;
+  const int M = kM == 1 ? 1 : a.M;
   reset_column_flags(a.flag_reset, Kpad);
-  const int n0 = blockIdx.x * kCols;                                 // < Npad: the grid covers whole groups only
-  int8_t* s_code = s_ops;
-  uint16_t* s_xf = reinterpret_cast<uint16_t*>(s_ops + (size_t)a.M * Kpad);
+  const int row_chunks = Kpad / 8, all_chunks = M * row_chunks;
+  int8_t* s_code = s_ops;                                            // [M][Kpad]
+  uint16_t* s_xf = reinterpret_cast<uint16_t*>(s_ops + (size_t)M * Kpad);    // [M][Kpad]
+  uint8_t* s_over = reinterpret_cast<uint8_t*>(s_xf + (size_t)M * Kpad);     // [all_chunks]: bits "at or above the threshold" (kM > 1)
+  int32_t* s_sum = reinterpret_cast<int32_t*>(s_over + (kM > 1 ? round_up(all_chunks, 16) : 0));   // [tile][int / float][wave][M][16]
+  const int tile_words = 2 * WAVES * M * 16;
 
-  const int mine = wave < n_slabs ? (n_slabs - wave + WAVES - 1) / WAVES : 0;   // slabs of this wave
-  // a group of 32 weight rows is 2 KB per slab: [k-step 0..1][lane group 0..1][row 0..31] 16-byte pieces
-  const int8_t* wgrp = a.Wt + (size_t)(n0 >> 8) * n_slabs * kBlockBytes + (size_t)((n0 & 255) >> 5) * 2048 +
-                       (kCols == 32 ? lane * 16 : (lg >> 1) * 1024 + (32 * (lg & 1) + (n0 & 16) + lr) * 16);
-  struct W2 {
-    v4i w[kPieces];
+  // ---- the rows, read once: a thread keeps its chunks (rows and columns flattened) in registers from the pass that finds
+  // the row scales to the pass that writes codes and fp16 critical columns
+  v4u raw[kChunks];
+  auto chunk_place = [&](int i, int& m, int& c) {                     // false: beyond the rows
+    const int q = i * kThreads + (int)threadIdx.x;
+    m = kM == 1 ? 0 : q / row_chunks;
+    c = q - m * row_chunks;
+    return q < all_chunks;
   };
-  auto fetch_w = [&](int i, W2& f) {                                  // this wave's i-th slab (clamped past the end)
-    const int slab = wave + WAVES * min(i, max(mine - 1, 0));
-    const int8_t* p = wgrp + (size_t)min(slab, n_slabs - 1) * kBlockBytes;
 #pragma unroll
-    for (int ks = 0; ks < kPieces; ++ks) f.w[ks] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p + ks * 1024));
-  };
-  W2 f[kAhead];
-#pragma unroll
-  for (int i = 0; i < kAhead; ++i) fetch_w(i, f[i]);
+  for (int i = 0; i < kChunks; ++i) {
+    int m, c;
+    const bool ok = chunk_place(i, m, c) && c * 8 < a.K;
+    raw[i] = *reinterpret_cast<const v4u*>(a.X + (ok ? (size_t)m * a.ldx + c * 8 : (size_t)0));
+  }
+  // the terms of the output that this thread will finish (all threads load, some use it)
+  const int tiles = ceil_div(ceil_div(a.N, 16) - (int)blockIdx.x, (int)gridDim.x);   // blockIdx.x, + gridDim.x, ...
+  const int out_tile = (int)threadIdx.x / (M * 16), out_m = (int)threadIdx.x % (M * 16) / 16;
+  const int out_n = ((int)blockIdx.x + out_tile * (int)gridDim.x) * 16 + lr;
+  const bool has_out = out_tile < tiles && out_n < a.N;
+  const int safe_n = has_out ? out_n : 0;
+  const float out_c = a.c[safe_n];
+  const uint16_t* no_term = reinterpret_cast<const uint16_t*>(a.c);   // any address that can be read
+  const uint16_t out_bias = *(a.bias ? a.bias + safe_n : no_term);
+  const uint16_t out_res = *(a.residual ? a.residual + (size_t)out_m * a.ldr + safe_n : no_term);
 
-  // ---- the activation side, once per workgroup (the weight requests above are in flight meanwhile).  The rows
-  // are read once: a thread keeps its 8-column chunks (at most kChunks, rows and columns flattened) in registers
-  // from the pass that finds the row scales to the pass that writes codes and fp16 critical columns.
-  constexpr int kChunks = (kRowsMaxOperandBytes / 3 / 8 + kThreads - 1) / kThreads;    // 6
+  // ---- weights: this wave's slabs of the tiles one after the other
+  const int mine = wave < n_slabs ? (n_slabs - wave + WAVES - 1) / WAVES : 0;   // slabs of this wave per tile: at most 64
+  const uint32_t lane_off = (lg >> 1) * 1024 + (32 * (lg & 1) + lr) * 16;
+  auto tile_base = [&](int t) {
+    const int n0 = ((int)blockIdx.x + t * (int)gridDim.x) * 16;
+    return a.Wt + (size_t)(n0 >> 8) * n_slabs * kBlockBytes + (size_t)((n0 & 255) >> 5) * 2048 + (n0 & 16) * 16;
+  };
+  int f_tile = 0, f_slab = 0;                                         // what is requested next; past the end the last slab again
+  const int8_t* f_base = tile_base(0);
+  auto fetch_w = [&](v4i& w) __attribute__((always_inline)) {
+    const int slab = min(wave + WAVES * f_slab, n_slabs - 1);
+    w = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(f_base + (size_t)slab * kBlockBytes + lane_off));
+    if (f_slab + 1 < mine) {
+      ++f_slab;
+    } else if (f_tile + 1 < tiles) {
+      f_slab = 0;
+      f_base = tile_base(++f_tile);
+    }
+  };
+  v4i f[kAhead];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) fetch_w(f[i]);
+  __builtin_amdgcn_sched_barrier(0);
+
   for (int t = threadIdx.x; t < n_slabs; t += kThreads) s_any[t] = 0;
   const us2 th2 = __builtin_bit_cast(us2, a.th | (a.th << 16));
-  const int row_chunks = Kpad / 8, all_chunks = a.M * row_chunks;
-  v4u raw[kChunks];
-  us2 best[kRowsMaxM];
+  us2 best[kM];
+  uint32_t over[kChunks];                                             // bit j: |element j| >= threshold
 #pragma unroll
-  for (int m = 0; m < kRowsMaxM; ++m) best[m] = __builtin_bit_cast(us2, 0u);
-#pragma unroll
-  for (int i = 0; i < kChunks; ++i) {
-    const int q = i * kThreads + threadIdx.x;
-    const int m = q / row_chunks, k = (q - m * row_chunks) * 8;
-    raw[i] = v4u{0, 0, 0, 0};
-    if (q < all_chunks && k < a.K) raw[i] = *reinterpret_cast<const v4u*>(a.X + (size_t)m * a.ldx + k);
-  }
+  for (int m = 0; m < kM; ++m) best[m] = __builtin_bit_cast(us2, 0u);
 #pragma unroll
   for (int i = 0; i < kChunks; ++i) {
-    const int q = i * kThreads + threadIdx.x;
+    int m, c;
+    const bool ok = chunk_place(i, m, c) && c * 8 < a.K;              // (the K padding: zeros, never critical)
     us2 t = __builtin_bit_cast(us2, 0u);
-    uint32_t over = 0;                                                // bit j: |element j| >= threshold
+    over[i] = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {   // per half, wraps mod 2^16: entries below the threshold get the top bit
+      raw[i][w] = ok ? raw[i][w] : 0u;
       const us2 d = (us2)(__builtin_bit_cast(us2, raw[i][w] & 0x7fff7fffu) - th2);
       t = __builtin_elementwise_max(t, d);
       const uint32_t dd = __builtin_bit_cast(uint32_t, d);
-      over |= ((~dd >> 15) & 1u) << (2 * w) | ((~dd >> 31) & 1u) << (2 * w + 1);
+      over[i] |= ((~dd >> 15) & 1u) << (2 * w) | ((~dd >> 31) & 1u) << (2 * w + 1);
     }
-    if (q < all_chunks) {                                               // (a chunk of the K padding is all zeros)
-      const int m = q / row_chunks, c = q - m * row_chunks;
+    if (!ok) over[i] = 0;
 #pragma unroll
-      for (int mm = 0; mm < kRowsMaxM; ++mm)
-        if (mm == m) best[mm] = __builtin_elementwise_max(best[mm], t);
-      s_over[q] = (c * 8 < a.K) ? (uint8_t)over : (uint8_t)0;           // K padding: never critical
+    for (int mm = 0; mm < kM; ++mm)
+      if (ok && mm == m) best[mm] = __builtin_elementwise_max(best[mm], t);
+    if constexpr (kM > 1) {
+      if (i * kThreads + (int)threadIdx.x < all_chunks) s_over[i * kThreads + threadIdx.x] = (uint8_t)over[i];
     }
   }
 #pragma unroll
-  for (int m = 0; m < kRowsMaxM; ++m) {
-    if (m < a.M) {
-      const uint32_t both = __builtin_bit_cast(uint32_t, best[m]);
-      const uint32_t wmax = wave_max_u32(max(both & 0xffffu, both >> 16));
-      if (lane == 0) s_part[m][wave] = wmax;
-    }
+  for (int m = 0; m < kM; ++m) {
+    const uint32_t both = __builtin_bit_cast(uint32_t, best[m]);
+    const uint32_t wmax = wave_max_u32(max(both & 0xffffu, both >> 16));
+    if (lane == 0) s_part[m][wave] = wmax;
   }
   __syncthreads();
-  if ((int)threadIdx.x < a.M) {
+  if ((int)threadIdx.x < M) {
     uint32_t mm = 0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) mm = max(mm, s_part[threadIdx.x][w]);
@@ -703,14 +731,17 @@ __global__ __launch_bounds__(512, 4) void k_gemm_rows(const SkinnyArgs a) {
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kChunks; ++i) {
-    const int q = i * kThreads + threadIdx.x;
-    // one chunk at a time (the 48 conversions of a thread in flight together would take 190 registers): the
-    // chunk passes through an opaque statement, and such statements keep their order
+    // one chunk at a time (bounded registers): the chunk passes through an opaque statement, and such statements keep
+    // their order
     asm volatile("" : "+v"(raw[i][0]), "+v"(raw[i][1]), "+v"(raw[i][2]), "+v"(raw[i][3]) : : "memory");
-    if (q < all_chunks) {
-      const int m = q / row_chunks, c = q - m * row_chunks, k = c * 8;
-      uint32_t crit = 0;                                              // bit j: column k + j is critical
-      for (int mm = 0; mm < a.M; ++mm) crit |= s_over[mm * row_chunks + c];
+    int m, c;
+    if (chunk_place(i, m, c)) {
+      const int k = c * 8;
+      uint32_t crit = over[i];                                        // bit j: column k + j is critical
+      if constexpr (kM > 1) {
+#pragma unroll
+        for (int mm = 0; mm < kM; ++mm) crit |= mm < M ? s_over[mm * row_chunks + c] : 0u;
+      }
       const float sc = s_scale[m];
       uint32_t code[2] = {0, 0}, xf[4];
 #pragma unroll
@@ -729,158 +760,158 @@ __global__ __launch_bounds__(512, 4) void k_gemm_rows(const SkinnyArgs a) {
   }
   __syncthreads();
 
-  // ---- this wave's slabs
-  typedef typename std::conditional<kCols == 32, v16i, v4i>::type AccI;
-  typedef typename std::conditional<kCols == 32, v16f, v4f>::type AccF;
-  AccI acc;
-  AccF accf;
-#pragma unroll
-  for (int e = 0; e < (kCols == 32 ? 16 : 4); ++e) acc[e] = 0, accf[e] = 0.0f;
-  const bool row_live = lr < a.M;
+  // ---- the products
+  v4i acc = v4i{0, 0, 0, 0};
+  v4f accf = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  const bool row_live = lr < M;
   const int row = row_live ? lr : 0;                                  // lanes beyond M read row 0 and feed zeros
   const int8_t* my_code = s_code + (size_t)row * Kpad + lg * 16;
   const uint16_t* my_xf = s_xf + (size_t)row * Kpad + lg * 16;
-  // "slab holds a critical column" for this wave's next 64 slabs as one scalar mask (a flag read from LDS when it
-  // is needed would stand between the slab's arrival and its MFMAs)
-  uint64_t any_mask = 0;
-  // this wave's i-th slab: multiply what was requested kAhead slabs ago, then request slab i + kAhead into the
-  // registers just used
-  auto step = [&](int i, auto u_tag) __attribute__((always_inline)) {
-    constexpr int u = decltype(u_tag)::value;                        // i % kAhead
-    const W2& w = f[u];
-    const int slab = wave + WAVES * i;
-    if constexpr (u == 0) {                                          // 64 is a multiple of kAhead: only here can i start a window
-      if ((i & 63) == 0) any_mask = __builtin_amdgcn_ballot_w64(s_any[wave + WAVES * min(i + lane, max(mine - 1, 0))] != 0);
-    }
-    const bool any = (any_mask >> (i & 63)) & 1u;                    // the same for the whole wave
-    if constexpr (kCols == 32) {
-      // lane group lg of k-step ks holds columns 32 ks + 16 lg .. + 16 of the slab
+  // "slab holds a critical column", this wave's slabs
+  const uint64_t any_mask = __builtin_amdgcn_ballot_w64(lane < mine && s_any[min(wave + WAVES * lane, n_slabs - 1)] != 0);
+  int tile = 0, i_slab = 0;
+  // C layout of the 16x16 MFMA: lane = column (lane % 16), register e = row 4 (lane / 16) + e
+  auto leave_sums = [&](int t) __attribute__((always_inline)) {
+    int32_t* d = s_sum + t * tile_words + wave * M * 16 + lr;
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        v4i xa = *reinterpret_cast<const v4i*>(my_code + slab * kSlabBytes + ks * 32);
-        if (!row_live) xa = v4i{0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(xa, w.w[ks], acc, 0, 0, 0);
-      }
-      if (any) {
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const v4u wu = __builtin_bit_cast(v4u, w.w[ks]) ^ 0x80808080u;
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            v4u xr = *reinterpret_cast<const v4u*>(my_xf + slab * kSlabBytes + ks * 32 + t * 8);
-            if (!row_live) xr = v4u{0, 0, 0, 0};
-            accf = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, xr), codes_to_half8(wu, t), accf, 0, 0, 0);
-          }
-        }
-      }
-    } else {
-      // lane group lg (0..3) holds columns 16 lg .. + 16 of the slab; the two fp16 instructions take the two
-      // halves of every lane group's piece (any split of the 64 columns does, as long as both operands agree)
-      v4i xa = *reinterpret_cast<const v4i*>(my_code + slab * kSlabBytes);
-      if (!row_live) xa = v4i{0, 0, 0, 0};
-      acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, w.w[0], acc, 0, 0, 0);
-      if (any) {
-        const v4u wu = __builtin_bit_cast(v4u, w.w[0]) ^ 0x80808080u;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          v4u xr = *reinterpret_cast<const v4u*>(my_xf + slab * kSlabBytes + t * 8);
-          if (!row_live) xr = v4u{0, 0, 0, 0};
-          accf = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, xr), codes_to_half8(wu, t), accf, 0, 0, 0);
-        }
+    for (int e = 0; e < 4; ++e) {
+      const int m = 4 * lg + e;
+      if (m < M) {
+        const float sum16 = accf[e];                                  // (a bit cast of a vector's element reads element 0)
+        d[m * 16] = acc[e];
+        d[(WAVES * M + m) * 16] = __builtin_bit_cast(int32_t, sum16);
       }
     }
-    fetch_w(i + kAhead, f[u]);
+    acc = v4i{0, 0, 0, 0};
+    accf = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  };
+  auto step = [&](v4i& w) __attribute__((always_inline)) {
+    const int slab = wave + WAVES * i_slab;
+    // lane group lg (0..3) holds columns 16 lg .. + 16 of the slab; the two fp16 instructions take the two
+    // halves of every lane group's piece (any split of the 64 columns does, as long as both operands agree)
+    v4i xa = *reinterpret_cast<const v4i*>(my_code + slab * kSlabBytes);
+    if (!row_live) xa = v4i{0, 0, 0, 0};
+    acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, w, acc, 0, 0, 0);
+    if ((any_mask >> i_slab) & 1u) {                                  // the same for the whole wave
+      const v4u wu = __builtin_bit_cast(v4u, w) ^ 0x80808080u;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        v4u xr = *reinterpret_cast<const v4u*>(my_xf + slab * kSlabBytes + t * 8);
+        if (!row_live) xr = v4u{0, 0, 0, 0};
+        accf = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, xr), codes_to_half8(wu, t), accf, 0, 0, 0);
+      }
+    }
+    fetch_w(w);
+    if (++i_slab == mine) {                                           // the tile is done
+      leave_sums(tile++);
+      i_slab = 0;
+    }
   };
   // Whole groups of kAhead slabs run without a way out in between (with an exit after every slab the compiler
-  // waited for every request in flight at the end of each group, emptying the queue of weights four slabs deep).
-  static_assert(64 % kAhead == 0, "a window of slab flags starts at the head of a group");
-  auto group = [&]<int... kU>(int i0, std::integer_sequence<int, kU...>) __attribute__((always_inline)) {
-    (step(i0 + kU, std::integral_constant<int, kU>{}), ...);
-  };
-  auto tail = [&]<int... kU>(int i0, std::integer_sequence<int, kU...>) __attribute__((always_inline)) {
-    (void)((i0 + kU < mine ? (step(i0 + kU, std::integral_constant<int, kU>{}), true) : false) && ...);
-  };
+  // waited for every request in flight at the end of each group, emptying the queue of weights).
+  const int total = tiles * mine;
   int i0 = 0;
-  for (; i0 + kAhead <= mine; i0 += kAhead) group(i0, std::make_integer_sequence<int, kAhead>{});
-  tail(i0, std::make_integer_sequence<int, kAhead - 1>{});
-
-  // ---- the eight partial results.  C layout of both MFMA shapes: lane = column (lane % kCols); row m < 4 is
-  // register m of the first kCols lanes
-  if (lg == 0) {
+  for (; i0 + kAhead <= total; i0 += kAhead) {
 #pragma unroll
-    for (int m = 0; m < kRowsMaxM; ++m) {
-      s_acc[wave][m][lr] = acc[m];
-      s_accf[wave][m][lr] = accf[m];
-    }
+    for (int u = 0; u < kAhead; ++u) step(f[u]);
   }
+#pragma unroll
+  for (int u = 0; u < kAhead - 1; ++u)
+    if (i0 + u < total) step(f[u]);
+  if (mine == 0)
+    for (int t = 0; t < tiles; ++t) leave_sums(t);                    // (fewer slabs than waves: zeros)
   __syncthreads();
-  if ((int)threadIdx.x < kCols * a.M) {
-    const int m = threadIdx.x / kCols, col = threadIdx.x % kCols, nn = n0 + col;
-    if (nn < a.N) {
-      int32_t sum = 0;
-      float sumf = 0.0f;
+
+  if (has_out) {
+    const int32_t* s = s_sum + out_tile * tile_words + out_m * 16 + lr;
+    int32_t sum = 0;
+    float sumf = 0.0f;
 #pragma unroll
-      for (int w = 0; w < WAVES; ++w) sum += s_acc[w][m][col], sumf += s_accf[w][m][col];
-      const float cn = a.c[nn];
-      float y = (float)sum * (s_r[m] * (cn / 16129.0f)) + sumf * (cn / 127.0f);
-      if (a.bias) y += half_lo_to_float(a.bias[nn]);
-      if (a.lora_r > 0) {                                             // the low-rank term, as k_skinny_finalize adds it
-        float low = 0.0f;
-        for (int j = 0; j < a.lora_r; j += 8) {
-          const v4u t = *reinterpret_cast<const v4u*>(a.lora_T + (size_t)m * a.lora_ldt + j);
-          const v4u b = *reinterpret_cast<const v4u*>(a.lora_B + (size_t)nn * a.lora_r + j);
+    for (int w = 0; w < WAVES; ++w) sum += s[w * M * 16], sumf += __builtin_bit_cast(float, s[(WAVES + w) * M * 16]);
+    float y = (float)sum * (s_r[out_m] * (out_c / 16129.0f)) + sumf * (out_c / 127.0f);
+    if (a.bias) y += half_lo_to_float(out_bias);
+    if (a.lora_r > 0) {                                               // the low-rank term, as k_skinny_finalize adds it
+      float low = 0.0f;
+      for (int j = 0; j < a.lora_r; j += 8) {
+        const v4u t = *reinterpret_cast<const v4u*>(a.lora_T + (size_t)out_m * a.lora_ldt + j);
+        const v4u b = *reinterpret_cast<const v4u*>(a.lora_B + (size_t)out_n * a.lora_r + j);
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            low += half_lo_to_float(t[e]) * half_lo_to_float(b[e]) + half_hi_to_float(t[e]) * half_hi_to_float(b[e]);
-        }
-        y += low;
+        for (int e = 0; e < 4; ++e)
+          low += half_lo_to_float(t[e]) * half_lo_to_float(b[e]) + half_hi_to_float(t[e]) * half_hi_to_float(b[e]);
       }
-      uint32_t h = float_to_half_bits(y);
-      if (a.gelu) h = gelu_to_half_bits(half_lo_to_float(h));
-      if (a.residual) h = float_to_half_bits(half_lo_to_float(h) + half_lo_to_float(a.residual[(size_t)m * a.ldr + nn]));
-      a.Y[(size_t)m * a.ldy + nn] = (uint16_t)h;
-      if constexpr (kTap) a.tap_acc[(size_t)m * a.N + nn] = sum;
+      y += low;
     }
+    uint32_t h = float_to_half_bits(y);
+    if (a.gelu) h = gelu_to_half_bits(half_lo_to_float(h));
+    if (a.residual) h = float_to_half_bits(half_lo_to_float(h) + half_lo_to_float(out_res));
+    a.Y[(size_t)out_m * a.ldy + out_n] = (uint16_t)h;
+    if (a.tap_acc) a.tap_acc[(size_t)out_m * a.N + out_n] = sum;
   }
 }
 
+constexpr int kRowsMaxChunks = 6;   // of the largest instantiation
+
+// dynamic LDS of a call whose workgroups have `tiles` tiles each
+static size_t rows_lds_bytes(int M, int Kpad, int tiles) {
+  return (size_t)3 * M * Kpad + (M > 1 ? round_up(M * Kpad / 8, 16) : 0) + (size_t)tiles * 2 * kRowsWaves * M * 16 * 4;
+}
+// most tiles a workgroup can have: their sums in LDS, an output per thread
+static int rows_tiles_max(int M, int Kpad) {
+  const long room = (long)kRowsMaxLds - (long)rows_lds_bytes(M, Kpad, 0);
+  return room <= 0 ? 0 : (int)min(room / (2 * kRowsWaves * M * 16 * 4), (long)(kRowsWaves * kWave / (16 * M)));
+}
+// Up to four rows wherever they fit in LDS; more where a compute unit can hold the sums of all its tiles, so that it
+// prepares once (six rows of a 7B layer 67 us, 74 with K split between workgroups; eight rows, where 4096 x 22016 prepares
+// twice, 38 us for that linear, 31 split).
+bool rows_kernel_fits(int M, int Kpad, int N) {
+  return M >= 1 && M <= kRowsMaxM && M * Kpad / 8 <= kRowsMaxChunks * kRowsWaves * kWave &&
+         rows_tiles_max(M, Kpad) >= (M <= 4 ? 1 : ceil_div(ceil_div(N, 16), device_cu_count()));
+}
+
 // more than the default 64 KB of LDS: an attribute per kernel and device
+template <int kM, int... kChunks>
+static hipError_t prepare_rows_of() {
+  for (const void* fn : {reinterpret_cast<const void*>(&k_gemm_rows<kM, kChunks>)...})
+    if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kRowsMaxLds); e != hipSuccess) return e;
+  return hipSuccess;
+}
 hipError_t prepare_rows_kernels() {
   static std::atomic<bool> attr_set[64] = {};                      // setting an attribute twice is harmless
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_set[dev]) return hipSuccess;
-  const void* fns[4] = {reinterpret_cast<const void*>(&k_gemm_rows<true, 32>), reinterpret_cast<const void*>(&k_gemm_rows<false, 32>),
-                        reinterpret_cast<const void*>(&k_gemm_rows<true, 16>), reinterpret_cast<const void*>(&k_gemm_rows<false, 16>)};
-  for (const void* fn : fns) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kRowsMaxOperandBytes);
-    if (e != hipSuccess) return e;
-  }
-  attr_set[dev] = true;
-  return hipSuccess;
+  hipError_t e = prepare_rows_of<1, 1, 2, 3, kRowsMaxChunks>();
+  if (e == hipSuccess) e = prepare_rows_of<2, 1, 2, 3, kRowsMaxChunks>();
+  if (e == hipSuccess) e = prepare_rows_of<4, 1, 2, 3, kRowsMaxChunks>();
+  if (e == hipSuccess) e = prepare_rows_of<8, 1, 2, 3, kRowsMaxChunks>();
+  if (e == hipSuccess) attr_set[dev] = true;
+  return e;
+}
+
+template <int kM>
+static hipError_t launch_rows_of(const SkinnyArgs& a, int chunks, int grid, size_t lds, hipStream_t stream) {
+  const dim3 g(grid), b(kRowsWaves * kWave);
+  if (chunks <= 1) hipLaunchKernelGGL((k_gemm_rows<kM, 1>), g, b, lds, stream, a);
+  else if (chunks <= 2) hipLaunchKernelGGL((k_gemm_rows<kM, 2>), g, b, lds, stream, a);
+  else if (chunks <= 3) hipLaunchKernelGGL((k_gemm_rows<kM, 3>), g, b, lds, stream, a);
+  else hipLaunchKernelGGL((k_gemm_rows<kM, kRowsMaxChunks>), g, b, lds, stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm_rows(SkinnyArgs a, hipStream_t stream) {
   a.n_slabs = packed_k(a.K) / kSlabBytes;
   const int Kpad = a.n_slabs * kSlabBytes;
-  if (!a.X || !rows_kernel_fits(a.M, Kpad) || a.codes) return hipErrorInvalidValue;
-  // 16 columns per workgroup when 32 would leave compute units without one
-  const bool narrow = packed_n(a.N) / 32 <= device_cu_count();
-  const unsigned grid = packed_n(a.N) / (narrow ? 16 : 32);
-  const size_t lds = (size_t)3 * a.M * Kpad;
+  if (!a.X || !rows_kernel_fits(a.M, Kpad, a.N) || a.codes) return hipErrorInvalidValue;
   if (hipError_t e = prepare_rows_kernels(); e != hipSuccess) return e;
-  if (narrow) {
-    if (a.tap_acc)
-      hipLaunchKernelGGL((k_gemm_rows<true, 16>), dim3(grid), dim3(512), lds, stream, a);
-    else
-      hipLaunchKernelGGL((k_gemm_rows<false, 16>), dim3(grid), dim3(512), lds, stream, a);
-  } else {
-    if (a.tap_acc)
-      hipLaunchKernelGGL((k_gemm_rows<true, 32>), dim3(grid), dim3(512), lds, stream, a);
-    else
-      hipLaunchKernelGGL((k_gemm_rows<false, 32>), dim3(grid), dim3(512), lds, stream, a);
-  }
-  return hipGetLastError();
+  // a workgroup per compute unit, its tiles one after the other; more workgroups where their sums would not fit in LDS
+  const int n_tiles = ceil_div(a.N, 16), per = min(ceil_div(n_tiles, device_cu_count()), rows_tiles_max(a.M, Kpad));
+  const int grid = per == ceil_div(n_tiles, device_cu_count()) ? min(n_tiles, device_cu_count()) : ceil_div(n_tiles, per);
+  const size_t lds = rows_lds_bytes(a.M, Kpad, ceil_div(n_tiles, grid));
+  const int chunks = ceil_div(a.M * Kpad / 8, kRowsWaves * kWave);
+  if (a.M == 1) return launch_rows_of<1>(a, chunks, grid, lds, stream);
+  if (a.M == 2) return launch_rows_of<2>(a, chunks, grid, lds, stream);
+  if (a.M <= 4) return launch_rows_of<4>(a, chunks, grid, lds, stream);
+  return launch_rows_of<8>(a, chunks, grid, lds, stream);
 }
 
 }  // namespace mmd8
