@@ -316,15 +316,11 @@ __device__ inline void gather_outlier_slab_one(const uint16_t* __restrict__ X, i
   }
 }
 
-// kFine (the decode kernels' operands, at most 64 rows): a wave takes one k-step of a slab and 32 rows, a quarter of
-// what it takes otherwise: the whole tensor is a few hundred KB and the kernel a chain of latencies, so what counts
-// is how little each wave has to do (64 x 4096: 5.4 us with the whole slab and 64 rows, 3.5 now).
-template <bool kFine>
 __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ X, int M, int K, int ldx,
                                                    const uint8_t* __restrict__ flag,
                                                    const float* __restrict__ r, int8_t* __restrict__ Xq,
                                                    int n_slabs, int8_t* __restrict__ tap_xq, int pack_blocks_y,
-                                                   uint16_t* __restrict__ Xf, const PackOutliers o) {
+                                                   const PackOutliers o) {
   if ((int)blockIdx.y >= pack_blocks_y) {
     // the extra blocks list the critical columns and prepare their slab; the first one publishes
     __shared__ int s_idx[kListedColumns];
@@ -332,7 +328,7 @@ __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ 
     __shared__ int s_wave_total[kThreads / kWave];
     const int b = ((int)blockIdx.y - pack_blocks_y) * gridDim.x + blockIdx.x;
     compact_critical_columns(flag, K, n_slabs * kSlabBytes, o, b == 0, s_idx, &s_n_out, s_wave_total);
-    if (!Xf) {
+    if (o.Xo) {
       gather_outlier_slab(X, M, ldx, n_slabs, o, b * kThreads + threadIdx.x, s_idx, s_n_out);
       gather_further_slabs(X, M, ldx, n_slabs, o, b * kThreads + threadIdx.x,
                              ((int)gridDim.y - pack_blocks_y) * (int)gridDim.x * kThreads, s_idx, s_n_out);
@@ -340,13 +336,12 @@ __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ 
     return;
   }
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int slab = kFine ? blockIdx.x * (kPackSlabs / 2) + (wave >> 1) : blockIdx.x * kPackSlabs + wave;
+  const int slab = blockIdx.x * kPackSlabs + wave;
   if (slab >= n_slabs) return;
   const int rl = lane & 31, g = lane >> 5;
-  constexpr int kRowSteps = kFine ? 1 : kPackRowSteps;
+  constexpr int kRowSteps = kPackRowSteps;
 #pragma unroll
-  for (int step = 0; step < (kFine ? 1 : 2); ++step) {
-    const int ks = kFine ? (wave & 1) : step;
+  for (int ks = 0; ks < 2; ++ks) {
     const int ch = 2 * ks + g;
     const int k0 = slab * kSlabBytes + ch * 16;
     const bool in_k = k0 < K;                         // K % 16 == 0: a piece is all inside or all padding
@@ -392,22 +387,6 @@ __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ 
       const v4u v = v4u{out[0], out[1], out[2], out[3]};
       *reinterpret_cast<v4u*>(Xq + packed_chunk_offset(m, slab, ch, n_slabs)) = v;
       if (tap_xq && in_k) *reinterpret_cast<v4u*>(tap_xq + (size_t)m * K + k0) = v;
-      if (Xf) {
-        // decode path: the critical columns of X as fp16, everything else (K padding included) zero
-        uint32_t fa[4], fb[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          // ~keep[] has 0xff per critical column byte; the fp16 pair w of a[] covers columns 2w, 2w+1
-          const uint32_t ca = (~keep[w >> 1]) >> (16 * (w & 1)), cb = (~keep[2 + (w >> 1)]) >> (16 * (w & 1));
-          const uint32_t ma = ((ca & 0xffu) * 0x0101u) | (((ca >> 8) & 0xffu) * 0x01010000u);
-          const uint32_t mb = ((cb & 0xffu) * 0x0101u) | (((cb >> 8) & 0xffu) * 0x01010000u);
-          fa[w] = in_k ? (a[i][w] & ma) : 0u;
-          fb[w] = in_k ? (b[i][w] & mb) : 0u;
-        }
-        int8_t* xf_bytes = reinterpret_cast<int8_t*>(Xf);
-        *reinterpret_cast<v4u*>(xf_bytes + xf_group_offset(m, k0)) = v4u{fa[0], fa[1], fa[2], fa[3]};
-        *reinterpret_cast<v4u*>(xf_bytes + xf_group_offset(m, k0 + 8)) = v4u{fb[0], fb[1], fb[2], fb[3]};
-      }
     }
   }
 }
@@ -585,6 +564,66 @@ __global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ 
   }
 }
 
+// The same for the decode kernels (at most 128 rows), which decide on the weight side which columns are critical: the
+// codes of every column stay as they are, and nothing follows.  A workgroup per row: these inputs are a few hundred KB, the
+// kernel is one latency for the row, one for its maximum and the launch (2.9 us at 64 x 4096, where scan and pack kernels
+// took 3.0 + 3.4).
+template <int kT, int kPasses>
+__global__ __launch_bounds__(kT) void k_prep_rows(const uint16_t* __restrict__ X, int K, int ldx, uint32_t th, int n_slabs,
+                                                  uint8_t* __restrict__ flag, float* __restrict__ r_out, int8_t* __restrict__ Xq) {
+  __shared__ uint32_t s_part[kT / kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int m = blockIdx.x, k_pieces = K / 16;                      // (the K padding keeps what it holds: its weights are zero)
+  const us2 th2 = as_us2(th | (th << 16));
+  v4u a[kPasses], b[kPasses];
+#pragma unroll
+  for (int q = 0; q < kPasses; ++q) {
+    const int piece = min(q * kT + (int)threadIdx.x, k_pieces - 1);  // (past the end the last one again: same maximum, same flags)
+    const uint16_t* src = X + (size_t)m * ldx + piece * 16;
+    a[q] = *reinterpret_cast<const v4u*>(src);
+    b[q] = *reinterpret_cast<const v4u*>(src + 8);
+  }
+  us2 rowt = as_us2(0u);
+#pragma unroll
+  for (int q = 0; q < kPasses; ++q) {
+    uint32_t t_and = 0xffffffffu;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const us2 t0 = as_us2(a[q][w] & 0x7fff7fffu) - th2, t1 = as_us2(b[q][w] & 0x7fff7fffu) - th2;
+      rowt = __builtin_elementwise_max(rowt, __builtin_elementwise_max(t0, t1));
+      t_and &= as_u32(t0) & as_u32(t1);
+    }
+    if ((~t_and) & 0x80008000u) {                                    // some entry of the piece reaches the threshold
+      uint8_t* fb = flag + min(q * kT + (int)threadIdx.x, k_pieces - 1) * 16;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if ((a[q][w] & 0x7fffu) >= th) fb[2 * w] = 1;
+        if (((a[q][w] >> 16) & 0x7fffu) >= th) fb[2 * w + 1] = 1;
+        if ((b[q][w] & 0x7fffu) >= th) fb[8 + 2 * w] = 1;
+        if (((b[q][w] >> 16) & 0x7fffu) >= th) fb[9 + 2 * w] = 1;
+      }
+    }
+  }
+  uint32_t mx = wave_max_u32(max(as_u32(rowt) & 0xffffu, as_u32(rowt) >> 16));
+  if (lane == 0) s_part[wave] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kT / kWave; ++w) mx = max(mx, s_part[w]);
+  // top bit set: a sub-threshold entry exists and its pattern is mx + th (mod 2^16)
+  const float r = (mx & 0x8000u) ? half_lo_to_float((mx + th) & 0xffffu) : 0.0f;
+  if (threadIdx.x == 0) r_out[m] = r;
+  const float scale = (r == 0.0f) ? 0.0f : 127.0f / r;              // IEEE division
+#pragma unroll
+  for (int q = 0; q < kPasses; ++q) {
+    const int piece = q * kT + threadIdx.x;
+    if (piece >= k_pieces) break;
+    uint32_t out[4];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) out[w] = to_code_word(a[q][2 * w], a[q][2 * w + 1], scale), out[2 + w] = to_code_word(b[q][2 * w], b[q][2 * w + 1], scale);
+    *reinterpret_cast<v4u*>(Xq + packed_chunk_offset(m, piece >> 2, piece & 3, n_slabs)) = v4u{out[0], out[1], out[2], out[3]};
+  }
+}
+
 // After k_prep: the first `slab_blocks` workgroups list the critical columns (the first one
 // publishes the list, the count and the byte mask) and build the fp16 slab of the first
 // kOutlierSlab of them; each of the remaining workgroups owns 64 rows (lane = row) and a share of the columns
@@ -680,22 +719,27 @@ hipError_t launch_row_absmax_noncritical(const uint16_t* X, int M, int K, int ld
 }
 
 hipError_t launch_pack(const uint16_t* X, int M, int K, int ldx, const uint8_t* flag, const float* r, int8_t* Xq,
-                       int Kpad, int8_t* tap_xq, uint16_t* Xf, const PackOutliers& o, hipStream_t stream, bool list_columns) {
+                       int Kpad, int8_t* tap_xq, const PackOutliers& o, hipStream_t stream) {
   const int n_slabs = Kpad / kSlabBytes;
-  const bool fine = Xf != nullptr;
-  const int gx = ceil_div(n_slabs, fine ? kPackSlabs / 2 : kPackSlabs), pack_y = ceil_div(M, fine ? 32 : kPackRows);
-  // the slabs of critical columns are for the tiled GEMM kernels; the decode kernel reads Xf instead
-  // (one extra block still lists the critical columns)
-  const int slab_items = Xf ? 0 : (M + o.N) * (kOutlierSlab / 8);
-  // (the list is a chain of dependent steps over all of K in one workgroup: the longest part of this kernel at
-  // decode sizes; the decode kernels can read the flags themselves)
-  if (!list_columns && !Xf) return hipErrorInvalidValue;
-  const int slab_y = list_columns ? max(1, ceil_div(ceil_div(slab_items, kThreads), gx)) : 0;
-  const dim3 grid(gx, pack_y + slab_y);
-  if (fine)
-    hipLaunchKernelGGL(k_pack<true>, grid, dim3(kThreads), 0, stream, X, M, K, ldx, flag, r, Xq, n_slabs, tap_xq, pack_y, Xf, o);
-  else
-    hipLaunchKernelGGL(k_pack<false>, grid, dim3(kThreads), 0, stream, X, M, K, ldx, flag, r, Xq, n_slabs, tap_xq, pack_y, Xf, o);
+  const int gx = ceil_div(n_slabs, kPackSlabs), pack_y = ceil_div(M, kPackRows);
+  // the slabs of critical columns are for the tiled GEMM kernels (null: one extra block still lists the critical columns)
+  const int slab_items = o.Xo ? (M + o.N) * (kOutlierSlab / 8) : 0;
+  const int slab_y = max(1, ceil_div(ceil_div(slab_items, kThreads), gx));
+  hipLaunchKernelGGL(k_pack, dim3(gx, pack_y + slab_y), dim3(kThreads), 0, stream, X, M, K, ldx, flag, r, Xq, n_slabs, tap_xq, pack_y, o);
+  return hipGetLastError();
+}
+
+hipError_t launch_prep_rows(const uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad, uint8_t* flag, float* r, int8_t* Xq, hipStream_t stream) {
+  static_assert(MMD8_MAX_K / 16 <= 4 * 1024, "pieces of the longest row");
+  const int n_slabs = Kpad / kSlabBytes, pieces = K / 16;
+#define MMD8_PREP_ROWS(T_, P_) \
+  hipLaunchKernelGGL((k_prep_rows<T_, P_>), dim3(M), dim3(T_), 0, stream, X, K, ldx, th, n_slabs, flag, r, Xq)
+  if (pieces <= 256) MMD8_PREP_ROWS(256, 1);
+  else if (pieces <= 512) MMD8_PREP_ROWS(512, 1);
+  else if (pieces <= 1024) MMD8_PREP_ROWS(1024, 1);
+  else if (pieces <= 2048) MMD8_PREP_ROWS(1024, 2);
+  else MMD8_PREP_ROWS(1024, 4);
+#undef MMD8_PREP_ROWS
   return hipGetLastError();
 }
 

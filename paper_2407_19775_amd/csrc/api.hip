@@ -59,7 +59,6 @@ static int check_linear_shape(int K, int N) {
 
 // Workspace layout.  The head (counters and the column flags, sized for the largest K so that
 // its place does not depend on the shape) is standing state: zero between calls.
-constexpr int kSkinnyChunkedMaxM = 2 * kSkinnyMaxM;   // most rows the decode kernels are used for (in passes of kSkinnyMaxM)
 constexpr size_t kHeadCounters = 256;
 constexpr size_t kHeadBytes = kHeadCounters + MMD8_MAX_K;
 struct Workspace {
@@ -79,9 +78,9 @@ struct Workspace {
   uint16_t* lora_t;    // adapter only: [M][kLoraMaxRank] fp16
   float* lora_part;    // adapter only: partial sums of the down-projection when K is split between workgroups
   int8_t* xq;          // Mpad x Kpad codes, blocked layout
-  uint16_t* xf;        // decode path only: [64][Kpad] fp16
   float* partial;      // split-K partial outputs, or null
   int gemm_splits;     // ranges of K of the tiled GEMM, 1: not split
+  SkinnyPlan decode_plan;   // ranges of K of the decode kernels (at most 128 rows)
   uint16_t* h;         // coded output only, where the encoder runs as a kernel of its own: [M][N] fp16
   size_t bytes;
 };
@@ -107,13 +106,13 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   w.r = reinterpret_cast<float*>(take((Mpad + 256) * 4));
   // (up to 128 rows the decode kernels do the work and these slabs are not used, except by calls that force the
   // tiled GEMM: one slab, further critical columns through its gather loop)
-  w.crit_slabs = M > kSkinnyChunkedMaxM ? kCriticalSlabs : 1;
+  w.crit_slabs = M > kSkinnyMaxM ? kCriticalSlabs : 1;
   w.f_slabs = w.crit_slabs + lora_slabs(r);
   w.xo = reinterpret_cast<uint16_t*>(take(Mpad * kOutlierSlab * 2 * w.f_slabs));
   w.wo = reinterpret_cast<uint16_t*>(take(Npad * kOutlierSlab * 2 * w.f_slabs));
   // (the same count decides for the dense pass with and without the further slabs: a workspace without them gathers
   // tile by tile up to that count)
-  w.gemm_splits = split_k && M > kSkinnyChunkedMaxM ? plan_gemm_splits(M, K, N) : 1;
+  w.gemm_splits = split_k && M > kSkinnyMaxM ? plan_gemm_splits(M, K, N) : 1;
   const CriticalPlan cp = plan_critical_columns(M, (int)(Kpad / kSlabBytes), Npad, w.crit_slabs == kCriticalSlabs, w.gemm_splits);
   w.g_slabs = gathered_rows ? cp.g_slabs : 0;
   w.dense_from = cp.dense_from;
@@ -121,16 +120,13 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   w.wg = w.g_slabs > 0 ? reinterpret_cast<uint16_t*>(take(Npad * kOutlierSlab * 2 * w.g_slabs)) : nullptr;
   if (!base) w.xg = w.wg = nullptr;
   w.xq = reinterpret_cast<int8_t*>(take(Mpad * Kpad));
-  w.xf = nullptr;
   w.partial = nullptr;
-  if (M > 0 && M <= kSkinnyChunkedMaxM) {
-    const int Mc = M < kSkinnyMaxM ? M : kSkinnyMaxM;              // rows per pass of the decode kernels
-    w.xf = reinterpret_cast<uint16_t*>(take((size_t)kSkinnyMaxM * Kpad * 2));
-    size_t pb = plan_skinny(Mc, K, N).partial_bytes;
-    // a low-rank term is added, an activation applied and a coded output encoded where the partial outputs are
-    // summed: room for one partial output even when K is not split
-    if (pb == 0) pb = (size_t)Mc * N * sizeof(float);
-    if (pb) w.partial = reinterpret_cast<float*>(take(pb));
+  w.decode_plan = {};
+  if (M > 0 && M <= kSkinnyMaxM) {
+    w.decode_plan = plan_skinny(K, N);
+    if (!split_k) w.decode_plan.splits = 1, w.decode_plan.slabs_per_split = w.decode_plan.n_slabs;
+    // (the sums go through memory even when K is not split: what follows them is the work of the kernel that adds them)
+    w.partial = reinterpret_cast<float*>(take((size_t)w.decode_plan.splits * M * N * sizeof(float)));
   }
   if (w.gemm_splits > 1) w.partial = reinterpret_cast<float*>(take((size_t)w.gemm_splits * M * N * sizeof(float)));
   w.lora_t = r > 0 ? reinterpret_cast<uint16_t*>(take((size_t)M * kLoraMaxRank * 2)) : nullptr;
@@ -163,11 +159,14 @@ static Workspace fit(void* base, size_t have, int M, int K, int N, int r, int ex
 static size_t workspace_bytes_for(int M, int K, int N, int r = 0, int exit_block = 0) {
   size_t sums = 0;
   const int last = device_cu_count() / 2 / (packed_n(N) / 256) * 128;   // (tiles on more than half of the compute units: no split)
-  for (int m = kSkinnyChunkedMaxM + 1; m <= M && m <= last; m += 128) {
+  for (int m = kSkinnyMaxM + 1; m <= M && m <= last; m += 128) {
     const size_t splits = plan_gemm_splits(m, K, N), rows = m + 127 < M ? m + 127 : M;
     if (splits > 1) sums = sums > splits * rows * N ? sums : splits * rows * N;
   }
-  return carve(nullptr, M, K, N, r, exit_block, true, false).bytes + round_up_sz(sums * sizeof(float), 256);
+  if (M <= kSkinnyMaxM) return carve(nullptr, M, K, N, r, exit_block).bytes;
+  const size_t tiled = carve(nullptr, M, K, N, r, exit_block, true, false).bytes + round_up_sz(sums * sizeof(float), 256);
+  const size_t decode = carve(nullptr, kSkinnyMaxM, K, N, r, exit_block).bytes;
+  return tiled > decode ? tiled : decode;
 }
 // A coded output is produced by the kernel that ends the layer when no block of it is shared between
 // workgroups: the tiled GEMM needs blocks inside its 256-column tiles; the decode path encodes where it sums
@@ -175,7 +174,7 @@ static size_t workspace_bytes_for(int M, int K, int N, int r = 0, int exit_block
 // first few rows are a single kernel with nothing to sum afterwards: the encoder follows it.
 static bool exit_fuses(int M, int K, int N, int block) {
   if (rows_kernel_fits(M, packed_k(K), N)) return false;
-  if (M <= kSkinnyChunkedMaxM) return M <= kSkinnyMaxM || ((size_t)kSkinnyMaxM * N) % block == 0;
+  if (M <= kSkinnyMaxM) return M <= 64 || ((size_t)64 * N) % block == 0;
   return (block == 64 || block == 128 || block == 256) && N % block == 0;
 }
 
@@ -290,7 +289,7 @@ int mmd8_linear_workspace_init(void* workspace, size_t workspace_bytes, void* st
   if (!workspace || !aligned(workspace, 256)) return MMD8_E_ARG;
   if (workspace_bytes < kHeadBytes) return MMD8_E_WORKSPACE;
   // kernel attributes of this device, so that no later call has to set one (a call may be under stream capture)
-  if (prepare_gemm_kernels() != hipSuccess || prepare_rows_kernels() != hipSuccess) return MMD8_E_HIP;
+  if (prepare_gemm_kernels() != hipSuccess || prepare_skinny_kernels() != hipSuccess) return MMD8_E_HIP;
   return launch_fill_u32(static_cast<uint32_t*>(workspace), 0u, (int)(kHeadBytes / 4),
                          static_cast<hipStream_t>(stream)) == hipSuccess
              ? MMD8_OK
@@ -366,36 +365,23 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   const PackOutliers po = {ws.idx, ws.n_out, ws.mask, t.outlier_mask, t.outlier_idx, t.n_outliers,
                            Wq_packed, col_absmax, N, ws.xo, ws.wo, ws.f_slabs, ws.crit_slabs,
                            readings ? readings->W_master : nullptr, readings ? readings->ldw : 0, ws.xg, ws.wg, ws.g_slabs, ws.dense_from};
-  // Up to 128 rows go through the decode kernels, 64 rows at a time (the weights are streamed twice for more than 64).
-  // The tiled GEMM takes over at 129.  The two routes at the border, us per call at 128 / 129 rows, weights from memory:
-  // 4096 -> 12288 59 / 41 with few critical columns, 64 / 69 with 90 % of them critical; 4096 -> 22016 88 / 49 and 92 / 91;
-  // 11008 -> 4096 61 / 44 and 66 / 74; 8192 -> 57344 205 / 139 and 248 / 355; 28672 -> 8192 146 / 108 and 150 / 227.  So the
-  // two passes lose on the usual input and win on the heavy-tailed input that decoding meets, and which of them a call
-  // brings is known only on the device.
+  // Up to 128 rows go through the decode kernels; the tiled GEMM takes over at 129.  The two routes at the border, us per
+  // layer at 128 / 129 rows, weights from memory: 7B shape 156 / 284 with heavy-tailed rows (nearly every column critical),
+  // 152 / 161 with few critical columns; 70B shape 392 / 736 and 366 / 332.
   // (the decode kernels multiply the critical columns with the weight codes themselves: original 16-bit rows go
   // through the tiled GEMM whatever the number of rows)
-  const bool skinny = M <= kSkinnyChunkedMaxM && !(readings && readings->W_master);
-  // A few rows (at most kPanelPrepMaxM): the decode GEMM kernel prepares its own operands (scales, codes, critical
-  // columns) from X, and the scan and pack kernels are left out.  Not when their outputs are asked for through the taps.
+  const bool skinny = M <= kSkinnyMaxM && !(readings && readings->W_master);
+  // The scan and pack kernels run when their outputs are asked for.
   const bool wants_prep_taps = t.outlier_mask || t.row_absmax || t.xq || t.n_outliers || t.outlier_idx;
   // A few rows (while their operands fit in LDS): the whole layer is one kernel (k_gemm_rows).  When the taps of the
   // preparation are asked for, the scan and pack kernels run ahead of it for their sake only.
   // (alternative readings: always the separate scan and pack kernels, which is where they differ)
-  const bool may_own_prep = !(t.tuning & MMD8_TUNE_SEPARATE_PREP) && !readings;
   const bool rows_path = !readings && !(t.tuning & MMD8_TUNE_NO_ROWS_KERNEL) && rows_kernel_fits(M, Kpad, N);
-  const bool own_prep = skinny && !rows_path && !wants_prep_taps && may_own_prep && panel_prep_fits(M, plan_skinny(M, K, N));
+  // The decode kernels' preparation in one kernel (the separate ones leave codes that serve as well).
+  const bool decode_prep = skinny && !rows_path && !wants_prep_taps && !(t.tuning & MMD8_TUNE_SEPARATE_PREP) && !readings;
   // coded activations are decoded by the one-pass preparation kernel itself where that kernel runs
   // (element offsets are held in 32 bits there); otherwise by the decoder, ahead of the usual kernels
   const bool one_pass = !skinny && prep_fits(K) && !readings;
-  // Decode kernels after the scan and pack kernels, nobody asking for the list of critical columns: the pack kernel
-  // leaves the list out (its longest part at these sizes) and the decode kernel reads the column flags themselves as
-  // its mask.  Every workgroup reads them, so they are put back to zero by the kernel after it, the one that sums
-  // the splits: only calls that have one.
-  bool lean_pack = false;
-  if (skinny && !rows_path && !own_prep && !wants_prep_taps) {
-    const SkinnyPlan plan = plan_skinny(M < kSkinnyMaxM ? M : kSkinnyMaxM, K, N);
-    lean_pack = plan.splits > 1 || lora || gelu || (exit && (exit->residual || exit_fused));
-  }
   const bool fused_decode = coded && one_pass && prep_from_codes_fits(K) && (size_t)M * K < ((size_t)1 << 31);
   if (coded && !fused_decode &&
       launch_dequantize_blockwise(coded->codes, coded->absmax, (size_t)M * K, coded->block, X, st) != hipSuccess)
@@ -405,16 +391,19 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     if (launch_prep(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, ws.xq, t.xq, po, fused_decode ? coded : nullptr,
                     t.event_prep_mid, st) != hipSuccess)
       return MMD8_E_HIP;
-  } else if (!own_prep && (!rows_path || wants_prep_taps)) {
+  } else if (decode_prep) {
+    if (launch_prep_rows(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, ws.xq, st) != hipSuccess) return MMD8_E_HIP;
+    if (!record(t.event_prep_mid)) return MMD8_E_HIP;
+  } else if (!rows_path || wants_prep_taps) {
     if (launch_scan(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, st) != hipSuccess) return MMD8_E_HIP;
     if (!record(t.event_prep_mid)) return MMD8_E_HIP;
     // the row scale over the non-critical columns only: needs the flags of every row, hence a pass of its own
     if (readings && readings->non_critical_scale &&
         launch_row_absmax_noncritical(X, M, K, ldx, ws.flag, ws.r, st) != hipSuccess)
       return MMD8_E_HIP;
-    // (the decode kernels' operands are packed 64 rows at a time, below)
-    if (!skinny && launch_pack(X, M, K, ldx, ws.flag, ws.r, ws.xq, Kpad, t.xq, nullptr, po, st) != hipSuccess)
-      return MMD8_E_HIP;
+    PackOutliers list = po;
+    if (skinny) list.Xo = nullptr;                                    // no slabs of critical columns
+    if (launch_pack(X, M, K, ldx, ws.flag, ws.r, ws.xq, Kpad, t.xq, list, st) != hipSuccess) return MMD8_E_HIP;
   }
   if (t.row_absmax &&
       hipMemcpyAsync(t.row_absmax, ws.r, (size_t)M * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
@@ -441,9 +430,6 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   }
 
   if (rows_path) {   // (a coded output: the encoder follows)
-    if (wants_prep_taps &&
-        launch_pack(X, M, K, ldx, ws.flag, ws.r, ws.xq, Kpad, t.xq, ws.xf, po, st) != hipSuccess)
-      return MMD8_E_HIP;
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
     SkinnyArgs g = {};
     g.flag_reset = wants_prep_taps ? ws.flag : nullptr;               // the scan set them
@@ -473,60 +459,42 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     g.th = threshold_pattern(tau);
     if (launch_gemm_rows(g, st) != hipSuccess) return MMD8_E_HIP;
   } else if (skinny) {
-    const SkinnyPlan plan = plan_skinny(M < kSkinnyMaxM ? M : kSkinnyMaxM, K, N);
-    for (int row0 = 0; row0 < M; row0 += kSkinnyMaxM) {
-      const int Mc = M - row0 < kSkinnyMaxM ? M - row0 : kSkinnyMaxM;
-      // codes and the fp16 copy of these rows, masked with the flags of all M rows; the list of critical columns is
-      // published again with every pass (the same list)
-      if (!own_prep && launch_pack(X + (size_t)row0 * ldx, Mc, K, ldx, ws.flag, ws.r + row0, ws.xq, Kpad,
-                                   t.xq ? t.xq + (size_t)row0 * K : nullptr, ws.xf, po, st, !lean_pack) != hipSuccess)
-        return MMD8_E_HIP;
-      if (row0 == 0 && !record(t.event_gemm_begin)) return MMD8_E_HIP;
-      SkinnyArgs g = {};
-      g.Xq = ws.xq;
-      g.Wt = Wq_packed;
-      g.Xf = ws.xf;
-      g.mask = ws.mask;
-      g.M = Mc;
-      g.N = N;
-      g.Kpad = Kpad;
-      g.r = ws.r + row0;
-      g.c = col_absmax;
-      g.bias = bias;
-      g.Y = Y ? Y + (size_t)row0 * ldy : nullptr;
-      g.ldy = ldy;
-      if (exit) {
-        g.residual = exit->residual ? exit->residual + (size_t)row0 * exit->ldr : nullptr;
-        g.ldr = exit->ldr;
-        if (exit_fused) {
-          g.codes = exit->codes + (size_t)row0 * N;
-          g.code_absmax = exit->absmax + (size_t)row0 * N / exit->block;
-          g.code_block = exit->block;
-        }
+    if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
+    SkinnyArgs g = {};
+    g.Xq = ws.xq;
+    g.Wt = Wq_packed;
+    g.mask = ws.flag;
+    g.M = M;
+    g.N = N;
+    g.Kpad = Kpad;
+    g.r = ws.r;
+    g.c = col_absmax;
+    g.bias = bias;
+    g.Y = Y;
+    g.ldy = ldy;
+    if (exit) {
+      g.residual = exit->residual;
+      g.ldr = exit->ldr;
+      if (exit_fused) {
+        g.codes = exit->codes;
+        g.code_absmax = exit->absmax;
+        g.code_block = exit->block;
       }
-      g.gelu = gelu ? 1 : 0;
-      g.partial = ws.partial;
-      g.tap_acc = t.acc ? t.acc + (size_t)row0 * N : nullptr;
-      g.flag_reset = (!own_prep && row0 + kSkinnyMaxM >= M) ? ws.flag : nullptr;   // the last pass zeroes the column flags again
-      if (lean_pack) {
-        g.mask = ws.flag;
-        g.flag_reset_late = g.flag_reset;
-        g.flag_reset = nullptr;
-      }
-      if (own_prep) {
-        g.X = X;
-        g.ldx = ldx;
-        g.K = K;
-        g.th = threshold_pattern(tau);
-      }
-      if (lora) {
-        g.lora_T = ws.lora_t + (size_t)row0 * kLoraMaxRank;
-        g.lora_ldt = kLoraMaxRank;
-        g.lora_B = lora->B;
-        g.lora_r = lora->r;
-      }
-      if (launch_gemm_skinny(g, plan, st) != hipSuccess) return MMD8_E_HIP;
     }
+    g.gelu = gelu ? 1 : 0;
+    g.partial = ws.partial;
+    g.tap_acc = t.acc;
+    g.flag_reset = ws.flag;
+    g.X = X;
+    g.ldx = ldx;
+    g.K = K;
+    if (lora) {
+      g.lora_T = ws.lora_t;
+      g.lora_ldt = kLoraMaxRank;
+      g.lora_B = lora->B;
+      g.lora_r = lora->r;
+    }
+    if (launch_gemm_skinny(g, ws.decode_plan, st) != hipSuccess) return MMD8_E_HIP;
   } else {
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
     GemmArgs g = {};
@@ -623,7 +591,7 @@ int mmd8_mixed_int8_linear_static(const mmd8_half* X, int M, int K, int ldx, con
     if (!w.ptr) {   // first call on this device: every GPU holds its own copy of the array at its own address
       void* p = nullptr;
       if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return MMD8_E_HIP;
-      if (prepare_gemm_kernels() != hipSuccess || prepare_rows_kernels() != hipSuccess) return MMD8_E_HIP;
+      if (prepare_gemm_kernels() != hipSuccess || prepare_skinny_kernels() != hipSuccess) return MMD8_E_HIP;
       w.ptr = p;
       w.head_zero = false;
     }

@@ -48,6 +48,21 @@ __device__ inline uint32_t to_code_byte(float x, float scale) {
   return (uint32_t)((int)q) & 0xffu;
 }
 
+// Four of them at once, without the clamp: two packed pairs of values -> four code bytes, where every value is at most the
+// row's largest (|x| scale rounds to at most 127); any byte for another value.  rint of the product rounded to fp32, as the
+// low byte of that product plus 1.5 x 2^23.
+__device__ inline uint32_t to_code_word(uint32_t pair0, uint32_t pair1, float scale) {
+  uint32_t b[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t pair = j < 2 ? pair0 : pair1;
+    float p = __builtin_fmaf(j & 1 ? half_hi_to_float(pair) : half_lo_to_float(pair), scale, 0.0f);
+    asm("" : "+v"(p));                                                // rounded here
+    b[j] = __builtin_bit_cast(uint32_t, p + 12582912.0f);
+  }
+  return __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
+}
+
 // Exact GELU, x Phi(x), of an fp16 value given as fp32; fp16 bit pattern of the result.  Branch-free:
 //   Phi(-|x|) = erfc(z) / 2, z = |x| / sqrt 2,   erfc(z) = t exp(-z^2 + g(t)), t = 1 / (1 + z / 2),
 // with g a degree-8 polynomial fitted to ln(exp(z^2) erfc(z) / t) on the t range of |x| <= 13.5 (beyond that the
@@ -97,6 +112,14 @@ __device__ inline uint32_t wave_max_u32(uint32_t v) {
 // behind it: completion is tracked by hand with vmcnt.
 __device__ __forceinline__ void dma16(const void* src, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(src), "s"(lds_addr)
+               : "memory");
+}
+
+// The same for bytes that nothing else will read (streamed past the caches' other contents).
+__device__ __forceinline__ void dma16_once(const void* src, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
                :
                : "v"(src), "s"(lds_addr)
                : "memory");

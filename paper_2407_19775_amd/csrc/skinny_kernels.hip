@@ -1,28 +1,19 @@
-// Decode-shaped (at most 64 tokens) mixed int8 GEMM ("Compression techniques", item 2): bound by
+// Decode-shaped (at most 128 tokens) mixed int8 GEMM ("Compression techniques", item 2): bound by
 // streaming the int8 weights once from HBM, not by the matrix pipes.
 //
-//   acc[m,n] = sum_k Xq[m,k] Wt[n,k]                                   v_mfma_i32_32x32x32_i8
+//   acc[m,n] = sum_k Xq[m,k] Wt[n,k]                                   int8 MFMA, exact
 //   Y[m,n]   = f16( acc r[m] c[n] / 127^2 + sum_{k critical} X[m,k] f16(Wt[n,k] c[n]/127) + bias[n] )
 //
-// No weight byte is used by more than one wave, so the weights go straight from HBM into the
-// registers of the lane that feeds them to the MFMA (no LDS): a wave owns 32 rows of Wt (32 output
-// columns) and reads their 64-byte slabs; the blocked layout is fragment-major, so each of the two
-// loads per slab is 1 KB of consecutive addresses.  The activation side of a slab is shared by the
-// waves of a workgroup through LDS.  When there are too few weight panels to give every CU a
-// workgroup, the K range is split between workgroups, which write fp32 partial outputs that a
-// second small kernel adds in a fixed order (the result does not depend on timing).
-//
 // Heavy-tailed decode activations flag a large share of the feature dimensions, so the 16-bit part
-// is a second product over the same weights rather than a small correction.  For a slab that holds
-// a critical column the lane turns the weight bytes it already has into fp16 and multiplies them
-// with Xf, a copy of X in which the non-critical columns are zero (written by the pack kernel).
-// To keep that conversion off the critical path the fp16 operand is the integer code itself (exact
+// is a second product over the same weights rather than a small correction.
+// To keep the conversion of the weights cheap the fp16 operand is the integer code itself (exact
 // in fp16, one byte permute and one packed fp16 subtraction per two codes) and the column step
 // c[n]/127 is applied in fp32 to the accumulated sum: the sum over the critical columns of
 // X[m,k] q[n,k] c[n]/127 with one rounding at the end, instead of rounding each dequantized weight
 // to fp16 first.  The two differ by at most the fp16 rounding of the weights (2^-11 relative per
-// term), far inside the tolerance of the fp16 output.  A slab without a critical column skips the
-// 16-bit part (the same decision for the whole workgroup).
+// term), far inside the tolerance of the fp16 output.
+#include <math.h>
+
 #include <type_traits>
 #include <utility>
 
@@ -35,306 +26,310 @@
 
 namespace mmd8 {
 
+typedef short ss2 __attribute__((ext_vector_type(2)));
+
 // ------------------------------------------------------------------------------------------------
-// If every wave fetched its own copy of the activation fragments from L2, that would be up to 6
-// times the bytes of the weights it streams (64 rows).  So the kWaves waves of a workgroup own
-// neighbouring 32-column groups of one weight panel and walk the same slabs together: the
-// activation side of a slab (int8 codes and the fp16 critical columns, kMT 32-row groups each) is
-// fetched once per workgroup, parked in LDS (a ring of four buffers) and read from there by every
-// wave; the weights go from HBM straight into the registers of the lane that feeds them to the
-// MFMA, three slabs ahead.  All waits are the compiler's.  Measured per workgroup: about 19 GB/s
-// of weights at 64 rows (the MFMAs and the code-to-fp16 conversions of a slab take about as long
-// as its 16 KB take to arrive), so every CU must have a workgroup.
+// A workgroup of eight waves multiplies up to kBM rows with one 256-column weight panel over a range of K, 64 columns of K
+// (a slab) at a time.  Everything of a slab comes through one ring of LDS buffers by global_load_lds_dwordx4: the
+// activation codes, the rows of X themselves (128 bytes per row, eight rows per request) and the weight codes.  Which
+// columns are critical is decided on the weight side: a weight code goes into the int8 product where its column is not
+// critical and into the fp16 product, as an integer, where it is (masks of 256 slabs at a time in LDS, a byte per column), so
+// the preparation need not know the critical columns when it writes the codes: one pass over X, no fp16 copy.  (Entries of
+// other columns are below the threshold, hence finite: zero times them is zero.)
+// A wave owns 64 columns: of all rows and one of the slab's two k-steps (up to 64 rows; the two halves are added in
+// LDS at the end), or of 64 rows and both k-steps (128 rows).  64 x 64 accumulators per wave keep the LDS reads below what
+// the fills take: with 32 columns per wave a slab's activation side was read twice as often, and 64 rows took 0.8 us per slab.
+// The ranges leave fp32 sums, added in a fixed order by a second kernel (the result does not depend on timing).
+//
+// What bounds it: a compute unit takes in about 57 bytes per ns where part of them comes from memory (its loads come back
+// in order), and a slab is 22 (32 rows), 28 (64) or 40 KB (128) for 16 KB of weights; 16 KB for every compute unit take
+// 0.65 us from HBM.  Measured on 4096 -> 22016 (172 workgroups of 32 slabs): 0.49, 0.65 and 1.1 us per slab, and before the
+// first and after the last of them 3 us (0.7 addresses, 2 first bytes from memory) and 1.6 to 3.5 us (sums to memory).  The
+// weights are requested as bytes that nothing else reads: with the plain request a 7B layer takes 95.8 instead of 87.3 us
+// at 32 rows.  Whole layers of that shape, weights from memory, where scan, pack and a kernel with the weights straight in
+// registers took (two passes of it for more than 64 rows): 16 rows 96 -> 79 us, 32 rows 98 -> 86, 64 rows 132 -> 109, 100
+// rows 246 -> 146, 128 rows 261 -> 156; of 70B shape 32 rows 214 -> 200, 128 rows 491 -> 392.
 // ------------------------------------------------------------------------------------------------
-template <int MT, int WAVES>
-struct PanelCfg {
-  static constexpr int kMT = MT, kWaves = WAVES;
-  static constexpr int kThreads = WAVES * kWave;
-  static constexpr int kCols = WAVES * 32;
-  static constexpr int XQ_BYTES = MT * 2048, XF_BYTES = MT * 4096, STAGE_BYTES = XQ_BYTES + XF_BYTES;
-  static constexpr int kPieces = STAGE_BYTES / 1024;               // 1 KB pieces of a slab's activation side
-  static constexpr int kFetch = (kPieces + WAVES - 1) / WAVES;     // per wave and slab; surplus ones repeat the last
-  static constexpr int kMaxSlabs = MMD8_MAX_K / kSlabBytes;        // flags "slab holds a critical column"
+template <int kBM_>
+struct DecodeCfg {
+  static constexpr int kBM = kBM_, kWaves = 8, kThreads = kWaves * kWave;
+  static constexpr bool kHalves = kBM <= 64;                         // the waves 4..7 take the second k-step of every slab
+  static constexpr int TI = kBM == 32 ? 1 : 2, TJ = 2;               // 32 x 32 tiles of a wave
+  static constexpr int kCodes = kBM * kSlabBytes, kRows = 2 * kCodes, kStage = kCodes + kRows + kBlockBytes;
+  static constexpr int kStages = kBM == 32 ? 5 : kBM == 64 ? 4 : 3;
+  static constexpr int kPieces = kStage / 1024;                      // 1 KB requests per slab
+  static constexpr int kReq = (kPieces + kWaves - 1) / kWaves;       // per wave; the waves from kFullWaves on make one less
+  static constexpr int kFullWaves = kPieces - kWaves * (kReq - 1);
+  static constexpr int kMaskSlabs = 256;
+  static constexpr int kMaskAt = kStages * kStage, kScalesAt = kMaskAt + kMaskSlabs * kSlabBytes;
+  static constexpr int LDS_BYTES = kScalesAt + 4 * kBM;
+  static_assert(LDS_BYTES <= 160 * 1024 && kScalesAt >= (kHalves ? 2 : 1) * kBM * 1024, "LDS, which also takes the sums");
+  static_assert((kStages - 1) * kReq <= 63, "requests in flight fit the wait instruction's count");
 };
 
-// kPrep (at most kPanelPrepMaxM rows): the activation side is not fetched from packed operands but made here.
-// Every workgroup streams the rows of X once for the row scales (the maximum of the magnitudes below the
-// threshold, as the scan kernel finds it), keeps the columns of its own K range in LDS with one "critical" flag
-// per column, and writes the codes and the fp16 critical columns of a slab into the ring two slabs ahead of the
-// MFMAs: wave w owns the 16-column piece w % 4 of the slab, a lane one column of one of four rows.  The
-// arithmetic is the pack kernel's (IEEE 127 / r, rint, clamp; critical columns zero in the codes and kept in the
-// fp16 copy).  Rows of the ring beyond M are zeroed once and never written.
-template <class Cfg, bool kSplit, bool kTap, bool kPrep>
-__global__ __launch_bounds__(Cfg::kThreads, 2) void k_gemm_panel(const SkinnyArgs a) {
-  constexpr int MT = Cfg::kMT, WAVES = Cfg::kWaves;
-  static_assert(!kPrep || MT == 1, "own preparation is for a few rows");
-  __shared__ __attribute__((aligned(16))) int8_t s_x[4][Cfg::STAGE_BYTES];
-  __shared__ uint8_t s_any[Cfg::kMaxSlabs];
-  __shared__ __attribute__((aligned(16))) uint16_t s_row[kPrep ? kPanelPrepMaxRowSlabs * kSlabBytes : 8];   // [M][cnt x 64]
-  __shared__ __attribute__((aligned(16))) uint8_t s_crit[kPrep ? kPanelPrepMaxSlabs * kSlabBytes : 16];                                    // [cnt x 64]
-  __shared__ uint32_t s_part[kPanelPrepMaxM][WAVES];
-  __shared__ float s_r[kPanelPrepMaxM], s_scale[kPanelPrepMaxM];
+// own requests are in but the newest kVm, own LDS reads have returned
+template <int kVm>
+__device__ __forceinline__ void wait_requests() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(kVm) : "memory");
+}
+
+template <int kBM>
+__global__ __launch_bounds__(DecodeCfg<kBM>::kThreads) void k_gemm_decode(const SkinnyArgs a) {
+  using Cfg = DecodeCfg<kBM>;
+  constexpr int TI = Cfg::TI, TJ = Cfg::TJ, kStages = Cfg::kStages, kReq = Cfg::kReq;
+  extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+  int8_t* s_mask = smem + Cfg::kMaskAt;
+  float* s_r = reinterpret_cast<float*>(smem + Cfg::kScalesAt);
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lr = lane & 31, lg = lane >> 5;
-  reset_column_flags(a.flag_reset, a.Kpad);
+  const int half = wave >> 2, wn = wave & 3;                         // half: k-step of the slab, or 64-row half of the tile
   const int tile = blockIdx.x % a.tiles_n, split = blockIdx.x / a.tiles_n;
-  const int n0 = tile * Cfg::kCols + wave * 32;                    // < Npad: the padding rows of Wt are zero
-  const int n = n0 + lr;
-  const int s_begin = split * a.slabs_per_split;
-  const int cnt = min(a.n_slabs, s_begin + a.slabs_per_split) - s_begin;   // >= 1 by construction of the plan
+  const int first = split * a.slabs_per_split, end = min(first + a.slabs_per_split, a.n_slabs), last = end - 1;
+  const int n0 = tile * 256 + wn * 64;
 
-  const int8_t* wgrp = a.Wt + (size_t)(n0 >> 8) * a.n_slabs * kBlockBytes + (size_t)((n0 & 255) >> 5) * 2048 + lane * 16 +
-                       (size_t)s_begin * kBlockBytes;
-  if constexpr (!kPrep) {
-    for (int t = threadIdx.x; t < cnt; t += Cfg::kThreads) {
-      const v4u* mk = reinterpret_cast<const v4u*>(a.mask + (size_t)(s_begin + t) * kSlabBytes);
-      const v4u m = mk[0] | mk[1] | mk[2] | mk[3];
-      s_any[t] = (m[0] | m[1] | m[2] | m[3]) != 0;
-    }
-  }
+  // ---- what is not part of the stream, asked for ahead of it: the terms of this wave's columns and of the rows (for the
+  // end), and the column flags of the range, copied to LDS where they become masks
+  float c[TJ];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) c[j] = a.c[min(n0 + j * 32 + lr, a.N - 1)];
+  const float r0 = a.r[min((int)threadIdx.x, a.M - 1)];
+  auto mask_words = [&](int s0) { return min(Cfg::kMaskSlabs, end - s0) * (kSlabBytes / 4); };
+  auto put_mask = [&](int t, uint32_t flags) {                       // 4 columns
+    flags &= 0x01010101u;
+    reinterpret_cast<uint32_t*>(s_mask)[t] = flags * 0xffu;
+  };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+  __builtin_amdgcn_sched_barrier(0);
+  // (whole KB, up to 15 slabs past the range: still inside the workspace)
+  for (int i = wave; 1024 * i < 4 * mask_words(first); i += Cfg::kWaves)
+    dma16(a.mask + (size_t)first * kSlabBytes + i * 1024 + lane * 16, lds0 + Cfg::kMaskAt + i * 1024);
 
-  // piece i of a slab's activation side: first the int8 codes (MT 32-row groups x 2 k-steps), then
-  // the fp16 pieces (MT groups x 4); the first MT groups of a slab are contiguous in both arrays
-  const int8_t* x_src[Cfg::kFetch];
-  int x_dst[Cfg::kFetch], x_step[Cfg::kFetch];
+  // ---- requests: piece 8 d + wave of a slab's 1 KB pieces, codes first, then rows, then weights
+  const bool full_wave = wave < Cfg::kFullWaves;
+  const int whole_slabs = a.K / kSlabBytes;
+  const int8_t* src[kReq];                                            // of the slab that is requested next
+  int step[kReq];                                                     // bytes from a slab to the next
+  int row_piece[kReq];                                                // first column of this lane's 16 bytes of a row of X
 #pragma unroll
-  for (int d = 0; d < Cfg::kFetch; ++d) {
-    const int i = min(wave + d * WAVES, Cfg::kPieces - 1);
-    const bool codes = i < MT * 2;
-    x_src[d] = (codes ? a.Xq + (size_t)s_begin * kBlockBytes + i * 1024
-                      : reinterpret_cast<const int8_t*>(a.Xf) + (size_t)s_begin * 8192 + (i - MT * 2) * 1024) + lane * 16;
-    x_step[d] = codes ? kBlockBytes : 8192;
-    x_dst[d] = i * 1024 + lane * 16;
-  }
-  auto fetch_x = [&](int j, v4i (&xr)[Cfg::kFetch]) {
-    if constexpr (kPrep) return;
-#pragma unroll
-    for (int d = 0; d < Cfg::kFetch; ++d) xr[d] = *reinterpret_cast<const v4i*>(x_src[d] + (size_t)j * x_step[d]);
-  };
-  // kPrep: slab j of the workgroup's range -> ring buffer `stage` (see the kernel's header comment)
-  const int row_stride = cnt * kSlabBytes;                         // elements of s_row per row
-  auto make_slab = [&](int j, int stage) {
-    const int ch = wave & 3, ks = ch >> 1, g = ch & 1, col = lane & 15;
-    const int kl = j * kSlabBytes + ch * 16 + col;
-    const bool crit = s_crit[kl] != 0;
-    for (int m = (wave >> 2) * 4 + (lane >> 4); m < a.M; m += WAVES) {
-      const uint32_t x = s_row[m * row_stride + kl];
-      const uint32_t code = crit ? 0u : to_code_byte(half_lo_to_float(x), s_scale[m]);
-      s_x[stage][ks * 1024 + (32 * g + m) * 16 + col] = (int8_t)code;
-      *reinterpret_cast<uint16_t*>(&s_x[stage][Cfg::XQ_BYTES + (2 * ks + (col >> 3)) * 1024 + (32 * g + m) * 16 +
-                                               (col & 7) * 2]) = crit ? (uint16_t)x : (uint16_t)0;
-    }
-  };
-  auto park_x = [&](int stage, const v4i (&xr)[Cfg::kFetch], int j) {   // j: the slab these pieces belong to
-    if constexpr (kPrep) {
-      make_slab(j, stage);
+  for (int d = 0; d < kReq; ++d) {
+    const int i = min(8 * d + wave, Cfg::kPieces - 1);
+    step[d] = kBlockBytes;
+    row_piece[d] = 0;
+    if (i < Cfg::kCodes / 1024) {
+      src[d] = a.Xq + i * 1024 + lane * 16;
+    } else if (i < (Cfg::kCodes + Cfg::kRows) / 1024) {
+      // row R keeps its 16-byte piece q at place q ^ (R / 2 % 8): 16 lanes of a fragment read meet every bank once
+      const int row = 8 * (i - Cfg::kCodes / 1024) + (lane >> 3);
+      row_piece[d] = 8 * ((lane & 7) ^ (row >> 1 & 7));
+      step[d] = 2 * kSlabBytes;
+      src[d] = reinterpret_cast<const int8_t*>(a.X + (size_t)min(row, a.M - 1) * a.ldx + row_piece[d]);
     } else {
-#pragma unroll
-      for (int d = 0; d < Cfg::kFetch; ++d) *reinterpret_cast<v4i*>(&s_x[stage][x_dst[d]]) = xr[d];
+      src[d] = a.Wt + (size_t)tile * a.n_slabs * kBlockBytes + (i - (Cfg::kCodes + Cfg::kRows) / 1024) * 1024 + lane * 16;
     }
+    src[d] += (size_t)first * step[d];
+  }
+  auto request = [&](int s, int stage, int d, auto whole_tag) __attribute__((always_inline)) {
+    const int8_t* p = src[d];
+    if (!decltype(whole_tag)::value && s >= whole_slabs && step[d] != kBlockBytes) {
+      // columns beyond K (a multiple of 16): the row's last piece in their place, their weights are zero
+      const int over = s * kSlabBytes + row_piece[d] - (a.K - 8);
+      p -= over > 0 ? 2 * over : 0;
+    }
+    const uint32_t dst = lds0 + stage * Cfg::kStage + (8 * d + wave) * 1024;
+    if (8 * d * 1024 >= Cfg::kCodes + Cfg::kRows) dma16_once(p, dst);   // (weights, whichever wave)
+    else dma16(p, dst);
+    src[d] += step[d];
   };
-  struct W2 {
-    v4i w[2];
+  auto request_slab = [&](int s, int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int d = 0; d < kReq; ++d)
+      if (d + 1 < kReq || full_wave) request(s, stage, d, std::false_type{});
   };
-  auto fetch_w = [&](int j, W2& f) {
-    const int8_t* p = wgrp + (size_t)j * kBlockBytes;
-    f.w[0] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
-    f.w[1] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p + 1024));
+  // own requests are in but those of the newest `behind` slabs (at most kStages - 1), own LDS reads have returned; then a
+  // barrier: the same holds for every wave
+  auto wait_for = [&](int behind) __attribute__((always_inline)) {
+    // (the usual count first)
+    auto wait = [&]<int... kB>(std::integer_sequence<int, kB...>, auto req_tag) __attribute__((always_inline)) {
+      (void)((behind == kStages - 1 - kB ? (wait_requests<(kStages - 1 - kB) * decltype(req_tag)::value>(), true) : false) || ...);
+    };
+    if (full_wave) wait(std::make_integer_sequence<int, kStages>{}, std::integral_constant<int, kReq>{});
+    else wait(std::make_integer_sequence<int, kStages>{}, std::integral_constant<int, kReq - 1>{});
+    asm volatile("s_barrier" : : : "memory");
   };
 
-  v16i acc[MT];
-  v16f accf[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[mt][e] = 0, accf[mt][e] = 0.0f;
-
+  // ---- fragments of one k-step
   struct Frags {
-    v4i x[MT][2];      // int8 codes, k-steps 0 and 1
-    v8h xf[MT][4];     // fp16 critical columns, pieces 2 ks + t (valid when the slab has any)
+    v4i x[TI], w[TJ];        // codes of both sides
+    v4u xf[2][TI], mk;       // rows of X, the two halves of the k-step; 0xff per critical column
   };
-  auto read_frags = [&](int stage, bool any, Frags& g) {
-    const int8_t* base = &s_x[stage][lane * 16];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) g.x[mt][ks] = *reinterpret_cast<const v4i*>(base + mt * 2048 + ks * 1024);
-    if (any) {                                                     // the same for the whole workgroup
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-          g.xf[mt][p] = *reinterpret_cast<const v8h*>(base + Cfg::XQ_BYTES + mt * 4096 + p * 1024);
-    }
-  };
-  auto multiply = [&](bool any, const Frags& g, const W2& f) {
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(g.x[mt][ks], f.w[ks], acc[mt], 0, 0, 0);
-    if (any) {
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const v4u wu = __builtin_bit_cast(v4u, f.w[ks]) ^ 0x80808080u;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const v8h wh = codes_to_half8(wu, t);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) accf[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(g.xf[mt][2 * ks + t], wh, accf[mt], 0, 0, 0);
-        }
-      }
+  const int row_group = Cfg::kHalves ? 0 : 2 * half;                  // first 32-row group of this wave
+  const int a_off = row_group * 2048 + lane * 16;
+  const int b_off = Cfg::kCodes + Cfg::kRows + wn * 4096 + lane * 16;
+  const int x_off = Cfg::kCodes + (row_group * 32 + lr) * (2 * kSlabBytes);
+  constexpr int kReads = TI + TJ + 1 + 2 * TI;
+  auto read_frag = [&](int s, int stage, int ks, Frags& f, int n) __attribute__((always_inline)) {
+    const int8_t* base = smem + stage * Cfg::kStage;
+    if (n < TJ)
+      f.w[n] = *reinterpret_cast<const v4i*>(base + b_off + n * 2048 + ks * 1024);
+    else if (n == TJ)
+      f.mk = *reinterpret_cast<const v4u*>(s_mask + ((s - first) & (Cfg::kMaskSlabs - 1)) * kSlabBytes + (2 * ks + lg) * 16);
+    else if (n < TJ + 1 + TI)
+      f.x[n - TJ - 1] = *reinterpret_cast<const v4i*>(base + a_off + (n - TJ - 1) * 2048 + ks * 1024);
+    else {
+      const int t = (n - TJ - 1 - TI) / TI, i = (n - TJ - 1 - TI) % TI;
+      const int q = 4 * ks + 2 * lg + t;                              // columns 8 q .. 8 q + 8 of the slab
+      f.xf[t][i] = *reinterpret_cast<const v4u*>(base + x_off + i * (32 * 2 * kSlabBytes) + ((q ^ (lr >> 1 & 7)) * 16));
     }
   };
 
-  // Software pipeline (past the end the requests repeat the last slab: L2 hits, uniform loop body).
-  // In iteration j: request the activation pieces of slab j + 5 and the weights of slab j + 3; read the fragments
-  // of slab j + 1 from LDS (they overlap the MFMAs of slab j, whose fragments were read an iteration
-  // ago); park the pieces of slab j + 2 (requested three iterations ago) in the buffer that slab j - 1
-  // used (a ring of four, so that every index is static in a loop unrolled four times); barrier.
-  const int last = cnt - 1;
-  W2 f[4];
-  // Activation pieces on their way from L2 to LDS: slab s >= 1 travels in xr[s % 4] (slab 0 in x0), requested three
-  // iterations before it is parked (the pieces were written by another kernel, possibly through another XCD's
-  // L2; four registers per set).
-  v4i x0[Cfg::kFetch], xr[4][Cfg::kFetch];
-  Frags fr[2];
-  // (requests in the order the loop issues them, so that what the compiler counts as in flight on entry to the
-  // loop is what it counts when coming round)
-  fetch_x(0, x0);
-  fetch_x(min(1, last), xr[1]);
-  fetch_x(min(2, last), xr[2]);
-  fetch_w(0, f[0]);
-  fetch_x(min(3, last), xr[3]);
-  fetch_w(min(1, last), f[1]);
-  fetch_x(min(4, last), xr[0]);
-  fetch_w(min(2, last), f[2]);
-  if constexpr (kPrep) {
-    // (the weight requests above are in flight meanwhile)
-    for (int i = threadIdx.x; i < 4 * Cfg::STAGE_BYTES / 16; i += Cfg::kThreads)
-      reinterpret_cast<v4u*>(&s_x[0][0])[i] = v4u{0, 0, 0, 0};
-    const us2 th2 = __builtin_bit_cast(us2, a.th | (a.th << 16));
-    // rows innermost, so that the loads of all rows are in flight together
-    us2 best[kPanelPrepMaxM];
+  v16i acc[TI][TJ];
+  v16f accf[TI][TJ];
 #pragma unroll
-    for (int m = 0; m < kPanelPrepMaxM; ++m) best[m] = __builtin_bit_cast(us2, 0u);
-    for (int c = threadIdx.x; c < a.K / 8; c += Cfg::kThreads) {
-      v4u raw[kPanelPrepMaxM];
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int m = 0; m < kPanelPrepMaxM; ++m) {
-        raw[m] = v4u{0, 0, 0, 0};
-        if (m < a.M) raw[m] = *reinterpret_cast<const v4u*>(a.X + (size_t)m * a.ldx + c * 8);
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0, accf[i][j][e] = 0.0f;
+
+  // The products of one k-step.  Between any two MFMAs `between(n)` (a fragment read of the next k-step, at times a
+  // request) and the conversion of weight codes ahead of their MFMA, fenced so that they stay there: a wave issues in
+  // order, and a burst of reads that finds the LDS queue full holds up the MFMAs behind it.
+  constexpr int kInt = TI * TJ, kAll = 3 * kInt;
+  auto multiply = [&](const Frags& g, auto&& between) __attribute__((always_inline)) {
+    v2u wh[2 * TJ][2];
+    v4i wi[TJ];
+#pragma unroll
+    for (int n = 0; n < kAll; ++n) {
+      if (n < kInt) {
+        const int i = n % TI, j = n / TI;
+        if (i == 0) wi[j] = __builtin_bit_cast(v4i, __builtin_bit_cast(v4u, g.w[j]) & ~g.mk);
+        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(g.x[i], wi[j], acc[i][j], 0, 0, 0);
+      } else {
+        const int q = (n - kInt) / TI, t = q / TJ, j = q % TJ, i = n % TI;
+        const v4u h = v4u{wh[q][0][0], wh[q][0][1], wh[q][1][0], wh[q][1][1]};
+        accf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, g.xf[t][i]), __builtin_bit_cast(v8h, h), accf[i][j], 0, 0, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      between(n);
+      // (word d of conversion q, kInt MFMAs ahead of its own)
 #pragma unroll
-      for (int m = 0; m < kPanelPrepMaxM; ++m)
-#pragma unroll
-        for (int w = 0; w < 4; ++w)   // per half, wraps mod 2^16: entries below the threshold get the top bit
-          best[m] = __builtin_elementwise_max(best[m], (us2)(__builtin_bit_cast(us2, raw[m][w] & 0x7fff7fffu) - th2));
-    }
-    // this workgroup's columns (the K padding reads as zero)
-    for (int c = threadIdx.x; c < cnt * (kSlabBytes / 8); c += Cfg::kThreads) {
-      const int k = s_begin * kSlabBytes + c * 8;
-      v4u raw[kPanelPrepMaxM];
-#pragma unroll
-      for (int m = 0; m < kPanelPrepMaxM; ++m) {
-        raw[m] = v4u{0, 0, 0, 0};
-        if (m < a.M && k < a.K) raw[m] = *reinterpret_cast<const v4u*>(a.X + (size_t)m * a.ldx + k);
+      for (int w = 0; w < 2 / TI; ++w) {
+        const int x = n * (2 / TI) + w, q = x >> 1, t = q / TJ, j = q % TJ, d = x & 1;
+        if (q < 2 * TJ) wh[q][d] = codes_to_half4(((uint32_t)g.w[j][2 * t + d] & g.mk[2 * t + d]) ^ 0x80808080u);   // other columns: zero
       }
-#pragma unroll
-      for (int m = 0; m < kPanelPrepMaxM; ++m)
-        if (m < a.M) *reinterpret_cast<v4u*>(&s_row[m * row_stride + c * 8]) = raw[m];
+      __builtin_amdgcn_sched_barrier(0);
     }
+  };
+
 #pragma unroll
-    for (int m = 0; m < kPanelPrepMaxM; ++m) {
-      if (m < a.M) {                                                  // the same for every lane
-        const uint32_t both = __builtin_bit_cast(uint32_t, best[m]);
-        const uint32_t wmax = wave_max_u32(max(both & 0xffffu, both >> 16));
-        if (lane == 0) s_part[m][wave] = wmax;
+  for (int q = 0; q < kStages; ++q)
+    if (first + q < end) request_slab(first + q, q);
+  Frags f[2];
+  wait_for(min(kStages - 1, last - first));                           // slab `first` has landed, and the flags
+  for (int t = threadIdx.x; t < mask_words(first); t += Cfg::kThreads) put_mask(t, reinterpret_cast<const uint32_t*>(s_mask)[t]);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
+  const int ks0 = Cfg::kHalves ? half : 0;
+#pragma unroll
+  for (int n = 0; n < kReads; ++n) read_frag(first, 0, ks0, f[0], n);
+  int stage = 0, s = first;
+  // Slab s (the fragments of its first k-step are in g): once slab s + 1 has landed everywhere, its fragments are read
+  // into `next` between the MFMAs, and slab s + kStages is requested into the buffer of slab s, whose fragments every
+  // wave has read by then.  steady: all of that is there, and within K.
+  auto slab = [&](Frags& g, Frags& next, auto steady_tag) __attribute__((always_inline)) {
+    constexpr bool kSteady = decltype(steady_tag)::value;
+    const int stage1 = stage + 1 == kStages ? 0 : stage + 1;
+    if constexpr (!Cfg::kHalves) {                                     // the second k-step of this slab
+      multiply(g, [&](int n) __attribute__((always_inline)) {
+        if (n < kReads) read_frag(s, stage, 1, next, n);
+      });
+    }
+    const bool ask = kSteady || s + kStages <= last;
+    if constexpr (kSteady) {
+      if (full_wave) wait_requests<(kStages - 2) * kReq>();
+      else wait_requests<(kStages - 2) * (kReq - 1)>();
+      asm volatile("s_barrier" : : : "memory");
+    } else if (s < last) {
+      wait_for(min(kStages - 2, last - s - 1));
+    }
+    Frags& from = Cfg::kHalves ? g : next;
+    Frags& to = Cfg::kHalves ? next : g;
+    // (past the end the fragments read are those of an older slab, and not used)
+    multiply(from, [&](int n) __attribute__((always_inline)) {
+      if (n < kReads) read_frag(s + 1, stage1, ks0, to, n);
+      const int d = n * kReq / kAll;
+      if (d < kReq && (d * kAll + kReq - 1) / kReq == n && ask && (d + 1 < kReq || full_wave)) request(s + kStages, stage, d, steady_tag);
+    });
+    stage = stage1;
+    ++s;
+  };
+  // (A short range runs the general form of the loop only: what is entered first has to be fetched as instructions.  With the
+  // steady form for every range 4096 -> 4096 took 12.3 us at 32 rows instead of 10.8, with the general form for every
+  // range 4096 -> 22016 25.2 instead of 23.2.)
+  const int steady_end = end - first >= 20 ? min(last, whole_slabs - 1) - kStages : first;
+  for (int window = first;; window += Cfg::kMaskSlabs) {
+    const int to = min(window + Cfg::kMaskSlabs, end);                 // (an even number of slabs but for the last window)
+    while (s < min(to, steady_end)) {                                  // (an even number of slabs)
+      slab(f[0], f[1], std::true_type{});
+      if constexpr (Cfg::kHalves) slab(f[1], f[0], std::true_type{});
+    }
+    while (s < to) {
+      slab(f[0], f[1], std::false_type{});
+      if constexpr (Cfg::kHalves) {
+        if (s < to) slab(f[1], f[0], std::false_type{});
       }
     }
+    if (to == end) break;
+    __syncthreads();                                                   // every wave has read the masks so far
+    for (int t = threadIdx.x; t < mask_words(to); t += Cfg::kThreads)
+      put_mask(t, reinterpret_cast<const uint32_t*>(a.mask + (size_t)to * kSlabBytes)[t]);
     __syncthreads();
-    for (int c = threadIdx.x; c < row_stride; c += Cfg::kThreads) {
-      bool crit = false;
-      for (int m = 0; m < a.M; ++m) crit = crit || (s_row[m * row_stride + c] & 0x7fffu) >= a.th;
-      s_crit[c] = crit ? 1 : 0;
-    }
-    if ((int)threadIdx.x < a.M) {
-      uint32_t mm = 0;
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) mm = max(mm, s_part[threadIdx.x][w]);
-      // top bit set: an entry below the threshold exists and its pattern is mm + th (mod 2^16)
-      const float r = (mm & 0x8000u) ? half_lo_to_float((mm + a.th) & 0xffffu) : 0.0f;
-      s_r[threadIdx.x] = r;
-      s_scale[threadIdx.x] = (r == 0.0f) ? 0.0f : 127.0f / r;       // IEEE division
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < cnt; t += Cfg::kThreads) {         // "slab t holds a critical column"
-      const v4u* fl = reinterpret_cast<const v4u*>(&s_crit[t * kSlabBytes]);
-      const v4u m = fl[0] | fl[1] | fl[2] | fl[3];
-      s_any[t] = (m[0] | m[1] | m[2] | m[3]) != 0;
-    }
+    read_frag(s, stage, ks0, f[0], TJ);                                // the mask of slab s again
   }
-  park_x(0, x0, 0);
-  park_x(1, xr[1], min(1, last));
+
+  // ---- the sums of this range, through LDS: as fp32 rows of 256 columns (of either half of the slabs), then in a loop whole
+  // rows to memory.  (This code runs once and is not in the instruction cache when it is reached: what counts is how
+  // little of it there is.  With the halves exchanged register by register and every element stored from its own register
+  // it took 2.7 us at 32 rows and 4.6 at 64.)
+  // C layout of the 32x32 MFMA: lane = column (lane % 32), register e = row 8 (e / 4) + 4 (lane / 32) + (e % 4); the rows
+  // of the upper lanes swap the two 32-column halves of every 64 (the other 32 banks).
+  if ((int)threadIdx.x < kBM) s_r[threadIdx.x] = r0;
   __syncthreads();
-  // The flags of the next 64 slabs as one scalar mask (bit i: slab base + i, the last slab repeated past the end),
-  // refilled every 64 iterations: no LDS read and no vector compare between a slab's fragments and its MFMAs.
-  uint64_t any_mask = __builtin_amdgcn_ballot_w64(s_any[min(lane, last)] != 0);
-  bool any_next = any_mask & 1u;
-  read_frags(0, any_next, fr[0]);
-  auto iteration = [&](int j, auto u_tag) {
-    constexpr int u = decltype(u_tag)::value;                        // j % 4
-    const bool any_cur = any_next;
-    if constexpr (u == 3) {                                          // 64 is a multiple of four: only here can j + 1 start a window
-      if (((j + 1) & 63) == 0) any_mask = __builtin_amdgcn_ballot_w64(s_any[min(j + 1 + lane, last)] != 0);
-    }
-    any_next = (any_mask >> ((j + 1) & 63)) & 1u;
-    fetch_x(min(j + 5, last), xr[(u + 1) & 3]);
-    fetch_w(min(j + 3, last), f[(u + 3) & 3]);
-    read_frags((u + 1) & 3, any_next, fr[(u + 1) & 1]);
-    multiply(any_cur, fr[u & 1], f[u & 3]);
-    park_x((u + 2) & 3, xr[(u + 2) & 3], min(j + 2, last));
-    __syncthreads();
-  };
-  // Whole groups of four iterations run without a way out in between: with an exit after every iteration the
-  // compiler's count of the requests still in flight is merged over all those paths, and it then waits for
-  // weights requested one iteration earlier instead of three (every iteration took a whole memory latency).
-  int j0 = 0;
-  for (; j0 + 4 <= cnt; j0 += 4) {
-    iteration(j0, std::integral_constant<int, 0>{});
-    iteration(j0 + 1, std::integral_constant<int, 1>{});
-    iteration(j0 + 2, std::integral_constant<int, 2>{});
-    iteration(j0 + 3, std::integral_constant<int, 3>{});
-  }
-  if (j0 < cnt) iteration(j0, std::integral_constant<int, 0>{});
-  if (j0 + 1 < cnt) iteration(j0 + 1, std::integral_constant<int, 1>{});
-  if (j0 + 2 < cnt) iteration(j0 + 2, std::integral_constant<int, 2>{});
-
-  // ---- outputs.  C layout of the 32x32 MFMA: lane = column n (lane % 32), register e = row
-  // 8 (e / 4) + 4 (lane / 32) + (e % 4).
-  const float cs = (n < a.N) ? a.c[n] / 16129.0f : 0.0f;
-  const float step = (n < a.N) ? a.c[n] / 127.0f : 0.0f;
-  const float b = (!kSplit && a.bias && n < a.N) ? half_lo_to_float(a.bias[n]) : 0.0f;
+  float* s_y = reinterpret_cast<float*>(smem);                        // [half][kBM][256]
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int j = 0; j < TJ; ++j) {
+    const float cs = c[j] / 16129.0f, col_step = c[j] / 127.0f;
+    float* const mine = s_y + ((Cfg::kHalves ? half * kBM : row_group * 32) + 4 * lg) * 256 + wn * 64 + ((j ^ lg) * 32 + lr);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int m = mt * 32 + 8 * (e >> 2) + 4 * lg + (e & 3);
-      if (m < a.M && n < a.N) {
-        const float rm = kPrep ? s_r[m] : a.r[m];
-        const float y = (float)acc[mt][e] * (rm * cs) + accf[mt][e] * step;
-        if constexpr (kSplit)
-          a.partial[((size_t)split * a.M + m) * a.N + n] = y;
-        else
-          a.Y[(size_t)m * a.ldy + n] = (uint16_t)float_to_half_bits(y + b);
-        if constexpr (kTap) {
-          if constexpr (kSplit)
-            atomicAdd(a.tap_acc + (size_t)m * a.N + n, acc[mt][e]);   // tap buffer zeroed by the launcher
-          else
-            a.tap_acc[(size_t)m * a.N + n] = acc[mt][e];
-        }
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const v4f rm = *reinterpret_cast<const v4f*>(s_r + (row_group + i) * 32 + 8 * q + 4 * lg);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mine[(i * 32 + 8 * q + e) * 256] = (float)acc[i][j][4 * q + e] * (rm[e] * cs) + accf[i][j][4 * q + e] * col_step;
       }
-    }
+  }
+  if (a.tap_acc) {                                                   // (zeroed by the launcher; integers, so in any order)
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int m = (row_group + i) * 32 + 8 * (e >> 2) + 4 * lg + (e & 3), n = n0 + j * 32 + lr;
+          if (m < a.M && n < a.N) atomicAdd(a.tap_acc + (size_t)m * a.N + n, acc[i][j][e]);
+        }
+  }
+  __syncthreads();
+  const int col = 4 * lane, n = tile * 256 + col;                     // a wave per row
+  if (n >= a.N) return;
+  float* dst = a.partial + (size_t)split * a.M * a.N + n;
+  for (int m = wave; m < a.M; m += Cfg::kWaves) {
+    const float* y = s_y + m * 256 + (col ^ ((m & 4) * 8));
+    v4f v = *reinterpret_cast<const v4f*>(y);
+    if constexpr (Cfg::kHalves) v += *reinterpret_cast<const v4f*>(y + kBM * 256);
+    *reinterpret_cast<v4f*>(dst + (size_t)m * a.N) = v;
+  }
 }
 
 // kCols neighbouring sums of `splits` ranges, added in index order, eight loads in flight at a time.  (Added one load
@@ -494,55 +489,43 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, size_t n) {
   if (i < n) p[i] = 0;
 }
 
-// Decode plan: `waves` neighbouring 32-column groups per workgroup.
-static SkinnyPlan plan_panel(int M, int K, int N, int waves) {
+// Ranges of K: a workgroup takes 0.45 us per slab, or its share of what HBM delivers (6.2 TB/s), and the fp32 sums of a range
+// cost their 8 bytes per output at 3 TB/s: the sum of both is least at sqrt(0.45 slabs / cost of a range), unless HBM is busy
+// with fewer workgroups.  Counted for 32 rows, not for the rows of the call, so that a workspace sized for more rows gives
+// the same ranges.
+SkinnyPlan plan_skinny(int K, int N) {
   SkinnyPlan p;
-  p.waves = waves;
   p.n_slabs = packed_k(K) / kSlabBytes;
-  p.tiles_n = packed_n(N) / (32 * waves);
-  // as many workgroups as the chip holds at once (two of four waves or one of eight per CU), every
-  // workgroup with at least 8 slabs, no second round
-  const int slots = device_cu_count() * (waves == 4 ? 2 : 1);
-  const int want = max(1, min(p.n_slabs / 8, slots / p.tiles_n));
-  p.slabs_per_split = ceil_div(p.n_slabs, want);
+  p.tiles_n = packed_n(N) / 256;
+  const int enough = ceil_div((int)(0.45 * 6.2e6 / kBlockBytes), p.tiles_n);          // workgroups per tile that keep HBM busy
+  const int cheapest = (int)(sqrt(0.45 * p.n_slabs * 3.0e6 / (32.0 * N * 8)) + 0.5);
+  const int best = max(1, min(min(enough, cheapest), min(device_cu_count() / p.tiles_n, p.n_slabs / 2)));
+  p.slabs_per_split = ceil_div(p.n_slabs, best);
   p.splits = ceil_div(p.n_slabs, p.slabs_per_split);
-  p.partial_bytes = p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
-  return p;
-}
-SkinnyPlan plan_skinny(int M, int K, int N) {
-  const SkinnyPlan p4 = plan_panel(M, K, N, 4), p8 = plan_panel(M, K, N, 8);
-  // measured on the Llama-7B linears: eight waves per panel beat four (half the LDS fills per weight byte)
-  SkinnyPlan p = p8;
-  p.partial_bytes = max(p4.partial_bytes, p8.partial_bytes);     // the workspace serves either
   return p;
 }
 
-template <class Cfg, bool kSplit, bool kTap, bool kPrep>
-static hipError_t launch_panel_one(const SkinnyArgs& a, int splits, hipStream_t stream) {
-  hipLaunchKernelGGL((k_gemm_panel<Cfg, kSplit, kTap, kPrep>), dim3(a.tiles_n * splits), dim3(Cfg::kThreads), 0, stream, a);
+template <int kBM>
+static hipError_t prepare_decode() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_decode<kBM>), hipFuncAttributeMaxDynamicSharedMemorySize, DecodeCfg<kBM>::LDS_BYTES);
+}
+template <int kBM>
+static hipError_t launch_decode(const SkinnyArgs& a, int splits, hipStream_t stream) {
+  hipLaunchKernelGGL(k_gemm_decode<kBM>, dim3(a.tiles_n * splits), dim3(DecodeCfg<kBM>::kThreads), DecodeCfg<kBM>::LDS_BYTES, stream, a);
   return hipGetLastError();
 }
-template <class Cfg, bool kPrep>
-static hipError_t launch_panel_cfg(const SkinnyArgs& a, int splits, hipStream_t stream) {
-  const bool split = splits > 1 || a.lora_r > 0 || a.residual || a.codes || a.gelu, tap = a.tap_acc != nullptr;
-  if (split)
-    return tap ? launch_panel_one<Cfg, true, true, kPrep>(a, splits, stream)
-               : launch_panel_one<Cfg, true, false, kPrep>(a, splits, stream);
-  return tap ? launch_panel_one<Cfg, false, true, kPrep>(a, splits, stream)
-             : launch_panel_one<Cfg, false, false, kPrep>(a, splits, stream);
-}
-static hipError_t launch_panel(const SkinnyArgs& a, const SkinnyPlan& plan, hipStream_t stream) {
-  const bool two = a.M > 32;
-  if (a.X) {                                                         // the kernel prepares its own operands
-    if (two || !panel_prep_fits(a.M, plan)) return hipErrorInvalidValue;
-    return plan.waves == 8 ? launch_panel_cfg<PanelCfg<1, 8>, true>(a, plan.splits, stream)
-                           : launch_panel_cfg<PanelCfg<1, 4>, true>(a, plan.splits, stream);
-  }
-  if (plan.waves == 8)
-    return two ? launch_panel_cfg<PanelCfg<2, 8>, false>(a, plan.splits, stream)
-               : launch_panel_cfg<PanelCfg<1, 8>, false>(a, plan.splits, stream);
-  return two ? launch_panel_cfg<PanelCfg<2, 4>, false>(a, plan.splits, stream)
-             : launch_panel_cfg<PanelCfg<1, 4>, false>(a, plan.splits, stream);
+
+hipError_t prepare_skinny_kernels() {
+  static std::atomic<bool> attr_set[64] = {};                      // setting an attribute twice is harmless
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (attr_set[dev]) return hipSuccess;
+  hipError_t e = prepare_decode<32>();
+  if (e == hipSuccess) e = prepare_decode<64>();
+  if (e == hipSuccess) e = prepare_decode<128>();
+  if (e == hipSuccess) e = prepare_rows_kernels();
+  if (e == hipSuccess) attr_set[dev] = true;
+  return e;
 }
 
 static hipError_t launch_finalize_coded(const FinalizedHalves& src, int block, uint8_t* codes, float* absmax,
@@ -569,24 +552,22 @@ hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t 
   a.n_slabs = plan.n_slabs;
   a.tiles_n = plan.tiles_n;
   a.slabs_per_split = plan.slabs_per_split;
-  // with a low-rank term, an activation, a residual or a coded output the result always goes through the partial
-  // buffer: the kernel that sums it adds the term, applies the activation and encodes
-  const bool split = plan.splits > 1 || a.lora_r > 0 || a.residual || a.codes || a.gelu, tap = a.tap_acc != nullptr;
+  if (a.M < 1 || a.M > kSkinnyMaxM || !a.partial || !a.X) return hipErrorInvalidValue;
+  if (hipError_t e = prepare_skinny_kernels(); e != hipSuccess) return e;
   const size_t n = (size_t)a.M * a.N;
-  if (split && tap) hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a.tap_acc, n);
-  if (a.flag_reset_late && !split) return hipErrorInvalidValue;    // no kernel after the panel kernel to clear them
-  hipError_t e = launch_panel(a, plan, stream);
+  if (a.tap_acc) hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a.tap_acc, n);
+  hipError_t e = a.M <= 32 ? launch_decode<32>(a, plan.splits, stream) : a.M <= 64 ? launch_decode<64>(a, plan.splits, stream) : launch_decode<128>(a, plan.splits, stream);
   if (e != hipSuccess) return e;
-  if (split && a.codes) {
+  // the sums go through memory whether K is split or not: the kernel that adds them is the rest of the layer (and it puts the
+  // column flags back to zero, which every workgroup of the kernel before it reads)
+  if (a.codes) {
     const FinalizedHalves src = {a.partial, plan.splits, a.N, n, a.bias, a.residual, a.ldr, a.Y};
-    e = launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, a.flag_reset_late, a.Kpad, stream);
-  } else if (split) {
-    hipLaunchKernelGGL(k_skinny_finalize, dim3(ceil_div(a.N, 256), a.M), dim3(256), 0, stream, a.partial, plan.splits,
-                       a.M, a.N, a.bias, a.lora_T, a.lora_ldt, a.lora_B, a.lora_r, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
-                       a.flag_reset_late, a.Kpad);
-    e = hipGetLastError();
+    return launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, a.flag_reset, a.Kpad, stream);
   }
-  return e;
+  hipLaunchKernelGGL(k_skinny_finalize, dim3(ceil_div(a.N, 256), a.M), dim3(256), 0, stream, a.partial, plan.splits,
+                     a.M, a.N, a.bias, a.lora_T, a.lora_ldt, a.lora_B, a.lora_r, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
+                     a.flag_reset, a.Kpad);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -696,16 +677,16 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
     int m, c;
     const bool ok = chunk_place(i, m, c) && c * 8 < a.K;              // (the K padding: zeros, never critical)
     us2 t = __builtin_bit_cast(us2, 0u);
-    over[i] = 0;
+    uint32_t bits = 0;                                                // element j in the low half: bit j, in the high half: bit 15 + j
 #pragma unroll
     for (int w = 0; w < 4; ++w) {   // per half, wraps mod 2^16: entries below the threshold get the top bit
       raw[i][w] = ok ? raw[i][w] : 0u;
       const us2 d = (us2)(__builtin_bit_cast(us2, raw[i][w] & 0x7fff7fffu) - th2);
       t = __builtin_elementwise_max(t, d);
-      const uint32_t dd = __builtin_bit_cast(uint32_t, d);
-      over[i] |= ((~dd >> 15) & 1u) << (2 * w) | ((~dd >> 31) & 1u) << (2 * w + 1);
+      const uint32_t below = __builtin_bit_cast(uint32_t, (ss2)(__builtin_bit_cast(ss2, d) >> 15));   // 0xffff per such entry
+      bits |= ~below & (0x00020001u << (2 * w));
     }
-    if (!ok) over[i] = 0;
+    over[i] = ok ? (bits | bits >> 16) & 0xffu : 0u;
 #pragma unroll
     for (int mm = 0; mm < kM; ++mm)
       if (ok && mm == m) best[mm] = __builtin_elementwise_max(best[mm], t);
@@ -743,16 +724,17 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
         for (int mm = 0; mm < kM; ++mm) crit |= mm < M ? s_over[mm * row_chunks + c] : 0u;
       }
       const float sc = s_scale[m];
-      uint32_t code[2] = {0, 0}, xf[4];
+      uint32_t code[2], xf[4], mask[2];                                // mask: 0xff per critical column
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t h = (raw[i][j >> 1] >> (16 * (j & 1))) & 0xffffu;
-        const bool cr = (crit >> j) & 1u;
-        code[j >> 2] |= (cr ? 0u : to_code_byte(half_lo_to_float(h), sc)) << (8 * (j & 3));
+      for (int q = 0; q < 2; ++q) {
+        const uint32_t ones = (((crit >> (4 * q)) & 0xfu) * 0x00204081u) & 0x01010101u;   // bit j to byte j
+        mask[q] = (ones << 8) - ones;
+        // (an entry of a column that is not critical is at most the row's largest)
+        code[q] = to_code_word(raw[i][2 * q], raw[i][2 * q + 1], sc) & ~mask[q];
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+          xf[2 * q + w] = raw[i][2 * q + w] & __builtin_amdgcn_perm(0u, mask[q], w ? 0x03030202u : 0x01010000u);
       }
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-        xf[w] = (((crit >> (2 * w)) & 1u) ? (raw[i][w] & 0xffffu) : 0u) | (((crit >> (2 * w + 1)) & 1u) ? (raw[i][w] & 0xffff0000u) : 0u);
       *reinterpret_cast<v2u*>(s_code + (size_t)m * Kpad + k) = v2u{code[0], code[1]};
       *reinterpret_cast<v4u*>(s_xf + (size_t)m * Kpad + k) = v4u{xf[0], xf[1], xf[2], xf[3]};
       if (crit) s_any[k >> 6] = 1;
@@ -860,12 +842,12 @@ static int rows_tiles_max(int M, int Kpad) {
   const long room = (long)kRowsMaxLds - (long)rows_lds_bytes(M, Kpad, 0);
   return room <= 0 ? 0 : (int)min(room / (2 * kRowsWaves * M * 16 * 4), (long)(kRowsWaves * kWave / (16 * M)));
 }
-// Up to four rows wherever they fit in LDS; more where a compute unit can hold the sums of all its tiles, so that it
-// prepares once (six rows of a 7B layer 67 us, 74 with K split between workgroups; eight rows, where 4096 x 22016 prepares
-// twice, 38 us for that linear, 31 split).
+// One or two rows wherever they fit in LDS; more where a compute unit can hold the sums of all its tiles, so that it
+// prepares once (8192 -> 57344 at four rows, where it would prepare twice, 93 us, with K split 80; a 7B layer of six rows 65 us
+// with every linear in this kernel, 71 split).
 bool rows_kernel_fits(int M, int Kpad, int N) {
   return M >= 1 && M <= kRowsMaxM && M * Kpad / 8 <= kRowsMaxChunks * kRowsWaves * kWave &&
-         rows_tiles_max(M, Kpad) >= (M <= 4 ? 1 : ceil_div(ceil_div(N, 16), device_cu_count()));
+         rows_tiles_max(M, Kpad) >= (M <= 2 ? 1 : ceil_div(ceil_div(N, 16), device_cu_count()));
 }
 
 // more than the default 64 KB of LDS: an attribute per kernel and device
@@ -880,10 +862,10 @@ hipError_t prepare_rows_kernels() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_set[dev]) return hipSuccess;
-  hipError_t e = prepare_rows_of<1, 1, 2, 3, kRowsMaxChunks>();
-  if (e == hipSuccess) e = prepare_rows_of<2, 1, 2, 3, kRowsMaxChunks>();
-  if (e == hipSuccess) e = prepare_rows_of<4, 1, 2, 3, kRowsMaxChunks>();
-  if (e == hipSuccess) e = prepare_rows_of<8, 1, 2, 3, kRowsMaxChunks>();
+  hipError_t e = prepare_rows_of<1, 1, 2, 3, 4, kRowsMaxChunks>();
+  if (e == hipSuccess) e = prepare_rows_of<2, 1, 2, 3, 4, kRowsMaxChunks>();
+  if (e == hipSuccess) e = prepare_rows_of<4, 1, 2, 3, 4, kRowsMaxChunks>();
+  if (e == hipSuccess) e = prepare_rows_of<8, 1, 2, 3, 4, kRowsMaxChunks>();
   if (e == hipSuccess) attr_set[dev] = true;
   return e;
 }
@@ -894,6 +876,7 @@ static hipError_t launch_rows_of(const SkinnyArgs& a, int chunks, int grid, size
   if (chunks <= 1) hipLaunchKernelGGL((k_gemm_rows<kM, 1>), g, b, lds, stream, a);
   else if (chunks <= 2) hipLaunchKernelGGL((k_gemm_rows<kM, 2>), g, b, lds, stream, a);
   else if (chunks <= 3) hipLaunchKernelGGL((k_gemm_rows<kM, 3>), g, b, lds, stream, a);
+  else if (chunks <= 4) hipLaunchKernelGGL((k_gemm_rows<kM, 4>), g, b, lds, stream, a);
   else hipLaunchKernelGGL((k_gemm_rows<kM, kRowsMaxChunks>), g, b, lds, stream, a);
   return hipGetLastError();
 }
