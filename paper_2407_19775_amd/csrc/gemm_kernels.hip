@@ -366,8 +366,7 @@ __device__ __forceinline__ void store_tile_coded(const GemmArgs& a, const WavePo
         const v16f y = __builtin_bit_cast(v16f, acc[i0 + ii][j]);
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
-          uint32_t h = float_to_half_bits(y[e] + bn[j]) | (float_to_half_bits(y[e + 1] + bn[j]) << 16);
-          if (a.gelu) h = gelu_half_pair(h);                         // the activation, on the rounded layer output
+          const uint32_t h = float_to_half_bits(y[e] + bn[j]) | (float_to_half_bits(y[e + 1] + bn[j]) << 16);
           const uint32_t q = (uint32_t)__builtin_amdgcn_mov_dpp((int)h, 0xb1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
           const uint32_t out = odd ? ((q >> 16) | (h & 0xffff0000u)) : ((h & 0xffffu) | (q << 16));
           const int row = ii * 32 + 8 * (e / 4) + (e % 4) + 4 * p.lg + odd;
@@ -377,26 +376,54 @@ __device__ __forceinline__ void store_tile_coded(const GemmArgs& a, const WavePo
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    // ---- phase A
-    if (a.residual || a.Y) {
-#pragma unroll
+    // The activation, on the rounded layer output: a loop of its own over the parked rows, not unrolled.  This code runs once
+    // per tile and comes from memory; with the activation written out at each of a lane's elements and stepped over where
+    // there is none, every element cost the fetch of its instructions (ViT-L block of 1576 rows 121 -> 116.4 us, with the residual as below; 70B-shaped layer
+    // of 4096 rows 2998 -> 2973).
+    if (a.gelu) {
+#pragma unroll 1
       for (int it = 0; it < RP * CH / kWave; ++it) {
-        const int idx = it * kWave + p.lane, row = idx / CH, ch = idx % CH;
-        int8_t* cell = base + row * STRIDE + ch * 16;
-        v4u v = *reinterpret_cast<const v4u*>(cell);
-        const int gm = p.mw + i0 * 32 + row, gn = p.nw + ch * 8;
-        bool ok = true;
-        if constexpr (!kFull) ok = gm < a.M && gn < a.N;
-        if (a.residual) {
-          v4u res = v4u{0, 0, 0, 0};
-          if (ok) res = *reinterpret_cast<const v4u*>(a.residual + (size_t)gm * a.ldr + gn);
+        const int idx = it * kWave + p.lane;
+        v4u* cell = reinterpret_cast<v4u*>(base + idx / CH * STRIDE + idx % CH * 16);
+        v4u v = *cell;
 #pragma unroll
-          for (int w = 0; w < 4; ++w)
-            v[w] = float_to_half_bits(half_lo_to_float(v[w]) + half_lo_to_float(res[w])) |
-                   (float_to_half_bits(half_hi_to_float(v[w]) + half_hi_to_float(res[w])) << 16);
-          *reinterpret_cast<v4u*>(cell) = v;
+        for (int w = 0; w < 4; ++w) v[w] = gelu_half_pair(v[w]);
+        *cell = v;
+      }
+    }
+    // ---- phase A.  The residual is asked for four pieces at a time: between the stores of H (which may be the same array)
+    // the loads would wait for each other, a memory latency each.
+    if (a.residual || a.Y) {
+      constexpr int kSteps = RP * CH / kWave, kBatch = kSteps < 4 ? kSteps : 4;
+      static_assert(kSteps % kBatch == 0, "whole batches");
+#pragma unroll
+      for (int it0 = 0; it0 < kSteps; it0 += kBatch) {
+        v4u res[kBatch];
+        if (a.residual) {
+#pragma unroll
+          for (int it = 0; it < kBatch; ++it) {
+            const int idx = (it0 + it) * kWave + p.lane, gm = p.mw + i0 * 32 + idx / CH, gn = p.nw + idx % CH * 8;
+            const bool ok = kFull || (gm < a.M && gn < a.N);
+            res[it] = *reinterpret_cast<const v4u*>(a.residual + (ok ? (size_t)gm * a.ldr + gn : (size_t)0));
+          }
         }
-        if (a.Y && ok) *reinterpret_cast<v4u*>(a.Y + (size_t)gm * a.ldy + gn) = v;
+#pragma unroll
+        for (int it = 0; it < kBatch; ++it) {
+          const int idx = (it0 + it) * kWave + p.lane, row = idx / CH, ch = idx % CH;
+          int8_t* cell = base + row * STRIDE + ch * 16;
+          v4u v = *reinterpret_cast<const v4u*>(cell);
+          const int gm = p.mw + i0 * 32 + row, gn = p.nw + ch * 8;
+          bool ok = true;
+          if constexpr (!kFull) ok = gm < a.M && gn < a.N;
+          if (a.residual) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+              v[w] = float_to_half_bits(half_lo_to_float(v[w]) + half_lo_to_float(res[it][w])) |
+                     (float_to_half_bits(half_hi_to_float(v[w]) + half_hi_to_float(res[it][w])) << 16);
+            if (a.codes) *reinterpret_cast<v4u*>(cell) = v;
+          }
+          if (a.Y && ok) *reinterpret_cast<v4u*>(a.Y + (size_t)gm * a.ldy + gn) = v;
+        }
       }
     }
     __syncthreads();                                                // the parked rows of every wave are final
@@ -520,6 +547,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
     srcB[j] = dma_source(a.Wt, p.n0, all_slabs, j, Cfg::kWaves, wave, lane) + (ptrdiff_t)first * kBlockBytes;
     srcWo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Wo), p.n0, a.f_slabs, j, Cfg::kWaves, wave, lane);
   }
+  // Where few tile rows share a weight panel its bytes are requested as ones that little else reads: 7B-shaped layers of 129
+  // rows 169 -> 160 us, 333 with an adapter 237 -> 231, 512 rows 215 -> 211, 1000 rows 308 -> 305; with twelve tile rows (1500
+  // rows) 440 -> 448, and the 256-row tiles of 2048 rows 491 -> 495: not there.
+  const bool weights_once = a.tiles_m <= 8;
   // request d (0 .. DMA_PER_SLAB-1) of the slab at position `pos` of the ring's sequence: the A rows first, then the
   // B rows.  kFp16 says which kind of slab that position holds (known where the request is written down, so that
   // the loop over the codes carries no choice between the two)
@@ -533,6 +564,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
       off = (d < Cfg::A_DMA ? to_more_x : to_more_w) + (ptrdiff_t)(f - crit_used) * kBlockBytes;
     if (d < Cfg::A_DMA)
       dma16((kF ? srcXo[d] : srcA[d]) + off, base + d * Cfg::kWaves * (kWave * 16));
+    else if (!kF && Cfg::BM == 128 && weights_once)
+      dma16_once(srcB[d - Cfg::A_DMA] + off, base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
     else
       dma16((kF ? srcWo[d - Cfg::A_DMA] : srcB[d - Cfg::A_DMA]) + off,
             base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
@@ -815,7 +848,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
       dma16(src, dst + D::kCodes + j * Cfg::kWaves * 1024);
     } else {
       const int j = d - Cfg::A_DMA - D::X_DMA;
-      dma16_scalar_base(baseB + (size_t)s * kBlockBytes + j * Cfg::kWaves * 1024, lane * 16,
+      dma16_once(baseB + (size_t)s * kBlockBytes + j * Cfg::kWaves * 1024 + lane * 16,
                         dst + D::kCodes + D::kRows + j * Cfg::kWaves * 1024);
     }
   };
