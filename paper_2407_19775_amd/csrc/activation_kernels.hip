@@ -9,6 +9,7 @@
 #include "dynamic_code.h"
 #include "gemm.h"
 #include "launchers.h"
+#include "lora_device.h"
 #include "operand_layout.h"
 #include "skinny.h"
 
@@ -629,18 +630,17 @@ __global__ __launch_bounds__(kT) void k_prep_rows(const uint16_t* __restrict__ X
 // kOutlierSlab of them; each of the remaining workgroups owns 64 rows (lane = row) and a share of the columns
 // and clears the codes of the critical columns in those rows with byte stores of zero.  Driven by the
 // flags themselves, so any number of critical columns is handled the same way.
-__global__ __launch_bounds__(kThreads) void k_outlier_columns(const uint16_t* __restrict__ X, int M, int K, int ldx,
-                                                              const uint8_t* __restrict__ flag, int8_t* __restrict__ Xq,
-                                                              int n_slabs, int8_t* __restrict__ tap_xq, int slab_blocks,
-                                                              int clear_units, const PackOutliers o) {
+__device__ __forceinline__ void outlier_columns_block(int block, const uint16_t* __restrict__ X, int M, int K, int ldx,
+                                                      const uint8_t* __restrict__ flag, int8_t* __restrict__ Xq, int n_slabs,
+                                                      int8_t* __restrict__ tap_xq, int slab_blocks, int clear_units, const PackOutliers& o) {
   const int Kpad = n_slabs * kSlabBytes;
-  if ((int)blockIdx.x < slab_blocks) {
+  if (block < slab_blocks) {
     __shared__ int s_idx[kListedColumns];
     __shared__ int s_n_out;
     __shared__ int s_wave_total[kThreads / kWave];
-    compact_critical_columns(flag, K, Kpad, o, blockIdx.x == 0, s_idx, &s_n_out, s_wave_total);
-    gather_outlier_slab(X, M, ldx, n_slabs, o, blockIdx.x * kThreads + threadIdx.x, s_idx, s_n_out);
-    gather_further_slabs(X, M, ldx, n_slabs, o, blockIdx.x * kThreads + threadIdx.x, slab_blocks * kThreads, s_idx, s_n_out);
+    compact_critical_columns(flag, K, Kpad, o, block == 0, s_idx, &s_n_out, s_wave_total);
+    gather_outlier_slab(X, M, ldx, n_slabs, o, block * kThreads + threadIdx.x, s_idx, s_n_out);
+    gather_further_slabs(X, M, ldx, n_slabs, o, block * kThreads + threadIdx.x, slab_blocks * kThreads, s_idx, s_n_out);
     return;
   }
   // A clearing workgroup owns 64 rows (lane = row) and clear_units units of 16 columns (a multiple of 4), a quarter
@@ -649,7 +649,7 @@ __global__ __launch_bounds__(kThreads) void k_outlier_columns(const uint16_t* __
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int units = Kpad / 16;
   const int unit_groups = ceil_div(units, clear_units);
-  const int cb = (int)blockIdx.x - slab_blocks;
+  const int cb = block - slab_blocks;
   const int m = (cb / unit_groups) * kWave + lane;
   const int wave_units = clear_units / (kThreads / kWave);
   const int u_begin = (cb % unit_groups) * clear_units + wave * wave_units;
@@ -689,6 +689,26 @@ __global__ __launch_bounds__(kThreads) void k_outlier_columns(const uint16_t* __
       }
     }
   }
+}
+__global__ __launch_bounds__(kThreads) void k_outlier_columns(const uint16_t* __restrict__ X, int M, int K, int ldx,
+                                                              const uint8_t* __restrict__ flag, int8_t* __restrict__ Xq,
+                                                              int n_slabs, int8_t* __restrict__ tap_xq, int slab_blocks,
+                                                              int clear_units, const PackOutliers o) {
+  outlier_columns_block(blockIdx.x, X, M, K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o);
+}
+// The same next to an adapter's down-projection, which needs nothing of it and is what takes the time (16 rows of X and all
+// of A through one compute unit: 4.5 us at K = 4096, on a few of them).  Both 10 us, 5.5 + 9.7 one after the other: a 7B-shaped
+// layer of 333 rows with rank 16 235 -> 214 us, 129 rows 213 -> 182, 2048 rows with rank 32 549 -> 530.
+template <int kTiles>
+__global__ __launch_bounds__(kThreads) void k_outlier_columns_lora(const uint16_t* __restrict__ X, int M, int K, int ldx,
+                                                                   const uint8_t* __restrict__ flag, int8_t* __restrict__ Xq,
+                                                                   int n_slabs, int8_t* __restrict__ tap_xq, int slab_blocks,
+                                                                   int clear_units, const PackOutliers o, const LoraArgs l, int lora_blocks,
+                                                                   int t_blocks, int splits, int steps_per_split, float* P) {
+  if ((int)blockIdx.x < lora_blocks)
+    lora_down_block<kTiles, kThreads / kWave>(l, blockIdx.x, t_blocks, splits, steps_per_split, P);
+  else
+    outlier_columns_block((int)blockIdx.x - lora_blocks, X, M, K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -749,7 +769,7 @@ bool prep_from_codes_fits(int K) { return packed_k(K) / 16 <= 16 * 16 * 4; }
 
 hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad, uint8_t* flag, float* r,
                        int8_t* Xq, int8_t* tap_xq, const PackOutliers& o, const CodedInput* coded, void* event_mid,
-                       hipStream_t stream) {
+                       hipStream_t stream, const LoraArgs* lora, float* lora_partial) {
   const int n_slabs = Kpad / kSlabBytes, n_pieces = Kpad / 16;
   const dim3 grid(ceil_div(M, 4));
   const CodedInput ci = coded ? *coded : CodedInput{};
@@ -786,6 +806,25 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
   const int few = max(16, round_up(ceil_div(row_groups * units, max(1, device_cu_count() / 4)), 4));
   const int clear_units = groups_256 <= 16 ? few : kThreads * merge;
   const int clear_blocks = row_groups * ceil_div(units, clear_units);
+  if (lora) {
+    const LoraPlan plan = plan_lora(lora->M, lora->K);
+    const int t_blocks = ceil_div(lora->M, kLoraRows);
+    const int lora_blocks = t_blocks * plan.splits + (lora->Wo ? ceil_div(lora->N * 4 * lora_slabs(lora->r), kThreads) : 0);
+#define MMD8_OUTLIER_LORA(T_)                                                                                                 \
+  hipLaunchKernelGGL(k_outlier_columns_lora<T_>, dim3(lora_blocks + slab_blocks + clear_blocks), dim3(kThreads), 0, stream, X, M, \
+                     K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o, *lora, lora_blocks, t_blocks, plan.splits,     \
+                     plan.steps_per_split, lora_partial)
+    switch (ceil_div(lora->r, 16)) {
+      case 1: MMD8_OUTLIER_LORA(1); break;
+      case 2: MMD8_OUTLIER_LORA(2); break;
+      case 3: MMD8_OUTLIER_LORA(3); break;
+      case 4: MMD8_OUTLIER_LORA(4); break;
+      default: return hipErrorInvalidValue;
+    }
+#undef MMD8_OUTLIER_LORA
+    e = hipGetLastError();
+    return e == hipSuccess ? launch_lora_reduce(*lora, plan, lora_partial, stream) : e;
+  }
   hipLaunchKernelGGL(k_outlier_columns, dim3(slab_blocks + clear_blocks), dim3(kThreads), 0, stream, X, M, K, ldx, flag, Xq,
                      n_slabs, tap_xq, slab_blocks, clear_units, o);
   return hipGetLastError();

@@ -386,10 +386,28 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   if (coded && !fused_decode &&
       launch_dequantize_blockwise(coded->codes, coded->absmax, (size_t)M * K, coded->block, X, st) != hipSuccess)
     return MMD8_E_HIP;
+  LoraArgs l = {};
+  if (lora) {
+    // T = f16(X A^T); for the tiled GEMM T and B also go into the fp16 slabs behind the critical columns
+    l.X = X;
+    l.M = M;
+    l.K = K;
+    l.ldx = ldx;
+    l.A = lora->A;
+    l.B = lora->B;
+    l.r = lora->r;
+    l.N = N;
+    l.T = ws.lora_t;
+    l.T_user = lora->T_out;
+    l.Xo = skinny ? nullptr : ws.xo;
+    l.Wo = skinny ? nullptr : ws.wo;
+    l.f_slabs = ws.f_slabs;
+    l.crit_slabs = ws.crit_slabs;
+  }
   if (one_pass) {
     // one pass over X: scales, flags and codes together, then the critical columns are cleared
     if (launch_prep(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, ws.xq, t.xq, po, fused_decode ? coded : nullptr,
-                    t.event_prep_mid, st) != hipSuccess)
+                    t.event_prep_mid, st, lora ? &l : nullptr, ws.lora_part) != hipSuccess)
       return MMD8_E_HIP;
   } else if (decode_prep) {
     if (launch_prep_rows(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, ws.xq, st) != hipSuccess) return MMD8_E_HIP;
@@ -409,25 +427,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
       hipMemcpyAsync(t.row_absmax, ws.r, (size_t)M * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
     return MMD8_E_HIP;
 
-  if (lora) {
-    // T = f16(X A^T); for the tiled GEMM T and B also go into the fp16 slabs behind the critical columns
-    LoraArgs l = {};
-    l.X = X;
-    l.M = M;
-    l.K = K;
-    l.ldx = ldx;
-    l.A = lora->A;
-    l.B = lora->B;
-    l.r = lora->r;
-    l.N = N;
-    l.T = ws.lora_t;
-    l.T_user = lora->T_out;
-    l.Xo = skinny ? nullptr : ws.xo;
-    l.Wo = skinny ? nullptr : ws.wo;
-    l.f_slabs = ws.f_slabs;
-    l.crit_slabs = ws.crit_slabs;
-    if (launch_lora_down(l, plan_lora(M, K), ws.lora_part, st) != hipSuccess) return MMD8_E_HIP;
-  }
+  if (lora && !one_pass && launch_lora_down(l, plan_lora(M, K), ws.lora_part, st) != hipSuccess) return MMD8_E_HIP;
 
   if (rows_path) {   // (a coded output: the encoder follows)
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;

@@ -2,6 +2,7 @@
 // blocks they share.  Each launcher is defined next to its kernels.
 #pragma once
 #include "common.h"
+#include "lora.h"
 
 namespace mmd8 {
 
@@ -72,6 +73,7 @@ bool prep_from_codes_fits(int K);   // likewise for launch_prep with coded activ
 // coded: null, or the blockwise-coded form of the activations (X is then written, not read).
 hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad, uint8_t* flag, float* r,
                        int8_t* Xq, int8_t* tap_xq, const PackOutliers& o, const CodedInput* coded, void* event_mid,
-                       hipStream_t stream);   // event_mid: null, or a hipEvent_t recorded between the two kernels
+                       hipStream_t stream,   // event_mid: null, or a hipEvent_t recorded between the two kernels
+                       const LoraArgs* lora = nullptr, float* lora_partial = nullptr);   // an adapter's down-projection along with it
 
 }  // namespace mmd8
