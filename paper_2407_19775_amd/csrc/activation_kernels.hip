@@ -808,12 +808,13 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
   const int clear_blocks = row_groups * ceil_div(units, clear_units);
   if (lora) {
     const LoraPlan plan = plan_lora(lora->M, lora->K);
+    if (plan.decode) return hipErrorInvalidValue;
     const int t_blocks = ceil_div(lora->M, kLoraRows);
     const int lora_blocks = t_blocks * plan.splits + (lora->Wo ? ceil_div(lora->N * 4 * lora_slabs(lora->r), kThreads) : 0);
 #define MMD8_OUTLIER_LORA(T_)                                                                                                 \
   hipLaunchKernelGGL(k_outlier_columns_lora<T_>, dim3(lora_blocks + slab_blocks + clear_blocks), dim3(kThreads), 0, stream, X, M, \
                      K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o, *lora, lora_blocks, t_blocks, plan.splits,     \
-                     plan.steps_per_split, lora_partial)
+                     plan.steps_per_split, plan.splits > 1 ? lora_partial : nullptr)
     switch (ceil_div(lora->r, 16)) {
       case 1: MMD8_OUTLIER_LORA(1); break;
       case 2: MMD8_OUTLIER_LORA(2); break;

@@ -448,10 +448,11 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
       g.ldr = exit->ldr;
     }
     if (lora) {
-      g.lora_T = ws.lora_t;
-      g.lora_ldt = kLoraMaxRank;
+      g.lora_P = ws.lora_part;
+      g.lora_splits = plan_lora(M, K).splits;
       g.lora_B = lora->B;
       g.lora_r = lora->r;
+      g.lora_T_user = lora->T_out;
     }
     g.X = X;
     g.ldx = ldx;
@@ -489,10 +490,11 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     g.ldx = ldx;
     g.K = K;
     if (lora) {
-      g.lora_T = ws.lora_t;
-      g.lora_ldt = kLoraMaxRank;
+      g.lora_P = ws.lora_part;
+      g.lora_splits = plan_lora(M, K).splits;
       g.lora_B = lora->B;
       g.lora_r = lora->r;
+      g.lora_T_user = lora->T_out;
     }
     if (launch_gemm_skinny(g, ws.decode_plan, st) != hipSuccess) return MMD8_E_HIP;
   } else {

@@ -25,9 +25,21 @@ struct LoraArgs {
 // how K is split between workgroups for this shape (depends on the device's CU count)
 struct LoraPlan {
   int splits, steps_per_split;   // ranges of K, each this many 64-column steps
-  size_t partial_bytes;          // fp32 [splits][M][kLoraMaxRank] when splits > 1
+  bool decode;                   // at most 128 rows: the ranges are left for sum_low_rank_activation
+  size_t partial_bytes;          // fp32 [splits][M][kLoraMaxRank] where they go through memory
 };
 LoraPlan plan_lora(int M, int K);
+// One value of T for the kernels that add the low-rank term themselves (at most 128 rows): the ranges' sums in index order,
+// rounded to fp16; fp16 bit pattern.  All loads are in flight together.
+constexpr int kLoraDecodeSplits = 16;
+__device__ __forceinline__ uint32_t sum_low_rank_activation(const float* __restrict__ P, int splits, int M, int m, int j) {
+  float v[kLoraDecodeSplits], sum = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kLoraDecodeSplits; ++s) v[s] = P[((size_t)min(s, splits - 1) * M + m) * kLoraMaxRank + j];
+#pragma unroll
+  for (int s = 0; s < kLoraDecodeSplits; ++s) sum += s < splits ? v[s] : 0.0f;
+  return float_to_half_bits(sum);
+}
 // T for every row (and, where Xo is given, T and B in the GEMM's slab layout)
 hipError_t launch_lora_down(const LoraArgs& a, const LoraPlan& plan, float* partial, hipStream_t stream);
 // its second kernel alone (nothing to do where K is not split)

@@ -13,9 +13,10 @@ constexpr int kLoraRows = 16;          // rows of X per workgroup
 // in a step lane l holds, for row (or rank index) l % 16, the 16 columns 16 (l / 16) .. + 16 as two
 // MFMA operands of 8 (which 8 columns meet in one MFMA does not matter: both operands use the same
 // assignment).  A^T is the first operand, X^T the second, so a lane ends up with four consecutive
-// rank indices of one row.  The waves' partial sums meet in LDS and are added in wave order; with one
-// range the sum is rounded and stored, with several it goes to P[range][m][64] as fp32 and k_lora_reduce
-// adds the ranges in index order (so the result does not depend on timing) and rounds.
+// rank indices of one row.  The waves' partial sums meet in LDS and are added in wave order; with P
+// null (one range) the sum is rounded and stored, else it goes to P[range][m][64] as fp32, and k_lora_reduce, or for at most
+// 128 rows the kernel that adds the low-rank term (sum_low_rank_activation), adds the ranges in index order (so the result
+// does not depend on timing) and rounds.
 // Workgroups from t_blocks * splits on copy B into the weight-side slabs.
 // eight sums of row m (rank indices 8 ch .. + 8; exact zeros past the rank): rounded to fp16 and stored as
 // part of T, of the caller's copy of T and of the activation-side slabs
@@ -113,7 +114,7 @@ __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, in
       }
     }
   }
-  if (splits > 1) {
+  if (P) {
     float* p = P + ((size_t)split * a.M + m) * kLoraMaxRank + j0;
     *reinterpret_cast<v4f*>(p) = v4f{sum[0], sum[1], sum[2], sum[3]};
     *reinterpret_cast<v4f*>(p + 4) = v4f{sum[4], sum[5], sum[6], sum[7]};

@@ -44,23 +44,28 @@ LoraPlan plan_lora(int M, int K) {
   // of a few microseconds, so the second kernel that adds the ranges must save more than that.  Then K is
   // split until there are two workgroups per compute unit, every range at least sixteen 64-column steps.
   const int t_blocks = ceil_div(M, kLoraRows), steps = ceil_div(K, 64), cus = device_cu_count();
+  // Up to 128 rows are a few tiles, and 16 rows and A through one compute unit take 4.5 us at K = 4096: there the ranges
+  // are short (four steps) and their sums are added by the kernel that needs them, without a launch in between (7B-shaped layer with rank 16:
+  // one row 74 -> 61.5 us, 32 rows 128 -> 112, 128 rows 198 -> 184; rank 64 at 64 rows 265 -> 179).
   LoraPlan p;
-  const int want = steps < 128 ? 1 : max(1, min(min(2 * cus / t_blocks, steps / 16), 32));
+  p.decode = M <= 128;
+  const int want = p.decode ? max(1, min(steps / 4, kLoraDecodeSplits)) : steps < 128 ? 1 : max(1, min(min(2 * cus / t_blocks, steps / 16), 32));
   p.steps_per_split = ceil_div(steps, want);
   p.splits = ceil_div(steps, p.steps_per_split);
-  p.partial_bytes = p.splits > 1 ? (size_t)p.splits * M * kLoraMaxRank * sizeof(float) : 0;
+  p.partial_bytes = p.splits > 1 || p.decode ? (size_t)p.splits * M * kLoraMaxRank * sizeof(float) : 0;
   return p;
 }
 
 hipError_t launch_lora_down(const LoraArgs& a, const LoraPlan& plan, float* partial, hipStream_t stream) {
   const int t_blocks = ceil_div(a.M, kLoraRows);
   const int b_blocks = a.Wo ? ceil_div(a.N * 4 * lora_slabs(a.r), kLoraThreads) : 0;
+  if (plan.decode && !partial) return hipErrorInvalidValue;
   const dim3 grid(t_blocks * plan.splits + b_blocks), block(kLoraThreads);
   switch (ceil_div(a.r, 16)) {
-    case 1: hipLaunchKernelGGL(k_lora_down<1>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, partial); break;
-    case 2: hipLaunchKernelGGL(k_lora_down<2>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, partial); break;
-    case 3: hipLaunchKernelGGL(k_lora_down<3>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, partial); break;
-    case 4: hipLaunchKernelGGL(k_lora_down<4>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, partial); break;
+    case 1: hipLaunchKernelGGL(k_lora_down<1>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, plan.splits > 1 || plan.decode ? partial : nullptr); break;
+    case 2: hipLaunchKernelGGL(k_lora_down<2>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, plan.splits > 1 || plan.decode ? partial : nullptr); break;
+    case 3: hipLaunchKernelGGL(k_lora_down<3>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, plan.splits > 1 || plan.decode ? partial : nullptr); break;
+    case 4: hipLaunchKernelGGL(k_lora_down<4>, grid, block, 0, stream, a, t_blocks, plan.splits, plan.steps_per_split, plan.splits > 1 || plan.decode ? partial : nullptr); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();
@@ -68,7 +73,7 @@ hipError_t launch_lora_down(const LoraArgs& a, const LoraPlan& plan, float* part
 }
 
 hipError_t launch_lora_reduce(const LoraArgs& a, const LoraPlan& plan, const float* partial, hipStream_t stream) {
-  if (plan.splits == 1) return hipSuccess;
+  if (plan.splits == 1 || plan.decode) return hipSuccess;
   hipLaunchKernelGGL(k_lora_reduce, dim3(ceil_div(a.M * 4 * lora_slabs(a.r), 256)), dim3(256), 0, stream, a, plan.splits, partial);
   return hipGetLastError();
 }

@@ -2,6 +2,7 @@
 #pragma once
 #include "common.h"
 #include "gemm.h"
+#include "lora.h"
 
 namespace mmd8 {
 
@@ -26,9 +27,10 @@ struct SkinnyArgs {
   float* partial;         // fp32 [splits][M][N]
   int32_t* tap_acc;       // [M][N] or null
   uint8_t* flag_reset;    // [Kpad] column flags: zeroed again by the last kernel of the call
-  const uint16_t* lora_T; // low-rank term T B^T added to the output: T [M][lora_ldt] fp16, B [N][lora_r] fp16
+  const float* lora_P;    // low-rank term T B^T added to the output: T as sums of lora_splits ranges (sum_low_rank_activation), B [N][lora_r] fp16
   const uint16_t* lora_B;
-  int lora_ldt, lora_r;   // lora_r == 0: none
+  int lora_splits, lora_r;   // lora_r == 0: none
+  uint16_t* lora_T_user;  // [M][lora_r] or null: receives T
   // The output with a residual added, H = f16(Y + residual), and / or leaving in blockwise-coded form (the rows
   // of this call as one flattened tensor of M N elements; Y, where given, is then contiguous: ldy == N).
   const uint16_t* residual;   // [M][ldr] fp16 or null

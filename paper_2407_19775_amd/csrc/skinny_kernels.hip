@@ -366,16 +366,25 @@ __device__ __forceinline__ void add_ranges(const float* __restrict__ p, int spli
 }
 
 // Y[m,n] = f16( sum_s partial[s][m][n] + bias[n] + sum_j T[m][j] B[n][j] ), splits added in index
-// order, then the bias, then the low-rank term (T: [M][ldt] fp16, B: [N][r] fp16, r a multiple of 8;
+// order, then the bias, then the low-rank term (T as sums P of ranges, B: [N][r] fp16, r a multiple of 8;
 // r == 0: no such term).  A row per blockIdx.y.
 __global__ __launch_bounds__(256) void k_skinny_finalize(const float* __restrict__ partial, int splits, int M, int N,
                                                          const uint16_t* __restrict__ bias,
-                                                         const uint16_t* __restrict__ T, int ldt,
-                                                         const uint16_t* __restrict__ B, int r,
+                                                         const float* __restrict__ P, int p_splits,
+                                                         const uint16_t* __restrict__ B, int r, uint16_t* __restrict__ T_user,
                                                          const uint16_t* residual /* may alias Y */, int ldr, int gelu,
                                                          uint16_t* Y, int ldy, uint8_t* flag_reset, int Kpad) {
   if (blockIdx.y == 0) reset_column_flags(flag_reset, Kpad);
   const int m = blockIdx.y, n = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  __shared__ __attribute__((aligned(16))) uint16_t s_T[kLoraMaxRank];
+  if (r > 0) {                                                       // this row of T
+    if ((int)threadIdx.x < r) {
+      const uint32_t t = sum_low_rank_activation(P, p_splits, M, m, threadIdx.x);
+      s_T[threadIdx.x] = (uint16_t)t;
+      if (T_user && blockIdx.x == 0) T_user[(size_t)m * r + threadIdx.x] = (uint16_t)t;
+    }
+    __syncthreads();
+  }
   if (n >= N) return;
   float sum[1];
   add_ranges<1>(partial + (size_t)m * N + n, splits, (size_t)M * N, sum);
@@ -384,7 +393,7 @@ __global__ __launch_bounds__(256) void k_skinny_finalize(const float* __restrict
   if (r > 0) {
     float low = 0.0f;
     for (int j = 0; j < r; j += 8) {
-      const v4u t = *reinterpret_cast<const v4u*>(T + (size_t)m * ldt + j);
+      const v4u t = *reinterpret_cast<const v4u*>(s_T + j);
       const v4u b = *reinterpret_cast<const v4u*>(B + (size_t)n * r + j);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -565,7 +574,7 @@ hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t 
     return launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, a.flag_reset, a.Kpad, stream);
   }
   hipLaunchKernelGGL(k_skinny_finalize, dim3(ceil_div(a.N, 256), a.M), dim3(256), 0, stream, a.partial, plan.splits,
-                     a.M, a.N, a.bias, a.lora_T, a.lora_ldt, a.lora_B, a.lora_r, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
+                     a.M, a.N, a.bias, a.lora_P, a.lora_splits, a.lora_B, a.lora_r, a.lora_T_user, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
                      a.flag_reset, a.Kpad);
   return hipGetLastError();
 }
@@ -601,6 +610,8 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
   __shared__ uint8_t s_any[MMD8_MAX_K / kSlabBytes];
   __shared__ uint32_t s_part[kM][WAVES];
   __shared__ float s_r[kM], s_scale[kM];
+  __shared__ __attribute__((aligned(16))) uint16_t s_T[kM][kLoraMaxRank];
+  static_assert(kM * kLoraMaxRank <= kRowsWaves * kWave, "a thread per value of T");
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   // the operand row / output column a lane stands for, and which 16-byte piece of the slab it holds
@@ -802,6 +813,12 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
     if (i0 + u < total) step(f[u]);
   if (mine == 0)
     for (int t = 0; t < tiles; ++t) leave_sums(t);                    // (fewer slabs than waves: zeros)
+  if ((int)threadIdx.x < M * a.lora_r) {                              // an adapter's T
+    const int m = (int)threadIdx.x / a.lora_r, j = (int)threadIdx.x % a.lora_r;
+    const uint32_t t = sum_low_rank_activation(a.lora_P, a.lora_splits, M, m, j);
+    s_T[m][j] = (uint16_t)t;
+    if (a.lora_T_user && blockIdx.x == 0) a.lora_T_user[threadIdx.x] = (uint16_t)t;
+  }
   __syncthreads();
 
   if (has_out) {
@@ -815,7 +832,7 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
     if (a.lora_r > 0) {                                               // the low-rank term, as k_skinny_finalize adds it
       float low = 0.0f;
       for (int j = 0; j < a.lora_r; j += 8) {
-        const v4u t = *reinterpret_cast<const v4u*>(a.lora_T + (size_t)out_m * a.lora_ldt + j);
+        const v4u t = *reinterpret_cast<const v4u*>(&s_T[out_m][j]);
         const v4u b = *reinterpret_cast<const v4u*>(a.lora_B + (size_t)out_n * a.lora_r + j);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
