@@ -81,6 +81,7 @@ struct Workspace {
   float* partial;      // split-K partial outputs, or null
   int gemm_splits;     // ranges of K of the tiled GEMM, 1: not split
   SkinnyPlan decode_plan;   // ranges of K of the decode kernels (at most 128 rows)
+  int pass_rows;       // rows per pass of the decode kernels: all of them where their partial outputs fit
   uint16_t* h;         // coded output only, where the encoder runs as a kernel of its own: [M][N] fp16
   size_t bytes;
 };
@@ -88,8 +89,9 @@ struct Workspace {
 static bool exit_fuses(int M, int K, int N, int block);
 // gathered_rows: room for further slabs of critical columns (not in the fixed-size static workspace)
 // split_k: room for the partial outputs of a tiled GEMM whose K is split
+// pass_rows: most rows whose partial outputs the decode kernels keep at a time
 static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_block = 0, bool gathered_rows = true,
-                       bool split_k = true) {
+                       bool split_k = true, int pass_rows = kSkinnyMaxM) {
   const size_t Kpad = packed_k(K), Mpad = packed_n(M), Npad = packed_n(N);
   Workspace w;
   size_t off = 0;
@@ -122,11 +124,13 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   w.xq = reinterpret_cast<int8_t*>(take(Mpad * Kpad));
   w.partial = nullptr;
   w.decode_plan = {};
+  w.pass_rows = 0;
   if (M > 0 && M <= kSkinnyMaxM) {
     w.decode_plan = plan_skinny(K, N);
     if (!split_k) w.decode_plan.splits = 1, w.decode_plan.slabs_per_split = w.decode_plan.n_slabs;
     // (the sums go through memory even when K is not split: what follows them is the work of the kernel that adds them)
-    w.partial = reinterpret_cast<float*>(take((size_t)w.decode_plan.splits * M * N * sizeof(float)));
+    w.pass_rows = M < pass_rows ? M : pass_rows;
+    w.partial = reinterpret_cast<float*>(take((size_t)w.decode_plan.splits * w.pass_rows * N * sizeof(float)));
   }
   if (w.gemm_splits > 1) w.partial = reinterpret_cast<float*>(take((size_t)w.gemm_splits * M * N * sizeof(float)));
   w.lora_t = r > 0 ? reinterpret_cast<uint16_t*>(take((size_t)M * kLoraMaxRank * 2)) : nullptr;
@@ -150,6 +154,8 @@ static Workspace fit(void* base, size_t have, int M, int K, int N, int r, int ex
   if (w.bytes > have) w = carve(base, M, K, N, r, exit_block, true, false);
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, true);
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, false);
+  // (128 x 8192 x 57344: the partial outputs of all rows are 29 MB)
+  if (w.bytes > have && may_drop_slabs && M <= kSkinnyMaxM) w = carve(base, M, K, N, r, exit_block, false, false, 64);
   return w;
 }
 // What a caller is told to bring for up to M rows.  A call of fewer rows has fewer codes and slabs, but it may be one
@@ -347,7 +353,8 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
                (lora->T_out && !aligned(lora->T_out, 16))))
     return MMD8_E_ARG;
   const Workspace ws = fit(workspace, workspace_bytes, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, may_drop_slabs);
-  if (workspace_bytes < ws.bytes) return MMD8_E_WORKSPACE;
+  // (several passes: the fixed-size workspace only, whose entry point has neither adapter nor residual nor codes)
+  if (workspace_bytes < ws.bytes || (ws.pass_rows > 0 && ws.pass_rows < M && (lora || exit))) return MMD8_E_WORKSPACE;
   // a coded output is written by the layer's last kernel where that is possible, otherwise by the encoder after it
   const bool encodes = exit && exit->block > 0;
   const bool exit_fused = encodes && exit_fuses(M, K, N, exit->block);
@@ -461,42 +468,45 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     if (launch_gemm_rows(g, st) != hipSuccess) return MMD8_E_HIP;
   } else if (skinny) {
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
-    SkinnyArgs g = {};
-    g.Xq = ws.xq;
-    g.Wt = Wq_packed;
-    g.mask = ws.flag;
-    g.M = M;
-    g.N = N;
-    g.Kpad = Kpad;
-    g.r = ws.r;
-    g.c = col_absmax;
-    g.bias = bias;
-    g.Y = Y;
-    g.ldy = ldy;
-    if (exit) {
-      g.residual = exit->residual;
-      g.ldr = exit->ldr;
-      if (exit_fused) {
-        g.codes = exit->codes;
-        g.code_absmax = exit->absmax;
-        g.code_block = exit->block;
+    for (int row0 = 0; row0 < M; row0 += ws.pass_rows) {
+      const int rows = M - row0 < ws.pass_rows ? M - row0 : ws.pass_rows;
+      SkinnyArgs g = {};
+      g.Xq = ws.xq + (size_t)row0 * kSlabBytes;              // (a panel's rows: 64 bytes each in every slab)
+      g.Wt = Wq_packed;
+      g.mask = ws.flag;
+      g.M = rows;
+      g.N = N;
+      g.Kpad = Kpad;
+      g.r = ws.r + row0;
+      g.c = col_absmax;
+      g.bias = bias;
+      g.Y = Y ? Y + (size_t)row0 * ldy : nullptr;
+      g.ldy = ldy;
+      if (exit) {
+        g.residual = exit->residual;
+        g.ldr = exit->ldr;
+        if (exit_fused) {
+          g.codes = exit->codes;
+          g.code_absmax = exit->absmax;
+          g.code_block = exit->block;
+        }
       }
+      g.gelu = gelu ? 1 : 0;
+      g.partial = ws.partial;
+      g.tap_acc = t.acc ? t.acc + (size_t)row0 * N : nullptr;
+      g.flag_reset = row0 + rows == M ? ws.flag : nullptr;
+      g.X = X + (size_t)row0 * ldx;
+      g.ldx = ldx;
+      g.K = K;
+      if (lora) {
+        g.lora_P = ws.lora_part;
+        g.lora_splits = plan_lora(M, K).splits;
+        g.lora_B = lora->B;
+        g.lora_r = lora->r;
+        g.lora_T_user = lora->T_out;
+      }
+      if (launch_gemm_skinny(g, ws.decode_plan, st) != hipSuccess) return MMD8_E_HIP;
     }
-    g.gelu = gelu ? 1 : 0;
-    g.partial = ws.partial;
-    g.tap_acc = t.acc;
-    g.flag_reset = ws.flag;
-    g.X = X;
-    g.ldx = ldx;
-    g.K = K;
-    if (lora) {
-      g.lora_P = ws.lora_part;
-      g.lora_splits = plan_lora(M, K).splits;
-      g.lora_B = lora->B;
-      g.lora_r = lora->r;
-      g.lora_T_user = lora->T_out;
-    }
-    if (launch_gemm_skinny(g, ws.decode_plan, st) != hipSuccess) return MMD8_E_HIP;
   } else {
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
     GemmArgs g = {};
