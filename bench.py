@@ -33,8 +33,8 @@ INT8_POWER_LIMITED_TOPS = 3468.0
 # (70B-shaped layer, 4096 tokens) and the 7B-shaped step.  Valid for the GEMM source they were measured on:
 # reported as null once that file has changed.
 GEMM_TRAFFIC_BYTES_PER_LAUNCH = 1185.3e6
-GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 182.8e6
-GEMM_TRAFFIC_SOURCE_SHA256 = "2e7e74ac7976a1b60842d4b51b17c4176509de018f1bbdb1187d20cbc5e20b33"
+GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 184.4e6
+GEMM_TRAFFIC_SOURCE_SHA256 = "85e03bf36f3837d3368eef5e76465b69b79360cfe266c5c6f340d43ef7694b52"
 
 
 def parse():
