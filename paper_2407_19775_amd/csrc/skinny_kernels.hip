@@ -603,6 +603,7 @@ hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t 
 // kM: rows, at most (1, 2, 4, 8).  kChunks: 8-column chunks of the rows per thread (a number the compiler knows, so that
 // they are loaded all together: a load under a condition is waited for before the next one is issued).
 // ------------------------------------------------------------------------------------------------
+constexpr int kRowsCodePad = 64, kRowsHalfPad = 72;   // bytes, halves (multiples of 16 bytes)
 template <int kM, int kChunks>
 __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyArgs a) {
   constexpr int WAVES = kRowsWaves, kThreads = WAVES * kWave, kAhead = 3;
@@ -620,9 +621,13 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
   const int M = kM == 1 ? 1 : a.M;
   reset_column_flags(a.flag_reset, Kpad);
   const int row_chunks = Kpad / 8, all_chunks = M * row_chunks;
-  int8_t* s_code = s_ops;                                            // [M][Kpad]
-  uint16_t* s_xf = reinterpret_cast<uint16_t*>(s_ops + (size_t)M * Kpad);    // [M][Kpad]
-  uint8_t* s_over = reinterpret_cast<uint8_t*>(s_xf + (size_t)M * Kpad);     // [all_chunks]: bits "at or above the threshold" (kM > 1)
+  // (rows a little further apart than they are long: a fragment read takes the same piece of every row, and rows whose
+  // distance is a multiple of 256 bytes keep it in the same banks: 57 % of the LDS cycles at eight rows, 4096 -> 4096 14.2 us,
+  // 11.7 now)
+  const int code_row = Kpad + kRowsCodePad, xf_row = Kpad + kRowsHalfPad;
+  int8_t* s_code = s_ops;                                            // [M][code_row]
+  uint16_t* s_xf = reinterpret_cast<uint16_t*>(s_ops + (size_t)M * code_row);    // [M][xf_row]
+  uint8_t* s_over = reinterpret_cast<uint8_t*>(s_xf + (size_t)M * xf_row);     // [all_chunks]: bits "at or above the threshold" (kM > 1)
   int32_t* s_sum = reinterpret_cast<int32_t*>(s_over + (kM > 1 ? round_up(all_chunks, 16) : 0));   // [tile][int / float][wave][M][16]
   const int tile_words = 2 * WAVES * M * 16;
 
@@ -746,8 +751,8 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
         for (int w = 0; w < 2; ++w)
           xf[2 * q + w] = raw[i][2 * q + w] & __builtin_amdgcn_perm(0u, mask[q], w ? 0x03030202u : 0x01010000u);
       }
-      *reinterpret_cast<v2u*>(s_code + (size_t)m * Kpad + k) = v2u{code[0], code[1]};
-      *reinterpret_cast<v4u*>(s_xf + (size_t)m * Kpad + k) = v4u{xf[0], xf[1], xf[2], xf[3]};
+      *reinterpret_cast<v2u*>(s_code + (size_t)m * code_row + k) = v2u{code[0], code[1]};
+      *reinterpret_cast<v4u*>(s_xf + (size_t)m * xf_row + k) = v4u{xf[0], xf[1], xf[2], xf[3]};
       if (crit) s_any[k >> 6] = 1;
     }
   }
@@ -758,8 +763,8 @@ __global__ __launch_bounds__(kRowsWaves * kWave) void k_gemm_rows(const SkinnyAr
   v4f accf = v4f{0.0f, 0.0f, 0.0f, 0.0f};
   const bool row_live = lr < M;
   const int row = row_live ? lr : 0;                                  // lanes beyond M read row 0 and feed zeros
-  const int8_t* my_code = s_code + (size_t)row * Kpad + lg * 16;
-  const uint16_t* my_xf = s_xf + (size_t)row * Kpad + lg * 16;
+  const int8_t* my_code = s_code + (size_t)row * code_row + lg * 16;
+  const uint16_t* my_xf = s_xf + (size_t)row * xf_row + lg * 16;
   // "slab holds a critical column", this wave's slabs
   const uint64_t any_mask = __builtin_amdgcn_ballot_w64(lane < mine && s_any[min(wave + WAVES * lane, n_slabs - 1)] != 0);
   int tile = 0, i_slab = 0;
@@ -852,7 +857,7 @@ constexpr int kRowsMaxChunks = 6;   // of the largest instantiation
 
 // dynamic LDS of a call whose workgroups have `tiles` tiles each
 static size_t rows_lds_bytes(int M, int Kpad, int tiles) {
-  return (size_t)3 * M * Kpad + (M > 1 ? round_up(M * Kpad / 8, 16) : 0) + (size_t)tiles * 2 * kRowsWaves * M * 16 * 4;
+  return (size_t)M * (3 * Kpad + kRowsCodePad + 2 * kRowsHalfPad) + (M > 1 ? round_up(M * Kpad / 8, 16) : 0) + (size_t)tiles * 2 * kRowsWaves * M * 16 * 4;
 }
 // most tiles a workgroup can have: their sums in LDS, an output per thread
 static int rows_tiles_max(int M, int Kpad) {
