@@ -35,7 +35,7 @@ typedef short ss2 __attribute__((ext_vector_type(2)));
 // columns are critical is decided on the weight side: a weight code goes into the int8 product where its column is not
 // critical and into the fp16 product, as an integer, where it is (masks of 256 slabs at a time in LDS, a byte per column), so
 // the preparation need not know the critical columns when it writes the codes: one pass over X, no fp16 copy.  (Entries of
-// other columns are below the threshold, hence finite: zero times them is zero.)
+// other columns are below the threshold, hence finite, and so is what stands in for the padding of K: zero times them is zero.)
 // A wave owns 64 columns: of all rows and one of the slab's two k-steps (up to 64 rows; the two halves are added in
 // LDS at the end), or of 64 rows and both k-steps (128 rows).  64 x 64 accumulators per wave keep the LDS reads below what
 // the fills take: with 32 columns per wave a slab's activation side was read twice as often, and 64 rows took 0.8 us per slab.
@@ -132,9 +132,9 @@ __global__ __launch_bounds__(DecodeCfg<kBM>::kThreads) void k_gemm_decode(const 
   auto request = [&](int s, int stage, int d, auto whole_tag) __attribute__((always_inline)) {
     const int8_t* p = src[d];
     if (!decltype(whole_tag)::value && s >= whole_slabs && step[d] != kBlockBytes) {
-      // columns beyond K (a multiple of 16): the row's last piece in their place, their weights are zero
-      const int over = s * kSlabBytes + row_piece[d] - (a.K - 8);
-      p -= over > 0 ? 2 * over : 0;
+      // columns beyond K (a multiple of 16): column flags in their place, as halves finite numbers; their weights are zero
+      // (entries of X would not do: a critical one may be infinite)
+      if (s * kSlabBytes + row_piece[d] >= a.K) p = reinterpret_cast<const int8_t*>(a.mask);
     }
     const uint32_t dst = lds0 + stage * Cfg::kStage + (8 * d + wave) * 1024;
     if (8 * d * 1024 >= Cfg::kCodes + Cfg::kRows) dma16_once(p, dst);   // (weights, whichever wave)

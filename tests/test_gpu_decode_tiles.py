@@ -48,3 +48,21 @@ def test_range_longer_than_the_masks(M):
     assert np.array_equal(to_np(t["acc"]), o["acc"])
     assert_y_close(to_np(out), o["Y"])
     assert_y_close(to_np(Y), o["Y"])
+
+
+@pytest.mark.parametrize("M,K,N", [(9, 4112, 72), (33, 1072, 264), (100, 2096, 72), (128, 16, 8)])
+def test_an_infinite_last_column_stays_infinite(M, K, N):
+    """K is no multiple of the padded length: what stands in for the columns beyond it meets weights of zero and must be finite.
+    Row 2 has an infinity among its last eight entries: its outputs are infinite with the sign of the weight (not a number where
+    the weight is zero), the other rows are what they are without it."""
+    X, W = inputs(M, K, N)
+    W[K - 3] = np.where(W[K - 3] == 0, np.float16(0.01), W[K - 3])
+    X[2, K - 3] = np.inf
+    pw, Wq = binding.prequantize_weight(to_gpu(W)), ml.prequantize_weight(W)
+    Y = to_np(binding.mixed_int8_linear(to_gpu(X), pw, wl.TAU))
+    q = Wq[0][K - 3].astype(np.float32)
+    want = np.where(q == 0, np.float32(np.nan), np.copysign(np.float32(np.inf), q))
+    assert np.array_equal(Y[2].astype(np.float32), want, equal_nan=True)
+    rest = np.arange(M) != 2
+    X[2, K - 3] = 30.0                                              # (critical as before)
+    assert_y_close(Y[rest], ml.mixed_int8_linear(X, *Wq, wl.TAU)["Y"][rest])
