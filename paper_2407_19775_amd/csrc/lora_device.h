@@ -32,6 +32,12 @@ __device__ inline void store_low_rank_activation(const LoraArgs& a, int m, int c
     *reinterpret_cast<v4u*>(reinterpret_cast<int8_t*>(a.Xo) + packed_chunk_offset(m, a.crit_slabs + ch / 4, ch % 4, a.f_slabs)) = v;
 }
 
+// What lane group kq reads in 64-column step s of a range that ends at step `end`: 16 columns, lora_lane_column + lora_step_column
+// on.  A group beyond the range or the end of the row (lora_reads false) masks what it reads, and that is within the row too.
+__host__ __device__ __forceinline__ bool lora_reads(int s, int end, int kq, int K) { return s < end && 64 * s + 16 * kq < K; }
+__host__ __device__ __forceinline__ int lora_lane_column(int kq, int K) { return 16 * kq < K ? 16 * kq : K - 16; }
+__host__ __device__ __forceinline__ int lora_step_column(int s, bool reads) { return reads ? 64 * s : 0; }
+
 // kTiles: 16-wide tiles of the rank, ceil(r / 16).  Called by every thread of a workgroup of kWaves waves.
 template <int kTiles, int kWaves>
 __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, int t_blocks, int splits, int steps_per_split, float* __restrict__ P) {
@@ -51,14 +57,15 @@ __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, in
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int m0 = (block % t_blocks) * kLoraRows, split = block / t_blocks;
   const int li = lane & 15, kq = lane >> 4;
-  const uint16_t* xrow = a.X + (size_t)min(m0 + li, a.M - 1) * a.ldx + 16 * kq;
+  const int lane_column = lora_lane_column(kq, a.K);
+  const uint16_t* xrow = a.X + (size_t)min(m0 + li, a.M - 1) * a.ldx + lane_column;
   const uint16_t* arow[kTiles];
   bool jvalid[kTiles];
 #pragma unroll
   for (int t = 0; t < kTiles; ++t) {
     const int j = 16 * t + li;
     jvalid[t] = j < a.r;
-    arow[t] = a.A + (size_t)min(j, a.r - 1) * a.K + 16 * kq;
+    arow[t] = a.A + (size_t)min(j, a.r - 1) * a.K + lane_column;
   }
   v4f acc[kTiles];
 #pragma unroll
@@ -72,8 +79,8 @@ __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, in
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int s = s0 + u * kWaves;
-      const bool ok = s < steps && 64 * s + 16 * kq < a.K;
-      const int k = ok ? 64 * s : 0;
+      const bool ok = lora_reads(s, steps, kq, a.K);
+      const int k = lora_step_column(s, ok);
       const uint32_t keep = ok ? 0xffffffffu : 0u;
 #pragma unroll
       for (int h = 0; h < 2; ++h) xf[u][h] = *reinterpret_cast<const v4u*>(xrow + k + 8 * h) & keep;

@@ -39,6 +39,9 @@ __global__ __launch_bounds__(256) void k_lora_reduce(const LoraArgs a, int split
 }
 }  // namespace
 
+// the host's view of the down-projection's reads: first of the 16 columns
+int lora_read_column(int s, int end, int kq, int K) { return lora_lane_column(kq, K) + lora_step_column(s, lora_reads(s, end, kq, K)); }
+
 LoraPlan plan_lora(int M, int K) {
   // One range of K per 16-row tile unless K is long (8192 columns or more): every kernel here has a floor
   // of a few microseconds, so the second kernel that adds the ranges must save more than that.  Then K is

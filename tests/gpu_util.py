@@ -51,3 +51,10 @@ def critical_column_plan(M: int, K: int, N: int, splits: int = None):
     f.argtypes, f.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_bool, ctypes.c_int], CriticalPlan
     p = f(M, (K + 127) // 128 * 2, (N + 255) // 256 * 256, True, splits or gemm_splits(M, K, N))
     return 32 * (8 + p.g_slabs), max(257, p.dense_from)          # (never for what the first eight slabs hold)
+
+
+def lora_read_column(s: int, end: int, kq: int, K: int) -> int:
+    """First of the 16 columns that a lane group of the adapter's down-projection reads (a C++ function of the library)."""
+    f = binding.lib()._ZN4mmd816lora_read_columnEiiii
+    f.argtypes, f.restype = [ctypes.c_int] * 4, ctypes.c_int
+    return f(s, end, kq, K)

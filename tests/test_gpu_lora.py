@@ -129,6 +129,12 @@ def test_dense_pass_next_to_the_adapter(variant):
     check_lora(X, wl.gaussian_weight(K, N, 0.02, rng), A, B, 6.0, tuning=binding.tune_gemm_tiles(variant))
 
 
+@pytest.mark.parametrize("M", [3, 40, 130])
+@pytest.mark.parametrize("K", [16, 32, 48])
+def test_rows_shorter_than_a_step(M, K):
+    check_lora(*rand_case(K, M, K, 72, 24, std=0.2), 6.0)
+
+
 @pytest.mark.parametrize("M", [1, 64])
 @pytest.mark.parametrize("shape", wl.LLAMA_7B_LINEARS, ids=lambda s: s.name)
 def test_decode_shapes(M, shape):

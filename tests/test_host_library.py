@@ -9,7 +9,7 @@ import pytest
 
 from oracle import dynamic_code as dc
 from paper_2407_19775_amd import binding
-from gpu_util import critical_column_plan
+from gpu_util import critical_column_plan, lora_read_column
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -190,6 +190,20 @@ def test_adapter_arguments_are_rejected_before_any_launch():
     assert call(A=odd) == -1 and call(T=odd) == -1
     assert call(K=100) == -2
     assert call(wsb=L.mmd8_linear_workspace_bytes(8, 128, 64)) == -3               # sized without the adapter
+
+
+@pytest.mark.parametrize("K", [16, 32, 48, 64, 80, 112, 128, 1040])
+def test_the_adapter_reads_within_its_rows(K):
+    """Whatever the step of the loop (it is unrolled past the end) and the lane group: 16 columns of the row, and every
+    column of it in the one group whose they are."""
+    steps = -(-K // 64)
+    for begin in range(steps):
+        for s in range(begin, steps + 128):
+            for kq in range(4):
+                col = lora_read_column(s, steps, kq, K)
+                assert 0 <= col <= K - 16
+                if s < steps and 64 * s + 16 * kq < K:
+                    assert col == 64 * s + 16 * kq
 
 
 def test_coded_output_arguments_are_rejected_before_any_launch():
