@@ -176,12 +176,11 @@ static size_t workspace_bytes_for(int M, int K, int N, int r = 0, int exit_block
 }
 // A coded output is produced by the kernel that ends the layer when no block of it is shared between
 // workgroups: the tiled GEMM needs blocks inside its 256-column tiles; the decode path encodes where it sums
-// its partial outputs, all rows of the call as one tensor, any block size (128 x 4096 -> 4104 in blocks of 4096: 34.8 us,
-// with the encoder after it 41.7).  The first few rows are a single kernel with nothing to sum afterwards: the encoder
-// follows it.
+// its partial outputs, any block size, as long as its second pass of 64 rows starts on a block boundary.  The
+// first few rows are a single kernel with nothing to sum afterwards: the encoder follows it.
 static bool exit_fuses(int M, int K, int N, int block) {
   if (rows_kernel_fits(M, packed_k(K), N)) return false;
-  if (M <= kSkinnyMaxM) return true;
+  if (M <= kSkinnyMaxM) return M <= 64 || ((size_t)64 * N) % block == 0;
   return (block == 64 || block == 128 || block == 256) && N % block == 0;
 }
 

@@ -105,7 +105,7 @@ def test_decode_path_encodes_where_it_sums(M, K, N, block, residual):
     run_and_check(X, W, b, R, block, want_h=N % 3 != 0, pad_r=16 if M % 2 else 0)
 
 
-# 65 to 128 rows whose row 64 does not start on a block boundary: all rows are one tensor to the encoding kernel
+# 65 to 128 rows whose second pass of 64 rows does not start on a block boundary: encoder afterwards
 @pytest.mark.parametrize("M,K,N,block", [(100, 528, 520, 4096), (128, 64, 72, 1024)])
 def test_decode_path_with_the_encoder_after_it(M, K, N, block):
     X, W, b, R = make_case(M, K, N, block)

@@ -120,13 +120,6 @@ def test_a_workspace_for_more_rows_serves_fewer(K, N):
         assert sizes == sorted(sizes)
 
 
-@pytest.mark.parametrize("M,K,N,block", [(65, 528, 520, 4096), (100, 11008, 4104, 4096), (128, 64, 72, 1024), (64, 528, 520, 4096)])
-def test_a_coded_output_up_to_128_rows_takes_no_room_of_its_own(M, K, N, block):
-    """Whether or not row 64 starts on a block boundary: the kernel that adds the partial outputs encodes them."""
-    L = binding.lib()
-    assert L.mmd8_linear_to_codes_workspace_bytes(M, K, N, block) == L.mmd8_linear_workspace_bytes(M, K, N)
-
-
 @pytest.mark.parametrize("M,K,N,at,walk", [(1576, 1024, 3072, 717, False), (1576, 1024, 3072, 922, True), (2048, 1024, 4096, 819, False),
                                            (2048, 1024, 4096, 922, True), (256, 4096, 12288, 410, False), (256, 4096, 12288, 819, True),
                                            (256, 11008, 4096, 440, False), (256, 11008, 4096, 1101, True), (140, 32768, 1024, 655, True),
