@@ -171,11 +171,12 @@ int mmd8_mixed_int8_linear(const mmd8_half* X /*DEVICE*/, int M, int K, int ldx,
  * and errors, without the workspace: the library's own device array of MMD8_STATIC_WORKSPACE_BYTES serves as one
  * (every GPU the library runs on holds it until the process ends; that is enough for up to 64 rows of every
  * Llama-7B- and 70B-shaped linear).  The array takes the layout of a workspace of
- * mmd8_linear_workspace_bytes(M, K, N) bytes or, where that does not fit, the first of these that does: the same
- * without the sums of a split K (more than 128 rows, few tiles); without the slabs in which calls of more than 128
- * rows gather the critical columns beyond the first 256 (those are then gathered tile by tile); without both.
- * Without the sums of a split, or without the slabs for an input that has so many critical columns, an output may
- * differ from the other entry point's in its last bit; all integers are the same.  A problem that does not fit in
+ * mmd8_linear_workspace_bytes(M, K, N) bytes or, where that does not fit, the first of these that does.  Up to 128
+ * rows: two passes of at most 64 rows (long K only); all rows without the sums of a split K; both.  More than 128 rows: without the
+ * sums of a split K (few tiles); without the slabs in which the critical columns beyond the first 256 are gathered
+ * (those are then gathered tile by tile); without both.
+ * In two passes, without the sums of a split, or without the slabs for an input that has so many critical columns, an
+ * output may differ from the other entry point's in its last bit; all integers are the same.  A problem that does not fit in
  * any of these ways returns MMD8_E_WORKSPACE and launches nothing.  The call allocates and frees nothing and
  * synchronises nothing; the first call on a device looks up the array's address and sets kernel attributes (make
  * it before a capture starts).  All calls on one GPU share the one array: calls that overlap in time (two streams,

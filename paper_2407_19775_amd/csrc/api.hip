@@ -146,17 +146,29 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
 }
 // The layout of a call in a workspace of `have` bytes: with room for the sums of a split K where that fits, else
 // without (what a workspace held before K was ever split still serves); may_drop_slabs (the fixed-size array): then
-// likewise without the further slabs.  The slabs go last: 200 x 4096 x 4096 in 32 MiB, which hold one of the two, takes
-// 58 us with them and 100 with the split when 15 % of the columns are critical; 30.5 and 30.0 us when few are.
+// likewise without the further slabs, and up to 128 rows in two passes.  The slabs go last: 200 x 4096 x 4096 in 32 MiB,
+// which hold one of the two, takes 58 us with them and 100 with the split when 15 % of the columns are critical; 30.5 and
+// 30.0 us when few are.
 // bytes > have: it fits in none of these ways.
 static Workspace fit(void* base, size_t have, int M, int K, int N, int r, int exit_block, bool may_drop_slabs) {
   Workspace w = carve(base, M, K, N, r, exit_block);
+  // 64 rows at a time, K split as ever, or all rows at once with K in one range: the weights twice, or a workgroup's walk
+  // longer by so many slabs.  128 rows, with K split in two 2048 -> 30720 (16 more) 58 and 55 us, 3072 -> 30720 (24) 68 and 71,
+  // 6144 -> 30720 (48) 101 and 116; in three 2048 -> 21504 (21) 51 and 51, 4096 -> 20480 (42) 62 and 79; in six 36864 -> 8192
+  // (480) 183 and 549.
+  if (w.bytes > have && may_drop_slabs && M <= kSkinnyMaxM && w.decode_plan.n_slabs - w.decode_plan.slabs_per_split > 20)
+    w = carve(base, M, K, N, r, exit_block, false, true, 64);
   if (w.bytes > have) w = carve(base, M, K, N, r, exit_block, true, false);
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, true);
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, false);
-  // (128 x 8192 x 57344: the partial outputs of all rows are 29 MB)
   if (w.bytes > have && may_drop_slabs && M <= kSkinnyMaxM) w = carve(base, M, K, N, r, exit_block, false, false, 64);
   return w;
+}
+// How the decode kernels (at most 128 rows) run in the fixed-size array; the host's view of the choice above.
+struct StaticDecode { int splits, pass_rows; };
+StaticDecode plan_static_decode(int M, int K, int N) {
+  const Workspace w = fit(nullptr, MMD8_STATIC_WORKSPACE_BYTES, M, K, N, 0, 0, true);
+  return {w.decode_plan.splits, w.pass_rows};
 }
 // What a caller is told to bring for up to M rows.  A call of fewer rows has fewer codes and slabs, but it may be one
 // whose K is split where that of M rows is not: room for the sums of any of them (at most 32 MB on 256 compute units),

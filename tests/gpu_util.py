@@ -58,3 +58,14 @@ def lora_read_column(s: int, end: int, kq: int, K: int) -> int:
     f = binding.lib()._ZN4mmd816lora_read_columnEiiii
     f.argtypes, f.restype = [ctypes.c_int] * 4, ctypes.c_int
     return f(s, end, kq, K)
+
+
+def static_decode_plan(M: int, K: int, N: int):
+    """Ranges of K and rows per pass of the decode kernels in the array of the entry point without a workspace (a C++ function
+    of the library)."""
+    class Plan(ctypes.Structure):
+        _fields_ = [("splits", ctypes.c_int), ("pass_rows", ctypes.c_int)]
+    f = binding.lib()._ZN4mmd818plan_static_decodeEiii
+    f.argtypes, f.restype = [ctypes.c_int] * 3, Plan
+    p = f(M, K, N)
+    return p.splits, p.pass_rows
