@@ -149,8 +149,8 @@ typedef struct {
  * Workspace protocol: a workspace is set up once with mmd8_linear_workspace_init (it zeroes a
  * small head of counters and column flags; everything else may hold anything).  Every call
  * leaves the head zeroed again, so the same workspace serves any number of calls of any shape
- * that fits, one after the other on one stream.  A size given for M rows does not fall with M from 129 rows on, and
- * a workspace of that size serves calls of 129 to M rows with the results, bit for bit, of one sized for them.  (A
+ * that fits, one after the other on one stream.  A size given for M rows does not fall with M, and a workspace of
+ * that size serves calls of up to M rows with the results, bit for bit, of one sized for them.  (A
  * smaller workspace that has no room for the sums of a split K, and is not too small otherwise, serves as well: K is
  * then not split, and an output may differ in its last bit.)  Two calls must not use one workspace at the
  * same time.  After a call that returned MMD8_E_HIP, set the workspace up again.

@@ -140,7 +140,9 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
     if (lb) w.lora_part = reinterpret_cast<float*>(take(lb));
   }
   w.h = nullptr;
-  if (exit_block > 0 && M > 0 && !exit_fuses(M, K, N, exit_block)) w.h = reinterpret_cast<uint16_t*>(take((size_t)M * N * 2));
+  // (a layer that is a single kernel has no partial outputs: their place)
+  if (exit_block > 0 && M > 0 && !exit_fuses(M, K, N, exit_block))
+    w.h = rows_kernel_fits(M, (int)Kpad, N) ? reinterpret_cast<uint16_t*>(w.partial) : reinterpret_cast<uint16_t*>(take((size_t)M * N * 2));
   w.bytes = off;
   return w;
 }
@@ -367,11 +369,6 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   const Workspace ws = fit(workspace, workspace_bytes, M, K, N, lora ? lora->r : 0, exit ? exit->block : 0, may_drop_slabs);
   // (several passes: the fixed-size workspace only, whose entry point has neither adapter nor residual nor codes)
   if (workspace_bytes < ws.bytes || (ws.pass_rows > 0 && ws.pass_rows < M && (lora || exit))) return MMD8_E_WORKSPACE;
-  // a coded output is written by the layer's last kernel where that is possible, otherwise by the encoder after it
-  const bool encodes = exit && exit->block > 0;
-  const bool exit_fused = encodes && exit_fuses(M, K, N, exit->block);
-  if (encodes && !exit_fused && !Y) Y = ws.h;
-
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int Kpad = packed_k(K);
   const mmd8_debug_taps none = {};
@@ -396,6 +393,11 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   // preparation are asked for, the scan and pack kernels run ahead of it for their sake only.
   // (alternative readings: always the separate scan and pack kernels, which is where they differ)
   const bool rows_path = !readings && !(t.tuning & MMD8_TUNE_NO_ROWS_KERNEL) && rows_kernel_fits(M, Kpad, N);
+  // a coded output is written by the layer's last kernel where that is possible, otherwise by the encoder after it (whose
+  // buffer is the place of the partial outputs where the layer would be a single kernel)
+  const bool encodes = exit && exit->block > 0;
+  const bool exit_fused = encodes && (exit_fuses(M, K, N, exit->block) || (skinny && !rows_path && M <= 64));
+  if (encodes && !exit_fused && !Y) Y = ws.h;
   // The decode kernels' preparation in one kernel (the separate ones leave codes that serve as well).
   const bool decode_prep = skinny && !rows_path && !wants_prep_taps && !(t.tuning & MMD8_TUNE_SEPARATE_PREP) && !readings;
   // coded activations are decoded by the one-pass preparation kernel itself where that kernel runs

@@ -105,6 +105,22 @@ def test_decode_path_encodes_where_it_sums(M, K, N, block, residual):
     run_and_check(X, W, b, R, block, want_h=N % 3 != 0, pad_r=16 if M % 2 else 0)
 
 
+# a few rows: the encoder behind the single kernel, its buffer in the place of the partial outputs, or (the single kernel left
+# out) encoded where these are added
+@pytest.mark.parametrize("M,K,N,block", [(1, 64, 72, 64), (4, 4096, 520, 4096), (8, 128, 1024, 256)])
+@pytest.mark.parametrize("tuning", [0, binding.TUNE_NO_ROWS_KERNEL])
+def test_a_few_rows_single_kernel_and_partial_outputs(M, K, N, block, tuning):
+    X, W, b, R = make_case(M, K, N, block, heavy=True)
+    run_and_check(X, W, b, R, block, want_h=False, tuning=tuning)
+    # likewise in a workspace made for one more row
+    pw, Xg, Rg, bg = binding.prequantize_weight(to_gpu(W)), to_gpu(X), to_gpu(R), to_gpu(b)
+    ws = binding.linear_workspace(M + 1, K, N, Xg.device, exit_block=block)
+    got = binding.mixed_int8_linear_to_codes(Xg, pw, wl.TAU, block, bias=bg, residual=Rg, workspace=ws, tuning=tuning)
+    want = binding.mixed_int8_linear_to_codes(Xg, pw, wl.TAU, block, bias=bg, residual=Rg, tuning=tuning)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
 # 65 to 128 rows whose second pass of 64 rows does not start on a block boundary: encoder afterwards
 @pytest.mark.parametrize("M,K,N,block", [(100, 528, 520, 4096), (128, 64, 72, 1024)])
 def test_decode_path_with_the_encoder_after_it(M, K, N, block):

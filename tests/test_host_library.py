@@ -120,6 +120,17 @@ def test_a_workspace_for_more_rows_serves_fewer(K, N):
         assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("K,N", [(4096, 40960), (128, 1024), (2048, 33024), (16, 8), (4096, 4096), (4096, 12288), (64, 72), (128, 90112),
+                                 (65536, 32), (20480, 5120)])
+@pytest.mark.parametrize("block", [0, 64, 256, 4096])
+def test_a_workspace_for_a_few_more_rows_serves_fewer(K, N, block):
+    """The encoder's buffer belongs to some row counts only, the partial outputs to others: neither lets the size fall."""
+    L = binding.lib()
+    size = (lambda m: L.mmd8_linear_to_codes_workspace_bytes(m, K, N, block)) if block else (lambda m: L.mmd8_linear_workspace_bytes(m, K, N))
+    sizes = [size(m) for m in list(range(1, 130)) + [257, 1000]]
+    assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("M,K,N,at,walk", [(1576, 1024, 3072, 717, False), (1576, 1024, 3072, 922, True), (2048, 1024, 4096, 819, False),
                                            (2048, 1024, 4096, 922, True), (256, 4096, 12288, 410, False), (256, 4096, 12288, 819, True),
                                            (256, 11008, 4096, 440, False), (256, 11008, 4096, 1101, True), (140, 32768, 1024, 655, True),
