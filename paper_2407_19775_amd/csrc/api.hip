@@ -184,7 +184,18 @@ static size_t workspace_bytes_for(int M, int K, int N, int r = 0, int exit_block
     if (splits > 1) sums = sums > splits * rows * N ? sums : splits * rows * N;
   }
   if (M <= kSkinnyMaxM) return carve(nullptr, M, K, N, r, exit_block).bytes;
-  const size_t tiled = carve(nullptr, M, K, N, r, exit_block, true, false).bytes + round_up_sz(sums * sizeof(float), 256);
+  size_t tiled = carve(nullptr, M, K, N, r, exit_block, true, false).bytes + round_up_sz(sums * sizeof(float), 256);
+  if (r > 0) {
+    // likewise the ranges of an adapter's down-projection, which are fewer the more tiles of rows there are (one from 16 cus
+    // rows on)
+    size_t most = plan_lora(M, K).partial_bytes;
+    tiled -= round_up_sz(most, 256);
+    for (int m = 16; m < M + 16 && m <= 16 * device_cu_count(); m += 16) {
+      const size_t bytes = plan_lora(m < M ? m : M, K).partial_bytes;
+      most = most > bytes ? most : bytes;
+    }
+    tiled += round_up_sz(most, 256);
+  }
   const size_t decode = carve(nullptr, kSkinnyMaxM, K, N, r, exit_block).bytes;
   return tiled > decode ? tiled : decode;
 }

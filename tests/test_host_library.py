@@ -131,6 +131,16 @@ def test_a_workspace_for_a_few_more_rows_serves_fewer(K, N, block):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("K,N", [(11008, 4096), (8192, 1024), (28672, 8192), (4096, 12288), (65536, 32), (64, 72)])
+@pytest.mark.parametrize("rank", [8, 64])
+def test_a_workspace_for_an_adapter_and_more_rows_serves_fewer(K, N, rank):
+    """The ranges of K of the down-projection get fewer as the rows get more: their sums do not let the size fall."""
+    L = binding.lib()
+    rows = sorted(list(range(1, 140)) + list(range(141, 5000, 53)) + list(range(144, 5000, 16)) + list(range(145, 5000, 16)))
+    sizes = [L.mmd8_linear_lora_workspace_bytes(m, K, N, rank) for m in rows]
+    assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("M,K,N,at,walk", [(1576, 1024, 3072, 717, False), (1576, 1024, 3072, 922, True), (2048, 1024, 4096, 819, False),
                                            (2048, 1024, 4096, 922, True), (256, 4096, 12288, 410, False), (256, 4096, 12288, 819, True),
                                            (256, 11008, 4096, 440, False), (256, 11008, 4096, 1101, True), (140, 32768, 1024, 655, True),
