@@ -105,9 +105,9 @@ int mmd8_unpack_weight(const int8_t* Wq_packed /*DEVICE*/, uint32_t Wq_layout, i
 
 /* Optional taps that expose the intermediates of one mmd8_mixed_int8_linear call (for parity
  * checks).  Any member may be NULL.  All are DEVICE pointers.  The output of a call does not depend on
- * which taps are asked for.  (For up to 8 rows the kernels that multiply also prepare their own operands;
- * asking for outlier_mask, row_absmax, xq, n_outliers or outlier_idx makes the separate preparation kernels
- * run as well, which produce the same quantities.) */
+ * which taps are asked for.  (For up to 8 rows the kernels that multiply may also prepare their own operands; asking for
+ * outlier_mask, row_absmax, xq, n_outliers or outlier_idx makes the separate preparation kernels run as well, which
+ * produce the same quantities.) */
 typedef struct {
   uint8_t* outlier_mask;  /* [K]    1 = critical feature dimension                         */
   float*   row_absmax;    /* [M]    r[m]                                                   */
@@ -130,8 +130,8 @@ typedef struct {
   uint32_t tuning;
 } mmd8_debug_taps;
 #define MMD8_TUNE_GEMM_TILES(v)    ((uint32_t)((v) + 1) & 0xfu) /* tiled GEMM (more than 128 rows): tile configuration v = 0..5 */
-#define MMD8_TUNE_SEPARATE_PREP    0x10u  /* up to 8 rows in the split-K kernels: run the scan and pack kernels instead of letting the multiplying kernel prepare its own operands */
-#define MMD8_TUNE_NO_ROWS_KERNEL   0x20u  /* up to 8 rows: use the split-K kernels where the layer would be a single kernel */
+#define MMD8_TUNE_SEPARATE_PREP    0x10u  /* up to 128 rows: run the scan and pack kernels instead of the one-pass preparation (where a preparation kernel runs at all) */
+#define MMD8_TUNE_NO_ROWS_KERNEL   0x20u  /* up to 8 rows: the kernels of 9 to 128 rows where others would prepare their own operands */
 
 /* The layer, per call (tau: threshold; X read as X[m*ldx + k]; Y written as Y[m*ldy + n]):
  *     flag[k]  = any_m |X[m,k]| >= tau

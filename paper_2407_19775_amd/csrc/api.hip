@@ -82,6 +82,7 @@ struct Workspace {
   int gemm_splits;     // ranges of K of the tiled GEMM, 1: not split
   SkinnyPlan decode_plan;   // ranges of K of the decode kernels (at most 128 rows)
   int pass_rows;       // rows per pass of the decode kernels: all of them where their partial outputs fit
+  SkinnyPlan panel_plan;    // ranges of K of k_gemm_panel (up to 8 rows); splits 0: not for this call
   uint16_t* h;         // coded output only, where the encoder runs as a kernel of its own: [M][N] fp16
   size_t bytes;
 };
@@ -123,14 +124,24 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   if (!base) w.xg = w.wg = nullptr;
   w.xq = reinterpret_cast<int8_t*>(take(Mpad * Kpad));
   w.partial = nullptr;
-  w.decode_plan = {};
+  w.decode_plan = w.panel_plan = {};
   w.pass_rows = 0;
   if (M > 0 && M <= kSkinnyMaxM) {
     w.decode_plan = plan_skinny(K, N);
     if (!split_k) w.decode_plan.splits = 1, w.decode_plan.slabs_per_split = w.decode_plan.n_slabs;
     // (the sums go through memory even when K is not split: what follows them is the work of the kernel that adds them)
     w.pass_rows = M < pass_rows ? M : pass_rows;
-    w.partial = reinterpret_cast<float*>(take((size_t)w.decode_plan.splits * w.pass_rows * N * sizeof(float)));
+    // (k_gemm_panel has more ranges of fewer rows: room for those of any number of rows up to these, so that the size does not
+    // fall where its rows end)
+    size_t rows = (size_t)w.decode_plan.splits * w.pass_rows;
+    if (split_k) {
+      w.panel_plan = plan_panel(M, K, N);
+      for (int m = 1; m <= kPanelMaxM && m <= M; ++m) {
+        const size_t r_m = (size_t)plan_panel(m, K, N).splits * m;
+        rows = rows > r_m ? rows : r_m;
+      }
+    }
+    w.partial = reinterpret_cast<float*>(take(rows * N * sizeof(float)));
   }
   if (w.gemm_splits > 1) w.partial = reinterpret_cast<float*>(take((size_t)w.gemm_splits * M * N * sizeof(float)));
   w.lora_t = r > 0 ? reinterpret_cast<uint16_t*>(take((size_t)M * kLoraMaxRank * 2)) : nullptr;
@@ -404,13 +415,16 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   // preparation are asked for, the scan and pack kernels run ahead of it for their sake only.
   // (alternative readings: always the separate scan and pack kernels, which is where they differ)
   const bool rows_path = !readings && !(t.tuning & MMD8_TUNE_NO_ROWS_KERNEL) && rows_kernel_fits(M, Kpad, N);
+  // ... or a kernel that prepares its own operands for a range of K, and the one that adds the ranges.
+  const bool panel_path = !readings && !(t.tuning & MMD8_TUNE_NO_ROWS_KERNEL) && !rows_path && ws.panel_plan.splits > 0;
+  const bool own_prep = rows_path || panel_path;
   // a coded output is written by the layer's last kernel where that is possible, otherwise by the encoder after it (whose
   // buffer is the place of the partial outputs where the layer would be a single kernel)
   const bool encodes = exit && exit->block > 0;
   const bool exit_fused = encodes && (exit_fuses(M, K, N, exit->block) || (skinny && !rows_path && M <= 64));
   if (encodes && !exit_fused && !Y) Y = ws.h;
   // The decode kernels' preparation in one kernel (the separate ones leave codes that serve as well).
-  const bool decode_prep = skinny && !rows_path && !wants_prep_taps && !(t.tuning & MMD8_TUNE_SEPARATE_PREP) && !readings;
+  const bool decode_prep = skinny && !own_prep && !wants_prep_taps && !(t.tuning & MMD8_TUNE_SEPARATE_PREP) && !readings;
   // coded activations are decoded by the one-pass preparation kernel itself where that kernel runs
   // (element offsets are held in 32 bits there); otherwise by the decoder, ahead of the usual kernels
   const bool one_pass = !skinny && prep_fits(K) && !readings;
@@ -444,7 +458,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   } else if (decode_prep) {
     if (launch_prep_rows(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, ws.xq, st) != hipSuccess) return MMD8_E_HIP;
     if (!record(t.event_prep_mid)) return MMD8_E_HIP;
-  } else if (!rows_path || wants_prep_taps) {
+  } else if (!own_prep || wants_prep_taps) {
     if (launch_scan(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, st) != hipSuccess) return MMD8_E_HIP;
     if (!record(t.event_prep_mid)) return MMD8_E_HIP;
     // the row scale over the non-critical columns only: needs the flags of every row, hence a pass of its own
@@ -461,7 +475,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
 
   if (lora && !one_pass && launch_lora_down(l, plan_lora(M, K), ws.lora_part, st) != hipSuccess) return MMD8_E_HIP;
 
-  if (rows_path) {   // (a coded output: the encoder follows)
+  if (own_prep) {   // (rows_path with a coded output: the encoder follows)
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
     SkinnyArgs g = {};
     g.flag_reset = wants_prep_taps ? ws.flag : nullptr;               // the scan set them
@@ -490,7 +504,13 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     g.ldx = ldx;
     g.K = K;
     g.th = threshold_pattern(tau);
-    if (launch_gemm_rows(g, st) != hipSuccess) return MMD8_E_HIP;
+    if (panel_path && exit_fused) {
+      g.codes = exit->codes;
+      g.code_absmax = exit->absmax;
+      g.code_block = exit->block;
+    }
+    g.partial = ws.partial;
+    if ((rows_path ? launch_gemm_rows(g, st) : launch_gemm_panel(g, ws.panel_plan, st)) != hipSuccess) return MMD8_E_HIP;
   } else if (skinny) {
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
     for (int row0 = 0; row0 < M; row0 += ws.pass_rows) {

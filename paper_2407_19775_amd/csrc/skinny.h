@@ -45,6 +45,10 @@ struct SkinnyArgs {
   int n_slabs, tiles_n, slabs_per_split;   // filled by the launcher
 };
 hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t stream);
+// Up to eight rows, the kernel that prepares its own operands and splits K (k_gemm_panel); splits 0: not for this call.
+constexpr int kPanelMaxM = 8;
+SkinnyPlan plan_panel(int M, int K, int N);
+hipError_t launch_gemm_panel(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t stream);
 
 // Y = f16(sum of the ranges of K, in order, + bias), then GELU, then the residual; with codes, the result (also stored
 // in Y, contiguous, where given) leaves blockwise-coded.

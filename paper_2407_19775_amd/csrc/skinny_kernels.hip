@@ -498,6 +498,219 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, size_t n) {
   if (i < n) p[i] = 0;
 }
 
+// ------------------------------------------------------------------------------------------------
+// A few rows whose operands do not fit in LDS (k_gemm_rows below): the eight waves of a workgroup own neighbouring 32-column
+// groups of a weight panel and walk a range of K together, weights straight from memory into the registers of the lane that
+// feeds them to the MFMA, three slabs ahead.  The activation side is made here: every workgroup streams the rows of X once for
+// the row scales, keeps the columns of its own range in LDS with one "critical" flag per column, and writes the codes and the
+// fp16 critical columns of a slab into a ring two slabs ahead of the MFMAs: wave w owns the 16-column piece w % 4 of the slab,
+// a lane one column of one of four rows.  Rows of the ring beyond M are zeroed once and never written.  With K in one range and
+// nothing behind the bias this is the whole layer.
+//
+// What bounds it: the rows through every compute unit ahead of the first product, and a barrier per slab.  What it saves
+// against k_prep_rows and k_gemm_decode is a launch, with K in one range two (plan_panel has both sides measured).
+// ------------------------------------------------------------------------------------------------
+constexpr int kPanelWaves = 8, kPanelThreads = kPanelWaves * kWave;
+constexpr int kPanelMaxSlabs = 128, kPanelMaxRowSlabs = 256;   // of a workgroup's range: its columns of X and their flags in LDS
+template <bool kSplit, bool kTap>
+__global__ __launch_bounds__(kPanelThreads, 2) void k_gemm_panel(const SkinnyArgs a) {
+  constexpr int kThreads = kPanelThreads, kCodes = 2048, kStage = kCodes + 4096;   // of a slab in the ring: 32 rows of codes, then of halves
+  __shared__ __attribute__((aligned(16))) int8_t s_x[4][kStage];
+  __shared__ uint8_t s_any[kPanelMaxSlabs];
+  __shared__ __attribute__((aligned(16))) uint16_t s_row[kPanelMaxRowSlabs * kSlabBytes];   // [M][cnt x 64]
+  __shared__ __attribute__((aligned(16))) uint8_t s_crit[kPanelMaxSlabs * kSlabBytes];      // [cnt x 64]
+  __shared__ uint32_t s_part[kPanelMaxM][kPanelWaves];
+  __shared__ float s_r[kPanelMaxM], s_scale[kPanelMaxM];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int lr = lane & 31, lg = lane >> 5;
+  reset_column_flags(a.flag_reset, a.Kpad);
+  const int tile = blockIdx.x % a.tiles_n, split = blockIdx.x / a.tiles_n;
+  const int n0 = tile * 256 + wave * 32;                              // < Npad: the padding rows of Wt are zero
+  const int n = n0 + lr;
+  const int s_begin = split * a.slabs_per_split;
+  const int cnt = min(a.n_slabs, s_begin + a.slabs_per_split) - s_begin;   // >= 1 by construction of the plan
+  const int last = cnt - 1;
+  const int8_t* wgrp = a.Wt + (size_t)tile * a.n_slabs * kBlockBytes + (size_t)wave * 2048 + lane * 16 + (size_t)s_begin * kBlockBytes;
+
+  struct Weights {
+    v4i w[2];
+  };
+  auto fetch_w = [&](int j, Weights& f) {
+    const int8_t* p = wgrp + (size_t)j * kBlockBytes;
+    f.w[0] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
+    f.w[1] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p + 1024));
+  };
+  Weights f[4];
+  fetch_w(0, f[0]);
+  fetch_w(min(1, last), f[1]);
+  fetch_w(min(2, last), f[2]);
+
+  // ---- scales, columns of the range, their flags (the weight requests above are in flight meanwhile)
+  for (int i = threadIdx.x; i < 4 * kStage / 16; i += kThreads) reinterpret_cast<v4u*>(&s_x[0][0])[i] = v4u{0, 0, 0, 0};
+  const us2 th2 = __builtin_bit_cast(us2, a.th | (a.th << 16));
+  us2 best[kPanelMaxM];
+#pragma unroll
+  for (int m = 0; m < kPanelMaxM; ++m) best[m] = __builtin_bit_cast(us2, 0u);
+  // (rows innermost, so that the loads of all rows are in flight together)
+  for (int c = threadIdx.x; c < a.K / 8; c += kThreads) {
+    v4u raw[kPanelMaxM];
+#pragma unroll
+    for (int m = 0; m < kPanelMaxM; ++m) {
+      raw[m] = v4u{0, 0, 0, 0};
+      if (m < a.M) raw[m] = *reinterpret_cast<const v4u*>(a.X + (size_t)m * a.ldx + c * 8);
+    }
+#pragma unroll
+    for (int m = 0; m < kPanelMaxM; ++m)
+#pragma unroll
+      for (int w = 0; w < 4; ++w)   // per half, wraps mod 2^16: entries below the threshold get the top bit
+        best[m] = __builtin_elementwise_max(best[m], (us2)(__builtin_bit_cast(us2, raw[m][w] & 0x7fff7fffu) - th2));
+  }
+  const int row_stride = cnt * kSlabBytes;                            // elements of s_row per row
+  for (int c = threadIdx.x; c < cnt * (kSlabBytes / 8); c += kThreads) {
+    const int k = s_begin * kSlabBytes + c * 8;                       // (the K padding reads as zero)
+    v4u raw[kPanelMaxM];
+#pragma unroll
+    for (int m = 0; m < kPanelMaxM; ++m) {
+      raw[m] = v4u{0, 0, 0, 0};
+      if (m < a.M && k < a.K) raw[m] = *reinterpret_cast<const v4u*>(a.X + (size_t)m * a.ldx + k);
+    }
+#pragma unroll
+    for (int m = 0; m < kPanelMaxM; ++m)
+      if (m < a.M) *reinterpret_cast<v4u*>(&s_row[m * row_stride + c * 8]) = raw[m];
+  }
+#pragma unroll
+  for (int m = 0; m < kPanelMaxM; ++m) {
+    if (m < a.M) {                                                    // the same for every lane
+      const uint32_t both = __builtin_bit_cast(uint32_t, best[m]);
+      const uint32_t wmax = wave_max_u32(max(both & 0xffffu, both >> 16));
+      if (lane == 0) s_part[m][wave] = wmax;
+    }
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < row_stride; c += kThreads) {
+    bool crit = false;
+    for (int m = 0; m < a.M; ++m) crit = crit || (s_row[m * row_stride + c] & 0x7fffu) >= a.th;
+    s_crit[c] = crit ? 1 : 0;
+  }
+  if ((int)threadIdx.x < a.M) {
+    uint32_t mm = 0;
+#pragma unroll
+    for (int w = 0; w < kPanelWaves; ++w) mm = max(mm, s_part[threadIdx.x][w]);
+    // top bit set: an entry below the threshold exists and its pattern is mm + th (mod 2^16)
+    const float r = (mm & 0x8000u) ? half_lo_to_float((mm + a.th) & 0xffffu) : 0.0f;
+    s_r[threadIdx.x] = r;
+    s_scale[threadIdx.x] = (r == 0.0f) ? 0.0f : 127.0f / r;           // IEEE division
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < cnt; t += kThreads) {                 // "slab t holds a critical column"
+    const v4u* fl = reinterpret_cast<const v4u*>(&s_crit[t * kSlabBytes]);
+    const v4u m = fl[0] | fl[1] | fl[2] | fl[3];
+    s_any[t] = (m[0] | m[1] | m[2] | m[3]) != 0;
+  }
+
+  // slab j of the range -> ring buffer `stage`
+  auto make_slab = [&](int j, int stage) {
+    const int ch = wave & 3, ks = ch >> 1, g = ch & 1, col = lane & 15;
+    const int kl = j * kSlabBytes + ch * 16 + col;
+    const bool crit = s_crit[kl] != 0;
+    for (int m = (wave >> 2) * 4 + (lane >> 4); m < a.M; m += kPanelWaves) {
+      const uint32_t x = s_row[m * row_stride + kl];
+      const uint32_t code = crit ? 0u : to_code_byte(half_lo_to_float(x), s_scale[m]);
+      s_x[stage][ks * 1024 + (32 * g + m) * 16 + col] = (int8_t)code;
+      *reinterpret_cast<uint16_t*>(&s_x[stage][kCodes + (2 * ks + (col >> 3)) * 1024 + (32 * g + m) * 16 + (col & 7) * 2]) =
+          crit ? (uint16_t)x : (uint16_t)0;
+    }
+  };
+  struct Frags {
+    v4i x[2];      // int8 codes, k-steps 0 and 1
+    v8h xf[4];     // fp16 critical columns, pieces 2 (k-step) + t (valid when the slab has any)
+  };
+  auto read_frags = [&](int stage, bool any, Frags& g) {
+    const int8_t* base = &s_x[stage][lane * 16];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) g.x[ks] = *reinterpret_cast<const v4i*>(base + ks * 1024);
+    if (any) {                                                        // the same for the whole workgroup
+#pragma unroll
+      for (int p = 0; p < 4; ++p) g.xf[p] = *reinterpret_cast<const v8h*>(base + kCodes + p * 1024);
+    }
+  };
+  v16i acc;
+  v16f accf;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0, accf[e] = 0.0f;
+  auto multiply = [&](bool any, const Frags& g, const Weights& w) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(g.x[ks], w.w[ks], acc, 0, 0, 0);
+    if (any) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const v4u wu = __builtin_bit_cast(v4u, w.w[ks]) ^ 0x80808080u;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) accf = __builtin_amdgcn_mfma_f32_32x32x16_f16(g.xf[2 * ks + t], codes_to_half8(wu, t), accf, 0, 0, 0);
+      }
+    }
+  };
+
+  // In iteration j: request the weights of slab j + 3 (past the end the last slab again: uniform loop body); read the fragments
+  // of slab j + 1; multiply slab j; make slab j + 2 in the buffer that slab j - 2 used (a ring of four, so that every index is
+  // static in a loop unrolled four times); barrier.
+  Frags fr[2];
+  make_slab(0, 0);
+  make_slab(min(1, last), 1);
+  __syncthreads();
+  // the flags of the next 64 slabs as one scalar mask (bit i: slab base + i, the last slab repeated past the end)
+  uint64_t any_mask = __builtin_amdgcn_ballot_w64(s_any[min(lane, last)] != 0);
+  bool any_next = any_mask & 1u;
+  read_frags(0, any_next, fr[0]);
+  auto iteration = [&](int j, auto u_tag) {
+    constexpr int u = decltype(u_tag)::value;                         // j % 4
+    const bool any_cur = any_next;
+    if constexpr (u == 3) {                                           // 64 is a multiple of four: only here can j + 1 start a window
+      if (((j + 1) & 63) == 0) any_mask = __builtin_amdgcn_ballot_w64(s_any[min(j + 1 + lane, last)] != 0);
+    }
+    any_next = (any_mask >> ((j + 1) & 63)) & 1u;
+    fetch_w(min(j + 3, last), f[(u + 3) & 3]);
+    read_frags((u + 1) & 3, any_next, fr[(u + 1) & 1]);
+    multiply(any_cur, fr[u & 1], f[u & 3]);
+    make_slab(min(j + 2, last), (u + 2) & 3);
+    __syncthreads();
+  };
+  // (whole groups of four without a way out in between: with an exit after every iteration the compiler waits for weights
+  // requested one iteration earlier instead of three)
+  int j0 = 0;
+  for (; j0 + 4 <= cnt; j0 += 4) {
+    iteration(j0, std::integral_constant<int, 0>{});
+    iteration(j0 + 1, std::integral_constant<int, 1>{});
+    iteration(j0 + 2, std::integral_constant<int, 2>{});
+    iteration(j0 + 3, std::integral_constant<int, 3>{});
+  }
+  if (j0 < cnt) iteration(j0, std::integral_constant<int, 0>{});
+  if (j0 + 1 < cnt) iteration(j0 + 1, std::integral_constant<int, 1>{});
+  if (j0 + 2 < cnt) iteration(j0 + 2, std::integral_constant<int, 2>{});
+
+  // ---- outputs.  C layout of the 32x32 MFMA: lane = column n (lane % 32), register e = row 8 (e / 4) + 4 (lane / 32) + (e % 4)
+  const float c = n < a.N ? a.c[n] : 0.0f;
+  const float b = (!kSplit && a.bias && n < a.N) ? half_lo_to_float(a.bias[n]) : 0.0f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {                                       // (rows 8 and on are not there)
+    const int m = 4 * lg + e;
+    if (m < a.M && n < a.N) {
+      const float y = (float)acc[e] * (s_r[m] * (c / 16129.0f)) + accf[e] * (c / 127.0f);
+      if constexpr (kSplit)
+        a.partial[((size_t)split * a.M + m) * a.N + n] = y;
+      else
+        a.Y[(size_t)m * a.ldy + n] = (uint16_t)float_to_half_bits(y + b);
+      if constexpr (kTap) {
+        if constexpr (kSplit)
+          atomicAdd(a.tap_acc + (size_t)m * a.N + n, acc[e]);         // tap buffer zeroed by the launcher
+        else
+          a.tap_acc[(size_t)m * a.N + n] = acc[e];
+      }
+    }
+  }
+}
+
 // Ranges of K: a workgroup takes 0.45 us per slab, or its share of what HBM delivers (6.2 TB/s), and the fp32 sums of a range
 // cost their 8 bytes per output at 3 TB/s: the sum of both is least at sqrt(0.45 slabs / cost of a range), unless HBM is busy
 // with fewer workgroups.  Counted for 32 rows, not for the rows of the call, so that a workspace sized for more rows gives
@@ -511,6 +724,27 @@ SkinnyPlan plan_skinny(int K, int N) {
   const int best = max(1, min(min(enough, cheapest), min(device_cu_count() / p.tiles_n, p.n_slabs / 2)));
   p.slabs_per_split = ceil_div(p.n_slabs, best);
   p.splits = ceil_div(p.n_slabs, p.slabs_per_split);
+  return p;
+}
+
+// k_gemm_panel: a range per compute unit, at least eight slabs each; the columns of a range have to fit in LDS.  splits 0: not
+// for this call.
+SkinnyPlan plan_panel(int M, int K, int N) {
+  const int Kpad = packed_k(K), cus = device_cu_count();
+  SkinnyPlan p = {Kpad / kSlabBytes, packed_n(N) / 256, 0, 0};
+  p.slabs_per_split = ceil_div(p.n_slabs, max(1, min(p.n_slabs / 8, cus / p.tiles_n)));
+  const int splits = ceil_div(p.n_slabs, p.slabs_per_split);
+  const bool fits = M >= 1 && M <= kPanelMaxM && p.slabs_per_split <= kPanelMaxSlabs && M * p.slabs_per_split <= kPanelMaxRowSlabs;
+  // The rows go through every workgroup, so not with too many of them; a slab takes it longer than k_gemm_decode (five rows and
+  // more, heavy-tailed), so only with short ranges or nearly every compute unit at work; and what it saves is a launch or two,
+  // which large weights do not show.  us, this kernel / k_prep_rows and k_gemm_decode: 8 x 11008 -> 4096 17.5 / 19.5, 3 x 16384 ->
+  // 2048 14.1 / 17.4, 5 x 512 -> 57344 10.7 / 14.5; at the lines 8 x 24576 -> 2048 (197k elements) 20.6 / 21.9, 8 x 65536 -> 1024
+  // (524k) 32.3 / 28.9; 8 x 4096 -> 24576 (192 workgroups, 32 slabs) 28.2 / 25.7, 3 x 17920 -> 6656 (234, 32) 28.1 / 30.6; 4 x
+  // 20480 -> 8192 (168 MB) 36.0 / 36.9, 4 x 24576 -> 8192 (201 MB) 43.3 / 40.5; two rows of 36864 -> 8192 56.9 / 60.6, of 49152 ->
+  // 8192 77.8 / 75.3.
+  const bool saves = (((size_t)Kpad * N <= 200000000 && M * Kpad <= 200000) || (M <= 2 && M * Kpad <= 80000)) &&
+                     (p.slabs_per_split <= 16 || 10 * p.tiles_n * splits >= 9 * cus);
+  if (fits && saves) p.splits = splits;
   return p;
 }
 
@@ -557,26 +791,56 @@ hipError_t launch_add_splits(const SplitSum& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// the sums of the ranges, and the rest of the layer
+static hipError_t launch_finalize(const SkinnyArgs& a, int splits, hipStream_t stream) {
+  if (a.codes) {
+    const FinalizedHalves src = {a.partial, splits, a.N, (size_t)a.M * a.N, a.bias, a.residual, a.ldr, a.Y};
+    return launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, a.flag_reset, a.Kpad, stream);
+  }
+  hipLaunchKernelGGL(k_skinny_finalize, dim3(ceil_div(a.N, 256), a.M), dim3(256), 0, stream, a.partial, splits,
+                     a.M, a.N, a.bias, a.lora_P, a.lora_splits, a.lora_B, a.lora_r, a.lora_T_user, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
+                     a.flag_reset, a.Kpad);
+  return hipGetLastError();
+}
+static void clear_tap(const SkinnyArgs& a, hipStream_t stream) {
+  const size_t n = (size_t)a.M * a.N;
+  if (a.tap_acc) hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a.tap_acc, n);
+}
+
 hipError_t launch_gemm_skinny(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t stream) {
   a.n_slabs = plan.n_slabs;
   a.tiles_n = plan.tiles_n;
   a.slabs_per_split = plan.slabs_per_split;
   if (a.M < 1 || a.M > kSkinnyMaxM || !a.partial || !a.X) return hipErrorInvalidValue;
   if (hipError_t e = prepare_skinny_kernels(); e != hipSuccess) return e;
-  const size_t n = (size_t)a.M * a.N;
-  if (a.tap_acc) hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a.tap_acc, n);
+  clear_tap(a, stream);
   hipError_t e = a.M <= 32 ? launch_decode<32>(a, plan.splits, stream) : a.M <= 64 ? launch_decode<64>(a, plan.splits, stream) : launch_decode<128>(a, plan.splits, stream);
-  if (e != hipSuccess) return e;
   // the sums go through memory whether K is split or not: the kernel that adds them is the rest of the layer (and it puts the
   // column flags back to zero, which every workgroup of the kernel before it reads)
-  if (a.codes) {
-    const FinalizedHalves src = {a.partial, plan.splits, a.N, n, a.bias, a.residual, a.ldr, a.Y};
-    return launch_finalize_coded(src, a.code_block, a.codes, a.code_absmax, a.flag_reset, a.Kpad, stream);
+  return e == hipSuccess ? launch_finalize(a, plan.splits, stream) : e;
+}
+
+hipError_t launch_gemm_panel(SkinnyArgs a, const SkinnyPlan& plan, hipStream_t stream) {
+  a.n_slabs = plan.n_slabs;
+  a.tiles_n = plan.tiles_n;
+  a.slabs_per_split = plan.slabs_per_split;
+  if (plan.splits < 1 || a.M < 1 || a.M > kPanelMaxM || !a.partial || !a.X || plan.slabs_per_split > kPanelMaxSlabs ||
+      a.M * plan.slabs_per_split > kPanelMaxRowSlabs)
+    return hipErrorInvalidValue;
+  const bool sums = plan.splits > 1 || a.lora_r > 0 || a.residual || a.codes || a.gelu;
+  const dim3 grid(plan.tiles_n * plan.splits), block(kPanelThreads);
+  if (sums) {
+    clear_tap(a, stream);
+    if (a.tap_acc) hipLaunchKernelGGL((k_gemm_panel<true, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((k_gemm_panel<true, false>), grid, block, 0, stream, a);
+  } else {
+    if (a.tap_acc) hipLaunchKernelGGL((k_gemm_panel<false, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((k_gemm_panel<false, false>), grid, block, 0, stream, a);
   }
-  hipLaunchKernelGGL(k_skinny_finalize, dim3(ceil_div(a.N, 256), a.M), dim3(256), 0, stream, a.partial, plan.splits,
-                     a.M, a.N, a.bias, a.lora_P, a.lora_splits, a.lora_B, a.lora_r, a.lora_T_user, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
-                     a.flag_reset, a.Kpad);
-  return hipGetLastError();
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !sums) return e;
+  a.flag_reset = nullptr;                                             // (done by the kernel before, which does not read them)
+  return launch_finalize(a, plan.splits, stream);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -864,12 +1128,19 @@ static int rows_tiles_max(int M, int Kpad) {
   const long room = (long)kRowsMaxLds - (long)rows_lds_bytes(M, Kpad, 0);
   return room <= 0 ? 0 : (int)min(room / (2 * kRowsWaves * M * 16 * 4), (long)(kRowsWaves * kWave / (16 * M)));
 }
-// One or two rows wherever they fit in LDS; more where a compute unit can hold the sums of all its tiles, so that it
-// prepares once (8192 -> 57344 at four rows, where it would prepare twice, 93 us, with K split 80; a 7B layer of six rows 65 us
-// with every linear in this kernel, 71 split).
+// Where a compute unit holds the sums of all its tiles, so that it prepares once; a single row wherever it fits (8192 -> 57344 at
+// four rows, where it would prepare twice, 93 us, with K split 80; 24576 -> 8192 at two rows 44.1 and 41.4; a 7B layer of six rows
+// 65 us with every linear in this kernel, 71 split).  Left to the kernels that split K, us here / there:
+//   fewer slabs than waves and many tiles: sixteen sums per tile, most of them zeros.  512 -> 57344 at three rows 11.1 / 9.9
+//   (28672: 8.0 / 8.5), 96 -> 65536 at four 11.5 / 7.0;
+//   long rows in a workgroup's registers, five of them and more, or few workgroups: 8192 -> 8192 at five rows 21.4 / 19.0 (6144 ->
+//   8192 at six 16.7 / 17.0, 11008 -> 8192 at four 21.7 / 22.8); 24576 -> 1024 at two 16.7 / 15.5 (4096: 23.6 / 25.5).
 bool rows_kernel_fits(int M, int Kpad, int N) {
-  return M >= 1 && M <= kRowsMaxM && M * Kpad / 8 <= kRowsMaxChunks * kRowsWaves * kWave &&
-         rows_tiles_max(M, Kpad) >= (M <= 2 ? 1 : ceil_div(ceil_div(N, 16), device_cu_count()));
+  if (M < 1 || M > kRowsMaxM || M * Kpad / 8 > kRowsMaxChunks * kRowsWaves * kWave) return false;
+  const int n_tiles = ceil_div(N, 16), cus = device_cu_count(), tiles = ceil_div(n_tiles, cus), n_slabs = Kpad / kSlabBytes;
+  if (rows_tiles_max(M, Kpad) < (M == 1 ? 1 : tiles)) return false;
+  if (M > 1 && n_slabs < kRowsWaves && 2 * tiles > 3 * n_slabs) return false;
+  return M * Kpad <= 40000 || M == 4 || (M < 4 && 4 * n_tiles > cus);
 }
 
 // more than the default 64 KB of LDS: an attribute per kernel and device

@@ -69,3 +69,21 @@ def static_decode_plan(M: int, K: int, N: int):
     f.argtypes, f.restype = [ctypes.c_int] * 3, Plan
     p = f(M, K, N)
     return p.splits, p.pass_rows
+
+
+def panel_plan(M: int, K: int, N: int):
+    """Ranges of K of the kernel for a few rows that prepares its own operands and splits K, and the 64-column slabs of a range (a
+    C++ function of the library); 0 ranges: not for this call."""
+    class Plan(ctypes.Structure):
+        _fields_ = [(name, ctypes.c_int) for name in ("n_slabs", "tiles_n", "splits", "slabs_per_split")]
+    f = binding.lib()._ZN4mmd810plan_panelEiii
+    f.argtypes, f.restype = [ctypes.c_int] * 3, Plan
+    p = f(M, K, N)
+    return p.splits, p.slabs_per_split
+
+
+def rows_kernel_fits(M: int, K: int, N: int) -> bool:
+    """Whether the layer is the single kernel for a few rows (a C++ function of the library)."""
+    f = binding.lib()._ZN4mmd816rows_kernel_fitsEiii
+    f.argtypes, f.restype = [ctypes.c_int] * 3, ctypes.c_bool
+    return f(M, (K + 127) // 128 * 128, N)
