@@ -1,10 +1,10 @@
-"""Up to eight rows: the decode GEMM kernel prepares its own operands (row scales, codes, critical columns) and
-the scan and pack kernels are left out.  The result must equal, bit for bit, the one obtained with those kernels
-(forced through the call's tuning word, or by asking for their taps), the int32 accumulators must equal the oracle's, and
-the output must meet the oracle's to the fp16 bar; with every companion of the layer (bias, adapter, activation,
-coded input, coded output).  One or two rows (while their operands fit in LDS) go through a single kernel that shares K out between the waves of a
-workgroup: same integers, and an output that may differ from the split-K kernels' in the last fp16 bit (another
-order of fp32 additions), so it is compared with theirs to a fifth of the usual bar and with the oracle to the usual bar."""
+"""Up to eight rows, by the kernels that prepare their own operands (the whole layer in one kernel, or a range of K each) and by
+those of 9 to 128 rows behind a preparation in one pass or behind the scan and pack kernels (forced through the call's tuning
+word, or by asking for their taps).  The last three must be equal bit for bit; the int32 accumulators of all must equal
+the oracle's and the output must meet the oracle's to the fp16 bar; with every companion of the layer (bias, adapter, activation, coded
+input, coded output).  A kernel that prepares its own operands adds the fp32 sums in another order: same integers, and an
+output that may differ from the others' in the last fp16 bit, so it is compared with theirs to a fifth of the usual bar
+and with the oracle to the usual bar."""
 import numpy as np
 import pytest
 import torch
@@ -12,7 +12,7 @@ import torch
 from oracle import blockwise_codec as bc
 from oracle import mixed_linear as ml
 from paper_2407_19775_amd import binding, workloads as wl
-from gpu_util import assert_y_close, to_gpu, to_np
+from gpu_util import assert_y_close, panel_plan, rows_kernel_fits, to_gpu, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -81,17 +81,18 @@ def test_own_preparation_equals_the_separate_kernels(K, N):
             Xbuf = torch.zeros((M, K + 8), dtype=torch.float16, device="cuda")
             Xg = Xbuf[:, :K]
             Xg.copy_(to_gpu(X))
-            rows_kernel(0)
+            rows_kernel(0)                                          # (nor the kernel for a range of K)
             Y_taps, taps = lin(Xg, pw, tau, bias=bg, taps=True)     # scan + pack (their taps asked for)
             own_prep(0)
             Y_off = lin(Xg, pw, tau, bias=bg)                       # scan + pack (hook)
             own_prep(1)
-            Y, t_acc = lin(Xg, pw, tau, bias=bg, taps=("acc",))   # own preparation in the panel kernel
+            Y, t_acc = lin(Xg, pw, tau, bias=bg, taps=("acc",))   # the preparation in one pass
             rows_kernel(1)
             torch.cuda.synchronize()
             assert torch.equal(Y, Y_off) and torch.equal(Y, Y_taps), (M, K, N, tau)
             assert torch.equal(t_acc["acc"], taps["acc"]), (M, K, N, tau)
-            if M <= 2 and 3 * M * ((K + 63) // 64 * 64) <= 66 * 1024:                     # the single kernel
+            # the kernels that prepare their own operands, where the layer is one of theirs
+            if rows_kernel_fits(M, K, N) or panel_plan(M, K, N)[0] > 0:
                 Y, t_acc = lin(Xg, pw, tau, bias=bg, taps=("acc",))
                 Y_all, t_all = lin(Xg, pw, tau, bias=bg, taps=True)   # scan + pack for their taps only
                 torch.cuda.synchronize()
@@ -123,26 +124,31 @@ def test_companions_of_the_layer(M):
         Xd = torch.empty((M, K), dtype=torch.float16, device="cuda")
         out.append(lin(Xd, pw, wl.TAU, bias=bg, coded=(cg, ag, 256)))
         out.append(Xd)
-        out.extend(lin_to_codes(Xg, pw, wl.TAU, 1024, bias=bg, residual=R))
+        H = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        codes, absmax = lin_to_codes(Xg, pw, wl.TAU, 1024, bias=bg, residual=R, H=H)
+        # behind the layer or where its sums are added, the codes are those of the tensor that it hands on
+        want = binding.quantize_blockwise(H, 1024)
         torch.cuda.synchronize()
-        return out
+        assert torch.equal(codes, want[0]) and torch.equal(absmax, want[1])
+        return out + [H, codes, absmax]
 
-    on = run_all()
+    assert rows_kernel_fits(M, K, N)
+    on = run_all()                                                   # the whole layer in one kernel
+    rows_kernel(0)
+    one_pass = run_all()                                             # the preparation in one pass, K split
     own_prep(0)
-    off = run_all()
+    off = run_all()                                                  # scan + pack, K split
     own_prep(1)
-    for i, (a, b_) in enumerate(zip(on, off)):
-        if a.dtype == torch.float16 and i == 1 and M <= 2:
+    rows_kernel(1)
+    assert all(torch.equal(a, b_) for a, b_ in zip(one_pass, off))
+    for i, (a, b_) in enumerate(zip(on[:-2], off[:-2])):
+        if i == 3:
+            assert torch.equal(a, b_)                                # the decoded input
+        elif i == 1:
             # GELU of a pre-activation that moved by one fp16 step: many steps of the much smaller output
-            assert torch.allclose(a.float(), b_.float(), rtol=1e-2, atol=1e-3), i
-        elif a.dtype == torch.float16 and M <= 2:
-            assert_y_close(to_np(a), to_np(b_), rel=2e-3)             # (one or two rows: the single kernel where it applies)
-        elif a.dtype == torch.float16:
-            assert torch.equal(a, b_), i
-        elif i < len(on) - 2:
-            assert torch.equal(a, b_), i
-    # the coded output (last two entries) is encoded by the kernel that sums the partial outputs on both ways
-    assert torch.equal(on[-2], off[-2]) and torch.equal(on[-1], off[-1])
+            assert torch.allclose(a.float(), b_.float(), rtol=1e-2, atol=1e-3)
+        else:
+            assert_y_close(to_np(a), to_np(b_), rel=2e-3)
     Rplain = lin(Xg, pw, wl.TAU, bias=bg, residual=R)
     rows_kernel(0)
     Rpanel = lin(Xg, pw, wl.TAU, bias=bg, residual=R)
@@ -161,7 +167,7 @@ def test_same_workspace_alternates_between_both_ways():
     ys = []
     for i in range(3):
         ys.append(lin(Xg, pw, wl.TAU, workspace=ws))
-        y64 = lin(X64, pw, wl.TAU, workspace=ws)           # scan + pack, leaves the flags zero again
+        y64 = lin(X64, pw, wl.TAU, workspace=ws)           # the preparation in one pass; leaves the flags zero again
         if i == 0:
             y64_first = y64
         else:
