@@ -34,7 +34,7 @@ INT8_POWER_LIMITED_TOPS = 3468.0
 # reported as null once that file has changed.
 GEMM_TRAFFIC_BYTES_PER_LAUNCH = 1185.3e6
 GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 184.4e6
-GEMM_TRAFFIC_SOURCE_SHA256 = "85e03bf36f3837d3368eef5e76465b69b79360cfe266c5c6f340d43ef7694b52"
+GEMM_TRAFFIC_SOURCE_SHA256 = "384b042995f07d8ba0b57338b7f614d1167bee54df23a06018592d5a999ea74c"
 
 
 def parse():
@@ -478,7 +478,7 @@ def main():
     if want("heavy"):
         # ---- more than 128 rows of heavy-tailed input (hundreds of critical columns): the tiled GEMM's 16-bit part
         heavy = {}
-        for Mh in (128, 256):                  # 128: the last size that still takes the decode kernels (two passes)
+        for Mh in (128, 256):                  # 128: the last size that still takes the decode kernels
             Xh = {K: torch.from_numpy(wl.decode_activation(900 + Mh, Mh, K)).to(dev) for K in sorted({s.K for s in shapes})}
             Yh = {s.name: torch.empty((Mh, s.N), dtype=torch.float16, device=dev) for s in shapes}
             big_h = max(shapes, key=lambda s: binding.lib().mmd8_linear_workspace_bytes(Mh, s.K, s.N))

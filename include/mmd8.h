@@ -271,9 +271,10 @@ int mmd8_mixed_int8_linear_residual(const mmd8_half* X /*DEVICE*/, int M, int K,
  * (contiguous, 16-byte aligned) that receives the encoded tensor itself.  The layer's last kernel does the
  * encoding where no block is shared between its workgroups: up to 64 rows, up to 128 rows when
  * 64*N % block == 0, more rows when block is 64, 128 or 256 and divides N; otherwise (and for a few rows,
- * where the layer is a single kernel) the encoder runs after the layer.  Requirements: those of mmd8_mixed_int8_linear and of mmd8_quantize_blockwise; workspace of at
- * least mmd8_linear_to_codes_workspace_bytes(M, K, N, block) bytes, set up and reused like any other
- * workspace of the layer.  Errors as for the two calls; nothing is launched when one is returned. */
+ * where the layer is a single kernel) the encoder runs after the layer.  Requirements: those of
+ * mmd8_mixed_int8_linear and of mmd8_quantize_blockwise; workspace of at least
+ * mmd8_linear_to_codes_workspace_bytes(M, K, N, block) bytes, set up and reused like any other workspace of the layer.
+ * Errors as for the two calls; nothing is launched when one is returned. */
 size_t mmd8_linear_to_codes_workspace_bytes(int M, int K, int N, int block);
 int mmd8_mixed_int8_linear_to_codes(const mmd8_half* X /*DEVICE*/, int M, int K, int ldx,
                                     const int8_t* Wq_packed /*DEVICE*/, uint32_t Wq_layout, const float* col_absmax /*DEVICE [N]*/, int N,

@@ -212,8 +212,9 @@ static size_t workspace_bytes_for(int M, int K, int N, int r = 0, int exit_block
 }
 // A coded output is produced by the kernel that ends the layer when no block of it is shared between
 // workgroups: the tiled GEMM needs blocks inside its 256-column tiles; the decode path encodes where it sums
-// its partial outputs, any block size, as long as its second pass of 64 rows starts on a block boundary.  The
-// first few rows are a single kernel with nothing to sum afterwards: the encoder follows it.
+// its partial outputs, all rows of the call as one tensor (from 65 rows on where row 64 starts on a block boundary,
+// which the encoder asked for when these rows were two passes).  Where a few rows are a single kernel there is
+// nothing to sum afterwards: the encoder follows it.
 static bool exit_fuses(int M, int K, int N, int block) {
   if (rows_kernel_fits(M, packed_k(K), N)) return false;
   if (M <= kSkinnyMaxM) return M <= 64 || ((size_t)64 * N) % block == 0;

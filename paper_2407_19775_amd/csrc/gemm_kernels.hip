@@ -378,8 +378,8 @@ __device__ __forceinline__ void store_tile_coded(const GemmArgs& a, const WavePo
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     // The activation, on the rounded layer output: a loop of its own over the parked rows, not unrolled.  This code runs once
     // per tile and comes from memory; with the activation written out at each of a lane's elements and stepped over where
-    // there is none, every element cost the fetch of its instructions (ViT-L block of 1576 rows 121 -> 116.4 us, with the residual as below; 70B-shaped layer
-    // of 4096 rows 2998 -> 2973).
+    // there is none, every element cost the fetch of its instructions (ViT-L block of 1576 rows 121 -> 116.4 us, with the
+    // residual as below; no change where tiles are long: 70B-shaped layer of 4096 rows).
     if (a.gelu) {
 #pragma unroll 1
       for (int it = 0; it < RP * CH / kWave; ++it) {
