@@ -34,7 +34,7 @@ INT8_POWER_LIMITED_TOPS = 3468.0
 # reported as null once that file has changed.
 GEMM_TRAFFIC_BYTES_PER_LAUNCH = 1185.3e6
 GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 184.4e6
-GEMM_TRAFFIC_SOURCE_SHA256 = "384b042995f07d8ba0b57338b7f614d1167bee54df23a06018592d5a999ea74c"
+GEMM_TRAFFIC_SOURCE_SHA256 = "fbb36fc8dcdc6e9cc38d59a1b791a60627642e2130d7539903c46d4f75807015"
 
 
 def parse():

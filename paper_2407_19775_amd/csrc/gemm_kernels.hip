@@ -497,7 +497,7 @@ __device__ __forceinline__ void load_column_terms(const GemmArgs& a, const WaveP
 // kSplit: the workgroup multiplies one of a.splits ranges of K (slabs of codes and of fp16 operands alike) and leaves
 // fp32 sums.
 // ------------------------------------------------------------------------------------------------
-template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit>
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit, bool kOnce>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
   constexpr int TI = Cfg::TI, TJ = Cfg::TJ, NKS = Cfg::NKS, STAGES = Cfg::kStages;
@@ -547,10 +547,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
     srcB[j] = dma_source(a.Wt, p.n0, all_slabs, j, Cfg::kWaves, wave, lane) + (ptrdiff_t)first * kBlockBytes;
     srcWo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Wo), p.n0, a.f_slabs, j, Cfg::kWaves, wave, lane);
   }
-  // Where few tile rows share a weight panel its bytes are requested as ones that little else reads: 7B-shaped layers of 129
-  // rows 169 -> 160 us, 333 with an adapter 237 -> 231, 512 rows 215 -> 211, 1000 rows 308 -> 305; with twelve tile rows (1500
-  // rows) 440 -> 448, and the 256-row tiles of 2048 rows 491 -> 495: not there.
-  const bool weights_once = a.tiles_m <= 8;
   // request d (0 .. DMA_PER_SLAB-1) of the slab at position `pos` of the ring's sequence: the A rows first, then the
   // B rows.  kFp16 says which kind of slab that position holds (known where the request is written down, so that
   // the loop over the codes carries no choice between the two)
@@ -564,7 +560,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
       off = (d < Cfg::A_DMA ? to_more_x : to_more_w) + (ptrdiff_t)(f - crit_used) * kBlockBytes;
     if (d < Cfg::A_DMA)
       dma16((kF ? srcXo[d] : srcA[d]) + off, base + d * Cfg::kWaves * (kWave * 16));
-    else if (!kF && Cfg::BM == 128 && weights_once)
+    else if constexpr (kOnce && !kF)
       dma16_once(srcB[d - Cfg::A_DMA] + off, base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
     else
       dma16((kF ? srcWo[d - Cfg::A_DMA] : srcB[d - Cfg::A_DMA]) + off,
@@ -811,7 +807,7 @@ struct DenseCfg {
                 "LDS (the output stages need that much of it at most)");
 };
 
-template <int kBN>
+template <int kBN, bool kOnce>
 __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, int split, int8_t* smem) {
   using D = DenseCfg<kBN>;
   using Cfg = typename D::Tile;
@@ -848,8 +844,10 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
       dma16(src, dst + D::kCodes + j * Cfg::kWaves * 1024);
     } else {
       const int j = d - Cfg::A_DMA - D::X_DMA;
-      dma16_once(baseB + (size_t)s * kBlockBytes + j * Cfg::kWaves * 1024 + lane * 16,
-                        dst + D::kCodes + D::kRows + j * Cfg::kWaves * 1024);
+      const int8_t* src = baseB + (size_t)s * kBlockBytes + j * Cfg::kWaves * 1024;
+      const uint32_t to = dst + D::kCodes + D::kRows + j * Cfg::kWaves * 1024;
+      if constexpr (kOnce) dma16_once(src + lane * 16, to);
+      else dma16_scalar_base(src, lane * 16, to);
     }
   };
   auto fill_masks = [&](int s0) {
@@ -1019,7 +1017,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
 // does not receive that address by itself, and arguments arrive in vector registers: made uniform again here, so that
 // the arguments are read into scalar registers as in the kernel) and that of the LDS buffers (named in here, their
 // address would be read from memory again for every use).
-template <int kBN>
+template <int kBN, bool kOnce>
 __device__ __noinline__ void gemm_tile_dense(uint32_t args_lo, uint32_t args_hi, uint32_t lds, uint32_t bm, uint32_t bn) {
   int8_t* smem = (int8_t*)(__attribute__((address_space(3))) int8_t*)(uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
   using constant_bytes = const __attribute__((address_space(4))) char*;
@@ -1030,7 +1028,7 @@ __device__ __noinline__ void gemm_tile_dense(uint32_t args_lo, uint32_t args_hi,
   int tm, tn, split;
   if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;
   for (int n0 = tn * BN; n0 < min((tn + 1) * BN, a.N); n0 += kBN)
-    for (int m0 = tm * BM; m0 < min((tm + 1) * BM, a.M); m0 += 128) dense_tile<kBN>(a, m0, n0, split, smem);
+    for (int m0 = tm * BM; m0 < min((tm + 1) * BM, a.M); m0 += 128) dense_tile<kBN, kOnce>(a, m0, n0, split, smem);
 }
 
 template <class Cfg>
@@ -1045,7 +1043,8 @@ static int launch_lds(const GemmArgs& a) {
   return dense_critical_path(a.K, a.crit_slabs, a.dense_from, a.W_master != nullptr) ? kMostLds<Cfg> : Cfg::LDS_BYTES;
 }
 
-template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
+// kOnce: the weights requested as bytes that nothing else reads (weights_read_once)
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit, bool kOnce>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixed(const GemmArgs a) {
   const int n_out = __builtin_amdgcn_readfirstlane(*a.n_out);
   reset_column_flags(a.flag_reset, a.Kpad);
@@ -1054,16 +1053,16 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixe
     extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
     uint32_t lds = (uint32_t)(uintptr_t)smem;
     asm volatile("" : "+s"(lds));                                      // (else the compiler names it in the function after all)
-    gemm_tile_dense<Cfg::kWaves == 8 ? 256 : 128>((uint32_t)address, (uint32_t)(address >> 32), lds, Cfg::BM, Cfg::BN);
+    gemm_tile_dense<Cfg::kWaves == 8 ? 256 : 128, kOnce>((uint32_t)address, (uint32_t)(address >> 32), lds, Cfg::BM, Cfg::BN);
     return;
   }
-  gemm_tile<Cfg, kTap, kFull, kCoded, kSplit>(a);
+  gemm_tile<Cfg, kTap, kFull, kCoded, kSplit, kOnce>(a);
 }
 
 // ------------------------------------------------------------------------------------------------
 // The kernels need more LDS than a kernel gets by default; the attribute is set once per instantiation and device,
 // by prepare_gemm_kernels() (called when a workspace is set up) or else by the first launch.
-template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false, bool kOnce = false>
 static hipError_t ensure_lds_attribute() {
   // per device: the attribute belongs to the device's code object.  Two threads may both find it unset and set
   // it twice, which is harmless.
@@ -1071,47 +1070,58 @@ static hipError_t ensure_lds_attribute() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   if (attr_set[dev]) return hipSuccess;
-  const void* fn = reinterpret_cast<const void*>(&k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit>);
+  const void* fn = reinterpret_cast<const void*>(&k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit, kOnce>);
   const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMostLds<Cfg>);
   if (e == hipSuccess) attr_set[dev] = true;
   return e;
 }
 
-template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false>
+template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false, bool kOnce = false>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t stream) {
-  if (hipError_t e = ensure_lds_attribute<Cfg, kTap, kFull, kCoded, kSplit>(); e != hipSuccess) return e;
+  if (hipError_t e = ensure_lds_attribute<Cfg, kTap, kFull, kCoded, kSplit, kOnce>(); e != hipSuccess) return e;
   const int grid = ceil_div(a.tiles_m * a.tiles_n * a.splits, 8) * 8;
-  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit>), dim3(grid), dim3(Cfg::kThreads), launch_lds<Cfg>(a), stream, a);
+  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit, kOnce>), dim3(grid), dim3(Cfg::kThreads), launch_lds<Cfg>(a), stream, a);
   return hipGetLastError();
 }
 
+template <class Cfg, bool kOnce>
+static hipError_t launch_output(const GemmArgs& a, bool full, hipStream_t stream) {
+  if (a.codes || a.residual || a.gelu)
+    return full ? launch_one<Cfg, false, true, true, false, kOnce>(a, stream) : launch_one<Cfg, false, false, true, false, kOnce>(a, stream);
+  return full ? launch_one<Cfg, false, true, false, false, kOnce>(a, stream) : launch_one<Cfg, false, false, false, false, kOnce>(a, stream);
+}
 template <class Cfg>
-static hipError_t launch_cfg(GemmArgs a, hipStream_t stream) {
+constexpr bool kHasOnce = std::is_same_v<Cfg, Cfg0> || std::is_same_v<Cfg, Cfg5>;
+template <class Cfg>
+static hipError_t launch_cfg(GemmArgs a, hipStream_t stream, bool once = false) {
   a.tiles_m = ceil_div(a.M, Cfg::BM);
   a.tiles_n = ceil_div(a.N, Cfg::BN);
   a.splits = 1;
   a.slabs_per_split = a.Kpad / BK;
-  const bool full = (a.M % Cfg::BM == 0) && (a.N % Cfg::BN == 0);
-  if (a.codes || a.residual || a.gelu) {
-    if (a.codes && Cfg::BN % (1 << a.code_log_block) != 0) return hipErrorInvalidValue;   // a block would leave the tile
-    if (a.tap_acc) return launch_one<Cfg, true, false, true>(a, stream);
-    return full ? launch_one<Cfg, false, true, true>(a, stream)
-                : launch_one<Cfg, false, false, true>(a, stream);
-  }
-  if (a.tap_acc) return launch_one<Cfg, true, false, false>(a, stream);
-  return full ? launch_one<Cfg, false, true, false>(a, stream)
-              : launch_one<Cfg, false, false, false>(a, stream);
+  const bool full = (a.M % Cfg::BM == 0) && (a.N % Cfg::BN == 0), coded = a.codes || a.residual || a.gelu;
+  if (a.codes && Cfg::BN % (1 << a.code_log_block) != 0) return hipErrorInvalidValue;   // a block would leave the tile
+  if (a.tap_acc) return coded ? launch_one<Cfg, true, false, true>(a, stream) : launch_one<Cfg, true, false, false>(a, stream);
+  if constexpr (kHasOnce<Cfg>)
+    if (once) return launch_output<Cfg, true>(a, full, stream);
+  return launch_output<Cfg, false>(a, full, stream);
 }
 
 // every instantiation launch_cfg can reach
+template <class Cfg, bool kOnce>
+static hipError_t prepare_output() {
+  hipError_t e = ensure_lds_attribute<Cfg, false, true, false, false, kOnce>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, false, false, false, kOnce>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, true, true, false, kOnce>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, false, true, false, kOnce>();
+  return e;
+}
 template <class Cfg>
 static hipError_t prepare_cfg() {
   hipError_t e = ensure_lds_attribute<Cfg, true, false, false>();
-  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, true, false>();
-  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, false, false>();
   if (e == hipSuccess) e = ensure_lds_attribute<Cfg, true, false, true>();
-  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, true, true>();
-  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, false, true>();
+  if (e == hipSuccess) e = prepare_output<Cfg, false>();
+  if constexpr (kHasOnce<Cfg>)
+    if (e == hipSuccess) e = prepare_output<Cfg, true>();
   return e;
 }
 hipError_t prepare_gemm_kernels() {
@@ -1123,10 +1133,11 @@ hipError_t prepare_gemm_kernels() {
   if (e == hipSuccess) e = prepare_cfg<Cfg5>();
   if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, true, false, false, true>();
   if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, false, false, false, true>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, false, false, false, true, true>();
   return e;
 }
 
-static hipError_t launch_variant(const GemmArgs& a, int variant, hipStream_t stream) {
+static hipError_t launch_variant(const GemmArgs& a, int variant, hipStream_t stream, bool once = false) {
   // coded output with blocks wider than the 128-column tiles (the dense pass of four-wave kernels has such tiles too)
   if (a.codes && a.code_log_block > 7 && variant < 3) variant = 5;
   switch (variant) {
@@ -1134,8 +1145,8 @@ static hipError_t launch_variant(const GemmArgs& a, int variant, hipStream_t str
     case 2: return launch_cfg<Cfg2>(a, stream);
     case 3: return launch_cfg<Cfg3>(a, stream);
     case 4: return launch_cfg<Cfg4>(a, stream);
-    case 5: return launch_cfg<Cfg5>(a, stream);
-    default: return launch_cfg<Cfg0>(a, stream);
+    case 5: return launch_cfg<Cfg5>(a, stream, once);
+    default: return launch_cfg<Cfg0>(a, stream, once);
   }
 }
 
@@ -1210,8 +1221,18 @@ CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further
   return p;
 }
 
+// Weights requested as bytes that nothing else reads leave the last-level cache (256 MB) to the rest of a layer: for up to
+// four rows of tiles, and for matrices so large that the model they belong to does not stay in that cache.  Us per
+// layer of four linears (weights from memory but for hidden size 1536 and less), few critical columns, with plain / such
+// requests: hidden size 3072, 256 rows 152 / 140; 4096, 129 rows 168 / 156; 5120, 333 rows 234 / 234.  For every matrix from
+// 9 MB on: hidden size 1536 87 / 91 us at 333 rows, 2048 93 / 101 at 129 rows (from 22 MB on 92), and a call of 512 x 4096 ->
+// 4096 whose weights are in the cache 33 / 41.  More rows: 768 x 4096 -> 22016 106 / 110, 1024 x 28672 -> 8192 244 / 256.
+// (A choice between the two inside the kernel cost the walk 2 %: two instantiations.)
+bool weights_read_once(int M, int Kpad, int N) { return M > 128 && M <= 512 && (size_t)Kpad * N >= 20000000; }
+
 hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
   if (variant >= 0 && variant <= 5) return launch_variant(a, variant, stream);
+  const bool once = weights_read_once(a.M, a.Kpad, a.N);
   if (a.partial && a.splits > 1) {
     const int n_slabs = a.Kpad / BK;
     a.slabs_per_split = ceil_div(n_slabs, a.splits);
@@ -1221,7 +1242,9 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
     hipError_t e = hipSuccess;
     if (a.tap_acc) e = launch_fill_u32(reinterpret_cast<uint32_t*>(a.tap_acc), 0u, (size_t)a.M * a.tap_ld, stream);
     if (e == hipSuccess)
-      e = a.tap_acc ? launch_one<Cfg5, true, false, false, true>(a, stream) : launch_one<Cfg5, false, false, false, true>(a, stream);
+      e = a.tap_acc ? launch_one<Cfg5, true, false, false, true>(a, stream)
+          : once    ? launch_one<Cfg5, false, false, false, true, true>(a, stream)
+                    : launch_one<Cfg5, false, false, false, true>(a, stream);
     if (e != hipSuccess) return e;
     const SplitSum sum = {a.partial, a.splits, a.M, a.N, a.bias, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
                           a.codes, a.code_absmax, a.codes ? 1 << a.code_log_block : 0};
@@ -1253,8 +1276,8 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
   // tiles would need a second round and the 256 x 256 ones fit in one, the large tiles win: 4096 -> 12288 at 768 rows 61
   // against 71 us, 4096 -> 22016 at 512 rows 61 against 70.
   if (a.M > 128 && tiles_128x256 > cus) return launch_variant(a, 4, stream);
-  if (a.M > 64 && !one_round_of_small_tiles(a.M, a.N)) return launch_variant(a, 5, stream);
-  return launch_variant(a, 0, stream);
+  if (a.M > 64 && !one_round_of_small_tiles(a.M, a.N)) return launch_variant(a, 5, stream, once);
+  return launch_variant(a, 0, stream, once);
 }
 
 }  // namespace mmd8
