@@ -547,16 +547,9 @@ __global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ 
     // the barrier they would double the registers)
     asm volatile("" : "+v"(piece), "+v"(a[q]), "+v"(b[q]));
     if (piece >= n_pieces) break;
-    uint32_t out[4];
+    uint32_t out[4];                                               // (entries at or above the threshold: any byte, cleared later)
 #pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      out[w] = to_code_byte(half_lo_to_float(a[q][2 * w]), scale) | (to_code_byte(half_hi_to_float(a[q][2 * w]), scale) << 8) |
-               (to_code_byte(half_lo_to_float(a[q][2 * w + 1]), scale) << 16) |
-               (to_code_byte(half_hi_to_float(a[q][2 * w + 1]), scale) << 24);
-      out[2 + w] = to_code_byte(half_lo_to_float(b[q][2 * w]), scale) | (to_code_byte(half_hi_to_float(b[q][2 * w]), scale) << 8) |
-                   (to_code_byte(half_lo_to_float(b[q][2 * w + 1]), scale) << 16) |
-                   (to_code_byte(half_hi_to_float(b[q][2 * w + 1]), scale) << 24);
-    }
+    for (int w = 0; w < 2; ++w) out[w] = to_code_word(a[q][2 * w], a[q][2 * w + 1], scale), out[2 + w] = to_code_word(b[q][2 * w], b[q][2 * w + 1], scale);
     const uint32_t in_k = piece < k_pieces ? 0xffffffffu : 0u;     // the K padding holds zeros
     const v4u v = v4u{out[0] & in_k, out[1] & in_k, out[2] & in_k, out[3] & in_k};
     *reinterpret_cast<v4u*>(Xq + packed_chunk_offset(m, piece >> 2, piece & 3, n_slabs)) = v;
