@@ -419,15 +419,14 @@ __device__ inline int row_quad_of_block(int b, int n_blocks) {
 }
 
 template <int kWaves, int kPasses, bool kFromCodes>
-__global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ X, int M, int K, int ldx, uint32_t th,
-                                                         int n_slabs, uint8_t* __restrict__ flag,
-                                                         float* __restrict__ r_out, int8_t* __restrict__ Xq,
-                                                         int8_t* __restrict__ tap_xq, const CodedInput coded) {
+__device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __restrict__ X, int M, int K, int ldx, uint32_t th,
+                                           int n_slabs, uint8_t* __restrict__ flag, float* __restrict__ r_out,
+                                           int8_t* __restrict__ Xq, int8_t* __restrict__ tap_xq, const CodedInput& coded) {
   __shared__ uint32_t s_part[kWaves][4];
   __shared__ float s_T[kFromCodes ? 256 : 1];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int j = lane & 3, i = lane >> 2;
-  const int m = row_quad_of_block(blockIdx.x, gridDim.x) * 4 + j;
+  const int m = row_quad_of_block(block, n_blocks) * 4 + j;
   const bool row_ok = m < M;
   const int Kpad = n_slabs * kSlabBytes;
   const int n_pieces = Kpad / 16, k_pieces = K / 16;
@@ -556,6 +555,35 @@ __global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ 
     if (tap_xq && piece < k_pieces) *reinterpret_cast<v4u*>(tap_xq + (size_t)m * K + piece * 16) = v;
     __builtin_amdgcn_sched_barrier(0);                    // one piece at a time: bounded registers
   }
+}
+
+template <int kWaves, int kPasses, bool kFromCodes>
+__global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ X, int M, int K, int ldx, uint32_t th,
+                                                         int n_slabs, uint8_t* __restrict__ flag,
+                                                         float* __restrict__ r_out, int8_t* __restrict__ Xq,
+                                                         int8_t* __restrict__ tap_xq, const CodedInput coded) {
+  prep_block<kWaves, kPasses, kFromCodes>(blockIdx.x, gridDim.x, X, M, K, ldx, th, n_slabs, flag, r_out, Xq, tap_xq, coded);
+}
+// The same next to an adapter's down-projection, which needs nothing of it: the first workgroups take the low-rank product (K in
+// ranges, whose sums the next launch adds) and the copy of its weight side, a multiple of eight of them, so that the rows keep their XCDs.
+// Both kernels end when the preparation does (6.5 us at 333 x 4096; in the second launch, K in one range, the product took that one
+// from 5.4 to 10.8).  7B-shaped layers, down-projection in the second launch / here: 333 rows with rank 16 219.8 / 202.6 us, 129
+// rows with rank 64 214 / 174, 2048 rows with rank 64 534 / 511, 4096 rows the same.  Three and four rank tiles take a step at a time:
+// with two in flight (120 registers) 4096 rows with rank 64 took 1 % longer than in the second launch.
+template <int kWaves, int kPasses, int kTiles>
+__global__ __launch_bounds__(kWaves * kWave) void k_prep_lora(uint16_t* __restrict__ X, int M, int K, int ldx, uint32_t th,
+                                                              int n_slabs, uint8_t* __restrict__ flag,
+                                                              float* __restrict__ r_out, int8_t* __restrict__ Xq,
+                                                              int8_t* __restrict__ tap_xq, const LoraArgs l, int lora_blocks,
+                                                              int t_blocks, int splits, int steps_per_split, float* P) {
+  constexpr int kLoraWaves = kWaves < 8 ? kWaves : 8;
+  if ((int)blockIdx.x < lora_blocks) {
+    if ((int)threadIdx.x < kLoraWaves * kWave)
+      lora_down_block<kTiles, kLoraWaves, (kTiles > 2 ? 1 : kWaves <= 4 ? 4 : 2)>(l, blockIdx.x, t_blocks, splits, steps_per_split, P);
+    return;
+  }
+  prep_block<kWaves, kPasses, false>((int)blockIdx.x - lora_blocks, (int)gridDim.x - lora_blocks, X, M, K, ldx, th, n_slabs, flag, r_out,
+                                     Xq, tap_xq, CodedInput{});
 }
 
 // The same for the decode kernels (at most 128 rows), which decide on the weight side which columns are critical: the
@@ -689,19 +717,16 @@ __global__ __launch_bounds__(kThreads) void k_outlier_columns(const uint16_t* __
                                                               int clear_units, const PackOutliers o) {
   outlier_columns_block(blockIdx.x, X, M, K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o);
 }
-// The same next to an adapter's down-projection, which needs nothing of it and is what takes the time (16 rows of X and all
-// of A through one compute unit: 4.5 us at K = 4096, on a few of them).  Both 10 us, 5.5 + 9.7 one after the other: a 7B-shaped
-// layer of 333 rows with rank 16 235 -> 214 us, 129 rows 213 -> 182, 2048 rows with rank 32 549 -> 530.
-template <int kTiles>
+// The same next to the sums of an adapter's down-projection (the first workgroups).
 __global__ __launch_bounds__(kThreads) void k_outlier_columns_lora(const uint16_t* __restrict__ X, int M, int K, int ldx,
                                                                    const uint8_t* __restrict__ flag, int8_t* __restrict__ Xq,
                                                                    int n_slabs, int8_t* __restrict__ tap_xq, int slab_blocks,
-                                                                   int clear_units, const PackOutliers o, const LoraArgs l, int lora_blocks,
-                                                                   int t_blocks, int splits, int steps_per_split, float* P) {
-  if ((int)blockIdx.x < lora_blocks)
-    lora_down_block<kTiles, kThreads / kWave>(l, blockIdx.x, t_blocks, splits, steps_per_split, P);
+                                                                   int clear_units, const PackOutliers o, const LoraArgs l, int sum_blocks,
+                                                                   int splits, const float* P) {
+  if ((int)blockIdx.x < sum_blocks)
+    reduce_low_rank_activation(l, blockIdx.x * kThreads + threadIdx.x, splits, P);
   else
-    outlier_columns_block((int)blockIdx.x - lora_blocks, X, M, K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o);
+    outlier_columns_block((int)blockIdx.x - sum_blocks, X, M, K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -766,9 +791,29 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
   const int n_slabs = Kpad / kSlabBytes, n_pieces = Kpad / 16;
   const dim3 grid(ceil_div(M, 4));
   const CodedInput ci = coded ? *coded : CodedInput{};
+  LoraPlan plan = {};
+  int t_blocks = 0, lora_tiles = 0;
+  if (lora) {
+    plan = plan_lora(lora->M, lora->K);
+    t_blocks = ceil_div(lora->M, kLoraRows);
+    lora_tiles = ceil_div(lora->r, 16);
+    if (coded || plan.decode || lora_tiles < 1 || lora_tiles > 4 || (plan.splits > 1 && !lora_partial)) return hipErrorInvalidValue;
+  }
+  // (a workgroup past the copy of the weight side does nothing)
+#define MMD8_PREP_LORA(W_, P_, T_)                                                                                        \
+  case T_: {                                                                                                              \
+    const int copy_blocks = lora->Wo ? ceil_div(lora->N * 4 * lora_slabs(lora->r), (W_ < 8 ? W_ : 8) * kWave) : 0;         \
+    const int lora_blocks = round_up(t_blocks * plan.splits + copy_blocks, 8);                                            \
+    hipLaunchKernelGGL((k_prep_lora<W_, P_, T_>), dim3(lora_blocks + grid.x), dim3(W_ * kWave), 0, stream, X, M, K, ldx, th, n_slabs, \
+                       flag, r, Xq, tap_xq, *lora, lora_blocks, t_blocks, plan.splits, plan.steps_per_split,              \
+                       plan.splits > 1 ? lora_partial : nullptr);                                                         \
+    break;                                                                                                                \
+  }
 #define MMD8_PREP(W_, P_)                                                                                                \
   do {                                                                                                                   \
-    if (coded)                                                                                                           \
+    if (lora) {                                                                                                          \
+      switch (lora_tiles) { MMD8_PREP_LORA(W_, P_, 1) MMD8_PREP_LORA(W_, P_, 2) MMD8_PREP_LORA(W_, P_, 3) MMD8_PREP_LORA(W_, P_, 4) } \
+    } else if (coded)                                                                                                           \
       hipLaunchKernelGGL((k_prep<W_, P_, true>), grid, dim3(W_ * kWave), 0, stream, X, M, K, ldx, th, n_slabs, flag, r, \
                          Xq, tap_xq, ci);                                                                                \
     else                                                                                                                 \
@@ -781,9 +826,11 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
   else if (n_pieces <= 512) MMD8_PREP(8, 4);
   else if (n_pieces <= 1024) MMD8_PREP(16, 4);
   else if (coded) return hipErrorInvalidValue;                     // the caller decodes first (prep_from_codes_fits)
+  else if (lora) switch (lora_tiles) { MMD8_PREP_LORA(16, 8, 1) MMD8_PREP_LORA(16, 8, 2) MMD8_PREP_LORA(16, 8, 3) MMD8_PREP_LORA(16, 8, 4) }
   else hipLaunchKernelGGL((k_prep<16, 8, false>), grid, dim3(16 * kWave), 0, stream, X, M, K, ldx, th, n_slabs, flag, r, Xq,
                           tap_xq, ci);
 #undef MMD8_PREP
+#undef MMD8_PREP_LORA
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (event_mid && (e = hipEventRecord(static_cast<hipEvent_t>(event_mid), stream)) != hipSuccess) return e;
@@ -799,25 +846,11 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
   const int few = max(16, round_up(ceil_div(row_groups * units, max(1, device_cu_count() / 4)), 4));
   const int clear_units = groups_256 <= 16 ? few : kThreads * merge;
   const int clear_blocks = row_groups * ceil_div(units, clear_units);
-  if (lora) {
-    const LoraPlan plan = plan_lora(lora->M, lora->K);
-    if (plan.decode) return hipErrorInvalidValue;
-    const int t_blocks = ceil_div(lora->M, kLoraRows);
-    const int lora_blocks = t_blocks * plan.splits + (lora->Wo ? ceil_div(lora->N * 4 * lora_slabs(lora->r), kThreads) : 0);
-#define MMD8_OUTLIER_LORA(T_)                                                                                                 \
-  hipLaunchKernelGGL(k_outlier_columns_lora<T_>, dim3(lora_blocks + slab_blocks + clear_blocks), dim3(kThreads), 0, stream, X, M, \
-                     K, ldx, flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o, *lora, lora_blocks, t_blocks, plan.splits,     \
-                     plan.steps_per_split, plan.splits > 1 ? lora_partial : nullptr)
-    switch (ceil_div(lora->r, 16)) {
-      case 1: MMD8_OUTLIER_LORA(1); break;
-      case 2: MMD8_OUTLIER_LORA(2); break;
-      case 3: MMD8_OUTLIER_LORA(3); break;
-      case 4: MMD8_OUTLIER_LORA(4); break;
-      default: return hipErrorInvalidValue;
-    }
-#undef MMD8_OUTLIER_LORA
-    e = hipGetLastError();
-    return e == hipSuccess ? launch_lora_reduce(*lora, plan, lora_partial, stream) : e;
+  if (lora && plan.splits > 1) {
+    const int sum_blocks = ceil_div(M * 4 * lora_slabs(lora->r), kThreads);
+    hipLaunchKernelGGL(k_outlier_columns_lora, dim3(sum_blocks + slab_blocks + clear_blocks), dim3(kThreads), 0, stream, X, M, K, ldx,
+                       flag, Xq, n_slabs, tap_xq, slab_blocks, clear_units, o, *lora, sum_blocks, plan.splits, lora_partial);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL(k_outlier_columns, dim3(slab_blocks + clear_blocks), dim3(kThreads), 0, stream, X, M, K, ldx, flag, Xq,
                      n_slabs, tap_xq, slab_blocks, clear_units, o);

@@ -42,7 +42,5 @@ __device__ __forceinline__ uint32_t sum_low_rank_activation(const float* __restr
 }
 // T for every row (and, where Xo is given, T and B in the GEMM's slab layout)
 hipError_t launch_lora_down(const LoraArgs& a, const LoraPlan& plan, float* partial, hipStream_t stream);
-// its second kernel alone (nothing to do where K is not split)
-hipError_t launch_lora_reduce(const LoraArgs& a, const LoraPlan& plan, const float* partial, hipStream_t stream);
 
 }  // namespace mmd8

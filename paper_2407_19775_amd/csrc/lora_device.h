@@ -14,9 +14,9 @@ constexpr int kLoraRows = 16;          // rows of X per workgroup
 // MFMA operands of 8 (which 8 columns meet in one MFMA does not matter: both operands use the same
 // assignment).  A^T is the first operand, X^T the second, so a lane ends up with four consecutive
 // rank indices of one row.  The waves' partial sums meet in LDS and are added in wave order; with P
-// null (one range) the sum is rounded and stored, else it goes to P[range][m][64] as fp32, and k_lora_reduce, or for at most
-// 128 rows the kernel that adds the low-rank term (sum_low_rank_activation), adds the ranges in index order (so the result
-// does not depend on timing) and rounds.
+// null (one range) the sum is rounded and stored, else it goes to P[range][m][64] as fp32, and a later kernel adds the ranges in
+// index order (so the result does not depend on timing) and rounds: the one that clears the critical columns or k_lora_reduce
+// (reduce_low_rank_activation), for at most 128 rows the one that adds the low-rank term (sum_low_rank_activation).
 // Workgroups from t_blocks * splits on copy B into the weight-side slabs.
 // eight sums of row m (rank indices 8 ch .. + 8; exact zeros past the rank): rounded to fp16 and stored as
 // part of T, of the caller's copy of T and of the activation-side slabs
@@ -32,14 +32,33 @@ __device__ inline void store_low_rank_activation(const LoraArgs& a, int m, int c
     *reinterpret_cast<v4u*>(reinterpret_cast<int8_t*>(a.Xo) + packed_chunk_offset(m, a.crit_slabs + ch / 4, ch % 4, a.f_slabs)) = v;
 }
 
+// Item (row, 8 rank indices) of T: the ranges' sums in index order, then as with one range.
+__device__ inline void reduce_low_rank_activation(const LoraArgs& a, int item, int splits, const float* __restrict__ P) {
+  const int n_chunks = 4 * lora_slabs(a.r);
+  if (item >= a.M * n_chunks) return;
+  const int m = item / n_chunks, ch = item % n_chunks;
+  float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int s = 0; s < splits; ++s) {
+    const float* p = P + ((size_t)s * a.M + m) * kLoraMaxRank + 8 * ch;
+    const v4f lo = *reinterpret_cast<const v4f*>(p), hi = *reinterpret_cast<const v4f*>(p + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sum[e] += lo[e];
+      sum[4 + e] += hi[e];
+    }
+  }
+  store_low_rank_activation(a, m, ch, sum);
+}
+
 // What lane group kq reads in 64-column step s of a range that ends at step `end`: 16 columns, lora_lane_column + lora_step_column
 // on.  A group beyond the range or the end of the row (lora_reads false) masks what it reads, and that is within the row too.
 __host__ __device__ __forceinline__ bool lora_reads(int s, int end, int kq, int K) { return s < end && 64 * s + 16 * kq < K; }
 __host__ __device__ __forceinline__ int lora_lane_column(int kq, int K) { return 16 * kq < K ? 16 * kq : K - 16; }
 __host__ __device__ __forceinline__ int lora_step_column(int s, bool reads) { return reads ? 64 * s : 0; }
 
-// kTiles: 16-wide tiles of the rank, ceil(r / 16).  Called by every thread of a workgroup of kWaves waves.
-template <int kTiles, int kWaves>
+// kTiles: 16-wide tiles of the rank, ceil(r / 16); kU: steps whose loads a wave has in flight together.  Called by every
+// thread of a workgroup of kWaves waves.
+template <int kTiles, int kWaves, int kU>
 __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, int t_blocks, int splits, int steps_per_split, float* __restrict__ P) {
   constexpr int kCols = kTiles * 16, kThreadsOfBlock = kWaves * kWave;
   __shared__ __attribute__((aligned(16))) float s_part[kWaves][kLoraRows][kCols];
@@ -47,7 +66,7 @@ __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, in
   const int n_chunks = 4 * lora_slabs(a.r);                         // 8-column chunks of the slabs
   if (block >= t_blocks * splits) {
     const int item = (block - t_blocks * splits) * kThreadsOfBlock + (int)threadIdx.x;
-    if (item >= a.N * n_chunks) return;
+    if (a.Wo == nullptr || item >= a.N * n_chunks) return;
     const int ch = item / a.N, n = item % a.N;
     v4u v = {0, 0, 0, 0};
     if (8 * ch < a.r) v = *reinterpret_cast<const v4u*>(a.B + (size_t)n * a.r + 8 * ch);
@@ -72,12 +91,11 @@ __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, in
   for (int t = 0; t < kTiles; ++t) acc[t] = v4f{0, 0, 0, 0};
 
   const int steps = min(ceil_div(a.K, 64), (split + 1) * steps_per_split);   // end of this range
-  constexpr int U = (kTiles <= 2 ? 4 : 2) * (kWaves <= 4 && kTiles == 1 ? 2 : 1);
-  for (int s0 = split * steps_per_split + wave; s0 < steps; s0 += kWaves * U) {
-    v4u xf[U][2], af[U][kTiles][2];
+  for (int s0 = split * steps_per_split + wave; s0 < steps; s0 += kWaves * kU) {
+    v4u xf[kU][2], af[kU][kTiles][2];
     // every load is issued before the first use; a step past the end re-reads step 0 and is masked
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < kU; ++u) {
       const int s = s0 + u * kWaves;
       const bool ok = lora_reads(s, steps, kq, a.K);
       const int k = lora_step_column(s, ok);
@@ -92,7 +110,7 @@ __device__ __forceinline__ void lora_down_block(const LoraArgs& a, int block, in
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < kU; ++u)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll

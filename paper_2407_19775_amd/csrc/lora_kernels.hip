@@ -16,26 +16,12 @@ constexpr int kLoraThreads = 512;
 template <int kTiles>
 __global__ __launch_bounds__(kLoraThreads) void k_lora_down(const LoraArgs a, int t_blocks, int splits, int steps_per_split,
                                                             float* __restrict__ P) {
-  lora_down_block<kTiles, kLoraThreads / kWave>(a, blockIdx.x, t_blocks, splits, steps_per_split, P);
+  lora_down_block<kTiles, kLoraThreads / kWave, (kTiles <= 2 ? 4 : 2)>(a, blockIdx.x, t_blocks, splits, steps_per_split, P);
 }
 
-// one thread per (row, 8 rank indices): the ranges' sums in index order, then as in the one-range case
+// one thread per (row, 8 rank indices)
 __global__ __launch_bounds__(256) void k_lora_reduce(const LoraArgs a, int splits, const float* __restrict__ P) {
-  const int n_chunks = 4 * lora_slabs(a.r);
-  const int item = blockIdx.x * 256 + threadIdx.x;
-  if (item >= a.M * n_chunks) return;
-  const int m = item / n_chunks, ch = item % n_chunks;
-  float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int s = 0; s < splits; ++s) {
-    const float* p = P + ((size_t)s * a.M + m) * kLoraMaxRank + 8 * ch;
-    const v4f lo = *reinterpret_cast<const v4f*>(p), hi = *reinterpret_cast<const v4f*>(p + 4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      sum[e] += lo[e];
-      sum[4 + e] += hi[e];
-    }
-  }
-  store_low_rank_activation(a, m, ch, sum);
+  reduce_low_rank_activation(a, blockIdx.x * 256 + threadIdx.x, splits, P);
 }
 }  // namespace
 
@@ -43,16 +29,15 @@ __global__ __launch_bounds__(256) void k_lora_reduce(const LoraArgs a, int split
 int lora_read_column(int s, int end, int kq, int K) { return lora_lane_column(kq, K) + lora_step_column(s, lora_reads(s, end, kq, K)); }
 
 LoraPlan plan_lora(int M, int K) {
-  // One range of K per 16-row tile unless K is long (8192 columns or more): every kernel here has a floor
-  // of a few microseconds, so the second kernel that adds the ranges must save more than that.  Then K is
-  // split until there are two workgroups per compute unit, every range at least sixteen 64-column steps.
+  // K is split until there are two workgroups per compute unit, every range at least sixteen 64-column steps: the sums are
+  // added in a launch that runs anyway.
   const int t_blocks = ceil_div(M, kLoraRows), steps = ceil_div(K, 64), cus = device_cu_count();
   // Up to 128 rows are a few tiles, and 16 rows and A through one compute unit take 4.5 us at K = 4096: there the ranges
   // are short (four steps) and their sums are added by the kernel that needs them, without a launch in between (7B-shaped layer with rank 16:
   // one row 74 -> 61.5 us, 32 rows 128 -> 112, 128 rows 198 -> 184; rank 64 at 64 rows 265 -> 179).
   LoraPlan p;
   p.decode = M <= 128;
-  const int want = p.decode ? max(1, min(steps / 4, kLoraDecodeSplits)) : steps < 128 ? 1 : max(1, min(min(2 * cus / t_blocks, steps / 16), 32));
+  const int want = p.decode ? max(1, min(steps / 4, kLoraDecodeSplits)) : max(1, min(min(2 * cus / t_blocks, steps / 16), 32));
   p.steps_per_split = ceil_div(steps, want);
   p.splits = ceil_div(steps, p.steps_per_split);
   p.partial_bytes = p.splits > 1 || p.decode ? (size_t)p.splits * M * kLoraMaxRank * sizeof(float) : 0;
@@ -72,11 +57,7 @@ hipError_t launch_lora_down(const LoraArgs& a, const LoraPlan& plan, float* part
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();
-  return e == hipSuccess ? launch_lora_reduce(a, plan, partial, stream) : e;
-}
-
-hipError_t launch_lora_reduce(const LoraArgs& a, const LoraPlan& plan, const float* partial, hipStream_t stream) {
-  if (plan.splits == 1 || plan.decode) return hipSuccess;
+  if (e != hipSuccess || plan.splits == 1 || plan.decode) return e;
   hipLaunchKernelGGL(k_lora_reduce, dim3(ceil_div(a.M * 4 * lora_slabs(a.r), 256)), dim3(256), 0, stream, a, plan.splits, partial);
   return hipGetLastError();
 }
