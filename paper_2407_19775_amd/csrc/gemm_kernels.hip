@@ -1011,20 +1011,13 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
     store_tile<Cfg, false>(a, p, acc, bn, smem, wave);
 }
 
-// ... as a function of its own: the kernels sit at the edge of their register budget, and with this rarely taken path
-// compiled into the same body every one of them spilled registers.  It walks the 128-row pieces of the kernel's
-// BM x BN tile.  Its address arguments are that of the kernel's own arguments where the launch put them (a function
-// does not receive that address by itself, and arguments arrive in vector registers: made uniform again here, so that
-// the arguments are read into scalar registers as in the kernel) and that of the LDS buffers (named in here, their
-// address would be read from memory again for every use).
+// ... over the 128-row pieces of the kernel's BM x BN tile.  The walk is part of the kernel's body, and reads the kernel's
+// arguments through an address that the compiler cannot see through, where they are needed: what it computes from them is then
+// not shared with the other way through the kernel, whose registers it would take.  (As a function of its own it saved and restored 120
+// registers a lane through scratch, 24 to 63 MB of writes a launch.)  The address of the LDS buffers is handed on as a number: named,
+// it would be read from memory again for every use.
 template <int kBN, bool kOnce>
-__device__ __noinline__ void gemm_tile_dense(uint32_t args_lo, uint32_t args_hi, uint32_t lds, uint32_t bm, uint32_t bn) {
-  int8_t* smem = (int8_t*)(__attribute__((address_space(3))) int8_t*)(uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
-  using constant_bytes = const __attribute__((address_space(4))) char*;
-  const uint64_t address = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)args_lo) |
-                           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)args_hi) << 32;
-  const GemmArgs a = *(const GemmArgs*)(constant_bytes)address;
-  const int BM = __builtin_amdgcn_readfirstlane((int)bm), BN = __builtin_amdgcn_readfirstlane((int)bn);
+__device__ __forceinline__ void gemm_tile_dense(const GemmArgs& a, int8_t* smem, int BM, int BN) {
   int tm, tn, split;
   if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;
   for (int n0 = tn * BN; n0 < min((tn + 1) * BN, a.N); n0 += kBN)
@@ -1049,11 +1042,13 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixe
   const int n_out = __builtin_amdgcn_readfirstlane(*a.n_out);
   reset_column_flags(a.flag_reset, a.Kpad);
   if (dense_critical_path(n_out, a.crit_slabs, a.dense_from, a.W_master != nullptr)) {
-    const uint64_t address = (uint64_t)(const char*)__builtin_amdgcn_kernarg_segment_ptr();   // `a` is the first argument
     extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+    uint64_t address = (uint64_t)(const char*)__builtin_amdgcn_kernarg_segment_ptr();   // `a` is the first argument
     uint32_t lds = (uint32_t)(uintptr_t)smem;
-    asm volatile("" : "+s"(lds));                                      // (else the compiler names it in the function after all)
-    gemm_tile_dense<Cfg::kWaves == 8 ? 256 : 128, kOnce>((uint32_t)address, (uint32_t)(address >> 32), lds, Cfg::BM, Cfg::BN);
+    asm volatile("" : "+s"(address), "+s"(lds));
+    using constant_bytes = const __attribute__((address_space(4))) char*;
+    gemm_tile_dense<Cfg::kWaves == 8 ? 256 : 128, kOnce>(*(const GemmArgs*)(constant_bytes)address,
+                                                         (int8_t*)(__attribute__((address_space(3))) int8_t*)lds, Cfg::BM, Cfg::BN);
     return;
   }
   gemm_tile<Cfg, kTap, kFull, kCoded, kSplit, kOnce>(a);
