@@ -477,16 +477,59 @@ __device__ __forceinline__ void store_partial(const GemmArgs& a, const WavePos<C
     }
 }
 
+// The scales and biases of a lane's columns: asked for by the constructor, waited for where they are first used (`use`).
 template <class Cfg>
-__device__ __forceinline__ void load_column_terms(const GemmArgs& a, const WavePos<Cfg>& p, float (&cs)[Cfg::TJ],
-                                         float (&bn)[Cfg::TJ]) {
+struct ColumnTerms {
+  float c[Cfg::TJ];
+  uint32_t b[Cfg::TJ];
+  __device__ __forceinline__ ColumnTerms(const GemmArgs& a, const WavePos<Cfg>& p) {
 #pragma unroll
-  for (int j = 0; j < Cfg::TJ; ++j) {
-    const int n = min(p.nw + j * 32 + p.lr, a.N - 1);
-    cs[j] = a.c[n] / 16129.0f;
-    bn[j] = a.bias ? half_lo_to_float(a.bias[n]) : 0.0f;
+    for (int j = 0; j < Cfg::TJ; ++j) c[j] = a.c[min(p.nw + j * 32 + p.lr, a.N - 1)];
+#pragma unroll
+    for (int j = 0; j < Cfg::TJ; ++j) b[j] = a.bias ? a.bias[min(p.nw + j * 32 + p.lr, a.N - 1)] : 0u;
   }
-}
+  __device__ __forceinline__ void use(float (&cs)[Cfg::TJ], float (&bn)[Cfg::TJ]) {
+#pragma unroll
+    for (int j = 0; j < Cfg::TJ; ++j) {
+      asm volatile("" : "+v"(c[j]), "+v"(b[j]));                      // (the division and the conversion stay behind this point)
+      cs[j] = c[j] / 16129.0f;
+      bn[j] = half_lo_to_float(b[j]);
+    }
+  }
+};
+
+// The requests of a tile's slabs of codes.  Instruction j of a wave fills LDS rows [(j kWaves + wave) ROWS_PER_DMA,
+// +ROWS_PER_DMA) of the operand tile: 1 KB, contiguous in HBM and in LDS.
+template <class Cfg, bool kOnce>
+struct CodeRequests {
+  uint32_t lds;
+  const int8_t* srcA[Cfg::A_DMA];
+  const int8_t* srcB[Cfg::B_DMA];
+  __device__ __forceinline__ CodeRequests(const GemmArgs& a, const WavePos<Cfg>& p, int wave, int first, uint32_t lds0)
+      : lds(lds0 + wave * (kWave * 16)) {
+    const int all_slabs = a.Kpad / BK;
+#pragma unroll
+    for (int j = 0; j < Cfg::A_DMA; ++j)
+      srcA[j] = dma_source(a.Xq, p.m0, all_slabs, j, Cfg::kWaves, wave, p.lane) + (ptrdiff_t)first * kBlockBytes;
+#pragma unroll
+    for (int j = 0; j < Cfg::B_DMA; ++j)
+      srcB[j] = dma_source(a.Wt, p.n0, all_slabs, j, Cfg::kWaves, wave, p.lane) + (ptrdiff_t)first * kBlockBytes;
+  }
+  // request d (0 .. DMA_PER_SLAB - 1) of the slab `pos` of the range: the A rows first, then the B rows
+  __device__ __forceinline__ void issue(int pos, int stage, int d) const {
+    const uint32_t base = lds + stage * Cfg::STAGE_BYTES;
+    const ptrdiff_t off = (ptrdiff_t)pos * kBlockBytes;
+    if (d < Cfg::A_DMA)
+      dma16(srcA[d] + off, base + d * Cfg::kWaves * (kWave * 16));
+    else if constexpr (kOnce)
+      dma16_once(srcB[d - Cfg::A_DMA] + off, base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
+    else
+      dma16(srcB[d - Cfg::A_DMA] + off, base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
+  }
+};
+// Slabs that a workgroup requests before anything else, the count of critical columns included, on which the rest of its
+// way depends (gemm_tile, dense_tile).
+__device__ inline int early_slabs(int n_slabs) { return n_slabs < 2 ? 1 : 2; }
 
 // ------------------------------------------------------------------------------------------------
 // One tile: the slabs of codes, then those of fp16 operands, then the epilogue.
@@ -498,20 +541,11 @@ __device__ __forceinline__ void load_column_terms(const GemmArgs& a, const WaveP
 // fp32 sums.
 // ------------------------------------------------------------------------------------------------
 template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit, bool kOnce>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& a, const WavePos<Cfg>& p, int wave, int split, int n_slabs, int n_out,
+                                          const CodeRequests<Cfg, kOnce>& codes_of) {
   extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
   constexpr int TI = Cfg::TI, TJ = Cfg::TJ, NKS = Cfg::NKS, STAGES = Cfg::kStages;
-
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  int tm, tn, split;
-  if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;
-  const WavePos<Cfg> p(tm * Cfg::BM, tn * Cfg::BN, wave, lane);
-  const int all_slabs = a.Kpad / BK;
-  // this workgroup's slabs of codes
-  const int first = kSplit ? split * a.slabs_per_split : 0;
-  const int n_slabs = kSplit ? min(a.slabs_per_split, all_slabs - first) : all_slabs;
-  const int n_out = __builtin_amdgcn_readfirstlane(*a.n_out);
+  ColumnTerms<Cfg> column_terms(a, p);
   // Behind the slabs of codes, through the same ring: the fp16 slabs of the critical columns that are in use (32
   // columns each: at most crit_slabs of them in Xo / Wo, then at most g_slabs further ones in Xg / Wg; columns
   // beyond those are gathered after the loop) and those of a low-rank adapter (T on the activation side, B on the
@@ -529,42 +563,28 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   const ptrdiff_t to_more_w = (ptrdiff_t)(reinterpret_cast<uintptr_t>(a.Wg) - reinterpret_cast<uintptr_t>(a.Wo)) +
                               (ptrdiff_t)(p.n0 >> 8) * (a.g_slabs - a.f_slabs) * kBlockBytes;
 
-  // ---- DMA plan of this lane: instruction j of this wave fills LDS rows
-  // [(j kWaves + wave) ROWS_PER_DMA, +ROWS_PER_DMA) of the operand tile: 1 KB, contiguous in
-  // HBM and in LDS.
-  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
-  const int8_t* srcA[Cfg::A_DMA];
-  const int8_t* srcB[Cfg::B_DMA];
+  // ---- the fp16 slabs' sources, as those of the codes
   const int8_t* srcXo[Cfg::A_DMA];
   const int8_t* srcWo[Cfg::B_DMA];
 #pragma unroll
-  for (int j = 0; j < Cfg::A_DMA; ++j) {
-    srcA[j] = dma_source(a.Xq, p.m0, all_slabs, j, Cfg::kWaves, wave, lane) + (ptrdiff_t)first * kBlockBytes;
-    srcXo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Xo), p.m0, a.f_slabs, j, Cfg::kWaves, wave, lane);
-  }
+  for (int j = 0; j < Cfg::A_DMA; ++j) srcXo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Xo), p.m0, a.f_slabs, j, Cfg::kWaves, wave, p.lane);
 #pragma unroll
-  for (int j = 0; j < Cfg::B_DMA; ++j) {
-    srcB[j] = dma_source(a.Wt, p.n0, all_slabs, j, Cfg::kWaves, wave, lane) + (ptrdiff_t)first * kBlockBytes;
-    srcWo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Wo), p.n0, a.f_slabs, j, Cfg::kWaves, wave, lane);
-  }
+  for (int j = 0; j < Cfg::B_DMA; ++j) srcWo[j] = dma_source(reinterpret_cast<const int8_t*>(a.Wo), p.n0, a.f_slabs, j, Cfg::kWaves, wave, p.lane);
   // request d (0 .. DMA_PER_SLAB-1) of the slab at position `pos` of the ring's sequence: the A rows first, then the
   // B rows.  kFp16 says which kind of slab that position holds (known where the request is written down, so that
   // the loop over the codes carries no choice between the two)
   auto issue_dma = [&](int pos, int stage, int d, auto fp16_tag) {
-    constexpr bool kF = decltype(fp16_tag)::value;
-    const uint32_t base = lds0 + stage * Cfg::STAGE_BYTES + wave * (kWave * 16);
+    if constexpr (!decltype(fp16_tag)::value) return codes_of.issue(pos, stage, d);
+    const uint32_t base = codes_of.lds + stage * Cfg::STAGE_BYTES;
     const int f = pos - n_slabs + first_fp16;                       // among the fp16 slabs in use
     // its place: slab f of Xo / Wo, slab f - crit_used of Xg / Wg, or an adapter's slab behind the crit_slabs of Xo / Wo
-    ptrdiff_t off = (ptrdiff_t)(!kF ? pos : f < crit_used ? f : f - crit_used - more_used + a.crit_slabs) * kBlockBytes;
-    if (kF && f >= crit_used && f < crit_used + more_used)
+    ptrdiff_t off = (ptrdiff_t)(f < crit_used ? f : f - crit_used - more_used + a.crit_slabs) * kBlockBytes;
+    if (f >= crit_used && f < crit_used + more_used)
       off = (d < Cfg::A_DMA ? to_more_x : to_more_w) + (ptrdiff_t)(f - crit_used) * kBlockBytes;
     if (d < Cfg::A_DMA)
-      dma16((kF ? srcXo[d] : srcA[d]) + off, base + d * Cfg::kWaves * (kWave * 16));
-    else if constexpr (kOnce && !kF)
-      dma16_once(srcB[d - Cfg::A_DMA] + off, base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
+      dma16(srcXo[d] + off, base + d * Cfg::kWaves * (kWave * 16));
     else
-      dma16((kF ? srcWo[d - Cfg::A_DMA] : srcB[d - Cfg::A_DMA]) + off,
-            base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
+      dma16(srcWo[d - Cfg::A_DMA] + off, base + Cfg::A_BYTES + (d - Cfg::A_DMA) * Cfg::kWaves * (kWave * 16));
   };
   auto issue_slab = [&](int pos, int stage) {
 #pragma unroll
@@ -619,8 +639,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   static_assert(DPS_ >= 1 && DPS_ <= SLOTS, "request spreading");
   // requests of the iteration that are out before the wait in the last k-step (slot (NKS-1) MFMAS)
   constexpr int kBeforeWait = ((NKS - 1) * MFMAS * DPS_ + SLOTS - 1) / SLOTS;
-  float cs[TJ], bn[TJ];
-  load_column_terms<Cfg>(a, p, cs, bn);
   int stage = 0;
   // kFp16: slab s is one of the fp16 slabs (fp16 operands, fp32 accumulation onto the accumulators, which
   // were dequantized before the first of them)
@@ -738,7 +756,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   using yes = std::true_type;
   using no = std::false_type;
 
-  int issued = 0;
+  int issued = early_slabs(n_slabs);
   for (; issued < AHEAD && issued < total_slabs; ++issued) issue_slab(issued, issued);
   // slab 0 has landed once only the requests of the others are out
   [&]<int... kLater>(std::integer_sequence<int, kLater...>) __attribute__((always_inline)) {
@@ -762,6 +780,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a) {
   for (; s < n_slabs && s + 1 < total_slabs; ++s) step(s, none{}, yes{}, no{});
   if (s < n_slabs) step(s++, none{}, no{}, no{});              // the last slab when nothing follows it
   if constexpr (kTap) tap_accumulators<Cfg, kSplit>(a, p, acc);
+  float cs[TJ], bn[TJ];
+  column_terms.use(cs, bn);
   dequantize_in_place<Cfg>(p, acc, a.r + p.m0, cs);
   for (; s + AHEAD < total_slabs; ++s) step(s, halves{}, yes{}, yes{});
   for (; s + 1 < total_slabs; ++s) step(s, none{}, yes{}, yes{});
@@ -798,17 +818,21 @@ struct DenseCfg {
   using Tile = typename std::conditional<kBN == 256, Cfg5, Cfg0>::type;   // wave positions and the output stages
   static_assert(Tile::BM == 128 && Tile::BN == kBN && Tile::WM == 64 && Tile::WN == 64, "128 rows, waves of 64 x 64");
   static constexpr int kCodes = 128 * BK, kRows = 128 * BK * 2, kWeights = kBN * BK;
-  static constexpr int kStage = kCodes + kRows + kWeights, kStages = 3;
+  // a ring of codes and weight codes, laid out like that of the tile configuration (whose first slabs are requested before it
+  // is known that the walk is taken), and one of rows of X behind it
+  static constexpr int kStages = 3, kStage = kCodes + kWeights, kRowsAt = kStages * kStage, kMasksAt = kRowsAt + kStages * kRows;
+  static_assert(kStage == Tile::STAGE_BYTES && kCodes == Tile::A_BYTES, "as in the tile's own ring");
   static constexpr int kMaskSlabs = 256;
-  static constexpr int LDS_BYTES = kStages * kStage + kMaskSlabs * BK;
+  static constexpr int LDS_BYTES = kMasksAt + kMaskSlabs * BK;
   static constexpr int X_DMA = 128 * BK * 2 / 1024 / Tile::kWaves;
   static constexpr int kPerSlab = Tile::A_DMA + X_DMA + Tile::B_DMA;       // requests per wave and slab
   static_assert(LDS_BYTES >= Tile::kWaves * 64 * (Tile::WN * 2 + 16) + DynamicCode::kCells * 8 && LDS_BYTES <= 160 * 1024,
                 "LDS (the output stages need that much of it at most)");
 };
 
+// early: early_slabs() slabs of codes have been requested into the ring.
 template <int kBN, bool kOnce>
-__device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, int split, int8_t* smem) {
+__device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, int split, int8_t* smem, bool early) {
   using D = DenseCfg<kBN>;
   using Cfg = typename D::Tile;
   constexpr int TI = Cfg::TI, TJ = Cfg::TJ;
@@ -817,7 +841,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
   const WavePos<Cfg> p(m0, n0, wave, lane);
   const int n_slabs = a.Kpad / BK;
   const int first = split * a.slabs_per_split, end = min(first + a.slabs_per_split, n_slabs), last = end - 1;
-  int8_t* s_mask = smem + D::kStages * D::kStage;
+  int8_t* s_mask = smem + D::kMasksAt;
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem + wave * (kWave * 16);
   // the codes: a scalar address per slab and a constant offset per lane and request (the loop's vector instructions
@@ -841,11 +865,11 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
       // a piece beyond the end of the row (the padding of K; K is a multiple of 16) is filled with mask bytes: finite
       // numbers, and its weights are masked to zero
       if (s >= whole_slabs && s * BK + piece >= a.K) src = reinterpret_cast<const uint16_t*>(a.mask);
-      dma16(src, dst + D::kCodes + j * Cfg::kWaves * 1024);
+      dma16(src, lds0 + D::kRowsAt + stage * D::kRows + j * Cfg::kWaves * 1024);
     } else {
       const int j = d - Cfg::A_DMA - D::X_DMA;
       const int8_t* src = baseB + (size_t)s * kBlockBytes + j * Cfg::kWaves * 1024;
-      const uint32_t to = dst + D::kCodes + D::kRows + j * Cfg::kWaves * 1024;
+      const uint32_t to = dst + D::kCodes + j * Cfg::kWaves * 1024;
       if constexpr (kOnce) dma16_once(src + lane * 16, to);
       else dma16_scalar_base(src, lane * 16, to);
     }
@@ -861,10 +885,10 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
     v4u xf[2][TI], mk;       // rows of X, the two halves of the k-step; 0xff per critical column
   };
   const int a_off = (p.wm * Cfg::WM / 32) * 2048 + lane * 16;
-  const int b_off = D::kCodes + D::kRows + (p.wn * Cfg::WN / 32) * 2048 + lane * 16;
+  const int b_off = D::kCodes + (p.wn * Cfg::WN / 32) * 2048 + lane * 16;
   int x_off[TI];
 #pragma unroll
-  for (int i = 0; i < TI; ++i) x_off[i] = D::kCodes + (p.wm * Cfg::WM + i * 32 + p.lr) * (BK * 2);
+  for (int i = 0; i < TI; ++i) x_off[i] = D::kRowsAt + (p.wm * Cfg::WM + i * 32 + p.lr) * (BK * 2);
   // read n (0 .. kReads - 1) of the fragments of k-step ks of slab s, in the order in which they are needed
   constexpr int kReads = TI + TJ + 1 + 2 * TI;
   auto read_frag = [&](int s, int stage, int ks, Frags& f, int n) __attribute__((always_inline)) {
@@ -880,7 +904,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
     } else {
       const int t = (n - 5) / TI, i = (n - 5) % TI;
       const int q = 4 * ks + 2 * p.lg + t;                             // columns 8 q .. 8 q + 8 of the slab
-      f.xf[t][i] = *reinterpret_cast<const v4u*>(base + x_off[i] + ((q ^ (p.lr >> 1 & 7)) * 16));
+      f.xf[t][i] = *reinterpret_cast<const v4u*>(smem + stage * D::kRows + x_off[i] + ((q ^ (p.lr >> 1 & 7)) * 16));
     }
   };
   static_assert(TI == 2 && TJ == 2, "the orders of reads, conversions and MFMAs are written for 2 x 2 tiles");
@@ -922,13 +946,23 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  __syncthreads();                                                     // (a second tile of this workgroup: LDS is free)
+  // (a second tile of this workgroup, or requests of another kind of tile: LDS is free only then)
+  if (!early) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" : : : "memory");
+  // the codes of two slabs, as far as they are not on their way, then the rows: slab `first` is there but for the newest X_DMA
+  const int on_their_way = early ? early_slabs(end - first) : 0;
 #pragma unroll
-  for (int d = 0; d < D::kPerSlab; ++d) request(first, 0, d);
+  for (int q = 0; q < 2; ++q)
+    if (q >= on_their_way) {
 #pragma unroll
-  for (int d = 0; d < D::kPerSlab; ++d) request(min(first + 1, last), 1, d);
+      for (int d = 0; d < D::kPerSlab; ++d)
+        if (d < Cfg::A_DMA || d >= Cfg::A_DMA + D::X_DMA) request(min(first + q, last), q, d);
+    }
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int d = Cfg::A_DMA; d < Cfg::A_DMA + D::X_DMA; ++d) request(min(first + q, last), q, d);
   fill_masks(first);
-  wait_slab_and_sync<D::kPerSlab>();
+  wait_slab_and_sync<D::X_DMA>();
 #pragma unroll
   for (int n = 0; n < kReads; ++n) read_frag(first, 0, 0, f[0], n);
   int stage = 0, s = first;
@@ -959,7 +993,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
   asm volatile("s_waitcnt vmcnt(0)" : : : "memory");                   // the requests repeated past the end
 
   float cs[TJ], bn[TJ];
-  load_column_terms<Cfg>(a, p, cs, bn);
+  ColumnTerms<Cfg>(a, p).use(cs, bn);
   if (a.tap_acc) {
     if (a.splits > 1)
       tap_accumulators<Cfg, true>(a, p, acc);
@@ -1016,12 +1050,18 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
 // not shared with the other way through the kernel, whose registers it would take.  (As a function of its own it saved and restored 120
 // registers a lane through scratch, 24 to 63 MB of writes a launch.)  The address of the LDS buffers is handed on as a number: named,
 // it would be read from memory again for every use.
-template <int kBN, bool kOnce>
-__device__ __forceinline__ void gemm_tile_dense(const GemmArgs& a, int8_t* smem, int BM, int BN) {
+template <class Cfg, bool kOnce>
+__device__ __forceinline__ void gemm_tile_dense(const GemmArgs& a, int8_t* smem) {
+  constexpr int kBN = Cfg::kWaves == 8 ? 256 : 128;
+  constexpr bool kSameTile = std::is_same_v<Cfg, typename DenseCfg<kBN>::Tile>;
   int tm, tn, split;
   if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;
-  for (int n0 = tn * BN; n0 < min((tn + 1) * BN, a.N); n0 += kBN)
-    for (int m0 = tm * BM; m0 < min((tm + 1) * BM, a.M); m0 += 128) dense_tile<kBN, kOnce>(a, m0, n0, split, smem);
+  if constexpr (kSameTile) {
+    dense_tile<kBN, kOnce>(a, tm * Cfg::BM, tn * Cfg::BN, split, smem, true);
+  } else {
+    for (int n0 = tn * Cfg::BN; n0 < min((tn + 1) * Cfg::BN, a.N); n0 += kBN)
+      for (int m0 = tm * Cfg::BM; m0 < min((tm + 1) * Cfg::BM, a.M); m0 += 128) dense_tile<kBN, kOnce>(a, m0, n0, split, smem, false);
+  }
 }
 
 template <class Cfg>
@@ -1039,19 +1079,38 @@ static int launch_lds(const GemmArgs& a) {
 // kOnce: the weights requested as bytes that nothing else reads (weights_read_once)
 template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit, bool kOnce>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWavesPerSimd) void k_gemm_mixed(const GemmArgs a) {
-  const int n_out = __builtin_amdgcn_readfirstlane(*a.n_out);
+  extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
+  using constant_bytes = const __attribute__((address_space(4))) char*;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int tm, tn, split;
+  if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;           // (workgroup 0 always has a tile)
+  const WavePos<Cfg> p(tm * Cfg::BM, tn * Cfg::BN, wave, threadIdx.x & (kWave - 1));
+  const int first = kSplit ? split * a.slabs_per_split : 0;
+  const int n_slabs = kSplit ? min(a.slabs_per_split, a.Kpad / BK - first) : a.Kpad / BK;
+  const CodeRequests<Cfg, kOnce> codes_of(a, p, wave, first, (uint32_t)(uintptr_t)smem);
+  // The first slabs, which both ways begin with, ahead of the count of critical columns and of the columns' scales: one after
+  // the other, each a memory latency, they held the first product back: 2.4 us from a workgroup's start to it, 1.9 now (ViT-L
+  // block of 1576 rows 111.9 -> 109.4 us, 7B-shaped layer of 256 heavy-tailed rows 242 -> 237).
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (q < early_slabs(n_slabs)) {
+#pragma unroll
+      for (int d = 0; d < Cfg::DMA_PER_SLAB; ++d) codes_of.issue(q, q, d);
+    }
+  // (through the scalar cache, so that the wait for it is not one for the requests; an address that the compiler cannot see
+  // through keeps the load behind them)
+  uint64_t count_at = reinterpret_cast<uint64_t>(a.n_out);
+  asm volatile("" : "+s"(count_at));
+  const int n_out = *(const __attribute__((address_space(4))) int*)(constant_bytes)count_at;
   reset_column_flags(a.flag_reset, a.Kpad);
   if (dense_critical_path(n_out, a.crit_slabs, a.dense_from, a.W_master != nullptr)) {
-    extern __shared__ __attribute__((aligned(1024))) int8_t smem[];
     uint64_t address = (uint64_t)(const char*)__builtin_amdgcn_kernarg_segment_ptr();   // `a` is the first argument
     uint32_t lds = (uint32_t)(uintptr_t)smem;
     asm volatile("" : "+s"(address), "+s"(lds));
-    using constant_bytes = const __attribute__((address_space(4))) char*;
-    gemm_tile_dense<Cfg::kWaves == 8 ? 256 : 128, kOnce>(*(const GemmArgs*)(constant_bytes)address,
-                                                         (int8_t*)(__attribute__((address_space(3))) int8_t*)lds, Cfg::BM, Cfg::BN);
+    gemm_tile_dense<Cfg, kOnce>(*(const GemmArgs*)(constant_bytes)address, (int8_t*)(__attribute__((address_space(3))) int8_t*)lds);
     return;
   }
-  gemm_tile<Cfg, kTap, kFull, kCoded, kSplit, kOnce>(a);
+  gemm_tile<Cfg, kTap, kFull, kCoded, kSplit, kOnce>(a, p, wave, split, n_slabs, n_out, codes_of);
 }
 
 // ------------------------------------------------------------------------------------------------
