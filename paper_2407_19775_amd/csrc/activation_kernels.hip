@@ -418,15 +418,23 @@ __device__ inline int row_quad_of_block(int b, int n_blocks) {
   return (b & ~63) | ((b & 7) << 3) | ((b >> 3) & 7);
 }
 
-template <int kWaves, int kPasses, bool kFromCodes>
+// The same with a row per workgroup.  XCD x gets the 32-row groups x, x + 8, ...; a row past the end has nothing to do.
+__device__ inline int row_of_block(int b) { return ((b >> 3) & 31) | (b & 7) << 5 | (b & ~255); }
+
+// kRows: 4, or 1 for a few hundred rows, where quads leave most compute units without a workgroup and the arithmetic on four rows
+// (about 16 vector instructions per element) is what takes the time: lane l then owns piece 64 (q kWaves + wave) + l.
+template <int kWaves, int kPasses, bool kFromCodes, int kRows>
 __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __restrict__ X, int M, int K, int ldx, uint32_t th,
                                            int n_slabs, uint8_t* __restrict__ flag, float* __restrict__ r_out,
                                            int8_t* __restrict__ Xq, int8_t* __restrict__ tap_xq, const CodedInput& coded) {
-  __shared__ uint32_t s_part[kWaves][4];
+  static_assert(kRows == 4 || kRows == 1, "rows of a workgroup");
+  constexpr int kLanes = kWave / kRows;                             // pieces of a row per wave and pass
+  __shared__ uint32_t s_part[kWaves][kRows];
   __shared__ float s_T[kFromCodes ? 256 : 1];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int j = lane & 3, i = lane >> 2;
-  const int m = row_quad_of_block(block, n_blocks) * 4 + j;
+  const int j = lane % kRows, i = lane / kRows;
+  const int m = kRows == 4 ? row_quad_of_block(block, n_blocks) * 4 + j : row_of_block(block);
+  if (kRows == 1 && m >= M) return;
   const bool row_ok = m < M;
   const int Kpad = n_slabs * kSlabBytes;
   const int n_pieces = Kpad / 16, k_pieces = K / 16;
@@ -438,7 +446,7 @@ __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __
   if constexpr (!kFromCodes) {
 #pragma unroll
     for (int q = 0; q < kPasses; ++q) {
-      const int piece = (q * kWaves + wave) * 16 + i;
+      const int piece = (q * kWaves + wave) * kLanes + i;
       const bool ok = row_ok && piece < k_pieces;
       const uint16_t* src = X + (ok ? (size_t)m * ldx + piece * 16 : (size_t)0);
       a[q] = *reinterpret_cast<const v4u*>(src);
@@ -449,7 +457,7 @@ __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __
     float sc[kPasses];
 #pragma unroll
     for (int q = 0; q < kPasses; ++q) {
-      const int piece = (q * kWaves + wave) * 16 + i;
+      const int piece = (q * kWaves + wave) * kLanes + i;
       const bool ok = row_ok && piece < k_pieces;
       const uint32_t e0 = ok ? (uint32_t)m * (uint32_t)K + piece * 16 : 0u;   // a piece lies inside one block
       cq[q] = *reinterpret_cast<const v4u*>(coded.codes + e0);
@@ -459,7 +467,7 @@ __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kPasses; ++q) {
-      const int piece = (q * kWaves + wave) * 16 + i;
+      const int piece = (q * kWaves + wave) * kLanes + i;
       uint32_t h[8];
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
@@ -481,7 +489,7 @@ __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __
   us2 rowt = as_us2(0u);
 #pragma unroll
   for (int q = 0; q < kPasses; ++q) {
-    const int piece = (q * kWaves + wave) * 16 + i;
+    const int piece = (q * kWaves + wave) * kLanes + i;
     uint32_t t_and = 0xffffffffu;
     us2 t_max = as_us2(0u);
 #pragma unroll
@@ -511,8 +519,10 @@ __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __
           bits |= (uint32_t)((b[q][w] & 0x7fffu) >= th) << (8 + 2 * w) | (uint32_t)(((b[q][w] >> 16) & 0x7fffu) >= th) << (9 + 2 * w);
         }
       }
-      bits |= (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, 0xb1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
-      bits |= (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, 0x4e, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+      if constexpr (kRows == 4) {
+        bits |= (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, 0xb1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
+        bits |= (uint32_t)__builtin_amdgcn_mov_dpp((int)bits, 0x4e, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+      }
       if (j == 0) {
         // plain byte stores of 1: every writer stores the same value, nobody reads before the
         // kernel ends, and nothing is waited for
@@ -527,21 +537,21 @@ __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __
   }
   uint32_t mx = max(as_u32(rowt) & 0xffffu, as_u32(rowt) >> 16);
 #pragma unroll
-  for (int d = 4; d < kWave; d <<= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, d, kWave));
-  if (lane < 4) s_part[wave][lane] = mx;
+  for (int d = kRows; d < kWave; d <<= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, d, kWave));
+  if (lane < kRows) s_part[wave][lane] = mx;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) mx = max(mx, s_part[w][j]);
   // top bit set: a sub-threshold entry exists and its pattern is mx + th (mod 2^16)
   const float r = (mx & 0x8000u) ? half_lo_to_float((mx + th) & 0xffffu) : 0.0f;
-  if (threadIdx.x < 4 && row_ok) r_out[m] = r;
+  if (threadIdx.x < kRows && row_ok) r_out[m] = r;
   const float scale = (r == 0.0f) ? 0.0f : 127.0f / r;            // IEEE division
 
   // ---- codes of every column (critical ones are cleared later); K padding gets zeros
   if (!row_ok) return;
 #pragma unroll
   for (int q = 0; q < kPasses; ++q) {
-    int piece = (q * kWaves + wave) * 16 + i;
+    int piece = (q * kWaves + wave) * kLanes + i;
     // keeps the address arithmetic and the fp16 -> fp32 conversions of this piece here (hoisted above
     // the barrier they would double the registers)
     asm volatile("" : "+v"(piece), "+v"(a[q]), "+v"(b[q]));
@@ -557,12 +567,12 @@ __device__ __forceinline__ void prep_block(int block, int n_blocks, uint16_t* __
   }
 }
 
-template <int kWaves, int kPasses, bool kFromCodes>
+template <int kWaves, int kPasses, bool kFromCodes, int kRows>
 __global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ X, int M, int K, int ldx, uint32_t th,
                                                          int n_slabs, uint8_t* __restrict__ flag,
                                                          float* __restrict__ r_out, int8_t* __restrict__ Xq,
                                                          int8_t* __restrict__ tap_xq, const CodedInput coded) {
-  prep_block<kWaves, kPasses, kFromCodes>(blockIdx.x, gridDim.x, X, M, K, ldx, th, n_slabs, flag, r_out, Xq, tap_xq, coded);
+  prep_block<kWaves, kPasses, kFromCodes, kRows>(blockIdx.x, gridDim.x, X, M, K, ldx, th, n_slabs, flag, r_out, Xq, tap_xq, coded);
 }
 // The same next to an adapter's down-projection, which needs nothing of it: the first workgroups take the low-rank product (K in
 // ranges, whose sums the next launch adds) and the copy of its weight side, a multiple of eight of them, so that the rows keep their XCDs.
@@ -570,7 +580,7 @@ __global__ __launch_bounds__(kWaves * kWave) void k_prep(uint16_t* __restrict__ 
 // from 5.4 to 10.8).  7B-shaped layers, down-projection in the second launch / here: 333 rows with rank 16 219.8 / 202.6 us, 129
 // rows with rank 64 214 / 174, 2048 rows with rank 64 534 / 511, 4096 rows the same.  Three and four rank tiles take a step at a time:
 // with two in flight (120 registers) 4096 rows with rank 64 took 1 % longer than in the second launch.
-template <int kWaves, int kPasses, int kTiles>
+template <int kWaves, int kPasses, int kTiles, int kRows>
 __global__ __launch_bounds__(kWaves * kWave) void k_prep_lora(uint16_t* __restrict__ X, int M, int K, int ldx, uint32_t th,
                                                               int n_slabs, uint8_t* __restrict__ flag,
                                                               float* __restrict__ r_out, int8_t* __restrict__ Xq,
@@ -582,7 +592,7 @@ __global__ __launch_bounds__(kWaves * kWave) void k_prep_lora(uint16_t* __restri
       lora_down_block<kTiles, kLoraWaves, (kTiles > 2 ? 1 : kWaves <= 4 ? 4 : 2)>(l, blockIdx.x, t_blocks, splits, steps_per_split, P);
     return;
   }
-  prep_block<kWaves, kPasses, false>((int)blockIdx.x - lora_blocks, (int)gridDim.x - lora_blocks, X, M, K, ldx, th, n_slabs, flag, r_out,
+  prep_block<kWaves, kPasses, false, kRows>((int)blockIdx.x - lora_blocks, (int)gridDim.x - lora_blocks, X, M, K, ldx, th, n_slabs, flag, r_out,
                                      Xq, tap_xq, CodedInput{});
 }
 
@@ -781,6 +791,12 @@ hipError_t launch_prep_rows(const uint16_t* X, int M, int K, int ldx, uint32_t t
   return hipGetLastError();
 }
 
+// A row per workgroup instead of four: for up to 512 rows, and for inputs of up to 6.5 million elements, where the chip still has
+// compute units to spare; not for rows that a quad's four waves hold in one pass.  Us per call with N = 1024, four rows / one:
+// 129 x 4096 23.3 / 22.4, 256 x 11008 31.8 / 30.0, 512 x 11008 31.7 / 30.8, 256 x 28672 42.3 / 37.5, 768 x 8192 31.8 / 31.2,
+// 1576 x 4096 32.2 / 31.7; no gain, and not taken: 768 x 11008 36.4 / 37.3, 1024 x 8192 36.0 / 36.2, 1576 x 11008 48.6 / 49.1.
+// (Coded input stays with four: every workgroup brings the code table into LDS.)
+static bool prep_single_rows(int M, int K) { return K > 1024 && (M <= 512 || (long)M * K <= 6500000); }
 bool prep_fits(int K) { return packed_k(K) / 16 <= 16 * 16 * 8; }
 // the variant that decodes coded activations holds more per lane: rows up to 16384 columns without spilling
 bool prep_from_codes_fits(int K) { return packed_k(K) / 16 <= 16 * 16 * 4; }
@@ -789,7 +805,8 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
                        int8_t* Xq, int8_t* tap_xq, const PackOutliers& o, const CodedInput* coded, void* event_mid,
                        hipStream_t stream, const LoraArgs* lora, float* lora_partial) {
   const int n_slabs = Kpad / kSlabBytes, n_pieces = Kpad / 16;
-  const dim3 grid(ceil_div(M, 4));
+  const bool single = !coded && prep_single_rows(M, K);
+  const dim3 grid(single ? round_up(M, 256) : ceil_div(M, 4));
   const CodedInput ci = coded ? *coded : CodedInput{};
   LoraPlan plan = {};
   int t_blocks = 0, lora_tiles = 0;
@@ -800,36 +817,47 @@ hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad
     if (coded || plan.decode || lora_tiles < 1 || lora_tiles > 4 || (plan.splits > 1 && !lora_partial)) return hipErrorInvalidValue;
   }
   // (a workgroup past the copy of the weight side does nothing)
-#define MMD8_PREP_LORA(W_, P_, T_)                                                                                        \
+#define MMD8_PREP_LORA(W_, P_, T_, R_)                                                                                      \
   case T_: {                                                                                                              \
     const int copy_blocks = lora->Wo ? ceil_div(lora->N * 4 * lora_slabs(lora->r), (W_ < 8 ? W_ : 8) * kWave) : 0;         \
     const int lora_blocks = round_up(t_blocks * plan.splits + copy_blocks, 8);                                            \
-    hipLaunchKernelGGL((k_prep_lora<W_, P_, T_>), dim3(lora_blocks + grid.x), dim3(W_ * kWave), 0, stream, X, M, K, ldx, th, n_slabs, \
+    hipLaunchKernelGGL((k_prep_lora<W_, P_, T_, R_>), dim3(lora_blocks + grid.x), dim3(W_ * kWave), 0, stream, X, M, K, ldx, th, n_slabs, \
                        flag, r, Xq, tap_xq, *lora, lora_blocks, t_blocks, plan.splits, plan.steps_per_split,              \
                        plan.splits > 1 ? lora_partial : nullptr);                                                         \
     break;                                                                                                                \
   }
+#define MMD8_PREP_LORA_TILES(W_, P_, R_)                                                                                 \
+  switch (lora_tiles) { MMD8_PREP_LORA(W_, P_, 1, R_) MMD8_PREP_LORA(W_, P_, 2, R_) MMD8_PREP_LORA(W_, P_, 3, R_) MMD8_PREP_LORA(W_, P_, 4, R_) }
+#define MMD8_PREP_ROWS_OF(W_, P_, C_, R_)                                                                                \
+  hipLaunchKernelGGL((k_prep<W_, P_, C_, R_>), grid, dim3(W_ * kWave), 0, stream, X, M, K, ldx, th, n_slabs, flag, r, Xq, tap_xq, ci)
 #define MMD8_PREP(W_, P_)                                                                                                \
   do {                                                                                                                   \
-    if (lora) {                                                                                                          \
-      switch (lora_tiles) { MMD8_PREP_LORA(W_, P_, 1) MMD8_PREP_LORA(W_, P_, 2) MMD8_PREP_LORA(W_, P_, 3) MMD8_PREP_LORA(W_, P_, 4) } \
-    } else if (coded)                                                                                                           \
-      hipLaunchKernelGGL((k_prep<W_, P_, true>), grid, dim3(W_ * kWave), 0, stream, X, M, K, ldx, th, n_slabs, flag, r, \
-                         Xq, tap_xq, ci);                                                                                \
-    else                                                                                                                 \
-      hipLaunchKernelGGL((k_prep<W_, P_, false>), grid, dim3(W_ * kWave), 0, stream, X, M, K, ldx, th, n_slabs, flag, r, \
-                         Xq, tap_xq, ci);                                                                                \
+    if (lora) MMD8_PREP_LORA_TILES(W_, P_, 4)                                                                            \
+    else if (coded) MMD8_PREP_ROWS_OF(W_, P_, true, 4);                                                                  \
+    else MMD8_PREP_ROWS_OF(W_, P_, false, 4);                                                                            \
   } while (0)
-  if (n_pieces <= 64) MMD8_PREP(4, 1);
+#define MMD8_PREP_SINGLE(W_, P_)                                                                                         \
+  do {                                                                                                                   \
+    if (lora) MMD8_PREP_LORA_TILES(W_, P_, 1)                                                                            \
+    else MMD8_PREP_ROWS_OF(W_, P_, false, 1);                                                                            \
+  } while (0)
+  if (single) {
+    if (n_pieces <= 256) MMD8_PREP_SINGLE(4, 1);
+    else if (n_pieces <= 512) MMD8_PREP_SINGLE(8, 1);
+    else if (n_pieces <= 1024) MMD8_PREP_SINGLE(16, 1);
+    else MMD8_PREP_SINGLE(16, 2);
+  } else if (n_pieces <= 64) MMD8_PREP(4, 1);
   else if (n_pieces <= 128) MMD8_PREP(4, 2);
   else if (n_pieces <= 256) MMD8_PREP(4, 4);
   else if (n_pieces <= 512) MMD8_PREP(8, 4);
   else if (n_pieces <= 1024) MMD8_PREP(16, 4);
   else if (coded) return hipErrorInvalidValue;                     // the caller decodes first (prep_from_codes_fits)
-  else if (lora) switch (lora_tiles) { MMD8_PREP_LORA(16, 8, 1) MMD8_PREP_LORA(16, 8, 2) MMD8_PREP_LORA(16, 8, 3) MMD8_PREP_LORA(16, 8, 4) }
-  else hipLaunchKernelGGL((k_prep<16, 8, false>), grid, dim3(16 * kWave), 0, stream, X, M, K, ldx, th, n_slabs, flag, r, Xq,
-                          tap_xq, ci);
+  else if (lora) MMD8_PREP_LORA_TILES(16, 8, 4)
+  else MMD8_PREP_ROWS_OF(16, 8, false, 4);
 #undef MMD8_PREP
+#undef MMD8_PREP_SINGLE
+#undef MMD8_PREP_ROWS_OF
+#undef MMD8_PREP_LORA_TILES
 #undef MMD8_PREP_LORA
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
