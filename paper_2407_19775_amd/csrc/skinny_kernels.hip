@@ -386,10 +386,15 @@ __global__ __launch_bounds__(256) void k_skinny_finalize(const float* __restrict
     __syncthreads();
   }
   if (n >= N) return;
+  // Asked for ahead of the sums and whether there or not (a dword of the sums in their place): behind the sums, under a
+  // condition, the residual was one more memory latency.
+  const uint16_t* at = reinterpret_cast<const uint16_t*>(partial + (size_t)m * N + n);
+  const uint16_t bias_n = *(bias ? bias + n : at), residual_n = *(residual ? residual + (size_t)m * ldr + n : at);
+  __builtin_amdgcn_sched_barrier(0);
   float sum[1];
   add_ranges<1>(partial + (size_t)m * N + n, splits, (size_t)M * N, sum);
   float y = sum[0];
-  if (bias) y += half_lo_to_float(bias[n]);
+  if (bias) y += half_lo_to_float(bias_n);
   if (r > 0) {
     float low = 0.0f;
     for (int j = 0; j < r; j += 8) {
@@ -403,7 +408,7 @@ __global__ __launch_bounds__(256) void k_skinny_finalize(const float* __restrict
   }
   uint32_t h = float_to_half_bits(y);
   if (gelu) h = gelu_to_half_bits(half_lo_to_float(h));
-  if (residual) h = float_to_half_bits(half_lo_to_float(h) + half_lo_to_float(residual[(size_t)m * ldr + n]));
+  if (residual) h = float_to_half_bits(half_lo_to_float(h) + half_lo_to_float(residual_n));
   Y[(size_t)m * ldy + n] = (uint16_t)h;
 }
 
@@ -476,16 +481,23 @@ __global__ __launch_bounds__(kCodecThreads) void k_skinny_finalize_coded(const F
 __global__ __launch_bounds__(256) void k_add_splits(const SplitSum a) {
   const int n = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4, m = blockIdx.y;
   if (n >= a.N) return;
+  // (ahead of the sums, as in k_skinny_finalize)
+  const uint16_t* at = reinterpret_cast<const uint16_t*>(a.partial + (size_t)m * a.N + n);
+  const uint16_t* bias_at = a.bias ? a.bias + n : at;                 // (halves: a bias need not be aligned to more)
+  const v2u res = *reinterpret_cast<const v2u*>(a.residual ? a.residual + (size_t)m * a.ldr + n : at);
+  uint16_t bias[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) bias[i] = bias_at[i];
+  __builtin_amdgcn_sched_barrier(0);
   float y[4];
   add_ranges<4>(a.partial + (size_t)m * a.N + n, a.splits, (size_t)a.M * a.N, y);
   uint32_t h[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    h[i] = float_to_half_bits(a.bias ? y[i] + half_lo_to_float(a.bias[n + i]) : y[i]);
+    h[i] = float_to_half_bits(a.bias ? y[i] + half_lo_to_float(bias[i]) : y[i]);
     if (a.gelu) h[i] = gelu_to_half_bits(half_lo_to_float(h[i]));
   }
   if (a.residual) {
-    const v2u res = *reinterpret_cast<const v2u*>(a.residual + (size_t)m * a.ldr + n);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       h[i] = float_to_half_bits(half_lo_to_float(h[i]) + ((i & 1) ? half_hi_to_float(res[i >> 1]) : half_lo_to_float(res[i >> 1])));
