@@ -80,10 +80,14 @@ struct GemmCfg {
   static_assert((BM + BN) * 32 <= RING_BYTES, "epilogue staging must fit in the slab buffers");
 };
 
-// The tile configurations, by the number a caller can force one with (gemm.h):
-using Cfg0 = GemmCfg<128, 128, 2, 2, 3, 2>;
-using Cfg1 = GemmCfg<256, 128, 2, 2, 3, 2>;
-using Cfg2 = GemmCfg<128, 256, 2, 2, 3, 2>;
+// The tile configurations, by the number a caller can force one with (gemm.h).  Eight waves each, two to a SIMD, one of which
+// multiplies while the other waits: 128 x 128 tiles of four waves (64 x 64 each, one to a SIMD, a three-slab ring) took 37.2 us
+// instead of 32.6 for 256 x 4096 x 12288, 37.7 instead of 32.3 for 512 x 4096 x 6144, 26.5 instead of 22.6 for 128 x 4096 x 4096 with
+// original weight rows; with heavy-tailed rows 40.7 instead of 35 for 256 x 2816 x 2048 and 63.3 instead of 59.6 for 256 x
+// 4096 x 12288.  (Held to 128 registers, two workgroups to a compute unit, the walk spills: 69.7 for the last of these.)
+using Cfg0 = GemmCfg<128, 128, 2, 4, 4, 2>;
+using Cfg1 = GemmCfg<256, 128, 4, 2, 3, 2>;
+using Cfg2 = GemmCfg<128, 256, 2, 4, 3, 2>;
 using Cfg3 = GemmCfg<256, 256, 2, 4, 3, 2>;
 using Cfg4 = GemmCfg<256, 256, 2, 4, 4, 2>;   // the large tile: whole rounds of one tile per CU
 using Cfg5 = GemmCfg<128, 256, 2, 4, 4, 2>;   // remainders and less than one round of large tiles
@@ -806,7 +810,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const WavePos<Cfg>&
 //           (codes_to_half8) as the decode kernels do.  The column's step c[n] / 127
 //           is applied once to the fp32 sum (against the prepared slabs the weights are not rounded to fp16 after
 //           scaling: at most 2^-11 relative per term).
-// A tile is 128 rows high, a wave owns 64 x 64 of it (two sets of four 32 x 32 accumulators: 128 registers), and
+// A tile is 128 rows high, a wave owns 64 x 64 of it (two sets of four 32 x 32 accumulators: 128 registers; 64 x 32 where it is
+// 128 columns wide), and
 // everything of a slab comes through one ring of three LDS buffers by global_load_lds_dwordx4, two slabs ahead:
 // codes and weight codes as in the main loop, the rows of X 128 bytes per row, eight rows per instruction.  Row R
 // keeps its 16-byte piece q at place q ^ (R / 2 % 8), which the per-lane source address arranges, so that 16 lanes of a
@@ -816,7 +821,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, const WavePos<Cfg>&
 template <int kBN>
 struct DenseCfg {
   using Tile = typename std::conditional<kBN == 256, Cfg5, Cfg0>::type;   // wave positions and the output stages
-  static_assert(Tile::BM == 128 && Tile::BN == kBN && Tile::WM == 64 && Tile::WN == 64, "128 rows, waves of 64 x 64");
+  static_assert(Tile::BM == 128 && Tile::BN == kBN && Tile::WM == 64 && Tile::kWaves == 8, "128 rows, eight waves of 64 rows");
   static constexpr int kCodes = 128 * BK, kRows = 128 * BK * 2, kWeights = kBN * BK;
   // a ring of codes and weight codes, laid out like that of the tile configuration (whose first slabs are requested before it
   // is known that the walk is taken), and one of rows of X behind it
@@ -890,24 +895,32 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
 #pragma unroll
   for (int i = 0; i < TI; ++i) x_off[i] = D::kRowsAt + (p.wm * Cfg::WM + i * 32 + p.lr) * (BK * 2);
   // read n (0 .. kReads - 1) of the fragments of k-step ks of slab s, in the order in which they are needed
-  constexpr int kReads = TI + TJ + 1 + 2 * TI;
+  constexpr int kReads = TI + TJ + 1 + 2 * TI, kInt = TI * TJ, kAll = 3 * kInt;
   auto read_frag = [&](int s, int stage, int ks, Frags& f, int n) __attribute__((always_inline)) {
     const int8_t* base = smem + stage * D::kStage;
     if (n == 2) {
       f.mk = *reinterpret_cast<const v4u*>(s_mask + ((s - first) % D::kMaskSlabs) * BK + (2 * ks + p.lg) * 16);
-    } else if (n < 5) {
+    } else if (n < TI + TJ + 1) {
       const int e = n > 2;
       if (n == 0 || n == 3)
         f.x[e] = *reinterpret_cast<const v4i*>(base + a_off + e * 2048 + ks * 1024);
       else
         f.w[e] = *reinterpret_cast<const v4i*>(base + b_off + e * 2048 + ks * 1024);
     } else {
-      const int t = (n - 5) / TI, i = (n - 5) % TI;
+      const int t = (n - TI - TJ - 1) / TI, i = (n - TI - TJ - 1) % TI;
       const int q = 4 * ks + 2 * p.lg + t;                             // columns 8 q .. 8 q + 8 of the slab
       f.xf[t][i] = *reinterpret_cast<const v4u*>(smem + stage * D::kRows + x_off[i] + ((q ^ (p.lr >> 1 & 7)) * 16));
     }
   };
-  static_assert(TI == 2 && TJ == 2, "the orders of reads, conversions and MFMAs are written for 2 x 2 tiles");
+  static_assert(TI == 2 && (TJ == 2 || TJ == 1), "the orders of reads, conversions and MFMAs are written for 2 x 2 and 2 x 1 tiles");
+
+  // ... those between MFMA n and the next: one, or two where there are more reads than MFMAs
+  auto reads = [&](int n, int s, int stage, int ks, Frags& f) __attribute__((always_inline)) {
+    constexpr int kTwice = kReads > kAll ? kReads - kAll : 0;
+#pragma unroll
+    for (int q = n + (n < kTwice ? n : kTwice); q < n + 1 + (n + 1 < kTwice ? n + 1 : kTwice); ++q)
+      if (q < kReads) read_frag(s, stage, ks, f, q);
+  };
 
   v16i acc[TI][TJ];
   v16f accf[TI][TJ];
@@ -921,26 +934,26 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
   Frags f[2];
   // In iteration s slab s + 2 is requested into the buffer of slab s - 1, which every wave finished reading before the
   // barrier of iteration s - 1; past the end the last slab is asked for again, so that the count in flight is fixed.
-  // One k-step: 12 MFMAs, and between any two of them one fragment read of the next k-step, the conversion of four
-  // weight codes (the first ones ahead of their MFMA by four) and at times a request, fenced so that they stay there: a
+  // One k-step: 12 (or 6) MFMAs, and between any two of them one fragment read of the next k-step (or two), the conversion of four
+  // weight codes (ahead of their MFMA by as many as there are tiles) and at times a request, fenced so that they stay there: a
   // wave issues in order, and a burst of reads that finds the LDS queue full holds up the MFMAs behind it (with the
   // reads in one go a slab took 1.05 us).
   auto multiply = [&](const Frags& g, auto&& between) __attribute__((always_inline)) {
     v2u wh[2 * TJ][2];
 #pragma unroll
-    for (int n = 0; n < 12; ++n) {
-      if (n < 4) {
+    for (int n = 0; n < kAll; ++n) {
+      if (n < kInt) {
         const int i = n & 1, j = n >> 1;
         acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(g.x[i], g.w[j], acc[i][j], 0, 0, 0);
       } else {
-        const int c = (n - 4) >> 1, t = c >> 1, j = c & 1, i = n & 1;
+        const int c = (n - kInt) >> 1, t = c / TJ, j = c % TJ, i = n & 1;
         const v4u h = v4u{wh[c][0][0], wh[c][0][1], wh[c][1][0], wh[c][1][1]};
         accf[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, g.xf[t][i]), __builtin_bit_cast(v8h, h), accf[i][j], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
       between(n);
-      if (n < 8) {
-        const int c = n >> 1, t = c >> 1, j = c & 1, d = n & 1;
+      if (n < 4 * TJ) {
+        const int c = n >> 1, t = c / TJ, j = c % TJ, d = n & 1;
         wh[c][d] = codes_to_half4(((uint32_t)g.w[j][2 * t + d] & g.mk[2 * t + d]) ^ 0x80808080u);   // other columns: zero
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -970,15 +983,15 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
     for (; s < min(s0, end); ++s) {
       const int stage1 = stage == 2 ? 0 : stage + 1, stage2 = stage1 == 2 ? 0 : stage1 + 1;
       multiply(f[0], [&](int n) __attribute__((always_inline)) {
-        if (n < kReads) read_frag(s, stage, 1, f[1], n);
+        reads(n, s, stage, 1, f[1]);
         // the requests of slab s + 2
-        const int d = n * D::kPerSlab / 12;
-        if (d < D::kPerSlab && (d * 12 + D::kPerSlab - 1) / D::kPerSlab == n) request(min(s + 2, last), stage2, d);
+        const int d = n * D::kPerSlab / kAll;
+        if (d < D::kPerSlab && (d * kAll + D::kPerSlab - 1) / D::kPerSlab == n) request(min(s + 2, last), stage2, d);
       });
       multiply(f[1], [&](int n) __attribute__((always_inline)) {
         // slab s + 1 has landed for every wave
         if (n == 0) wait_slab_and_sync<D::kPerSlab>();
-        if (n < kReads) read_frag(min(s + 1, last), stage1, 0, f[0], n);
+        reads(n, min(s + 1, last), stage1, 0, f[0]);
       });
       stage = stage1;
     }
@@ -1052,7 +1065,7 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
 // it would be read from memory again for every use.
 template <class Cfg, bool kOnce>
 __device__ __forceinline__ void gemm_tile_dense(const GemmArgs& a, int8_t* smem) {
-  constexpr int kBN = Cfg::kWaves == 8 ? 256 : 128;
+  constexpr int kBN = Cfg::BN;
   constexpr bool kSameTile = std::is_same_v<Cfg, typename DenseCfg<kBN>::Tile>;
   int tm, tn, split;
   if (!tile_of_block(a, blockIdx.x, tm, tn, split)) return;
@@ -1065,16 +1078,10 @@ __device__ __forceinline__ void gemm_tile_dense(const GemmArgs& a, int8_t* smem)
 }
 
 template <class Cfg>
-using DenseOf = DenseCfg<Cfg::kWaves == 8 ? 256 : 128>;
-// LDS of a launch: the walk's only where a call can come to it (never with original weight rows, nor where its line lies
-// beyond K), so that two workgroups of 128 x 128 tiles fit a compute unit otherwise: 64 x 8192 x 57344 with original rows,
-// two rounds of such tiles, 118 us; 129 with room for the walk, 126 with the three workgroups of fewer registers before.
+using DenseOf = DenseCfg<Cfg::BN>;
+// LDS of a launch: also the walk's (registers already keep a second workgroup off the compute unit)
 template <class Cfg>
 constexpr int kMostLds = Cfg::LDS_BYTES > DenseOf<Cfg>::LDS_BYTES ? Cfg::LDS_BYTES : DenseOf<Cfg>::LDS_BYTES;
-template <class Cfg>
-static int launch_lds(const GemmArgs& a) {
-  return dense_critical_path(a.K, a.crit_slabs, a.dense_from, a.W_master != nullptr) ? kMostLds<Cfg> : Cfg::LDS_BYTES;
-}
 
 // kOnce: the weights requested as bytes that nothing else reads (weights_read_once)
 template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit, bool kOnce>
@@ -1134,7 +1141,7 @@ template <class Cfg, bool kTap, bool kFull, bool kCoded, bool kSplit = false, bo
 static hipError_t launch_one(const GemmArgs& a, hipStream_t stream) {
   if (hipError_t e = ensure_lds_attribute<Cfg, kTap, kFull, kCoded, kSplit, kOnce>(); e != hipSuccess) return e;
   const int grid = ceil_div(a.tiles_m * a.tiles_n * a.splits, 8) * 8;
-  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit, kOnce>), dim3(grid), dim3(Cfg::kThreads), launch_lds<Cfg>(a), stream, a);
+  hipLaunchKernelGGL((k_gemm_mixed<Cfg, kTap, kFull, kCoded, kSplit, kOnce>), dim3(grid), dim3(Cfg::kThreads), kMostLds<Cfg>, stream, a);
   return hipGetLastError();
 }
 
@@ -1325,8 +1332,8 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
     return launch_variant(a, 4, stream);
   }
   // Less than one round of large tiles: 128 x 128 tiles where they fit one round, else 128 x 256 with eight waves and the
-  // four-slab ring.  (Measured, 128 x 128 / 128 x 256: 256 x 4096 x 12288 32 / 36 us, 1000 x 4096 x 4096 37 / 42, 1024 x
-  // 2048 x 1024 24 / 27; 300 x 4096 x 12288, where the small tiles are a round and a bit, 52 / 39.)  Where the 128 x 256
+  // four-slab ring.  (Measured, 128 x 128 / 128 x 256, the former still with four waves: 256 x 4096 x 12288 32 / 36 us, 1000 x
+  // 4096 x 4096 37 / 42, 1024 x 2048 x 1024 24 / 27; 300 x 4096 x 12288, where the small tiles are a round and a bit, 52 / 39.)  Where the 128 x 256
   // tiles would need a second round and the 256 x 256 ones fit in one, the large tiles win: 4096 -> 12288 at 768 rows 61
   // against 71 us, 4096 -> 22016 at 512 rows 61 against 70.
   if (a.M > 128 && tiles_128x256 > cus) return launch_variant(a, 4, stream);
