@@ -1145,6 +1145,23 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// K in ranges
+template <class Cfg>
+static hipError_t launch_split(GemmArgs a, bool once, hipStream_t stream) {
+  a.tiles_m = ceil_div(a.M, Cfg::BM);
+  a.tiles_n = ceil_div(a.N, Cfg::BN);
+  return a.tap_acc ? launch_one<Cfg, true, false, false, true>(a, stream)
+         : once    ? launch_one<Cfg, false, false, false, true, true>(a, stream)
+                   : launch_one<Cfg, false, false, false, true>(a, stream);
+}
+template <class Cfg>
+static hipError_t prepare_split() {
+  hipError_t e = ensure_lds_attribute<Cfg, true, false, false, true>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, false, false, true>();
+  if (e == hipSuccess) e = ensure_lds_attribute<Cfg, false, false, false, true, true>();
+  return e;
+}
+
 template <class Cfg, bool kOnce>
 static hipError_t launch_output(const GemmArgs& a, bool full, hipStream_t stream) {
   if (a.codes || a.residual || a.gelu)
@@ -1192,9 +1209,8 @@ hipError_t prepare_gemm_kernels() {
   if (e == hipSuccess) e = prepare_cfg<Cfg3>();
   if (e == hipSuccess) e = prepare_cfg<Cfg4>();
   if (e == hipSuccess) e = prepare_cfg<Cfg5>();
-  if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, true, false, false, true>();
-  if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, false, false, false, true>();
-  if (e == hipSuccess) e = ensure_lds_attribute<Cfg5, false, false, false, true, true>();
+  if (e == hipSuccess) e = prepare_split<Cfg0>();
+  if (e == hipSuccess) e = prepare_split<Cfg5>();
   return e;
 }
 
@@ -1230,25 +1246,37 @@ static GemmArgs column_range(const GemmArgs& a, int n0, int n) {
   return b;
 }
 
-// 128 x 128 tiles that fit in one round
-static bool one_round_of_small_tiles(int M, int N) { return (long)ceil_div(M, 128) * ceil_div(N, 128) <= device_cu_count(); }
+// 128 x 128 tiles (of `splits` ranges of K) that fit in one round
+static bool one_round_of_small_tiles(int M, int N, int splits = 1) { return (long)ceil_div(M, 128) * ceil_div(N, 128) * splits <= device_cu_count(); }
+// Ranges of K on 128 x 128 tiles: where those of all tiles fit one round and K is at most 6144; beyond that more ranges on
+// 128 x 256 tiles are as fast or faster (figures below; 129 x 7168 x 1024 24.2 us, on small tiles 25.0).
+constexpr int kLongSplitSlabs = 98;
+static bool small_split_tiles(int M, int N, int n_slabs, int splits) { return n_slabs < kLongSplitSlabs && one_round_of_small_tiles(M, N, splits); }
 int plan_gemm_splits(int M, int K, int N) {
   const int n_slabs = packed_k(K) / BK, cus = device_cu_count();
   const long tiles = (long)ceil_div(M, Cfg5::BM) * ceil_div(N, Cfg5::BN);
   if (M <= 128 || 2 * tiles > cus) return 1;
-  // us of a call with s ranges: the slabs of a workgroup (0.45 each, 0.37 in one round of small tiles), its start and end,
-  // and with more than one range the kernel that adds them up and the 8 bytes per output and range that the sums cost.
-  // Measured (whole calls, few critical columns, weights that come from memory, without / with the split this rule takes):
-  // 256 x 11008 x 4096 79 / 50 us (8 ranges), 256 x 4096 x 4096 39.7 / 31.5 (5), 1024 x 8192 x 2048 66 / 49 (4), 1576 x
-  // 4096 x 1024 43.8 / 39.8 (4), 1024 x 11008 x 4096 84 / 72 (2), 200 x 2816 x 2048 31.9 / 29.6 (9).  No gain, and none
-  // taken: 512 x 2048 x 2048 26.3 / 29.1 (2), 256 x 4096 x 12288 41.4 / 42.2 (2).  The rule takes more ranges than would be
-  // best here and there (256 x 11008 x 4096 44.6 with 5, 200 x 2816 x 2048 25.8 with 4) and leaves out some that pay (2048 x
-  // 4096 x 1024 44.0 / 38.5 with 3): 5 % off the best count on average over 38 shapes, never slower than no split.  With
-  // weights that are still in the last-level cache the split gains less (200 x 2816 x 2048 24.5 / 27.1).
+  // us of a call with s ranges: the slabs of a workgroup (0.45 each on 128 x 256 tiles, 0.3 on the small ones of
+  // small_split_tiles), its start and end, and with more than one range the kernel that adds them up and the bytes of the sums.  (Without a
+  // split 0.41 a slab on small tiles: more than they take with few critical columns, as heavy-tailed input, where the walk with
+  // both products takes 0.8 a slab, gains more from a split than other input loses.)  Measured, weights from memory, whole calls
+  // without a split / with ranges of 128 x 256 tiles / as taken here, few critical columns and then heavy-tailed rows:
+  // 256 x 4096 x 4096 25.0 / 28.1 (5 ranges) / 25.8 (4) and 46.6 / 35.8 / 32.6; 200 x 2816 x 2048 20.1 / 25.2 (9) / 19.4 (4)
+  // and 35.4 / 29.1 / 23.4; 512 x 4096 x 2048 25.4 / 29.1 (4) / 25.5 (4) and 48.3 / 36.5 / 33.0; 129 x 4096 x 4096 23.9 / 25.1 /
+  // 22.3 (4) and 45.8 / 30.4 / 28.6; few critical columns only: 1576 x 4096 x 1024 28.5 / 30.5 (4) / 28.0 (2), 333 x 4096 x 4096
+  // 25.1 / 28.4 (5) / 24.7 (2).  No split taken: 400 x 2048 x 2048 18.8 and 30.2, with two ranges 21.6 and 27.0; 129 x 2048 x
+  // 6144 18.7 and 30.4, with two 21.1 and 27.5.  Longer K, 128 x 256 tiles taken: 256 x 11008 x 4096 60.0 and 112.9 without
+  // a split, 37.3 and 55.7 with 8 ranges, 37.1 and 54.8 with 4 of small tiles; 333 x 11008 x 4096 61.0, 40.0 (5), 44.4 (2 of small
+  // tiles); 1024 x 8192 x 2048 40.9 and 113.3, 40.5 and 96.7 (4), 38.1 and 97.7 (2 of small tiles).
+  // Before / now, small tiles: 200 x 3072 x 1024 22.2 / 19.4 and 24.9 / 22.4, 256 x 6144 x 2048 27.6 / 25.0 and 35.1 / 31.0.
+  // (The count falls as M grows within a row of tiles: linear_workspace_bytes relies on it.)
   int best = 1;
-  double least = (one_round_of_small_tiles(M, N) ? 0.37 : 0.45) * n_slabs + 5.0;
+  const bool long_k = n_slabs >= kLongSplitSlabs;
+  double least = (!one_round_of_small_tiles(M, N) ? 0.45 : long_k ? 0.37 : 0.41) * n_slabs + 5.0;
+  const double byte_us = (long_k ? 8.0 : 12.0) / 8.0e6;
   for (int s = 2; s * tiles <= cus && n_slabs / s >= 4; ++s) {
-    const double cost = 0.45 * ceil_div(n_slabs, s) + 5.0 + 10.0 + (double)s * M * N * 8.0 / 8.0e6;
+    const bool small = small_split_tiles(M, N, n_slabs, s);
+    const double cost = (small ? 0.3 : 0.45) * ceil_div(n_slabs, s) + (small ? 16.7 : 15.0) + byte_us * s * M * N;
     if (cost < least) best = s, least = cost;
   }
   return ceil_div(n_slabs, ceil_div(n_slabs, best));
@@ -1275,8 +1303,11 @@ CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further
   }
   const int in_slabs = kOutlierSlab * (kCriticalSlabs + p.g_slabs);
   const double rounds = (double)ceil_div(M, 128) * ((double)Npad / 256) / device_cu_count();   // of 128 x 256 tiles
-  double from = 0.35 * M + 64.0 * n_slabs / splits * (0.13 + 0.12 * rounds);
-  if (splits > 1) from += 75e-6 * splits * M * (double)Npad;
+  // (ranges on 128 x 128 tiles count for 1.3 each, which leaves the line where it was fitted: 256 x 4096 x 4096 602 columns with
+  // five ranges of 128 x 256 tiles, 612 with four of these)
+  const double ranges = splits * (splits > 1 && small_split_tiles(M, (int)Npad, n_slabs, splits) ? 1.3 : 1.0);
+  double from = 0.35 * M + 64.0 * n_slabs / ranges * (0.13 + 0.12 * rounds);
+  if (splits > 1) from += 75e-6 * ranges * M * (double)Npad;
   if (from > in_slabs) from = in_slabs + (from - in_slabs) * (0.028 + 0.014 * rounds) / (0.14 * (rounds > 1 ? rounds : 1));
   p.dense_from = from < 1e9 ? (int)from : 1000000000;
   return p;
@@ -1298,14 +1329,9 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
     const int n_slabs = a.Kpad / BK;
     a.slabs_per_split = ceil_div(n_slabs, a.splits);
     if (ceil_div(n_slabs, a.slabs_per_split) != a.splits) return hipErrorInvalidValue;   // every range has a slab
-    a.tiles_m = ceil_div(a.M, Cfg5::BM);
-    a.tiles_n = ceil_div(a.N, Cfg5::BN);
     hipError_t e = hipSuccess;
     if (a.tap_acc) e = launch_fill_u32(reinterpret_cast<uint32_t*>(a.tap_acc), 0u, (size_t)a.M * a.tap_ld, stream);
-    if (e == hipSuccess)
-      e = a.tap_acc ? launch_one<Cfg5, true, false, false, true>(a, stream)
-          : once    ? launch_one<Cfg5, false, false, false, true, true>(a, stream)
-                    : launch_one<Cfg5, false, false, false, true>(a, stream);
+    if (e == hipSuccess) e = small_split_tiles(a.M, a.N, n_slabs, a.splits) ? launch_split<Cfg0>(a, once, stream) : launch_split<Cfg5>(a, once, stream);
     if (e != hipSuccess) return e;
     const SplitSum sum = {a.partial, a.splits, a.M, a.N, a.bias, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
                           a.codes, a.code_absmax, a.codes ? 1 << a.code_log_block : 0};
