@@ -33,8 +33,8 @@ INT8_POWER_LIMITED_TOPS = 3468.0
 # (70B-shaped layer, 4096 tokens) and the 7B-shaped step.  Valid for the GEMM source they were measured on:
 # reported as null once that file has changed.
 GEMM_TRAFFIC_BYTES_PER_LAUNCH = 1185.3e6
-GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 184.4e6
-GEMM_TRAFFIC_SOURCE_SHA256 = "fbb36fc8dcdc6e9cc38d59a1b791a60627642e2130d7539903c46d4f75807015"
+GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 183.2e6
+GEMM_TRAFFIC_SOURCE_SHA256 = "e0770f13c472732dc68fe89fb6ce4c6fe9051562d65f0fb526fffcea856ba94d"
 
 
 def parse():
