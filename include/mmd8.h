@@ -151,9 +151,9 @@ typedef struct {
  * leaves the head zeroed again, so the same workspace serves any number of calls of any shape
  * that fits, one after the other on one stream.  A size given for M rows does not fall with M, and a workspace of
  * that size serves calls of up to M rows with the results, bit for bit, of one sized for them.  (A
- * smaller workspace that has no room for the sums of a split K, and is not too small otherwise, serves as well: K is
- * then not split, and an output may differ in its last bit.)  Two calls must not use one workspace at the
- * same time.  After a call that returned MMD8_E_HIP, set the workspace up again.
+ * smaller workspace that has no room for the sums of a split K, be it the layer's or, above 128 rows, an adapter's
+ * down-projection's, and is not too small otherwise, serves as well: that K is then not split, and an output may differ in
+ * its last bit.)  Two calls must not use one workspace at the same time.  After a call that returned MMD8_E_HIP, set the workspace up again.
  * mmd8_linear_workspace_init also sets the kernels' attributes on the current device; the calls of the layer made
  * after it allocate nothing, synchronise nothing and change no device state, so they can be captured in a HIP
  * graph (set the workspace up before the capture starts). */

@@ -816,18 +816,17 @@ bool prep_from_codes_fits(int K) { return packed_k(K) / 16 <= 16 * 16 * 4; }
 
 hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad, uint8_t* flag, float* r,
                        int8_t* Xq, int8_t* tap_xq, const PackOutliers& o, const CodedInput* coded, void* event_mid,
-                       hipStream_t stream, const LoraArgs* lora, float* lora_partial) {
+                       hipStream_t stream, const LoraArgs* lora, const LoraPlan& plan, float* lora_partial) {
   const int n_slabs = Kpad / kSlabBytes, n_pieces = Kpad / 16;
   const bool single = !coded && prep_single_rows(M, K);
   const dim3 grid(single ? round_up(M, 256) : ceil_div(M, 4));
   const CodedInput ci = coded ? *coded : CodedInput{};
-  LoraPlan plan = {};
   int t_blocks = 0, lora_tiles = 0;
   if (lora) {
-    plan = plan_lora(lora->M, lora->K);
     t_blocks = ceil_div(lora->M, kLoraRows);
     lora_tiles = ceil_div(lora->r, 16);
-    if (coded || plan.decode || lora_tiles < 1 || lora_tiles > 4 || (plan.splits > 1 && !lora_partial)) return hipErrorInvalidValue;
+    if (coded || plan.decode || plan.splits < 1 || lora_tiles < 1 || lora_tiles > 4 || (plan.splits > 1 && !lora_partial))
+      return hipErrorInvalidValue;
   }
   // (a workgroup past the copy of the weight side does nothing)
 #define MMD8_PREP_LORA(W_, P_, T_, R_)                                                                                      \

@@ -76,6 +76,7 @@ struct Workspace {
   int f_slabs;         // fp16 slabs: crit_slabs for the critical columns, then the low-rank operands of an adapter of rank r
   int crit_slabs;      // 32 critical columns each: kCriticalSlabs where the tiled GEMM is the usual path, else 1
   uint16_t* lora_t;    // adapter only: [M][kLoraMaxRank] fp16
+  LoraPlan lora_plan;  // adapter only: ranges of K of its down-projection
   float* lora_part;    // adapter only: partial sums of the down-projection when K is split between workgroups
   int8_t* xq;          // Mpad x Kpad codes, blocked layout
   float* partial;      // split-K partial outputs, or null
@@ -90,9 +91,10 @@ struct Workspace {
 static bool exit_fuses(int M, int K, int N, int block);
 // gathered_rows: room for further slabs of critical columns (not in the fixed-size static workspace)
 // split_k: room for the partial outputs of a tiled GEMM whose K is split
+// split_lora: likewise for those of an adapter's down-projection (more than 128 rows)
 // pass_rows: most rows whose partial outputs the decode kernels keep at a time
 static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_block = 0, bool gathered_rows = true,
-                       bool split_k = true, int pass_rows = kSkinnyMaxM) {
+                       bool split_k = true, int pass_rows = kSkinnyMaxM, bool split_lora = true) {
   const size_t Kpad = packed_k(K), Mpad = packed_n(M), Npad = packed_n(N);
   Workspace w;
   size_t off = 0;
@@ -146,9 +148,10 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   if (w.gemm_splits > 1) w.partial = reinterpret_cast<float*>(take((size_t)w.gemm_splits * M * N * sizeof(float)));
   w.lora_t = r > 0 ? reinterpret_cast<uint16_t*>(take((size_t)M * kLoraMaxRank * 2)) : nullptr;
   w.lora_part = nullptr;
+  w.lora_plan = {};
   if (r > 0 && M > 0) {
-    const size_t lb = plan_lora(M, K).partial_bytes;
-    if (lb) w.lora_part = reinterpret_cast<float*>(take(lb));
+    w.lora_plan = plan_lora(M, K, split_lora);
+    if (w.lora_plan.partial_bytes) w.lora_part = reinterpret_cast<float*>(take(w.lora_plan.partial_bytes));
   }
   w.h = nullptr;
   // (a layer that is a single kernel has no partial outputs: their place)
@@ -158,9 +161,9 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   return w;
 }
 // The layout of a call in a workspace of `have` bytes: with room for the sums of a split K where that fits, else
-// without (what a workspace held before K was ever split still serves); may_drop_slabs (the fixed-size array): then
-// likewise without the further slabs, and up to 128 rows in two passes.  The slabs go last: 200 x 4096 x 4096 in 32 MiB,
-// which hold one of the two, takes 58 us with them and 100 with the split when 15 % of the columns are critical; 30.5 and
+// without (what a workspace held before K was ever split still serves), those of an adapter's down-projection, which gains
+// less, before those of the layer; may_drop_slabs (the fixed-size array): then likewise without the further slabs, and up to
+// 128 rows in two passes.  The slabs go last: 200 x 4096 x 4096 in 32 MiB, which hold one of the two, takes 58 us with them and 100 with the split when 15 % of the columns are critical; 30.5 and
 // 30.0 us when few are.
 // bytes > have: it fits in none of these ways.
 static Workspace fit(void* base, size_t have, int M, int K, int N, int r, int exit_block, bool may_drop_slabs) {
@@ -171,11 +174,19 @@ static Workspace fit(void* base, size_t have, int M, int K, int N, int r, int ex
   // (480) 183 and 549.
   if (w.bytes > have && may_drop_slabs && M <= kSkinnyMaxM && w.decode_plan.n_slabs - w.decode_plan.slabs_per_split > 20)
     w = carve(base, M, K, N, r, exit_block, false, true, 64);
+  if (w.bytes > have && r > 0) w = carve(base, M, K, N, r, exit_block, true, true, kSkinnyMaxM, false);
   if (w.bytes > have) w = carve(base, M, K, N, r, exit_block, true, false);
+  if (w.bytes > have && r > 0) w = carve(base, M, K, N, r, exit_block, true, false, kSkinnyMaxM, false);
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, true);
   if (w.bytes > have && may_drop_slabs) w = carve(base, M, K, N, r, exit_block, false, false);
   if (w.bytes > have && may_drop_slabs && M <= kSkinnyMaxM) w = carve(base, M, K, N, r, exit_block, false, false, 64);
   return w;
+}
+// Ranges of an adapter's down-projection in a workspace of `have` bytes, 0 where the call is refused; the host's view of
+// the choice above.
+int plan_lora_in(size_t have, int M, int K, int N, int r) {
+  const Workspace w = fit(nullptr, have, M, K, N, r, 0, false);
+  return w.bytes > have ? 0 : w.lora_plan.splits;
 }
 // How the decode kernels (at most 128 rows) run in the fixed-size array; the host's view of the choice above.
 struct StaticDecode { int splits, pass_rows; };
@@ -454,7 +465,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
   if (one_pass) {
     // one pass over X: scales, flags and codes together, then the critical columns are cleared
     if (launch_prep(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, ws.xq, t.xq, po, fused_decode ? coded : nullptr,
-                    t.event_prep_mid, st, lora ? &l : nullptr, ws.lora_part) != hipSuccess)
+                    t.event_prep_mid, st, lora ? &l : nullptr, ws.lora_plan, ws.lora_part) != hipSuccess)
       return MMD8_E_HIP;
   } else if (decode_prep) {
     if (launch_prep_rows(X, M, K, ldx, threshold_pattern(tau), Kpad, ws.flag, ws.r, ws.xq, st) != hipSuccess) return MMD8_E_HIP;
@@ -474,7 +485,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
       hipMemcpyAsync(t.row_absmax, ws.r, (size_t)M * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
     return MMD8_E_HIP;
 
-  if (lora && !one_pass && launch_lora_down(l, plan_lora(M, K), ws.lora_part, st) != hipSuccess) return MMD8_E_HIP;
+  if (lora && !one_pass && launch_lora_down(l, ws.lora_plan, ws.lora_part, st) != hipSuccess) return MMD8_E_HIP;
 
   if (own_prep) {   // (rows_path with a coded output: the encoder follows)
     if (!record(t.event_gemm_begin)) return MMD8_E_HIP;
@@ -496,7 +507,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
     }
     if (lora) {
       g.lora_P = ws.lora_part;
-      g.lora_splits = plan_lora(M, K).splits;
+      g.lora_splits = ws.lora_plan.splits;
       g.lora_B = lora->B;
       g.lora_r = lora->r;
       g.lora_T_user = lora->T_out;
@@ -546,7 +557,7 @@ static int run_linear(mmd8_half* X, int M, int K, int ldx, const int8_t* Wq_pack
       g.K = K;
       if (lora) {
         g.lora_P = ws.lora_part;
-        g.lora_splits = plan_lora(M, K).splits;
+        g.lora_splits = ws.lora_plan.splits;
         g.lora_B = lora->B;
         g.lora_r = lora->r;
         g.lora_T_user = lora->T_out;

@@ -74,6 +74,6 @@ bool prep_from_codes_fits(int K);   // likewise for launch_prep with coded activ
 hipError_t launch_prep(uint16_t* X, int M, int K, int ldx, uint32_t th, int Kpad, uint8_t* flag, float* r,
                        int8_t* Xq, int8_t* tap_xq, const PackOutliers& o, const CodedInput* coded, void* event_mid,
                        hipStream_t stream,   // event_mid: null, or a hipEvent_t recorded between the two kernels
-                       const LoraArgs* lora = nullptr, float* lora_partial = nullptr);   // an adapter's down-projection along with it
+                       const LoraArgs* lora = nullptr, const LoraPlan& lora_plan = {}, float* lora_partial = nullptr);   // an adapter's down-projection along with it
 
 }  // namespace mmd8

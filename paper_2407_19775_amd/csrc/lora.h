@@ -28,7 +28,8 @@ struct LoraPlan {
   bool decode;                   // at most 128 rows: the ranges are left for sum_low_rank_activation
   size_t partial_bytes;          // fp32 [splits][M][kLoraMaxRank] where they go through memory
 };
-LoraPlan plan_lora(int M, int K);
+// split: whether the ranges' sums have room; false: one range for more than 128 rows (up to 128 there are always ranges)
+LoraPlan plan_lora(int M, int K, bool split = true);
 // One value of T for the kernels that add the low-rank term themselves (at most 128 rows): the ranges' sums in index order,
 // rounded to fp16; fp16 bit pattern.  All loads are in flight together.
 constexpr int kLoraDecodeSplits = 16;

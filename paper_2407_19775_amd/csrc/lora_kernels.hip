@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void k_lora_reduce(const LoraArgs a, int split
 // the host's view of the down-projection's reads: first of the 16 columns
 int lora_read_column(int s, int end, int kq, int K) { return lora_lane_column(kq, K) + lora_step_column(s, lora_reads(s, end, kq, K)); }
 
-LoraPlan plan_lora(int M, int K) {
+LoraPlan plan_lora(int M, int K, bool split) {
   // K is split until there are two workgroups per compute unit, every range at least sixteen 64-column steps: the sums are
   // added in a launch that runs anyway.
   const int t_blocks = ceil_div(M, kLoraRows), steps = ceil_div(K, 64), cus = device_cu_count();
@@ -37,7 +37,7 @@ LoraPlan plan_lora(int M, int K) {
   // one row 74 -> 61.5 us, 32 rows 128 -> 112, 128 rows 198 -> 184; rank 64 at 64 rows 265 -> 179).
   LoraPlan p;
   p.decode = M <= 128;
-  const int want = p.decode ? max(1, min(steps / 4, kLoraDecodeSplits)) : max(1, min(min(2 * cus / t_blocks, steps / 16), 32));
+  const int want = p.decode ? max(1, min(steps / 4, kLoraDecodeSplits)) : split ? max(1, min(min(2 * cus / t_blocks, steps / 16), 32)) : 1;
   p.steps_per_split = ceil_div(steps, want);
   p.splits = ceil_div(steps, p.steps_per_split);
   p.partial_bytes = p.splits > 1 || p.decode ? (size_t)p.splits * M * kLoraMaxRank * sizeof(float) : 0;

@@ -60,6 +60,14 @@ def lora_read_column(s: int, end: int, kq: int, K: int) -> int:
     return f(s, end, kq, K)
 
 
+def lora_ranges_in(nbytes: int, M: int, K: int, N: int, r: int) -> int:
+    """Ranges of K of an adapter's down-projection in a workspace of that many bytes, 0 where the call is refused (a C++
+    function of the library)."""
+    f = binding.lib()._ZN4mmd812plan_lora_inEmiiii
+    f.argtypes, f.restype = [ctypes.c_size_t] + [ctypes.c_int] * 4, ctypes.c_int
+    return f(nbytes, M, K, N, r)
+
+
 def static_decode_plan(M: int, K: int, N: int):
     """Ranges of K and rows per pass of the decode kernels in the array of the entry point without a workspace (a C++ function
     of the library)."""

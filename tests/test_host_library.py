@@ -9,7 +9,7 @@ import pytest
 
 from oracle import dynamic_code as dc
 from paper_2407_19775_amd import binding
-from gpu_util import critical_column_plan, lora_read_column
+from gpu_util import critical_column_plan, lora_ranges_in, lora_read_column
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -211,6 +211,18 @@ def test_adapter_arguments_are_rejected_before_any_launch():
     assert call(A=odd) == -1 and call(T=odd) == -1
     assert call(K=100) == -2
     assert call(wsb=L.mmd8_linear_workspace_bytes(8, 128, 64)) == -3               # sized without the adapter
+
+
+@pytest.mark.parametrize("M,K,N,r,without", [(2048, 4096, 12288, 16, 76248320), (1024, 4096, 22016, 16, 112583936),
+                                             (1024, 2048, 8192, 8, 26754304)])
+def test_a_workspace_without_the_sums_of_the_down_projection_serves(M, K, N, r, without):
+    """Sizes that hold everything but the sums of an adapter's split down-projection (256 compute units): one range of K
+    then, and the head of the workspace is what cannot be left out."""
+    L = binding.lib()
+    full = L.mmd8_linear_lora_workspace_bytes(M, K, N, r)
+    assert full > without and lora_ranges_in(full, M, K, N, r) > 1
+    assert lora_ranges_in(without, M, K, N, r) == 1
+    assert lora_ranges_in(without // 2, M, K, N, r) == 0
 
 
 @pytest.mark.parametrize("K", [16, 32, 48, 64, 80, 112, 128, 1040])
