@@ -94,6 +94,8 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream);
 // Ranges of K for a call of more than 128 rows whose 128 x 256 tiles leave half of the chip or more without a
 // workgroup; 1: no split.
 int plan_gemm_splits(int M, int K, int N);
+// Whether 128 x 128 tiles, of `splits` ranges of K each, fit in one round: such a call, and such ranges, take them.
+bool one_round_of_small_tiles(int M, int N, int splits = 1);
 // sets the LDS attribute of every GEMM kernel on the current device (otherwise done by a kernel's first launch,
 // which must then not happen while a stream is being captured)
 hipError_t prepare_gemm_kernels();

@@ -1246,37 +1246,32 @@ static GemmArgs column_range(const GemmArgs& a, int n0, int n) {
   return b;
 }
 
-// 128 x 128 tiles (of `splits` ranges of K) that fit in one round
-static bool one_round_of_small_tiles(int M, int N, int splits = 1) { return (long)ceil_div(M, 128) * ceil_div(N, 128) * splits <= device_cu_count(); }
-// Ranges of K on 128 x 128 tiles: where those of all tiles fit one round and K is at most 6144; beyond that more ranges on
-// 128 x 256 tiles are as fast or faster (figures below; 129 x 7168 x 1024 24.2 us, on small tiles 25.0).
-constexpr int kLongSplitSlabs = 98;
-static bool small_split_tiles(int M, int N, int n_slabs, int splits) { return n_slabs < kLongSplitSlabs && one_round_of_small_tiles(M, N, splits); }
+// 128 x 128 tiles (of `splits` ranges of K) that fit in one round.  Ranges go on such tiles wherever they do, else on 128 x 256:
+// at the same count of ranges the small tiles measured faster in 2309 of 2321 pairs.
+bool one_round_of_small_tiles(int M, int N, int splits) { return (long)ceil_div(M, 128) * ceil_div(N, 128) * splits <= device_cu_count(); }
 int plan_gemm_splits(int M, int K, int N) {
   const int n_slabs = packed_k(K) / BK, cus = device_cu_count();
   const long tiles = (long)ceil_div(M, Cfg5::BM) * ceil_div(N, Cfg5::BN);
   if (M <= 128 || 2 * tiles > cus) return 1;
-  // us of a call with s ranges: the slabs of a workgroup (0.45 each on 128 x 256 tiles, 0.3 on the small ones of
-  // small_split_tiles), its start and end, and with more than one range the kernel that adds them up and the bytes of the sums.  (Without a
-  // split 0.41 a slab on small tiles: more than they take with few critical columns, as heavy-tailed input, where the walk with
-  // both products takes 0.8 a slab, gains more from a split than other input loses.)  Measured, weights from memory, whole calls
-  // without a split / with ranges of 128 x 256 tiles / as taken here, few critical columns and then heavy-tailed rows:
-  // 256 x 4096 x 4096 25.0 / 28.1 (5 ranges) / 25.8 (4) and 46.6 / 35.8 / 32.6; 200 x 2816 x 2048 20.1 / 25.2 (9) / 19.4 (4)
-  // and 35.4 / 29.1 / 23.4; 512 x 4096 x 2048 25.4 / 29.1 (4) / 25.5 (4) and 48.3 / 36.5 / 33.0; 129 x 4096 x 4096 23.9 / 25.1 /
-  // 22.3 (4) and 45.8 / 30.4 / 28.6; few critical columns only: 1576 x 4096 x 1024 28.5 / 30.5 (4) / 28.0 (2), 333 x 4096 x 4096
-  // 25.1 / 28.4 (5) / 24.7 (2).  No split taken: 400 x 2048 x 2048 18.8 and 30.2, with two ranges 21.6 and 27.0; 129 x 2048 x
-  // 6144 18.7 and 30.4, with two 21.1 and 27.5.  Longer K, 128 x 256 tiles taken: 256 x 11008 x 4096 60.0 and 112.9 without
-  // a split, 37.3 and 55.7 with 8 ranges, 37.1 and 54.8 with 4 of small tiles; 333 x 11008 x 4096 61.0, 40.0 (5), 44.4 (2 of small
-  // tiles); 1024 x 8192 x 2048 40.9 and 113.3, 40.5 and 96.7 (4), 38.1 and 97.7 (2 of small tiles).
-  // Before / now, small tiles: 200 x 3072 x 1024 22.2 / 19.4 and 24.9 / 22.4, 256 x 6144 x 2048 27.6 / 25.0 and 35.1 / 31.0.
-  // (The count falls as M grows within a row of tiles: linear_workspace_bytes relies on it.)
+  // The cost of s ranges: the slabs of a workgroup, the launch that adds the ranges up, and the sums.  The constants are
+  // fitted to the choice and not to the time: 950 calls (129 to 2600 rows, K 512 to 16384, N 256 to 8192), each without a split and
+  // with up to 24 ranges of either tile, weights from memory and still in the last-level cache, where a split gains less, few critical
+  // columns and heavy-tailed rows, where it gains more (the walk with both products takes twice as long per slab); the host cannot
+  // tell these apart.  Over these calls the count taken is 1.3 % slower than the best one with few critical columns and weights from
+  // memory, 2.4 % with cached ones, 4.1 and 3.2 % with heavy-tailed rows; at worst 45 %, where K of 600 to 1500 is not split.  Us, few
+  // and heavy-tailed, weights from memory, without a split / as taken / other ranges: 333 x 4096 x 4096 31.1 and 51.8 / 27.6 and 39.7
+  // (2) / 29.8 and 40.0 (4 of 128 x 256 tiles); 256 x 4096 x 4096 30.6 and 49.9 / 25.6 and 32.5 (3) / 27.5 and 32.3 (4); 247 x 2400 x
+  // 880 22.3 and 34.3 / 17.7 and 21.1 (5) / 20.1 and 24.8 (6 of 128 x 256); 175 x 3296 x 1352 25.8 and 40.7 / 19.3 and 22.8 (6) / 23.7
+  // and 26.7 (12 of 128 x 256); 175 x 3440 x 5648 27.7 and 44.0 / 25.7 and 34.0 (2) / 27.0 and 34.7 (4 of 128 x 256); 256 x 11008 x 4096
+  // 61.3 and 112.8 / 38.2 and 56.0 (4) / 43.0 and 56.7 (8 of 128 x 256); 333 x 11008 x 4096 61.5 and 138.8 / 43.2 and 97.2 (5 of 128 x
+  // 256) / 45.2 and 102.7 (2).  No split taken: 400 x 2048 x 2048 20.7 and 30.8, with two ranges 21.6 and 27.4.
+  // (The term of the sums is the same for both tiles, so that the count falls as M grows within a row of tiles:
+  // linear_workspace_bytes relies on it.)
   int best = 1;
-  const bool long_k = n_slabs >= kLongSplitSlabs;
-  double least = (!one_round_of_small_tiles(M, N) ? 0.45 : long_k ? 0.37 : 0.41) * n_slabs + 5.0;
-  const double byte_us = (long_k ? 8.0 : 12.0) / 8.0e6;
+  double least = (one_round_of_small_tiles(M, N) ? 0.2551 : 0.1277) * n_slabs;
   for (int s = 2; s * tiles <= cus && n_slabs / s >= 4; ++s) {
-    const bool small = small_split_tiles(M, N, n_slabs, s);
-    const double cost = (small ? 0.3 : 0.45) * ceil_div(n_slabs, s) + (small ? 16.7 : 15.0) + byte_us * s * M * N;
+    const int slabs = ceil_div(n_slabs, s);
+    const double cost = (one_round_of_small_tiles(M, N, s) ? 4.44 + 0.2185 * slabs : 3.972 + 0.281 * slabs) + 1.4555e-6 * s * M * N;
     if (cost < least) best = s, least = cost;
   }
   return ceil_div(n_slabs, ceil_div(n_slabs, best));
@@ -1305,7 +1300,7 @@ CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further
   const double rounds = (double)ceil_div(M, 128) * ((double)Npad / 256) / device_cu_count();   // of 128 x 256 tiles
   // (ranges on 128 x 128 tiles count for 1.3 each, which leaves the line where it was fitted: 256 x 4096 x 4096 602 columns with
   // five ranges of 128 x 256 tiles, 612 with four of these)
-  const double ranges = splits * (splits > 1 && small_split_tiles(M, (int)Npad, n_slabs, splits) ? 1.3 : 1.0);
+  const double ranges = splits * (splits > 1 && one_round_of_small_tiles(M, (int)Npad, splits) ? 1.3 : 1.0);
   double from = 0.35 * M + 64.0 * n_slabs / ranges * (0.13 + 0.12 * rounds);
   if (splits > 1) from += 75e-6 * ranges * M * (double)Npad;
   if (from > in_slabs) from = in_slabs + (from - in_slabs) * (0.028 + 0.014 * rounds) / (0.14 * (rounds > 1 ? rounds : 1));
@@ -1331,7 +1326,7 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
     if (ceil_div(n_slabs, a.slabs_per_split) != a.splits) return hipErrorInvalidValue;   // every range has a slab
     hipError_t e = hipSuccess;
     if (a.tap_acc) e = launch_fill_u32(reinterpret_cast<uint32_t*>(a.tap_acc), 0u, (size_t)a.M * a.tap_ld, stream);
-    if (e == hipSuccess) e = small_split_tiles(a.M, a.N, n_slabs, a.splits) ? launch_split<Cfg0>(a, once, stream) : launch_split<Cfg5>(a, once, stream);
+    if (e == hipSuccess) e = one_round_of_small_tiles(a.M, a.N, a.splits) ? launch_split<Cfg0>(a, once, stream) : launch_split<Cfg5>(a, once, stream);
     if (e != hipSuccess) return e;
     const SplitSum sum = {a.partial, a.splits, a.M, a.N, a.bias, a.residual, a.ldr, a.gelu, a.Y, a.ldy,
                           a.codes, a.code_absmax, a.codes ? 1 << a.code_log_block : 0};

@@ -40,6 +40,14 @@ def gemm_splits(M: int, K: int, N: int) -> int:
     return f(M, K, N)
 
 
+def ranges_on_small_tiles(M: int, K: int, N: int) -> bool:
+    """Whether those ranges go on 128 x 128 tiles (a C++ function of the library)."""
+    f = binding.lib()._ZN4mmd824one_round_of_small_tilesEiii
+    f.argtypes, f.restype = [ctypes.c_int] * 3, ctypes.c_bool
+    s = gemm_splits(M, K, N)
+    return s > 1 and f(M, N, s)
+
+
 class CriticalPlan(ctypes.Structure):
     _fields_ = [("g_slabs", ctypes.c_int), ("dense_from", ctypes.c_int)]
 

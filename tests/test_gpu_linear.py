@@ -280,15 +280,17 @@ def test_counts_of_critical_columns_around_the_change_to_the_dense_pass(n_crit, 
 @pytest.mark.parametrize("variant", [4, 5, 0])
 @pytest.mark.parametrize("n_crit", [257, 300, "last in slabs", "first of the dense pass", 1344, 1345, 1486, 1550])
 def test_counts_of_critical_columns_around_the_change_to_the_dense_pass_with_few_rows(n_crit, variant):
-    """With 300 rows the walk over K takes over long before the slabs are full (1344 columns)."""
-    M, K, N = 300, 2096, 264
+    """With 1100 rows the walk over K takes over long before the slabs are full (1344 columns), later than with 300, whose K
+    is in so many ranges that it takes over with the ninth slab."""
+    M, K, N = 1100, 2096, 264
+    rows = np.concatenate([np.arange(0, 260), np.arange(900, M)])
     in_slabs, dense_from = critical_column_plan(M, K, N)
     assert in_slabs == 1344 and 300 < dense_from - 1 and dense_from < 1344
     n_crit = {"last in slabs": dense_from - 1, "first of the dense pass": dense_from}.get(n_crit, n_crit)
     rng = np.random.default_rng([n_crit, variant, 7])
     X, cols = exactly_n_critical(rng, M, K, n_crit)
     assert np.array_equal(np.flatnonzero(ml.outlier_mask(X, 6.0)), cols)
-    check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=wl.gaussian_bias(N, 0.1, rng),
+    check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=wl.gaussian_bias(N, 0.1, rng), rows=rows,
                  tuning=binding.tune_gemm_tiles(variant))
 
 
