@@ -118,7 +118,7 @@ static Workspace carve(void* base, int M, int K, int N, int r = 0, int exit_bloc
   // (the same count decides for the dense pass with and without the further slabs: a workspace without them gathers
   // tile by tile up to that count)
   w.gemm_splits = split_k && M > kSkinnyMaxM ? plan_gemm_splits(M, K, N) : 1;
-  const CriticalPlan cp = plan_critical_columns(M, (int)(Kpad / kSlabBytes), Npad, w.crit_slabs == kCriticalSlabs, w.gemm_splits);
+  const CriticalPlan cp = plan_critical_columns(M, (int)(Kpad / kSlabBytes), N, w.crit_slabs == kCriticalSlabs, w.gemm_splits);
   w.g_slabs = gathered_rows ? cp.g_slabs : 0;
   w.dense_from = cp.dense_from;
   w.xg = w.g_slabs > 0 ? reinterpret_cast<uint16_t*>(take(Mpad * kOutlierSlab * 2 * w.g_slabs)) : nullptr;

@@ -24,7 +24,7 @@ struct CriticalPlan {
   int dense_from;   // critical columns from which a call takes the dense pass
 };
 // splits: ranges into which the tiled GEMM's K is split (plan_gemm_splits; 1: not split)
-CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further_slabs, int splits);
+CriticalPlan plan_critical_columns(int M, int n_slabs, int N, bool further_slabs, int splits);
 // Whether a call takes the dense pass for its critical columns.  Then no fp16 slab is prepared or read at all.  The
 // same decision in the kernel that prepares the slabs and in the GEMM, from the count that both read; never with
 // original 16-bit weight rows (the dense pass multiplies the weight codes).

@@ -1277,18 +1277,22 @@ int plan_gemm_splits(int M, int K, int N) {
   return ceil_div(n_slabs, ceil_div(n_slabs, best));
 }
 
-// Where the line between slabs and dense_tile lies.  The walk with both products costs the same whatever their number:
-// more than the walk over the codes by an amount that grows with the slabs of a range, with the rounds of tiles and, where
-// the ranges leave fp32 sums, with those.  A column in a slab costs its preparation and, per round, its place in the ring,
-// 0.028 + 0.014 us per round; a column beyond the slabs 0.14 us per round.  The formula is a fit to 75 calls of 130 to
-// 4096 rows, K of 512 to 32768, split and not, each measured both ways with 2 to 100 % of the columns critical and
-// weights that come from memory: the way taken is 0.3 % slower than the better one on average, 6 % at worst where it is the
-// walk (333 x 4096 x 22016 at 30 %) and 31 % where it is the slabs (1024 x 1024 x 1024 at 45 %).  Whole calls, us, walk /
-// slabs: 256 x 4096 x 4096 48 / 49 at 10 %, 48 / 74 at 25 %; 256 x 11008 x 4096 78 / 93 at 10 %, not split 137 / 148 at
-// 16 %; 1024 x 4096 x 12288 167 / 164 at 40 %, 169 / 186 at 50 %; 2048 x 4096 x 12288 326 / 280 at 50 %, 329 / 488 at 70 %;
-// 2048 x 1024 x 4096 84 / 69 at 70 %, 85 / 90 at 90 %; 4096 x 8192 x 10240 896 / 661 at 30 %, 907 / 1108 at 40 %.
-CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further_slabs, int splits) {
+// Where the line between slabs and dense_tile lies.  The walk with both products costs the same whatever their number: more than
+// the walk over the codes by an amount that grows with the slabs of a range, on 128 x 256 tiles and taller ones also with the rounds of
+// tiles, and where the ranges leave fp32 sums, with those.  The slabs cost their preparation, whose first microseconds are the
+// offset, and per column a place in the ring, so that beyond two thirds of a range's columns (`most`) the walk is never the dearer
+// one; a column beyond the slabs is gathered tile by tile.  The constants are fitted to the choice: 1201 calls (129 to 4096 rows,
+// K 288 to 16384 and 32768, N 256 to 22016; split, and without the split that a small workspace has no room for; weights from memory and, a
+// fifth of them, still in the last-level cache), each measured both ways with 3 to 97 % of the columns critical.  With weights from memory
+// the way taken is 0.4 % slower than the better one on average (the line fitted to the kernels before these 3.0 %, for split calls
+// 5.6), more than 10 % in one of ninety, at worst 33 % where it is the slabs (163 x 15040 x 20848 at 17 %) and 21 % where it is the
+// walk (2059 x 4816 x 1744 at 28 %).  Whole calls, us, walk / slabs: 256 x 4096 x 4096 33.0 / 38.0 at 7.5 %, not split 48.7 / 46.5 at 10 %,
+// 48.9 / 52.2 at 13 %; 256 x 11008 x 4096 48.8 / 59.6 at 5 %; 333 x 4096 x 22016 135 / 117 at 22 %, 136 / 154 at 36 %; 2048 x 4096 x
+// 12288 293 / 263 at 46 %, 298 / 350 at 60 %; 2048 x 1024 x 4096 66 / 64 at 60 %, 66 / 74 at 80 %; 4096 x 8192 x 10240 855 / 563 at
+// 28 %, 866 / 924 at 36 %.
+CriticalPlan plan_critical_columns(int M, int n_slabs, int N, bool further_slabs, int splits) {
   CriticalPlan p = {0, 0};
+  const size_t Npad = packed_n(N);
   if (further_slabs) {
     size_t cols = (size_t)n_slabs * 32;                              // half of the columns at most
     if (cols > (size_t)kGatherMax) cols = kGatherMax;
@@ -1298,12 +1302,12 @@ CriticalPlan plan_critical_columns(int M, int n_slabs, size_t Npad, bool further
   }
   const int in_slabs = kOutlierSlab * (kCriticalSlabs + p.g_slabs);
   const double rounds = (double)ceil_div(M, 128) * ((double)Npad / 256) / device_cu_count();   // of 128 x 256 tiles
-  // (ranges on 128 x 128 tiles count for 1.3 each, which leaves the line where it was fitted: 256 x 4096 x 4096 602 columns with
-  // five ranges of 128 x 256 tiles, 612 with four of these)
-  const double ranges = splits * (splits > 1 && one_round_of_small_tiles(M, (int)Npad, splits) ? 1.3 : 1.0);
-  double from = 0.35 * M + 64.0 * n_slabs / ranges * (0.13 + 0.12 * rounds);
-  if (splits > 1) from += 75e-6 * ranges * M * (double)Npad;
-  if (from > in_slabs) from = in_slabs + (from - in_slabs) * (0.028 + 0.014 * rounds) / (0.14 * (rounds > 1 ? rounds : 1));
+  const int slabs = ceil_div(n_slabs, splits);
+  const double per_slab = one_round_of_small_tiles(M, N, splits) ? 9.6 : 13.0 + 6.7 * rounds, most = slabs * BK * (0.64 + 0.09 * rounds);
+  double from = 0.475 * M + per_slab * slabs - 360.0;
+  if (splits > 1) from += 27e-6 * splits * M * (double)Npad;
+  if (from > most) from = most;
+  if (from > in_slabs) from = in_slabs + (from - in_slabs) * (0.144 + 0.072 * rounds) / (rounds > 1 ? rounds : 1);
   p.dense_from = from < 1e9 ? (int)from : 1000000000;
   return p;
 }

@@ -55,9 +55,9 @@ class CriticalPlan(ctypes.Structure):
 def critical_column_plan(M: int, K: int, N: int, splits: int = None):
     """How many critical columns the tiled GEMM takes as fp16 slabs through its ring, and from how many on it makes
     its dense pass instead, by the library's own plan (a C++ function of it, outside its C ABI)."""
-    f = binding.lib()._ZN4mmd821plan_critical_columnsEiimbi
-    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_bool, ctypes.c_int], CriticalPlan
-    p = f(M, (K + 127) // 128 * 2, (N + 255) // 256 * 256, True, splits or gemm_splits(M, K, N))
+    f = binding.lib()._ZN4mmd821plan_critical_columnsEiiibi
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.c_int], CriticalPlan
+    p = f(M, (K + 127) // 128 * 2, N, True, splits or gemm_splits(M, K, N))
     return 32 * (8 + p.g_slabs), max(257, p.dense_from)          # (never for what the first eight slabs hold)
 
 

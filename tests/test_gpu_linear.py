@@ -252,7 +252,7 @@ def test_counts_of_critical_columns_around_the_slab_limits(n_crit, variant):
     """The tiled GEMM takes critical columns 32 at a time as fp16 slabs, up to 256 of them, and the rest as further
     slabs that the preparation gathered (all of them below the count from which it walks K with both products): counts on both sides of every border between those paths, over several row
     panels and a ragged tail."""
-    M, K, N = 600, 1040, 520
+    M, K, N = 1200, 1040, 520
     rng = np.random.default_rng([n_crit, variant])
     X, cols = exactly_n_critical(rng, M, K, n_crit)
     flag = ml.outlier_mask(X, 6.0)
@@ -262,28 +262,29 @@ def test_counts_of_critical_columns_around_the_slab_limits(n_crit, variant):
 
 
 @pytest.mark.parametrize("variant", [None, 4, 5, 0])
-@pytest.mark.parametrize("n_crit", [257, 300, 800, 832, 833, "last in the epilogue", "first of the dense pass", 1000])
+@pytest.mark.parametrize("n_crit", [257, 300, 1300, 1344, 1345, "last in the epilogue", "first of the dense pass", 1700])
 def test_counts_of_critical_columns_around_the_change_to_the_dense_pass(n_crit, variant):
-    """18 slabs of K: up to 832 critical columns travel as fp16 slabs (8, then up to 18 further ones), a few more are
+    """34 slabs of K: up to 1344 critical columns travel as fp16 slabs (8, then up to 34 further ones), a few more are
     gathered in the GEMM's epilogue, and from the planned count on all of them go with the codes in one walk over K."""
-    M, K, N = 2600, 1040, 264
+    M, K, N = 2600, 2064, 1544
+    rows = np.concatenate([np.arange(0, 260), np.arange(2400, M)])
     in_slabs, dense_from = critical_column_plan(M, K, N)
-    assert gemm_splits(M, K, N) == 1 and in_slabs == 832 and in_slabs + 1 < dense_from - 1 and dense_from < 1000
+    assert gemm_splits(M, K, N) == 1 and in_slabs == 1344 and in_slabs + 1 < dense_from - 1 and dense_from < 1700
     n_crit = {"last in the epilogue": dense_from - 1, "first of the dense pass": dense_from}.get(n_crit, n_crit)
     rng = np.random.default_rng([n_crit, 0 if variant is None else variant, 7])
     X, cols = exactly_n_critical(rng, M, K, n_crit)
     assert np.array_equal(np.flatnonzero(ml.outlier_mask(X, 6.0)), cols)
-    check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=wl.gaussian_bias(N, 0.1, rng),
+    check_linear(X, wl.gaussian_weight(K, N, 0.05, rng), 6.0, bias=wl.gaussian_bias(N, 0.1, rng), rows=rows,
                  tuning=0 if variant is None else binding.tune_gemm_tiles(variant))
 
 
 @pytest.mark.parametrize("variant", [4, 5, 0])
 @pytest.mark.parametrize("n_crit", [257, 300, "last in slabs", "first of the dense pass", 1344, 1345, 1486, 1550])
 def test_counts_of_critical_columns_around_the_change_to_the_dense_pass_with_few_rows(n_crit, variant):
-    """With 1100 rows the walk over K takes over long before the slabs are full (1344 columns), later than with 300, whose K
+    """With 1500 rows the walk over K takes over long before the slabs are full (1344 columns), later than with 300, whose K
     is in so many ranges that it takes over with the ninth slab."""
-    M, K, N = 1100, 2096, 264
-    rows = np.concatenate([np.arange(0, 260), np.arange(900, M)])
+    M, K, N = 1500, 2096, 264
+    rows = np.concatenate([np.arange(0, 260), np.arange(1300, M)])
     in_slabs, dense_from = critical_column_plan(M, K, N)
     assert in_slabs == 1344 and 300 < dense_from - 1 and dense_from < 1344
     n_crit = {"last in slabs": dense_from - 1, "first of the dense pass": dense_from}.get(n_crit, n_crit)

@@ -79,7 +79,7 @@ def test_critical_column_slabs_next_to_the_adapter(n_crit, r, variant):
     """1 to 8 fp16 slabs of critical columns in use (the unused ones are skipped), then the adapter's one or two
     slabs behind them in the same ring; 257: one more column, in a ninth slab from the further ones; 700 and 830: the walk
     over K."""
-    M, K, N = 300, 1040, 520
+    M, K, N = 1200, 1040, 520
     assert (n_crit >= critical_column_plan(M, K, N)[1]) == (n_crit >= 700)
     rng = np.random.default_rng([n_crit, r, variant])
     x = np.clip(rng.standard_normal((M, K)), -5.0, 5.0).astype(np.float32)
@@ -94,12 +94,13 @@ def test_critical_column_slabs_next_to_the_adapter(n_crit, r, variant):
 
 
 @pytest.mark.parametrize("variant", [None, 0])
-@pytest.mark.parametrize("n_crit,r", [(700, 16), (830, 40), (850, 64)])
+@pytest.mark.parametrize("n_crit,r", [(1000, 16), (1340, 40), (1350, 64)])
 def test_further_slabs_and_the_epilogue_gather_next_to_the_adapter(n_crit, r, variant):
-    """Many rows: 700 and 830 columns in the first and the further slabs, 850 a few more than those hold (832)."""
-    M, K, N = 2600, 1040, 520
+    """Many rows: 1000 and 1340 columns in the first and the further slabs, 1350 a few more than those hold (1344)."""
+    M, K, N = 2600, 2064, 1544
+    rows = np.concatenate([np.arange(0, 260), np.arange(2400, M)])
     in_slabs, dense_from = critical_column_plan(M, K, N)
-    assert in_slabs == 832 and 850 < dense_from
+    assert in_slabs == 1344 and 1350 < dense_from
     rng = np.random.default_rng([n_crit, r])
     x = np.clip(rng.standard_normal((M, K)), -5.0, 5.0).astype(np.float32)
     cols = np.sort(rng.choice(K, n_crit, replace=False))
@@ -107,7 +108,7 @@ def test_further_slabs_and_the_epilogue_gather_next_to_the_adapter(n_crit, r, va
         x[(11 * j) % M, k] = (-1.0) ** j * (7.0 + j % 40)
     A = wl.to_fp16(rng.standard_normal((r, K)).astype(np.float32) * 0.05)
     B = wl.to_fp16(rng.standard_normal((N, r)).astype(np.float32) * 0.05)
-    check_lora(wl.to_fp16(x), wl.gaussian_weight(K, N, 0.02, rng), A, B, 6.0,
+    check_lora(wl.to_fp16(x), wl.gaussian_weight(K, N, 0.02, rng), A, B, 6.0, rows=rows,
                tuning=0 if variant is None else binding.tune_gemm_tiles(variant))
 
 

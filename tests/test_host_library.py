@@ -154,12 +154,14 @@ def test_ranges_of_k_and_their_tiles(M, K, N, ranges, small):
     assert gemm_splits(M, K, N) == ranges and ranges_on_small_tiles(M, K, N) == small
 
 
-@pytest.mark.parametrize("M,K,N,at,walk", [(1576, 1024, 3072, 717, False), (1576, 1024, 3072, 922, True), (2048, 1024, 4096, 819, False),
-                                           (2048, 1024, 4096, 922, True), (256, 4096, 12288, 410, False), (256, 4096, 12288, 819, True),
-                                           (256, 11008, 4096, 440, False), (256, 11008, 4096, 1101, True), (140, 32768, 1024, 655, True),
-                                           (2048, 4096, 12288, 2048, False), (2048, 4096, 12288, 2867, True),
-                                           (4096, 8192, 10240, 2458, False), (4096, 8192, 10240, 3277, True),
-                                           (1024, 4096, 12288, 1434, False), (1024, 4096, 12288, 2048, True)])
+@pytest.mark.parametrize("M,K,N,at,walk", [(256, 4096, 4096, 307, True), (256, 11008, 4096, 550, True), (348, 6192, 312, 309, True),
+                                           (175, 3296, 1352, 329, True), (140, 32768, 1024, 983, True), (256, 4096, 12288, 532, True),
+                                           (333, 4096, 22016, 901, False), (333, 4096, 22016, 1474, True),
+                                           (1576, 1024, 3072, 286, False), (1576, 1024, 3072, 819, True),
+                                           (2048, 1024, 4096, 286, False), (2048, 1024, 4096, 819, True),
+                                           (1024, 4096, 12288, 1146, False), (1024, 4096, 12288, 1884, True),
+                                           (2048, 4096, 12288, 1884, False), (2048, 4096, 12288, 2457, True),
+                                           (4096, 8192, 10240, 2293, False), (4096, 8192, 10240, 3768, True)])
 def test_dense_pass_from_where_it_is_the_faster_way(M, K, N, at, walk):
     """Counts of critical columns at which one way measured 10 % or more faster than the other (256 compute units)."""
     assert (at >= critical_column_plan(M, K, N)[1]) == walk
