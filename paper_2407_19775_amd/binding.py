@@ -103,11 +103,17 @@ def _check(status: int):
         raise Mmd8Error("mmd8 status %d: %s" % (status, lib().mmd8_status_string(status).decode()))
 
 
+# torch's own way to the current stream's number, where this torch has it under these names
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None
+
+
 def _stream() -> int:
     # torch.cuda.current_stream().cuda_stream without the stream object that it builds to read one number from: 0.2 instead of
     # 2.7 us (every caller holds a GPU tensor, so the device is initialised).  Encoding one token's keys and values, two calls whose
     # kernels take 3 us each, is bound by the host.
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch._C._cuda_getDevice())
 
 
 def _dev(t: torch.Tensor, dtype, name: str):

@@ -394,3 +394,12 @@ def test_variant_entry_points_check_their_arguments():
     assert call(ctypes.byref(R(1, 0x2008, 64))) == -1          # misaligned
     assert call(ctypes.byref(R(1, 0x2000, 64)), layout=tag + 1) == -5
     assert call(ctypes.byref(R(1, 0x2000, 64)), wsb=ws - 1) == -3
+
+
+def test_the_current_stream_without_torch_private_names(monkeypatch):
+    """A torch that does not have its number under those names: the public stream object's."""
+    class Stream:
+        cuda_stream = 0x5000
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream() == 0x5000
