@@ -158,6 +158,7 @@ constexpr int kPackRowSteps = 2;
 constexpr int kPackRows = 32 * kPackRowSteps;          // rows per workgroup
 constexpr int kPackSlabs = kThreads / kWave;            // slabs per workgroup (one per wave)
 
+constexpr int kPrepMaxK = 32768;                        // the longest rows of k_prep and k_outlier_columns
 constexpr int kListedColumns = kOutlierSlab * kCriticalSlabs + kGatherMax;   // critical columns a workgroup keeps in LDS
 
 // The ascending list of critical columns and their count, computed by one whole workgroup from
@@ -241,16 +242,20 @@ __device__ __forceinline__ void compact_critical_columns_n(const uint8_t* __rest
   __syncthreads();
 }
 
-// (a thread's loads are all issued whether it owns that many units or not, so the count is a template argument)
+// (a thread's loads are all issued whether it owns that many units or not, so the count is a template argument; kMaxK: the longest
+// rows that come here.  Sixteen units, which only k_pack meets, take 138 registers where eight take 70.  k_pack's 134 leave three waves to
+// a SIMD: held to 128, four of them, calls on 36864 to 65536 columns took 0.5 to 4 % longer.)
+template <int kMaxK>
 __device__ __forceinline__ void compact_critical_columns(const uint8_t* __restrict__ flag, int K, int Kpad,
                                                          const PackOutliers& o, bool publish, int* s_idx, int* s_n_out,
                                                          int* s_wave_total) {
-  static_assert(MMD8_MAX_K / 16 / kThreads == 16, "largest number of units per thread");
+  constexpr int kMost = kMaxK / 16 / kThreads;
+  static_assert(kMost == 8 || kMost == 16, "largest number of units per thread");
   const int per = ceil_div(Kpad / 16, kThreads);
   if (per <= 2) compact_critical_columns_n<2>(flag, K, Kpad, o, publish, s_idx, s_n_out, s_wave_total);
   else if (per <= 4) compact_critical_columns_n<4>(flag, K, Kpad, o, publish, s_idx, s_n_out, s_wave_total);
   else if (per <= 8) compact_critical_columns_n<8>(flag, K, Kpad, o, publish, s_idx, s_n_out, s_wave_total);
-  else compact_critical_columns_n<16>(flag, K, Kpad, o, publish, s_idx, s_n_out, s_wave_total);
+  else if constexpr (kMost > 8) compact_critical_columns_n<16>(flag, K, Kpad, o, publish, s_idx, s_n_out, s_wave_total);
 }
 
 // Rows of the critical-column slabs, 8 columns (16 bytes) per thread and slab: Xo[m][j] = X[m, O_j] for
@@ -341,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void k_pack(const uint16_t* __restrict__ 
     __shared__ int s_n_out;
     __shared__ int s_wave_total[kThreads / kWave];
     const int b = ((int)blockIdx.y - pack_blocks_y) * gridDim.x + blockIdx.x;
-    compact_critical_columns(flag, K, n_slabs * kSlabBytes, o, b == 0, s_idx, &s_n_out, s_wave_total);
+    compact_critical_columns<MMD8_MAX_K>(flag, K, n_slabs * kSlabBytes, o, b == 0, s_idx, &s_n_out, s_wave_total);
     if (o.Xo) {
       gather_outlier_slab(X, M, ldx, n_slabs, o, b * kThreads + threadIdx.x, s_idx, s_n_out);
       gather_further_slabs(X, M, ldx, n_slabs, o, b * kThreads + threadIdx.x,
@@ -682,7 +687,7 @@ __device__ __forceinline__ void outlier_columns_block(int block, const uint16_t*
     __shared__ int s_idx[kListedColumns];
     __shared__ int s_n_out;
     __shared__ int s_wave_total[kThreads / kWave];
-    compact_critical_columns(flag, K, Kpad, o, block == 0, s_idx, &s_n_out, s_wave_total);
+    compact_critical_columns<kPrepMaxK>(flag, K, Kpad, o, block == 0, s_idx, &s_n_out, s_wave_total);
     gather_outlier_slab(X, M, ldx, n_slabs, o, block * kThreads + threadIdx.x, s_idx, s_n_out);
     gather_further_slabs(X, M, ldx, n_slabs, o, block * kThreads + threadIdx.x, slab_blocks * kThreads, s_idx, s_n_out);
     return;
@@ -810,7 +815,7 @@ hipError_t launch_prep_rows(const uint16_t* X, int M, int K, int ldx, uint32_t t
 // 1576 x 4096 32.2 / 31.7; no gain, and not taken: 768 x 11008 36.4 / 37.3, 1024 x 8192 36.0 / 36.2, 1576 x 11008 48.6 / 49.1.
 // (Coded input stays with four: every workgroup brings the code table into LDS.)
 static bool prep_single_rows(int M, int K) { return K > 1024 && (M <= 512 || (long)M * K <= 6500000); }
-bool prep_fits(int K) { return packed_k(K) / 16 <= 16 * 16 * 8; }
+bool prep_fits(int K) { return packed_k(K) <= kPrepMaxK; }
 // the variant that decodes coded activations holds more per lane: rows up to 16384 columns without spilling
 bool prep_from_codes_fits(int K) { return packed_k(K) / 16 <= 16 * 16 * 4; }
 
