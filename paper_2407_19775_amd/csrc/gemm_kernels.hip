@@ -1215,8 +1215,8 @@ hipError_t prepare_gemm_kernels() {
 }
 
 static hipError_t launch_variant(const GemmArgs& a, int variant, hipStream_t stream, bool once = false) {
-  // coded output with blocks wider than the 128-column tiles (the dense pass of four-wave kernels has such tiles too)
-  if (a.codes && a.code_log_block > 7 && variant < 3) variant = 5;
+  // coded output with blocks wider than the 128-column tiles
+  if (a.codes && a.code_log_block > 7 && variant <= 1) variant = 5;
   switch (variant) {
     case 1: return launch_cfg<Cfg1>(a, stream);
     case 2: return launch_cfg<Cfg2>(a, stream);

@@ -143,6 +143,13 @@ def test_every_tile_configuration_encodes_alike():
             run_and_check(X, W, b, R, block, want_h=bool(variant % 2), tuning=binding.tune_gemm_tiles(variant))
 
 
+@pytest.mark.parametrize("variant", range(6))
+def test_the_walk_with_both_products_encodes_alike(variant):
+    """Every column critical, blocks as wide as the widest tile."""
+    X, W, b, R = make_case(300, 272, 768, 1)
+    run_and_check(X, W, b, R, 256, tau=0.0, want_h=bool(variant % 2), tuning=binding.tune_gemm_tiles(variant))
+
+
 def test_zero_rows_and_blocks_take_the_zero_code():
     # an all-zero hidden state: every absmax is 0 and every code is the code of 0 (127)
     M, K, N, block = 260, 64, 256, 128
