@@ -812,9 +812,15 @@ hipError_t launch_prep_rows(const uint16_t* X, int M, int K, int ldx, uint32_t t
 // A row per workgroup instead of four: for up to 512 rows, and for inputs of up to 6.5 million elements, where the chip still has
 // compute units to spare; not for rows that a quad's four waves hold in one pass.  Us per call with N = 1024, four rows / one:
 // 129 x 4096 23.3 / 22.4, 256 x 11008 31.8 / 30.0, 512 x 11008 31.7 / 30.8, 256 x 28672 42.3 / 37.5, 768 x 8192 31.8 / 31.2,
-// 1576 x 4096 32.2 / 31.7; no gain, and not taken: 768 x 11008 36.4 / 37.3, 1024 x 8192 36.0 / 36.2, 1576 x 11008 48.6 / 49.1.
+// 1576 x 4096 31.3 / 30.4, 1200 x 5120 28.2 / 27.1 (N = 512); beyond the line little or nothing: 2000 x 4096 32.0 / 31.7, 1000 x 8192
+// 33.2 / 33.3.  Above 512 rows not where the row takes sixteen waves (640 x 11008 32.2 / 33.8, 600 x 8208 with an adapter 27.6 / 28.8), nor for
+// so many rows that workgroups follow one another: 2800, and 1024 of less than 2048 columns, which leave more than half of the lanes
+// without a piece (3200 x 2048 27.9 / 28.6, 2600 x 2048 with N = 512 24.6 / 24.6, 5000 x 1296 29.5 / 30.7, 1576 x 1040 17.6 / 17.8).
 // (Coded input stays with four: every workgroup brings the code table into LDS.)
-static bool prep_single_rows(int M, int K) { return K > 1024 && (M <= 512 || (long)M * K <= 6500000); }
+bool prep_single_rows(int M, int K) {
+  if (K <= 1024 || M <= 512) return K > 1024;
+  return K <= 8192 && M <= (K < 2048 ? 1024 : 2800) && (long)M * K <= 6500000;
+}
 bool prep_fits(int K) { return packed_k(K) <= kPrepMaxK; }
 // the variant that decodes coded activations holds more per lane: rows up to 16384 columns without spilling
 bool prep_from_codes_fits(int K) { return packed_k(K) / 16 <= 16 * 16 * 4; }

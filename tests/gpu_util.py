@@ -87,6 +87,13 @@ def static_decode_plan(M: int, K: int, N: int):
     return p.splits, p.pass_rows
 
 
+def prep_single_rows(M: int, K: int) -> bool:
+    """Whether more than 128 rows are prepared with a row per workgroup (a C++ function of the library)."""
+    f = binding.lib()._ZN4mmd816prep_single_rowsEii
+    f.argtypes, f.restype = [ctypes.c_int] * 2, ctypes.c_bool
+    return f(M, K)
+
+
 def panel_plan(M: int, K: int, N: int):
     """Ranges of K of the kernel for a few rows that prepares its own operands and splits K, and the 64-column slabs of a range (a
     C++ function of the library); 0 ranges: not for this call."""

@@ -1,6 +1,6 @@
 """More than 128 rows prepared with a row per workgroup: each row length's kernel (4, 8 and 16 waves, one and two passes, a last
 piece that is not whole), counts of rows around the 256 that the compute units' order repeats with, rows apart by more than
-their length, the last size before four rows share a workgroup and the first one after; integers against the oracle."""
+their length, the last size before four rows share a workgroup and the first one after, at each end of the rule; integers against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -13,8 +13,8 @@ from test_gpu_linear import check_weight
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K", [(129, 1024), (129, 1040), (255, 2064), (257, 4096), (512, 4112), (513, 8208), (130, 8192), (200, 16368), (131, 16400),
-                                 (129, 32752), (1586, 4096), (1587, 4096)])
+@pytest.mark.parametrize("M,K", [(129, 1024), (129, 1040), (255, 2064), (257, 4096), (512, 4112), (512, 8208), (513, 8208), (130, 8192), (200, 16368), (131, 16400),
+                                 (129, 32752), (1586, 4096), (1587, 4096), (1024, 1040), (1025, 1040), (2800, 2064), (2801, 2064)])
 def test_row_per_workgroup(M, K):
     N = 24
     rng = np.random.default_rng([M, K])

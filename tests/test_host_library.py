@@ -9,7 +9,7 @@ import pytest
 
 from oracle import dynamic_code as dc
 from paper_2407_19775_amd import binding
-from gpu_util import critical_column_plan, gemm_splits, lora_ranges_in, lora_read_column, ranges_on_small_tiles
+from gpu_util import critical_column_plan, gemm_splits, lora_ranges_in, lora_read_column, prep_single_rows, ranges_on_small_tiles
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -165,6 +165,14 @@ def test_ranges_of_k_and_their_tiles(M, K, N, ranges, small):
 def test_dense_pass_from_where_it_is_the_faster_way(M, K, N, at, walk):
     """Counts of critical columns at which one way measured 10 % or more faster than the other (256 compute units)."""
     assert (at >= critical_column_plan(M, K, N)[1]) == walk
+
+
+@pytest.mark.parametrize("M,K,single", [(129, 4096, True), (512, 28672, True), (1576, 4096, True), (1200, 5120, True), (768, 8192, True),
+                                        (1000, 1040, True), (129, 1024, False), (640, 11008, False), (600, 8208, False), (3072, 2048, False),
+                                        (5000, 1296, False), (1576, 1040, False), (4096, 4096, False)])
+def test_a_row_per_workgroup_where_it_is_the_faster_way(M, K, single):
+    """Each measured both ways, rows from memory and cached."""
+    assert prep_single_rows(M, K) == single
 
 
 def test_bad_arguments_are_rejected_before_any_launch():
