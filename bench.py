@@ -33,8 +33,8 @@ INT8_POWER_LIMITED_TOPS = 3468.0
 # (70B-shaped layer, 4096 tokens) and the 7B-shaped step.  Valid for the GEMM source they were measured on:
 # reported as null once that file has changed.
 GEMM_TRAFFIC_BYTES_PER_LAUNCH = 1185.3e6
-GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 183.2e6
-GEMM_TRAFFIC_SOURCE_SHA256 = "e0770f13c472732dc68fe89fb6ce4c6fe9051562d65f0fb526fffcea856ba94d"
+GEMM_TRAFFIC_BYTES_PER_LAUNCH_7B = 183.9e6
+GEMM_TRAFFIC_SOURCE_SHA256 = "f358c61c66776e305f6d0948e2e42c379ec8562e04539d7bf1973e2f18b00f8c"
 
 
 def parse():

@@ -286,7 +286,9 @@ __device__ __forceinline__ void gather_outlier_columns(const GemmArgs& a, const 
 // sub-tile at a time as fp16 rows in a region of its own and writes them out 16 bytes per lane, eight lanes
 // per 128-byte row segment: a store instruction covers whole lines.  (Storing the 4-byte pairs directly
 // takes four times as many store instructions and writes half lines that do not always meet in L2 before
-// write-back: 2-5 % slower on the 256 x 256 tiles, 1.3 times the output in HBM write traffic.)
+// write-back: 2-5 % slower on the 256 x 256 tiles, 1.3 times the output in HBM write traffic.)  On the 128 x 128 tiles, whose waves
+// own 32 columns, four lanes write 64 bytes of a row and another wave the rest of the line; these halves do meet: 1024 x 1024 x 4096
+// writes 8.39 MB, 256 x 4096 x 12288 6.30, the output once, as with every other tile.
 template <class Cfg, bool kFull>
 __device__ __forceinline__ void store_tile(const GemmArgs& a, const WavePos<Cfg>& p, v16i (&acc)[Cfg::TI][Cfg::TJ],
                                       const float (&bn)[Cfg::TJ], int8_t* smem, int wave) {
@@ -1062,7 +1064,9 @@ __device__ __forceinline__ void dense_tile(const GemmArgs& a, int m0, int n0, in
 // arguments through an address that the compiler cannot see through, where they are needed: what it computes from them is then
 // not shared with the other way through the kernel, whose registers it would take.  (As a function of its own it saved and restored 120
 // registers a lane through scratch, 24 to 63 MB of writes a launch.)  The address of the LDS buffers is handed on as a number: named,
-// it would be read from memory again for every use.
+// it would be read from memory again for every use.  Where the tile is walked in pieces, on the 256 x 256 tiles and configuration 2, the
+// kernel still keeps 20 to 44 bytes a lane in scratch: the loops over pieces around the walk, its epilogue and, on 256 x 256 tiles, the
+// gathering of columns beyond the slabs use them; the loops over slabs have no access to scratch.
 template <class Cfg, bool kOnce>
 __device__ __forceinline__ void gemm_tile_dense(const GemmArgs& a, int8_t* smem) {
   constexpr int kBN = Cfg::BN;
@@ -1357,8 +1361,9 @@ hipError_t launch_gemm_mixed(GemmArgs a, int variant, hipStream_t stream) {
     return launch_variant(a, 4, stream);
   }
   // Less than one round of large tiles: 128 x 128 tiles where they fit one round, else 128 x 256 with eight waves and the
-  // four-slab ring.  (Measured, 128 x 128 / 128 x 256, the former still with four waves: 256 x 4096 x 12288 32 / 36 us, 1000 x
-  // 4096 x 4096 37 / 42, 1024 x 2048 x 1024 24 / 27; 300 x 4096 x 12288, where the small tiles are a round and a bit, 52 / 39.)  Where the 128 x 256
+  // four-slab ring.  (Measured, the kernel alone, 128 x 128 / 128 x 256: 256 x 4096 x 12288 21.0 / 28.6 us, 1000 x 4096 x 4096
+  // 24.0 / 30.1, 1024 x 1024 x 4096 12.6 / 14.0; whole calls, the former still with four waves, 300 x 4096 x 12288, where the small
+  // tiles are a round and a bit, 52 / 39.)  Where the 128 x 256
   // tiles would need a second round and the 256 x 256 ones fit in one, the large tiles win: 4096 -> 12288 at 768 rows 61
   // against 71 us, 4096 -> 22016 at 512 rows 61 against 70.
   if (a.M > 128 && tiles_128x256 > cus) return launch_variant(a, 4, stream);
